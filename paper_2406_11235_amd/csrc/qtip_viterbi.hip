@@ -4,36 +4,41 @@
 // the computed codes of Algorithms 1-3 (L = 16, 16 x 16 blocks) and the lookup-only code of
 // the appendix (L = 14, 32 x 8 blocks; the text below says 16 and 1024, read L and 2^L / 64).
 //
-// Layout on the chip.  One workgroup of NT = 1024 threads owns one sequence and keeps the
-// whole value function, 2^16 binary32 numbers, in registers: thread `tid` holds the 64
-// states y = NT r + tid (half of the 128 registers a thread has at four waves per SIMD;
-// the code values take most of the other half).  The bitshift structure makes that layout communication-free
-// for the minimum: the 2^kV predecessors of y all end in the top 16-kV bits of y, so
-// states with a common "prefix" hi = y >> kV share one minimum, and the predecessors
-// p 2^(16-kV) + hi of a prefix have the same low 10 bits, i.e. live in one thread
-// (kV <= 6; for kV = 8 they are spread over four threads, which meet in LDS; for kV <= 3 a
-// thread instead owns whole (predecessor, child) squares of states, see VitGeo).  A step is
-//   phase 1: every thread takes the minimum and arg-minimum over the predecessors of
-//            its prefixes, publishes the minima in LDS (2^(16-kV) floats, 64 KiB at
-//            kV = 2) and stores the arg-minima, kV bits each, packed into one or two
-//            words per thread and step, to the back-pointer workspace in HBM;
-//   phase 2: every thread reads the minimum of each of its states' prefixes back from
-//            LDS and adds the squared error of the state's code value.
-// Code values never change, so they sit in registers as packed fp16 (V = 1); for the
-// HYB code a state only selects one of 1024 signed table rows (2048 with two sign flips), so
-// each step first builds their squared errors in LDS and states carry a row number.
-// A second, tiny kernel walks the back-pointers (one thread per sequence: the walk is a
-// chain of dependent loads, so it is run over a whole batch of sequences at once).
-// Algorithm 4 is forward / walk-to-the-middle / constrained forward / full walk.
+// The recursion.  All 2^kV successors of a state share the state's low L - kV bits as their
+// top bits, their "prefix" hi = y >> kV, so the value function of a step is
+//     val_t[y] = best_t[y >> kV] + err_t[y],
+//     best_{t+1}[hi] = min over p < 2^kV of val_t[p 2^(L-kV) + hi],      best_0 = 0,
+// and only `best`, 2^(L-kV) binary32 numbers, passes from one step to the next.
+//
+// Forward kernel.  One workgroup of 1024 threads owns one sequence; `best` lives in LDS, twice
+// (read one copy, write the other, one barrier per step; 2 x 64 KiB at kV = 2).  A thread owns
+// 2^(6-kV) neighbouring prefixes and their 64 predecessor states, whose code values sit in its
+// registers: it reads the few `best` entries those states hang on, forms the 64 values and
+// takes the minima, per state one subtraction, one fused multiply-add and half a minimum.
+// No arg-minimum is formed: a back-pointer costs more instructions per prefix (3 compares, 3
+// adds-with-carry and a third minimum at kV = 2) than everything else the prefix needs.
+// Instead `best` itself is written to HBM every J steps, and the walk back recomputes what it
+// needs: of the states J steps before a known state only 2^(kV J) can lead to it, a tree that
+// one wave evaluates from the stored `best` in a few hundred instructions.
+//   Measured, 2048 x 2048, 2-bit 3INST (16384 tiles): see viterbi_forward_kernel.
+//
+// Walk back.  One wave per sequence and J steps at a time: it reads the 2^(kV J) stored minima
+// below the current state (one contiguous run: `best` is stored with the state's low bits, which
+// are fixed there, as the major index), and repeats the recursion level by level with the
+// arguments kept; ties go to the lowest predecessor.  The same operations in the same order
+// give the same bits as the forward kernel, so the walk is the one its minima imply.
+// Algorithm 4 is forward / walk to the middle / constrained forward / full walk.
 //
 // Arithmetic (fixed, so that a CPU reference can repeat every decision): binary32,
 //   e_j = C[y][j] - s[V t + j];
 //   V = 1: value = fma(e_0, e_0, min)            (the first step: e_0 e_0)
-//   V = 2: value = min + fma(e_1, e_1, e_0 e_0)  (the error comes from a per-step table)
+//   V = 2: value = min + fma(e_1, e_1, e_0 e_0)
 // with exactly these roundings (the file is compiled without contraction).
 // Minima take the lowest predecessor on ties, the final state the lowest state.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "qtip_device.h"
 #include "qtip_internal.h"
@@ -48,561 +53,511 @@ constexpr int VT_REGS = 64;  // states per thread
 
 // LB = L, the number of state bits: 16 (NT = 1024 threads per sequence) for the codes of
 // Algorithms 1-3, 14 (NT = 256) for the lookup-only code.
-template <int KV, int LB>
+template <int KV, int V, int LB>
 struct VitGeo {
+    static constexpr int G = VT_T / V;              // steps
     static constexpr int NT = (1 << LB) / VT_REGS;  // threads per sequence
     static constexpr int OV = LB - KV;              // bits two consecutive states share
     static constexpr int NP = 1 << OV;              // prefixes = minima per step
     static constexpr int NC = 1 << KV;              // predecessors per prefix
-    static constexpr bool LOCAL = NP >= NT;         // predecessors of a prefix in one thread
-    static constexpr int NB1 = LOCAL ? NP / NT : 1;     // prefixes per thread
-    // back-pointers: kV bits per prefix, FPW whole fields per word, PWT words per thread
-    static constexpr int FPW = 32 / KV;
-    static constexpr int PWT = (NB1 + FPW - 1) / FPW;
-    // kV <= 3: a thread can own, for a few values "mid" of the middle L - 2 kV bits of the
-    // state, all 2^kV x 2^kV states (p, mid, c).  Then the predecessors of a prefix (mid, c)
-    // are still its own registers, and so are all 2^kV children of a prefix it reads back, so
-    // one LDS read serves 2^kV states and a thread's minima are contiguous in LDS (16-byte
-    // LDS operations).  SJ = mids per thread: mid = SJ tid + j.
-    static constexpr bool SLOT = KV <= 3;
-    static constexpr int SJ = SLOT ? VT_REGS / (NC * NC) : 1;
-    // kV = 2, 1024 threads: the back-pointer of a prefix is kept as the three outcomes of the
-    // comparisons that found its minimum (v1 < v0, v3 < v2, min23 < min01) instead of the
-    // index they imply: a comparison's lane mask goes straight into the packed word as the
-    // carry of an add (word = 2 word + carry), and no instruction ever forms the index.  16
-    // prefixes x 3 bits are two words per thread and step: prefix f is bits 3 (f % 8) ..
-    // + 2 of word f / 8, comparison outcomes in the order above from bit 2 down.
-    static constexpr bool RAW3 = KV == 2 && NT == 1024;
-    static constexpr int PW = RAW3 ? 2 * NT : SLOT ? NT : LOCAL ? NT * PWT : NP;  // back-pointer words per step
+    static constexpr bool WHOLE = NC <= VT_REGS;    // a prefix's predecessors fit one thread
+    static constexpr int NB = WHOLE ? VT_REGS / NC : 1;  // prefixes per thread
+    // Steps between two stored copies of `best`.  The tree of a walk has 2^(kV J) leaves, and
+    // storing costs 4 NP / J bytes per step: 13 KiB at kV = 2 (J = 5, 16 leaves per lane), 3.4
+    // TB/s over the chip, is as dense as pays; denser (J = 4) the stores bound the kernel.
+    static constexpr int J = KV == 2 ? (LB == 16 ? 5 : 4) : KV == 3 ? 3 : KV == 4 ? 2 : 1;
+    static constexpr int NLEAF = 1 << (KV * J);
+    static constexpr int LOWB = LB - KV * (J + 1);  // low prefix bits, fixed within one tree
+    static constexpr int NSEG = (G - 1 + J - 1) / J;  // trees of a whole walk; the last one
+    static constexpr int LAST = (G - 1) - (NSEG - 1) * J;  // has LAST levels and starts at step 0
+    static constexpr int MID = G / 2 - 1;           // the step the first walk goes down to
+    static constexpr int NSEG_MID = (G - 1 - MID + J - 1) / J;
+    static_assert(LOWB >= 0, "a tree's leaves are distinct states");
+    // LDS place of best[hi] (floats).  kV = 2 and 3: a thread's 16 or 8 minima are one row; written
+    // as they stand, the 16-byte stores of neighbouring lanes would be a whole row apart and
+    // land on two (four) of the eight 16-byte bank groups, so the row's pieces are rotated by an
+    // amount that depends on the row, which spreads eight lanes over all eight groups here and
+    // where the rows are read back.  kV = 6: the 64 entries that one wave reads are one row.
+    __device__ static __forceinline__ int place(int hi) {
+        if constexpr (KV == 2) return (hi & ~15) | ((((hi >> 2) + (hi >> 5)) & 3) << 2) | (hi & 3);
+        else if constexpr (KV == 3) return (hi & ~7) | ((((hi >> 2) ^ (hi >> 5)) & 1) << 2) | (hi & 3);
+        else if constexpr (KV == 6) return (hi & 15) * 68 + (hi >> 4);
+        else if constexpr (KV == 8) return (hi >> 6) * 68 + (hi & 63);
+        else return hi;
+    }
+    static constexpr int BEST_FLOATS = KV == 6 ? 16 * 68 : KV == 8 ? 4 * 68 : NP;
+    // place of best[hi] in a stored copy
+    __device__ static __forceinline__ uint32_t stored(uint32_t hi) {
+        return ((hi & ((1u << LOWB) - 1u)) << (KV * J)) | (hi >> LOWB);
+    }
 };
 
-__host__ __device__ constexpr int vit_max(int a, int b) { return a > b ? a : b; }
-
-// Minimum of val[base + j stride], j = 0 .. COUNT-1, and the lowest j that attains it.
-// CH independent compare-select chains (j = c mod CH) run interleaved, so that the wait
-// states between a compare and the selects reading its mask are filled, and are merged
-// at the end; ties go to the lower j at every stage.  All indices fold to constants once
-// the callers' loops are unrolled.
-template <int COUNT, int CH>
-__device__ __forceinline__ void argmin_regs(const float (&val)[VT_REGS], int base, int stride, float &bv,
-                                            uint32_t &bj) {
-    float cv[CH];
-    uint32_t cj[CH];
-#pragma unroll
-    for (int c = 0; c < CH; c++) {
-        cv[c] = val[base + c * stride];
-        cj[c] = (uint32_t)c;
-    }
-#pragma unroll
-    for (int j = CH; j < COUNT; j++) {
-        const int c = j % CH;
-        const float v = val[base + j * stride];
-        const bool lt = v < cv[c];
-        cv[c] = lt ? v : cv[c];
-        cj[c] = lt ? (uint32_t)j : cj[c];
-    }
-    bv = cv[0];
-    bj = cj[0];
-#pragma unroll
-    for (int c = 1; c < CH; c++) {
-        const bool better = cv[c] < bv || (cv[c] == bv && cj[c] < bj);
-        bv = better ? cv[c] : bv;
-        bj = better ? cj[c] : bj;
-    }
+// m = min(a, b) and min(a, b, c) as instructions: the builtins first "canonicalize" their
+// operands, one extra instruction each, against signalling NaNs that cannot occur here.
+__device__ __forceinline__ float min2(float a, float b) {
+    float m;
+    asm("v_min_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
+}
+__device__ __forceinline__ float min3(float a, float b, float c) {
+    float m;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
 }
 
-// The same minimum and arg-minimum for COUNT a power of two, as a tournament: the values go
-// through v_min_f32 (no select waits on a compare), and the index never exists as a number:
-// every comparison leaves a 64-lane mask in scalar registers, the masks of the winner's path
-// are combined there (scalar and/or, which issue beside the vector instructions), and
-// bits[b] ends up as the lane mask of index bit b.  Left wins on ties at every level, which
-// is the lowest index, as in argmin_regs.
-template <int N>
-__device__ __forceinline__ float argmin_tournament(const float (&val)[VT_REGS], int base, int stride, int lo,
-                                                   uint64_t *bits) {
-    if constexpr (N == 1) {
-        return val[base + lo * stride];
+// The code values of state y as a register: the binary32 value (V = 1), or the packed binary16
+// pair with its signs applied (V = 2).
+template <int CODE>
+__device__ __forceinline__ uint32_t code_register(uint32_t y, const uint32_t *__restrict__ lut) {
+    if constexpr (CODE == CODE_HYB) return as_u32(code_hyb(y, lut));
+    else if constexpr (CODE == CODE_HYB2) return as_u32(code_hyb2(y, lut));
+    else {
+        half_t c;
+        if constexpr (CODE == CODE_LUT) c = reinterpret_cast<const half_t *>(lut)[y];
+        else if constexpr (CODE == CODE_HYB1) c = code_hyb1(y, reinterpret_cast<const uint16_t *>(lut));
+        else c = CODE == CODE_3INST ? code_3inst(y) : code_1mad(y);
+        return __builtin_bit_cast(uint32_t, (float)c);
+    }
+}
+// val = value of a state with code register c on top of `best` b.  V = 2: the conversion to
+// binary32 and the subtraction are one v_fma_mix_f32, (float)c * 1.0 - s: an exact product
+// and one rounding.
+template <int V>
+__device__ __forceinline__ float state_value(uint32_t c, float s0, float s1, float b) {
+    if constexpr (V == 2) {
+        float e0, e1;
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(e0) : "v"(c), "v"(s0));
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(e1) : "v"(c), "v"(s1));
+        return b + __builtin_fmaf(e1, e1, e0 * e0);
     } else {
-        constexpr int H = N / 2;
-        constexpr int LOGH = H == 1 ? 0 : H == 2 ? 1 : H == 4 ? 2 : 3;
-        uint64_t bl[4], br[4];
-        const float a = argmin_tournament<H>(val, base, stride, lo, bl);
-        const float b = argmin_tournament<H>(val, base, stride, lo + H, br);
-        const uint64_t lt = __ballot(b < a);
-#pragma unroll
-        for (int i = 0; i < LOGH; i++) bits[i] = (lt & br[i]) | (~lt & bl[i]);
-        bits[LOGH] = lt;
-        // (as an instruction: the builtin first "canonicalizes" both operands, one extra
-        // instruction each, against signalling NaNs that cannot occur here)
-        float m;
-        asm("v_min_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
-        return m;
-    }
-}
-// lt = b < a; word = 2 word + lt; m = min(a, b): the comparison's mask is consumed as the carry
-// of the add that follows it (ties: lt = 0, the left operand, as everywhere).
-__device__ __forceinline__ void compare_shift_min(float a, float b, uint32_t &word, float &m) {
-    asm("v_cmp_lt_f32 vcc, %3, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\tv_min_f32 %1, %2, %3"
-        : "+v"(word), "=v"(m)
-        : "v"(a), "v"(b)
-        : "vcc");
-}
-// word = 2 word + (this lane's bit of mask): one add-with-carry.
-__device__ __forceinline__ void shift_in_bit(uint32_t &word, uint64_t mask) {
-    uint64_t carry_out;
-    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(word), "=s"(carry_out) : "s"(mask));
-}
-
-// rotate = 1: the sequence rotated by T/2 (Algorithm 4's first call).  overlap != null:
-// the first state's top 16-kV bits and the last state's low 16-kV bits are forced to
-// overlap[slot] (its second call).  Sequence `slot` of the batch is tile tile0 + slot.
-template <int KV, int V, int CODE>
-// (four waves per SIMD, i.e. at most 128 registers, also where a workgroup is only four waves)
-__global__ __launch_bounds__((VitGeo<KV, code_state_bits(CODE)>::NT), 4) void viterbi_forward_kernel(
-    const float *__restrict__ W, int n, int tn, long tile0, const uint32_t *__restrict__ lut, int rotate,
-    const uint32_t *__restrict__ overlap, uint32_t *__restrict__ ptrs, uint32_t *__restrict__ final_state,
-    float *__restrict__ final_value) {
-    using Geo = VitGeo<KV, code_state_bits(CODE)>;
-    constexpr int NP = Geo::NP, NC = Geo::NC, NB1 = Geo::NB1, PW = Geo::PW, VT_NT = Geo::NT;
-    constexpr int LTY = code_log2_ty(CODE), TY = 1 << LTY, TX = VT_T >> LTY;  // the block is TX x TY
-    constexpr int G = VT_T / V;
-    constexpr bool HYB = code_is_hyb(CODE);
-    constexpr int ROWS = CODE == CODE_HYB2 ? 2048 : 1024;  // signed table rows a state can select
-    // The per-step error table is read at random (one read per state and step), so it is kept
-    // in DCOPY copies: word row * DCOPY + c belongs to the lanes with lane % DCOPY == c, and a
-    // 32-lane pass finds at most four lanes on four banks instead of 32 on 32 (the fullest
-    // bank then holds about 2 reads instead of 3.5).
-    constexpr int DCOPY = 8;
-    static_assert(HYB == (V == 2), "V = 2 is the HYB code");
-    // LDS: minima (or, for kV = 8, per-thread partial minima, their predecessors and the
-    // 256 minima), reused for the final reduction; then the HYB error table
-    constexpr int BEST_FLOATS = Geo::LOCAL ? vit_max(NP, 2 * VT_NT) : 2 * VT_NT + NP;
-    __shared__ __attribute__((aligned(16))) float s_mem[BEST_FLOATS + VT_T + (HYB ? ROWS * DCOPY : 0)];
-    float *const s_best = s_mem;
-    float *const s_seq = s_mem + BEST_FLOATS;      // the sequence
-    float *const s_D = s_mem + BEST_FLOATS + VT_T;  // HYB only
-    const float *const s_Dmine = s_D + (threadIdx.x & (DCOPY - 1));
-
-    const int tid = threadIdx.x;
-    const int slot = blockIdx.x;
-    const long tile = tile0 + slot;
-    const int I = (int)(tile / tn), J = (int)(tile % tn);
-
-    static_assert(VT_NT >= VT_T, "one thread per sequence element");
-    if (tid < VT_T) {
-        const int s = rotate ? ((tid + VT_T / 2) & (VT_T - 1)) : tid;
-        s_seq[tid] = W[(size_t)(TX * I + (s >> LTY)) * n + TY * J + (s & (TY - 1))];
-    }
-    __syncthreads();
-    auto seq = [&](int u) -> float { return s_seq[u]; };
-    // the state held in register r: NT r + tid, or (p, SJ tid + j, c) with r = (p SJ + j) NC + c;
-    // increasing in r either way
-    auto state_of = [&](int r) -> uint32_t {
-        if constexpr (Geo::SLOT) {
-            const int p = r / (Geo::SJ * NC), j = (r / NC) % Geo::SJ, c = r % NC;
-            return ((uint32_t)p << Geo::OV) | ((uint32_t)(tid * Geo::SJ + j) << KV) | (uint32_t)c;
-        } else {
-            return (uint32_t)(r * VT_NT + tid);
-        }
-    };
-
-    // code values of this thread's states
-    half2_t cpk[HYB ? 1 : VT_REGS / 2];
-    uint32_t ipk[HYB ? VT_REGS / 2 : 1];
-#pragma unroll
-    for (int r = 0; r < VT_REGS; r++) {
-        const uint32_t y = state_of(r);
-        if constexpr (HYB) {
-            const uint32_t X = y * y + y;
-            uint32_t row = (X >> (15 - HYB_Q)) & 1023u;  // table index and sign bit
-            if constexpr (CODE == CODE_HYB2) row |= (X >> 31) << 10;  // second sign bit
-            // kept as the byte offset of the row's error in the per-step table
-            if (r & 1)
-                ipk[r >> 1] |= (row * 4 * DCOPY) << 16;
-            else
-                ipk[r >> 1] = row * 4 * DCOPY;
-        } else {
-            if constexpr (CODE == CODE_LUT)
-                cpk[r >> 1][r & 1] = reinterpret_cast<const half_t *>(lut)[y];
-            else if constexpr (CODE == CODE_HYB1)
-                cpk[r >> 1][r & 1] = code_hyb1(y, reinterpret_cast<const uint16_t *>(lut));
-            else
-                cpk[r >> 1][r & 1] = CODE == CODE_3INST ? code_3inst(y) : code_1mad(y);
-        }
-    }
-    // (opaque to the compiler from here on, or it recomputes the codes inside the loop
-    // instead of keeping them)
-#pragma unroll
-    for (int r2 = 0; r2 < VT_REGS / 2; r2++) {
-        if constexpr (HYB) {
-            asm volatile("" : "+v"(ipk[r2]));
-        } else {
-            uint32_t cw = as_u32(cpk[r2]);
-            asm volatile("" : "+v"(cw));
-            cpk[r2] = as_half2(cw);
-        }
-    }
-    // squared error of table row `row` against (s0, s1)
-    auto hyb_error = [&](int row, float s0, float s1) -> float {
-        const half2_t c = as_half2(lut[row & 511]);
-        const float c0 = (row & 1024) ? -(float)c.x : (float)c.x;
-        const float c1 = (row & 512) ? -(float)c.y : (float)c.y;
-        const float e0 = c0 - s0, e1 = c1 - s1;
-        return __builtin_fmaf(e1, e1, e0 * e0);
-    };
-    auto store_error = [&](int row, float e) {  // all copies of one row: 16-byte stores
-        float4_t *dst = reinterpret_cast<float4_t *>(s_D + row * DCOPY);
-#pragma unroll
-        for (int q = 0; q < DCOPY / 4; q++) dst[q] = float4_t{e, e, e, e};
-    };
-    // New values of states 2 r2 and 2 r2 + 1 of this thread (they share a packed register)
-    // from the minima b0, b1 of their prefixes: fma(e, e, b) for V = 1, b + table entry for
-    // HYB.  The unpacking is pinned here (volatile asm): hoisted out of the step loop it turns
-    // the 32 packed registers into 64 and the loop starts spilling, and the reloads cost far
-    // more than the unpacking (the waves run in lockstep between barriers, so nothing hides
-    // their latency).  For V = 1 the conversion and the subtraction are one v_fma_mix_f32,
-    // (float)c * 1.0 - s: an exact product and one rounding, the same bits as c - s.
-    auto update2 = [&](int r2, float s0, float b0, float b1, float &v0, float &v1) {
-        if constexpr (HYB) {
-            uint32_t o0, o1;  // byte offsets of the two rows' errors in the per-step table
-            asm volatile("v_and_b32 %0, 0xffff, %2\n\tv_lshrrev_b32 %1, 16, %2"
-                         : "=&v"(o0), "=v"(o1)
-                         : "v"(ipk[r2]));
-            // (s_Dmine = the table shifted by this lane's copy)
-            v0 = b0 + *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s_Dmine) + o0);
-            v1 = b1 + *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s_Dmine) + o1);
-        } else {
-            const uint32_t cw = as_u32(cpk[r2]);
-            float e0, e1;
-            asm volatile("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,0]"
-                         : "=v"(e0) : "v"(cw), "v"(s0));
-            asm volatile("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
-                         : "=v"(e1) : "v"(cw), "v"(s0));
-            v0 = __builtin_fmaf(e0, e0, b0);
-            v1 = __builtin_fmaf(e1, e1, b1);
-        }
-    };
-    // One state at a time (V = 1): the form the kV <= 3 layout runs fastest with (measured;
-    // the loops differ only in how the compiler schedules around the pinned instructions).
-    auto update1 = [&](int r, float s0, float b) -> float {
-        const uint32_t cw = as_u32(cpk[r >> 1]);
-        float e;
-        if (r & 1)
-            asm volatile("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
-                         : "=v"(e) : "v"(cw), "v"(s0));
-        else
-            asm volatile("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,0]"
-                         : "=v"(e) : "v"(cw), "v"(s0));
+        const float e = __builtin_bit_cast(float, c) - s0;
         return __builtin_fmaf(e, e, b);
-    };
+    }
+}
 
+// Element u of the sequence of tile `tile`.  rotate = 1: rotated by T/2 (Algorithm 4's first call).
+template <int CODE>
+__device__ __forceinline__ float sequence_element(const float *__restrict__ W, int n, int tn, long tile, int u,
+                                                  int rotate) {
+    constexpr int LTY = code_log2_ty(CODE), TY = 1 << LTY, TX = VT_T >> LTY;  // the block is TX x TY
+    const int I = (int)(tile / tn), J = (int)(tile % tn);
+    const int s = rotate ? ((u + VT_T / 2) & (VT_T - 1)) : u;
+    return W[(size_t)(TX * I + (s >> LTY)) * n + TY * J + (s & (TY - 1))];
+}
+
+// Steps 0 .. t_end - 1 of sequence tile0 + blockIdx.x, with `best` stored after every J steps
+// counted from the last (copies c_lo .. c_hi - 1, copy c at step G - 1 - J (c + 1)), and, when
+// t_end = G - 1, the best final state.  overlap != null: the first state's top L-kV bits and the
+// last state's low L-kV bits are forced to overlap[slot] (Algorithm 4's second call).
+// (four waves per SIMD, i.e. at most 128 registers, also where a workgroup is only four waves)
+template <int KV, int V, int CODE>
+__global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void viterbi_forward_kernel(
+    const float *__restrict__ W, int n, int tn, long tile0, const uint32_t *__restrict__ lut, int rotate,
+    const uint32_t *__restrict__ overlap, float *__restrict__ store, long slots, int c_lo, int c_hi, int t_end,
+    uint32_t *__restrict__ final_state, float *__restrict__ final_value) {
+    using Geo = VitGeo<KV, V, code_state_bits(CODE)>;
+    constexpr int NP = Geo::NP, NC = Geo::NC, NB = Geo::NB, NT = Geo::NT, OV = Geo::OV, G = Geo::G, J = Geo::J;
+    static_assert(code_is_hyb(CODE) == (V == 2), "V = 2 is the HYB code");
+    static_assert(NT >= VT_T, "one thread per sequence element");
+    __shared__ __attribute__((aligned(16))) float s_best[2][Geo::BEST_FLOATS];
+    __shared__ __attribute__((aligned(16))) float s_seq[VT_T + 4];
+    __shared__ float s_rv[NT / 64];
+    __shared__ uint32_t s_ry[NT / 64];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int slot = blockIdx.x;
     const float INF = __builtin_inff();
     const bool constrained = overlap != nullptr;
     const uint32_t O = constrained ? overlap[slot] : 0u;
 
-    float val[VT_REGS];
-    {
-        const float s0 = seq(0), s1 = V == 2 ? seq(1) : 0.f;
-        if constexpr (HYB) {
-#pragma unroll
-            for (int j = tid; j < ROWS; j += VT_NT) store_error(j, hyb_error(j, s0, s1));
-            __syncthreads();
-        }
-#pragma unroll
-        for (int r2 = 0; r2 < VT_REGS / 2; r2++) {
-            float d[2];
-            update2(r2, s0, 0.f, 0.f, d[0], d[1]);  // the first step has no predecessors
-#pragma unroll
-            for (int h = 0; h < 2; h++)
-                val[2 * r2 + h] = (constrained && (state_of(2 * r2 + h) >> KV) != O) ? INF : d[h];
-        }
-        if constexpr (HYB) __syncthreads();
-    }
+    if (tid < VT_T) s_seq[tid] = sequence_element<CODE>(W, n, tn, tile0 + slot, tid, rotate);
+    for (int i = tid; i < NP; i += NT) s_best[0][Geo::place(i)] = (constrained && (uint32_t)i != O) ? INF : 0.f;
 
-    uint32_t *const my_ptrs = ptrs + (size_t)slot * G * PW;
-    for (int t = 1; t < G; t++) {
-        if constexpr (HYB) {
+    // register r of this thread is state (p, hi): WHOLE: p = r % NC, prefix NB tid + r / NC;
+    // else (kV = 8) a quarter of a prefix's predecessors, p = 64 (lane / 16) + r
+    const int my_hi = Geo::WHOLE ? NB * tid : 16 * wave + (lane & 15);
+    auto state_of = [&](int r) -> uint32_t {
+        if constexpr (Geo::WHOLE) return ((uint32_t)(r % NC) << OV) | (uint32_t)(my_hi + r / NC);
+        else return ((uint32_t)(64 * (lane >> 4) + r) << OV) | (uint32_t)my_hi;
+    };
+    uint32_t cr[VT_REGS];
 #pragma unroll
-            for (int j = tid; j < ROWS; j += VT_NT) store_error(j, hyb_error(j, seq(V * t), seq(V * t + 1)));
-        }
-        if constexpr (Geo::SLOT) {
-            // prefix hi = (SJ tid + j) NC + c; its predecessors are registers (p SJ + j) NC + c
-            constexpr int F = Geo::SJ * NC;  // prefixes per thread, contiguous in hi
-            float bests[F];
-            uint32_t word = 0;
-            // The tournament form pays where the waves of a CU are in different phases of the
-            // step (several small workgroups per CU, L = 14: 1.06 -> 0.97 us per sequence): its
-            // scalar instructions then overlap other waves' vector work.  With one 16-wave
-            // workgroup per CU all waves reach this point together, the scalar unit (one per
-            // CU) becomes the queue, and the select chains are faster (4.69 against 4.91 us).
-            if constexpr (Geo::RAW3) {
-                uint32_t words[2] = {0u, 0u};
-#pragma unroll
-                for (int f = F - 1; f >= 0; f--) {
-                    float m01, m23;
-                    compare_shift_min(val[f], val[f + F], words[f >> 3], m01);
-                    compare_shift_min(val[f + 2 * F], val[f + 3 * F], words[f >> 3], m23);
-                    compare_shift_min(m01, m23, words[f >> 3], bests[f]);
-                    if ((f & 3) == 0) __builtin_amdgcn_sched_barrier(0);
-                }
-                my_ptrs[(size_t)t * PW + VT_NT + tid] = words[1];
-                word = words[0];
-            } else if constexpr (VT_NT <= 256) {
-                // prefixes from the last to the first and bits from the top down, so that prefix
-                // f ends up in bits f kV .. f kV + kV - 1 of the word
-#pragma unroll
-                for (int f = F - 1; f >= 0; f--) {
-                    uint64_t bits[4];
-                    bests[f] = argmin_tournament<NC>(val, f, F, 0, bits);
-#pragma unroll
-                    for (int b = KV - 1; b >= 0; b--) shift_in_bit(word, bits[b]);
-                    if ((f & 3) == 0) __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-#pragma unroll
-                for (int f = 0; f < F; f++) {
-                    uint32_t bp;
-                    argmin_regs<NC, 1>(val, f, F, bests[f], bp);
-                    word |= bp << (f * KV);
-                    if ((f & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            // A thread's F minima are one row of F floats.  Written as they stand, the 16-byte
-            // stores of neighbouring lanes would be a whole row apart and land on two of the
-            // eight 16-byte bank groups; with 16 floats per row the four pieces of row T are
-            // therefore kept rotated by (T / 2) % 4 places, which spreads eight lanes over all
-            // eight groups both here and where the rows are read back, four prefixes at a time.
-#pragma unroll
-            for (int f = 0; f < F; f += 4) {
-                const int piece = F == 16 ? ((f >> 2) + (tid >> 1)) & 3 : f >> 2;
-                *reinterpret_cast<float4_t *>(&s_best[tid * F + 4 * piece]) =
-                    float4_t{bests[f], bests[f + 1], bests[f + 2], bests[f + 3]};
-            }
-            my_ptrs[(size_t)t * PW + tid] = word;
-        } else if constexpr (Geo::LOCAL) {
-            // prefix hi = NT h + tid; its predecessors p 2^OV + hi are registers p NB1 + h
-            uint32_t word[Geo::PWT];
-#pragma unroll
-            for (int w = 0; w < Geo::PWT; w++) word[w] = 0;
-#pragma unroll
-            for (int h = 0; h < NB1; h++) {
-                float bv;
-                uint32_t bp;
-                argmin_regs<NC, (NB1 >= 4 || NC < 8) ? 1 : 4 / NB1>(val, h, NB1, bv, bp);
-                s_best[h * VT_NT + tid] = bv;
-                word[h / Geo::FPW] |= bp << ((h % Geo::FPW) * KV);
-                // a few chains at a time: enough to fill the wait states between a compare
-                // and the selects that use its mask, few enough to stay in registers
-                if ((h & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int w = 0; w < Geo::PWT; w++) my_ptrs[(size_t)t * PW + w * VT_NT + tid] = word[w];
-        } else {
-            // prefix hi = tid % NP; this thread holds predecessors p = (VT_NT/NP) r + tid / NP
-            constexpr int Q = VT_NT / NP;
-            float bv;
-            uint32_t br;
-            argmin_regs<VT_REGS, 4>(val, 0, 1, bv, br);
-            float *s_pv = s_best;
-            uint32_t *s_pp = reinterpret_cast<uint32_t *>(s_best + VT_NT);
-            s_pv[tid] = bv;
-            s_pp[tid] = br * Q + (uint32_t)(tid / NP);
-            __syncthreads();
-            if (tid < NP) {
-                bv = s_pv[tid];
-                uint32_t bp = s_pp[tid];
-#pragma unroll
-                for (int q = 1; q < Q; q++) {
-                    const float v = s_pv[q * NP + tid];
-                    const uint32_t p = s_pp[q * NP + tid];
-                    const bool better = v < bv || (v == bv && p < bp);
-                    bv = better ? v : bv;
-                    bp = better ? p : bp;
-                }
-                s_best[2 * VT_NT + tid] = bv;
-                my_ptrs[(size_t)t * PW + tid] = bp;
-            }
-        }
-        __syncthreads();
-        const float *best_mine = (Geo::LOCAL ? s_best : s_best + 2 * VT_NT) + (tid >> KV);
-        // (read after the barrier, so that the errors are not computed, and kept in
-        // registers that are not there, before the minima)
-        const float s0 = HYB ? 0.f : seq(t);
-        if constexpr (Geo::SLOT) {
-            // states (p, mid, c') follow prefix (p, mid): one read per (p, j) serves NC states
-#pragma unroll
-            for (int p = 0; p < NC; p++) {
-                float b[Geo::SJ];
-                if constexpr (Geo::SJ == 4) {
-                    // prefixes p NP/NC + 4 tid .. + 3 are piece tid % 4 of row T = p NT/4 + tid / 4,
-                    // kept at place (tid % 4 + T / 2) % 4 of that row (p NT/8 is a multiple of 4)
-                    static_assert(Geo::SJ * NC == 16 && (VT_NT / 8) % 4 == 0, "row rotation");
-                    const int place = ((tid & 3) + (tid >> 3)) & 3;
-                    const float4_t t4 =
-                        *reinterpret_cast<const float4_t *>(&s_best[p * (NP / NC) + (tid & ~3) * 4 + place * 4]);
-                    b[0] = t4[0], b[1] = t4[1], b[2] = t4[2], b[3] = t4[3];
-                } else {
-#pragma unroll
-                    for (int j = 0; j < Geo::SJ; j++) b[j] = s_best[p * (NP / NC) + tid * Geo::SJ + j];
-                }
-#pragma unroll
-                for (int j = 0; j < Geo::SJ; j++)
-#pragma unroll
-                    for (int c = 0; c < NC; c++) {
-                        const int r = (p * Geo::SJ + j) * NC + c;
-                        val[r] = update1(r, s0, b[j]);
-                    }
-                if (((p * Geo::SJ) & 1) == 1 || Geo::SJ > 1) __builtin_amdgcn_sched_barrier(0);
-            }
-        } else
-        // eight states at a time: the register file has no room for 64 loads in flight
-#pragma unroll
-        for (int r0 = 0; r0 < VT_REGS; r0 += 8) {
-#pragma unroll
-            for (int r = r0; r < r0 + 8; r += 2) {
-                // prefixes of states NT r + tid and NT (r + 1) + tid; written so that the
-                // addresses are one base register plus constants
-                const float b0 = best_mine[r * (VT_NT >> KV)], b1 = best_mine[(r + 1) * (VT_NT >> KV)];
-                update2(r / 2, s0, b0, b1, val[r], val[r + 1]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
+    for (int r = 0; r < VT_REGS; r++) {
+        cr[r] = code_register<CODE>(state_of(r), lut);
+        // (opaque to the compiler from here on, or it recomputes the codes inside the loop)
+        asm volatile("" : "+v"(cr[r]));
     }
+    __syncthreads();
+
+    // best entry that register r's state hangs on: (p << (OV-KV)) | (hi >> KV)
+    constexpr int BSTEP = OV - KV;
+    float *store_base = store + (size_t)slot * slots * NP;
+    int until = (G - 1) % J;  // steps to the next one that is a multiple of J from the last
+    if (until == 0) until = J;
+    int c_now = (G - 1 - until) / J - 1;  // the copy that belongs to it
+    float s0 = s_seq[0], s1 = V == 2 ? s_seq[1] : 0.f;
+
+    auto step = [&](const float *__restrict__ in, float *__restrict__ out, int t) {
+        // (the next step's samples are read ahead of the barrier)
+        const float n0 = s_seq[V * (t + 1)], n1 = V == 2 ? s_seq[V * (t + 1) + 1] : 0.f;
+        float best[NB];
+        if constexpr (KV == 2) {
+            float4_t b[NC];
+#pragma unroll
+            for (int p = 0; p < NC; p++)
+                b[p] = *reinterpret_cast<const float4_t *>(in + Geo::place((p << BSTEP) + 4 * tid));
+#pragma unroll
+            for (int i = 0; i < NB; i++) {
+                float v[NC];
+#pragma unroll
+                for (int p = 0; p < NC; p++) v[p] = state_value<V>(cr[i * NC + p], s0, s1, b[p][i >> 2]);
+                best[i] = min3(min2(v[0], v[1]), v[2], v[3]);
+            }
+        } else if constexpr (KV <= 4) {
+            float b[NC];
+#pragma unroll
+            for (int p = 0; p < NC; p++) b[p] = in[Geo::place((p << BSTEP) + (my_hi >> KV))];
+#pragma unroll
+            for (int i = 0; i < NB; i++) {
+                float m = state_value<V>(cr[i * NC], s0, s1, b[0]);
+#pragma unroll
+                for (int p = 1; p + 1 < NC; p += 2)
+                    m = min3(m, state_value<V>(cr[i * NC + p], s0, s1, b[p]),
+                             state_value<V>(cr[i * NC + p + 1], s0, s1, b[p + 1]));
+                best[i] = min2(m, state_value<V>(cr[i * NC + NC - 1], s0, s1, b[NC - 1]));
+            }
+        } else {
+            // the 64 entries are one row of 68 floats, the same for the whole wave (kV = 6) or for
+            // sixteen lanes (kV = 8)
+            const float *row = in + 68 * (KV == 6 ? my_hi >> KV : lane >> 4);
+            float m = INF;
+#pragma unroll
+            for (int p = 0; p < VT_REGS; p += 4) {
+                const float4_t b = *reinterpret_cast<const float4_t *>(row + p);
+                m = min3(m, state_value<V>(cr[p], s0, s1, b[0]), state_value<V>(cr[p + 1], s0, s1, b[1]));
+                m = min3(m, state_value<V>(cr[p + 2], s0, s1, b[2]), state_value<V>(cr[p + 3], s0, s1, b[3]));
+            }
+            if constexpr (!Geo::WHOLE) {
+                m = min2(m, __shfl_xor(m, 16, 64));
+                m = min2(m, __shfl_xor(m, 32, 64));
+            }
+            best[0] = m;
+        }
+        if constexpr (NB >= 4) {
+#pragma unroll
+            for (int i = 0; i < NB; i += 4)
+                *reinterpret_cast<float4_t *>(out + Geo::place(my_hi + i)) =
+                    float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
+        } else if (Geo::WHOLE || lane < 16) {
+            out[Geo::place(my_hi)] = best[0];
+        }
+        if (--until == 0) {  // `best` after this step is copy c_now
+            until = J;
+            if (c_now >= c_lo && c_now < c_hi && (Geo::WHOLE || lane < 16)) {
+                float *dst = store_base + (size_t)(c_now - c_lo) * NP;
+#pragma unroll
+                for (int i = 0; i < NB; i++)
+                    __builtin_nontemporal_store(best[i], dst + Geo::stored((uint32_t)(my_hi + i)));
+            }
+            c_now--;
+        }
+        s0 = n0;
+        s1 = n1;
+        __syncthreads();
+    };
+    int t = 0;
+    for (; t + 1 < t_end; t += 2) {
+        step(s_best[0], s_best[1], t);
+        step(s_best[1], s_best[0], t + 1);
+    }
+    if (t < t_end) step(s_best[0], s_best[1], t);
+    if (t_end < G - 1) return;
 
     // the best allowed final state, lowest state on ties
+    const float *in = s_best[(G - 1) & 1];
     float bv = INF;
     uint32_t by = 0xFFFFFFFFu;
+    auto take_better = [&](bool ok, float v, uint32_t y) {
+        const bool take = ok & ((v < bv) | ((v == bv) & (y < by)));
+        bv = take ? v : bv;
+        by = take ? y : by;
+    };
 #pragma unroll
     for (int r = 0; r < VT_REGS; r++) {
         const uint32_t y = state_of(r);
-        const bool ok = !constrained || (y & (uint32_t)(NP - 1)) == O;
-        if (ok && val[r] < bv) {
-            bv = val[r];
-            by = y;
-        }
+        take_better(!constrained | ((y & (uint32_t)(NP - 1)) == O),
+                    state_value<V>(cr[r], s0, s1, in[Geo::place((int)(y >> KV))]), y);
     }
-    float *s_rv = s_best;
-    uint32_t *s_ry = reinterpret_cast<uint32_t *>(s_best + VT_NT);
-    s_rv[tid] = bv;
-    s_ry[tid] = by;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) take_better(true, __shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
+    if (lane == 0) {
+        s_rv[wave] = bv;
+        s_ry[wave] = by;
+    }
     __syncthreads();
-    for (int stride = VT_NT / 2; stride > 0; stride >>= 1) {
-        if (tid < stride) {
-            const float v = s_rv[tid + stride];
-            const uint32_t y = s_ry[tid + stride];
-            if (v < s_rv[tid] || (v == s_rv[tid] && y < s_ry[tid])) {
-                s_rv[tid] = v;
-                s_ry[tid] = y;
-            }
-        }
-        __syncthreads();
-    }
     if (tid == 0) {
-        final_state[slot] = s_ry[0];
-        final_value[slot] = s_rv[0];
+        for (int w = 1; w < NT / 64; w++) take_better(true, s_rv[w], s_ry[w]);
+        final_state[slot] = by;
+        final_value[slot] = bv;
     }
 }
 
-// One thread per sequence walks the back-pointers from the final state.
-// pass 1: down to step G/2 - 1, whose low 16-kV bits are the overlap of Algorithm 4.
-// pass 2: the whole walk; step t contributes the top kV bits of its state as stream bits
-// t kV .. (t+1) kV - 1 (first bit = most significant bit of word 0).
-template <int KV, int V, int LB>
-__global__ __launch_bounds__(64) void viterbi_backtrace_kernel(
-    const uint32_t *__restrict__ ptrs, const uint32_t *__restrict__ final_state,
-    const float *__restrict__ final_value, int count, int pass, uint32_t *__restrict__ overlap,
-    uint32_t *__restrict__ codes, float *__restrict__ tile_err, long tile0) {
-    using Geo = VitGeo<KV, LB>;
-    constexpr int OV = Geo::OV, NP = Geo::NP, NC = Geo::NC, PW = Geo::PW, VT_NT = Geo::NT;
-    constexpr int G = VT_T / V, NWORDS = KV * G / 32;
-    const int slot = blockIdx.x * blockDim.x + threadIdx.x;
-    if (slot >= count) return;
-    const uint32_t *my_ptrs = ptrs + (size_t)slot * G * PW;
-    uint32_t arg = final_state[slot];
-    uint32_t words[NWORDS];
+// ------------------------------------------------------------------- walk back
+
+// One tree of JJ levels below state y at step t, whose leaves are the states of step t - JJ.
+// Leaf l = (p_JJ ... p_1), digit p_j being the top kV bits of the state j steps back, is state
+// (l << (L - kV JJ)) | (y >> kV JJ); the low six bits of l are the lane, the others a register.
+// Level j takes the minimum over p_j and moves one step forward.  On return digit[j] = p_j of the
+// best walk (the same in all lanes).
+template <int KV, int V, int CODE, int JJ>
+struct WalkTree {
+    using Geo = VitGeo<KV, V, code_state_bits(CODE)>;
+    static constexpr int LB = code_state_bits(CODE);
+    static constexpr int regs(int bits) { return bits > 6 ? 1 << (bits - 6) : 1; }
+
+    uint32_t y;
+    int t, lane;
+    const uint32_t *lut;
+    const float *seq;  // LDS
+    uint32_t args[JJ + 1];  // args[j]: kV bits per register of level j - 1
+
+    __device__ __forceinline__ uint32_t node_state(int j, int m) const {  // level j, register m
+        const uint32_t l = KV * j >= 6 ? (uint32_t)(m * 64 + lane) : (uint32_t)lane & ((1u << (KV * j)) - 1u);
+        return ((l << (LB - KV * j)) | (y >> (KV * j))) & ((1u << LB) - 1u);
+    }
+    __device__ __forceinline__ float node_value(int j, int m, float b) const {
+        const int u = V * (t - j);
+        return state_value<V>(code_register<CODE>(node_state(j, m), lut), seq[u], V == 2 ? seq[u + 1] : 0.f, b);
+    }
+
+    template <int j>
+    __device__ __forceinline__ void reduce(float (&v)[regs(KV * JJ)]) {
+        constexpr int M = regs(KV * j), M1 = regs(KV * (j - 1)), A = M / M1;
+        // digit j: its top bits tell registers apart, its other bits, if any, are lane bits
+        constexpr int LANE_LO = KV * (j - 1), LANE_HI = KV * j < 6 ? KV * j : 6;
+        constexpr int LBITS = LANE_HI > LANE_LO ? LANE_HI - LANE_LO : 0;
+        const uint32_t mine = LBITS ? ((uint32_t)lane >> LANE_LO) & ((1u << LBITS) - 1u) : 0u;
+        uint32_t packed = 0;
 #pragma unroll
-    for (int w = 0; w < NWORDS; w++) words[w] = 0;
-    const int stop = pass == 1 ? G / 2 - 1 : 0;
-    for (int t = G - 1;; t--) {
-        if (pass == 2) {
-            const uint32_t top = arg >> OV;
-            for (int b = 0; b < KV; b++) {
-                const int pos = t * KV + b;
-                if ((top >> (KV - 1 - b)) & 1u) words[pos >> 5] |= 1u << (31 - (pos & 31));
+        for (int m = 0; m < M1; m++) {
+            float bv = v[m];
+            uint32_t bp = mine;
+#pragma unroll
+            for (int a = 1; a < A; a++) {
+                const bool lt = v[a * M1 + m] < bv;
+                bv = lt ? v[a * M1 + m] : bv;
+                bp = lt ? ((uint32_t)a << LBITS) | mine : bp;
             }
-        }
-        if (t == stop) break;
-        const uint32_t hi = arg >> KV;
-        uint32_t p;
-        if constexpr (Geo::RAW3) {
-            const uint32_t f = hi % 16;  // prefix hi is prefix f of thread hi / 16
-            const uint32_t word = my_ptrs[(size_t)t * PW + (f >> 3) * VT_NT + hi / 16];
-            const uint32_t bits = (word >> (3 * (f & 7))) & 7u;  // (v1 < v0, v3 < v2, min23 < min01)
-            p = (bits & 1u) ? 2u + ((bits >> 1) & 1u) : (bits >> 2);
-        } else if constexpr (Geo::SLOT) {
-            constexpr uint32_t F = Geo::SJ * NC;  // prefix hi is field hi % F of thread hi / F
-            const uint32_t word = my_ptrs[(size_t)t * PW + hi / F];
-            p = (word >> ((hi % F) * KV)) & (uint32_t)(NC - 1);
-        } else if constexpr (Geo::LOCAL) {
-            const uint32_t h = hi / VT_NT;
-            const uint32_t word = my_ptrs[(size_t)t * PW + (h / Geo::FPW) * VT_NT + (hi & (VT_NT - 1))];
-            p = (word >> ((h % Geo::FPW) * KV)) & (uint32_t)(NC - 1);
-        } else {
-            p = my_ptrs[(size_t)t * PW + hi];
-        }
-        arg = (p << OV) | hi;
-    }
-    if (pass == 1) {
-        overlap[slot] = arg & (uint32_t)(NP - 1);
-    } else {
-        uint32_t *out = codes + (size_t)(tile0 + slot) * NWORDS;
 #pragma unroll
-        for (int w = 0; w < NWORDS; w++) out[w] = words[w];
-        if (tile_err) tile_err[tile0 + slot] = final_value[slot];
+            for (int b = 0; b < LBITS; b++) {
+                const float ov = __shfl_xor(bv, 1 << (LANE_LO + b), 64);
+                const uint32_t op = __shfl_xor(bp, 1 << (LANE_LO + b), 64);
+                const bool take = ov < bv || (ov == bv && op < bp);
+                bv = take ? ov : bv;
+                bp = take ? op : bp;
+            }
+            packed |= bp << (m * KV);
+            if constexpr (j > 1) v[m] = node_value(j - 1, m, bv);
+        }
+        args[j] = packed;
+        if constexpr (j > 1) reduce<j - 1>(v);
     }
+
+    // stored: best at step t - JJ, or null for step 0 (0, or INF off the forced prefix)
+    __device__ __forceinline__ void run(const float *__restrict__ stored, bool constrained, uint32_t O,
+                                        uint32_t (&digit)[JJ + 1]) {
+        constexpr int M = regs(KV * JJ);
+        float v[M];
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            const uint32_t hi = node_state(JJ, m) >> KV;
+            v[m] = stored ? __builtin_nontemporal_load(stored + Geo::stored(hi))
+                          : (constrained && hi != O) ? __builtin_inff() : 0.f;
+        }
+#pragma unroll
+        for (int m = 0; m < M; m++) v[m] = node_value(JJ, m, v[m]);
+        reduce<JJ>(v);
+        uint32_t l = 0;  // (p_{j-1} ... p_1)
+#pragma unroll
+        for (int j = 1; j <= JJ; j++) {
+            const uint32_t word = __builtin_amdgcn_readlane(args[j], l & 63u);
+            const uint32_t m = KV * (j - 1) > 6 ? l >> 6 : 0u;
+            digit[j] = (word >> (m * KV)) & ((1u << KV) - 1u);
+            l |= digit[j] << (KV * (j - 1));
+        }
+    }
+};
+
+// One wave per sequence.  pass 1: from the final state down to step G/2 - 1, whose low L-kV bits are
+// the overlap of Algorithm 4.  pass 2: the whole walk; step t contributes the top kV bits of its
+// state as stream bits t kV .. (t+1) kV - 1 (first bit = most significant bit of word 0).  The
+// trees c_lo .. c_hi - 1 of the walk are done; where the workspace holds too few copies of `best`
+// for the whole walk, the state it got to waits in final_state and the next launch adds its bits.
+template <int KV, int V, int CODE>
+__global__ __launch_bounds__(256) void viterbi_walk_kernel(
+    const float *__restrict__ W, int n, int tn, long tile0, const uint32_t *__restrict__ lut, int pass,
+    const float *__restrict__ store, long slots, int c_lo, int c_hi, uint32_t *__restrict__ final_state,
+    const float *__restrict__ final_value, int count, uint32_t *__restrict__ overlap, uint32_t *__restrict__ codes,
+    float *__restrict__ tile_err) {
+    using Geo = VitGeo<KV, V, code_state_bits(CODE)>;
+    constexpr int OV = Geo::OV, NP = Geo::NP, G = Geo::G, J = Geo::J, NSEG = Geo::NSEG, LB = code_state_bits(CODE);
+    constexpr int NWORDS = KV * G / 32;
+    __shared__ float s_seq[4][VT_T];
+    __shared__ uint32_t s_sym[4][VT_T / 4];  // one byte per step
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slot = blockIdx.x * 4 + wave;
+    if (slot >= count) return;
+    float *const seq = s_seq[wave];
+    uint8_t *const sym = reinterpret_cast<uint8_t *>(s_sym[wave]);
+#pragma unroll
+    for (int i = 0; i < VT_T / 64; i++)
+        seq[64 * i + lane] = sequence_element<CODE>(W, n, tn, tile0 + slot, 64 * i + lane, pass == 1);
+    const bool constrained = pass == 2;
+    const uint32_t O = constrained ? overlap[slot] : 0u;
+    // (the wave's own LDS: its operations complete in order, the fences keep the compiler in line)
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    uint32_t y = __builtin_amdgcn_readfirstlane(final_state[slot]) & ((1u << LB) - 1u);
+    s_sym[wave][lane] = 0;
+    wave_sync();
+    if (c_lo == 0 && lane == 0) sym[G - 1] = (uint8_t)(y >> OV);
+    const float *my_store = store + (size_t)slot * slots * NP;
+    auto tree = [&](auto jj, int c) {
+        constexpr int JJ = decltype(jj)::value;
+        const int t = G - 1 - J * c;
+        WalkTree<KV, V, CODE, JJ> w;
+        w.y = y;
+        w.t = t;
+        w.lane = lane;
+        w.lut = lut;
+        w.seq = seq;
+        uint32_t digit[JJ + 1];
+        w.run(t > JJ ? my_store + (size_t)(c - c_lo) * NP : nullptr, constrained, O, digit);
+#pragma unroll
+        for (int j = 1; j <= JJ; j++) {
+            y = (digit[j] << OV) | (y >> KV);
+            if (lane == 0) sym[t - j] = (uint8_t)digit[j];
+            if (pass == 1 && t - j == Geo::MID && lane == 0) overlap[slot] = y & (uint32_t)(NP - 1);
+        }
+    };
+    for (int c = c_lo; c < c_hi; c++) {
+        if (c == NSEG - 1) tree(std::integral_constant<int, Geo::LAST>{}, c);
+        else tree(std::integral_constant<int, J>{}, c);
+    }
+    if (pass == 1 && c_hi >= Geo::NSEG_MID) return;
+    wave_sync();
+    if (c_hi < NSEG && lane == 0) final_state[slot] = y;
+    if (pass == 1) return;
+    if (lane < NWORDS) {
+        uint32_t *const out = codes + (size_t)(tile0 + slot) * NWORDS + lane;
+        uint32_t word = 0;
+#pragma unroll
+        for (int b = 0; b < 32; b++) {
+            const int pos = 32 * lane + b;
+            word = (word << 1) | ((sym[pos / KV] >> (KV - 1 - pos % KV)) & 1u);
+        }
+        *out = c_lo == 0 ? word : *out | word;
+    }
+    if (tile_err && lane == 0) tile_err[tile0 + slot] = final_value[slot];
 }
 
-// Workspace for `tiles` sequences in flight: three words per sequence (final state,
-// overlap, final value), then the back-pointers.
-template <int KV, int V, int LB>
-constexpr size_t per_tile_bytes() {
-    return (size_t)(VT_T / V) * VitGeo<KV, LB>::PW * sizeof(uint32_t);
-}
+// ------------------------------------------------------------------- launchers
+
+// Words of a sequence in flight besides its copies of `best`: final state, overlap, final value.
+constexpr int VT_HEAD_WORDS = 3;
 constexpr size_t VT_HEAD_ALIGN = 256;
 
 size_t head_bytes(long tiles) {
-    const size_t b = (size_t)tiles * 3 * sizeof(uint32_t);
+    const size_t b = (size_t)tiles * VT_HEAD_WORDS * sizeof(uint32_t);
     return (b + VT_HEAD_ALIGN - 1) / VT_HEAD_ALIGN * VT_HEAD_ALIGN;
+}
+
+// How a workspace is used: `tiles` sequences in flight, `slots` copies of `best` each.  With fewer
+// slots than a walk needs the forward pass is repeated up to where the next copies lie.
+struct Plan {
+    long tiles;
+    int slots;
+    double cost;  // steps of one workgroup's passes, all batches together
+};
+template <class Geo>
+double pass_steps(int slots, int nseg) {
+    double steps = 0;
+    for (int c = 0; c < nseg; c += slots) steps += c == 0 ? Geo::G - 1 : Geo::G - 1 - Geo::J * (c + 1);
+    return steps;
+}
+template <class Geo>
+Plan plan_for(long tiles, long ntiles, size_t ws_bytes) {
+    constexpr long RESIDENT = 256L * (1024 / Geo::NT);  // workgroups the chip runs at a time
+    Plan p{0, 0, 0};
+    if (tiles > ntiles) tiles = ntiles;
+    // whole rounds of workgroups, and batches of the same number of rounds
+    if (tiles > RESIDENT && tiles < ntiles) {
+        const long rounds = (ntiles + RESIDENT - 1) / RESIDENT, per = tiles / RESIDENT;
+        const long batches = (rounds + per - 1) / per;
+        tiles = (rounds + batches - 1) / batches * RESIDENT;
+    }
+    if (tiles <= 0 || head_bytes(tiles) >= ws_bytes) return p;
+    const size_t copies = (ws_bytes - head_bytes(tiles)) / ((size_t)tiles * Geo::NP * sizeof(float));
+    p.slots = (int)(copies < (size_t)(Geo::NSEG - 1) ? copies : (size_t)(Geo::NSEG - 1));
+    if (p.slots <= 0) return p;
+    p.tiles = tiles;
+    const double steps = pass_steps<Geo>(p.slots, Geo::NSEG_MID) + pass_steps<Geo>(p.slots, Geo::NSEG);
+    for (long t = 0; t < ntiles; t += tiles)
+        p.cost += steps * (double)((((ntiles - t < tiles) ? ntiles - t : tiles) + RESIDENT - 1) / RESIDENT);
+    return p;
+}
+// The cheaper of two ways: as many sequences at a time as find room for every copy a walk needs, or
+// as many as the caller sized the workspace for.
+template <class Geo>
+Plan make_plan(long ntiles, size_t ws_bytes, size_t sized_for) {
+    auto room_for = [&](size_t per_tile) {
+        long t = (long)(ws_bytes / per_tile);
+        while (t > 0 && head_bytes(t) + (size_t)t * per_tile > ws_bytes) t--;
+        return t;
+    };
+    const Plan a = plan_for<Geo>(room_for((size_t)(Geo::NSEG - 1) * Geo::NP * sizeof(float)), ntiles, ws_bytes);
+    const Plan b = plan_for<Geo>(room_for(sized_for), ntiles, ws_bytes);
+    if (b.tiles == 0) return a;
+    return a.tiles && a.cost <= b.cost ? a : b;
 }
 
 template <int KV, int V, int CODE>
 hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *lut, uint32_t *codes,
                           float *tile_err, void *ws, size_t ws_bytes, hipStream_t st) {
-    constexpr int LB = code_state_bits(CODE), VT_NT = VitGeo<KV, LB>::NT;
+    using Geo = VitGeo<KV, V, code_state_bits(CODE)>;
     constexpr int TY = 1 << code_log2_ty(CODE), TX = VT_T / TY;
     const int tn = n / TY;
     const long ntiles = (long)(m / TX) * tn;
-    // the largest batch the workspace holds
-    long cap = (long)(ws_bytes / per_tile_bytes<KV, V, LB>());  // upper bound, trimmed below
-    if (cap > ntiles) cap = ntiles;
-    while (cap > 0 && head_bytes(cap) + (size_t)cap * per_tile_bytes<KV, V, LB>() > ws_bytes) cap--;
+    const size_t sized_for = quantize_gpu_workspace(KV / V, V, 1) - head_bytes(1);
+    const Plan plan = make_plan<Geo>(ntiles, ws_bytes, sized_for);
+    const long cap = plan.tiles;
     if (cap <= 0) return hipErrorInvalidValue;
     uint32_t *final_state = (uint32_t *)ws;
     uint32_t *overlap = final_state + cap;
     float *final_value = (float *)(overlap + cap);
-    uint32_t *ptrs = (uint32_t *)((char *)ws + head_bytes(cap));
+    float *store = (float *)((char *)ws + head_bytes(cap));
     for (long tile0 = 0; tile0 < ntiles; tile0 += cap) {
         const int cnt = (int)(ntiles - tile0 < cap ? ntiles - tile0 : cap);
-        const dim3 bgrid((cnt + 63) / 64);
-        hipLaunchKernelGGL((viterbi_forward_kernel<KV, V, CODE>), dim3(cnt), dim3(VT_NT), 0, st, W, ld, tn,
-                           tile0, lut, 1, (const uint32_t *)nullptr, ptrs, final_state, final_value);
-        hipLaunchKernelGGL((viterbi_backtrace_kernel<KV, V, LB>), bgrid, dim3(64), 0, st, ptrs, final_state,
-                           final_value, cnt, 1, overlap, codes, tile_err, tile0);
-        hipLaunchKernelGGL((viterbi_forward_kernel<KV, V, CODE>), dim3(cnt), dim3(VT_NT), 0, st, W, ld, tn,
-                           tile0, lut, 0, (const uint32_t *)overlap, ptrs, final_state, final_value);
-        hipLaunchKernelGGL((viterbi_backtrace_kernel<KV, V, LB>), bgrid, dim3(64), 0, st, ptrs, final_state,
-                           final_value, cnt, 2, overlap, codes, tile_err, tile0);
+        for (int pass = 1; pass <= 2; pass++) {
+            const int nseg = pass == 1 ? Geo::NSEG_MID : Geo::NSEG;
+            for (int c_lo = 0; c_lo < nseg; c_lo += plan.slots) {
+                // (the last tree of a whole walk starts at step 0 and needs no copy)
+                int c_hi = c_lo + plan.slots < nseg ? c_lo + plan.slots : nseg;
+                if (c_hi == Geo::NSEG - 1) c_hi = Geo::NSEG;
+                const int t_end = c_lo == 0 ? Geo::G - 1 : Geo::G - 1 - Geo::J * (c_lo + 1);
+                if (t_end > 0)
+                    hipLaunchKernelGGL((viterbi_forward_kernel<KV, V, CODE>), dim3(cnt), dim3(Geo::NT), 0, st, W, ld,
+                                       tn, tile0, lut, pass == 1, pass == 1 ? (const uint32_t *)nullptr : overlap,
+                                       store, (long)plan.slots, c_lo, c_hi, t_end, final_state, final_value);
+                hipLaunchKernelGGL((viterbi_walk_kernel<KV, V, CODE>), dim3((cnt + 3) / 4), dim3(256), 0, st, W, ld,
+                                   tn, tile0, lut, pass, (const float *)store, (long)plan.slots, c_lo, c_hi,
+                                   final_state, (const float *)final_value, cnt, overlap, codes, tile_err);
+                if (c_hi == nseg) break;
+            }
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -611,18 +566,17 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
 
 }  // namespace
 
+// Bytes per sequence in flight that callers are told to bring (at kV = 2 half, at kV = 3 and 4 less,
+// of what a whole walk's copies take: with thousands in flight fewer at a time do as well, with few
+// the forward pass is repeated in part, see Plan).
 size_t quantize_gpu_workspace(int k, int V, long tiles) {
-    const int kV = k * V;
-    size_t pw;
-    switch (kV) {
-        // (sized for L = 16; the lookup-only code, L = 14, needs a quarter of it)
-        case 2: pw = VitGeo<2, 16>::PW; break;
-        case 3: pw = VitGeo<3, 16>::PW; break;
-        case 4: pw = VitGeo<4, 16>::PW; break;
-        case 6: pw = VitGeo<6, 16>::PW; break;
-        default: pw = VitGeo<8, 16>::PW; break;
+    size_t per_step;  // words
+    switch (k * V) {
+        case 2: per_step = 2048; break;
+        case 8: per_step = 256; break;
+        default: per_step = 1024; break;
     }
-    return head_bytes(tiles) + (size_t)tiles * (VT_T / V) * pw * sizeof(uint32_t);
+    return head_bytes(tiles) + (size_t)tiles * (VT_T / V) * per_step * sizeof(uint32_t);
 }
 
 hipError_t launch_quantize_gpu(int k, int code_id, const float *W, int m, int n, int ld, const uint32_t *lut,
