@@ -1,4 +1,5 @@
-"""ctypes binding of libqtip.so: same names as include/qtip.h, argument marshalling only.
+"""Binding of libqtip.so: same names as include/qtip.h, argument marshalling only (ctypes for what runs on
+the host, the _call extension for what enqueues GPU work).
 
 GPU entry points take torch tensors that already live on the device (or raw
 integer device pointers) and enqueue on torch's current stream unless a stream is
@@ -115,57 +116,82 @@ def _check(rc):
     return rc
 
 
+# The entry points that enqueue work are callable objects of the _call extension (csrc/qtip_call.cpp),
+# which turns their arguments into the C ones itself.
+_GPU_ENTRIES = ["qtip_rht", "qtip_rht_f32", "qtip_decode_matvec", "qtip_rht_decode_matvec",
+                "qtip_rht_decode_matvec_noalloc", "qtip_decode_matmat", "qtip_dequantize", "qtip_decode_states",
+                "qtip_quantize_gpu", "qtip_block_ldl", "qtip_quantize_ldlq"]
+_call = None
+
+
+def _connect():
+    """Give the entry points of _call the addresses of the loaded library's functions."""
+    import torch
+    L = lib()
+    # torch's own getters of the current device and of its current stream as an integer; without
+    # them (or without a GPU) _stream() asks the public interface
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if device is None or raw is None or not torch.cuda.is_available():
+        device = raw = None
+    else:
+        torch.cuda.init()
+    _call.hooks(_ptr, _stream, _check, _connect, device, raw)
+    for name in _GPU_ENTRIES:
+        _call.connect(getattr(_call, name), ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+
+
+def _load_call():
+    global _call
+    if _call is None:
+        import importlib
+        try:
+            _call = importlib.import_module("._call", __package__)
+        except ImportError as e:
+            raise FileNotFoundError(
+                f"the _call extension of {__package__} is missing ({e}): run `python -m paper_2406_11235_amd.build`"
+            ) from e
+        _call.hooks(_ptr, _stream, _check, _connect, None, None)
+    return _call
+
+
+def _entry(name):
+    """The callable for one entry point; a stand-in that looks for it when called where nothing is built yet."""
+    try:
+        return getattr(_load_call(), name)
+    except FileNotFoundError:
+        def entry(*args, **kwargs):
+            return getattr(_load_call(), name)(*args, **kwargs)
+        entry.__name__ = name
+        return entry
+
+
+qtip_rht = _entry("qtip_rht")  # (x, signs, n, block, batch, side, out, stream=None)
+qtip_rht_f32 = _entry("qtip_rht_f32")  # (x, signs, n, block, batch, side, out, stream=None)
+# (codes, L, k, V, code_id, lut, m, n, x, y, stream=None)
+qtip_decode_matvec = _entry("qtip_decode_matvec")
+# (codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y, xt_scratch=None, stream=None)
+qtip_rht_decode_matvec = _entry("qtip_rht_decode_matvec")
+# (codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y, stream=None)
+qtip_rht_decode_matvec_noalloc = _entry("qtip_rht_decode_matvec_noalloc")
+# (codes, L, k, V, code_id, lut, m, n, X, B, row_scale, Y, stream=None)
+qtip_decode_matmat = _entry("qtip_decode_matmat")
+# (codes, L, k, V, code_id, lut, m, n, W, stream=None)
+qtip_dequantize = _entry("qtip_dequantize")
+qtip_decode_states = _entry("qtip_decode_states")  # (states, count, L, V, code_id, lut, out, stream=None)
+# (W, m, n, L, k, V, code_id, lut, codes_out, tile_err, workspace, workspace_bytes, stream=None)
+qtip_quantize_gpu = _entry("qtip_quantize_gpu")
+qtip_block_ldl = _entry("qtip_block_ldl")  # (H, n, g, A_out, D_out, workspace, workspace_bytes, stream=None)
+# (W, A, m, n, L, k, V, code_id, lut, codes_out, What_out, tile_err, workspace, workspace_bytes, stream=None)
+qtip_quantize_ldlq = _entry("qtip_quantize_ldlq")
+
+
 def qtip_version():
     return int(lib().qtip_version())
 
 
 def qtip_last_error():
     return lib().qtip_last_error().decode()
-
-
-def qtip_rht(x, signs, n, block, batch, side, out, stream=None):
-    return _check(lib().qtip_rht(_ptr(x), _ptr(signs), n, block, batch, side, _ptr(out),
-                                 _stream(stream)))
-
-
-def qtip_rht_f32(x, signs, n, block, batch, side, out, stream=None):
-    return _check(lib().qtip_rht_f32(_ptr(x), _ptr(signs), n, block, batch, side, _ptr(out),
-                                     _stream(stream)))
-
-
-def qtip_decode_matvec(codes, L, k, V, code_id, lut, m, n, x, y, stream=None):
-    return _check(lib().qtip_decode_matvec(_ptr(codes), L, k, V, code_id, _ptr(lut), m, n,
-                                           _ptr(x), _ptr(y), _stream(stream)))
-
-
-def qtip_rht_decode_matvec(codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y,
-                           xt_scratch=None, stream=None):
-    return _check(lib().qtip_rht_decode_matvec(_ptr(codes), L, k, V, code_id, _ptr(lut), m, n, _ptr(x),
-                                               _ptr(signs_n), block, _ptr(row_scale), _ptr(y),
-                                               _ptr(xt_scratch), _stream(stream)))
-
-
-def qtip_rht_decode_matvec_noalloc(codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y,
-                                   stream=None):
-    return _check(lib().qtip_rht_decode_matvec_noalloc(_ptr(codes), L, k, V, code_id, _ptr(lut), m, n, _ptr(x),
-                                                       _ptr(signs_n), block, _ptr(row_scale), _ptr(y),
-                                                       _stream(stream)))
-
-
-def qtip_decode_matmat(codes, L, k, V, code_id, lut, m, n, X, B, row_scale, Y, stream=None):
-    return _check(lib().qtip_decode_matmat(_ptr(codes), L, k, V, code_id, _ptr(lut), m, n,
-                                           _ptr(X), B, _ptr(row_scale), _ptr(Y),
-                                           _stream(stream)))
-
-
-def qtip_dequantize(codes, L, k, V, code_id, lut, m, n, W, stream=None):
-    return _check(lib().qtip_dequantize(_ptr(codes), L, k, V, code_id, _ptr(lut), m, n, _ptr(W),
-                                        _stream(stream)))
-
-
-def qtip_decode_states(states, count, L, V, code_id, lut, out, stream=None):
-    return _check(lib().qtip_decode_states(_ptr(states), count, L, V, code_id, _ptr(lut),
-                                           _ptr(out), _stream(stream)))
 
 
 def qtip_quantize(W, m, n, L, k, V, code_id, lut=None):
@@ -186,28 +212,11 @@ def qtip_quantize_gpu_workspace(k, V, tiles):
     return int(lib().qtip_quantize_gpu_workspace(k, V, tiles))
 
 
-def qtip_quantize_gpu(W, m, n, L, k, V, code_id, lut, codes_out, tile_err, workspace,
-                      workspace_bytes, stream=None):
-    return _check(lib().qtip_quantize_gpu(_ptr(W), m, n, L, k, V, code_id, _ptr(lut),
-                                          _ptr(codes_out), _ptr(tile_err), _ptr(workspace),
-                                          workspace_bytes, _stream(stream)))
-
-
 def qtip_block_ldl_workspace(n):
     return int(lib().qtip_block_ldl_workspace(n))
-
-
-def qtip_block_ldl(H, n, g, A_out, D_out, workspace, workspace_bytes, stream=None):
-    return _check(lib().qtip_block_ldl(_ptr(H), n, g, _ptr(A_out), _ptr(D_out), _ptr(workspace),
-                                       workspace_bytes, _stream(stream)))
 
 
 def qtip_quantize_ldlq_workspace(m, n, k, V, tiles):
     return int(lib().qtip_quantize_ldlq_workspace(m, n, k, V, tiles))
 
 
-def qtip_quantize_ldlq(W, A, m, n, L, k, V, code_id, lut, codes_out, What_out, tile_err, workspace,
-                       workspace_bytes, stream=None):
-    return _check(lib().qtip_quantize_ldlq(_ptr(W), _ptr(A), m, n, L, k, V, code_id, _ptr(lut),
-                                           _ptr(codes_out), _ptr(What_out), _ptr(tile_err),
-                                           _ptr(workspace), workspace_bytes, _stream(stream)))

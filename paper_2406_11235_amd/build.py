@@ -1,11 +1,14 @@
-"""Build libqtip.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Build libqtip.so for gfx950 with hipcc (cross-compiles without a GPU), and the _call extension (plain C++)."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqtip.so")
+CALL = os.path.join(HERE, "_call.so")
+CALL_SOURCE = os.path.join(CSRC, "qtip_call.cpp")
 SOURCES = ["qtip_api.hip", "qtip_decode.hip", "qtip_lut14.hip", "qtip_rht.hip", "qtip_viterbi.hip", "qtip_ldlq.hip", "qtip_quantize.cpp"]
 HEADERS = ["qtip_device.h", "qtip_rht_device.h", "qtip_internal.h", os.path.join("..", "..", "include", "qtip.h")]
 
@@ -16,18 +19,29 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-pth
 
 
 def is_stale():
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS] + [os.path.abspath(__file__)]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
+    deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS] + [CALL_SOURCE, os.path.abspath(__file__)]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def build_call(verbose=False):
+    """Compile paper_2406_11235_amd/_call.so, the Python side of the entry points."""
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-I" + sysconfig.get_paths()["include"], CALL_SOURCE, "-o", CALL]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    subprocess.run(cmd, check=True)
 
 
 def build(force=True, extra_flags=(), verbose=False, out=None, jobs=None):
     """Compile every source into paper_2406_11235_amd/libqtip.so (or `out`): one hipcc
-    process per source file, a few at a time, then one link."""
+    process per source file, a few at a time, then one link.  Without `out` also _call.so."""
     if out is None and not force and not is_stale():
         return LIB
+    if out is None:
+        build_call(verbose)
     import concurrent.futures
     import tempfile
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

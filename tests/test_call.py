@@ -1,0 +1,33 @@
+"""Argument handling of the entry points' callable objects (host only: every call here is refused by the
+library's own checks or before it)."""
+import numpy as np
+import pytest
+
+import paper_2406_11235_amd as q
+from paper_2406_11235_amd import binding
+
+
+def test_positions_and_keywords_are_the_same_call():
+    buf = np.zeros(64, dtype=np.uint32)
+    for args, kw in (((buf, buf, 64, 48, 1, 0, buf), {"stream": 0}), ((buf, buf, 64, 48, 1, 0, buf, 0), {}),
+                     ((buf, buf), {"out": buf, "side": 0, "batch": 1, "block": 48, "n": 64, "stream": 0}),
+                     ((buf.ctypes.data, buf, 64, np.int64(48), True, 0, None), {"stream": 0})):
+        with pytest.raises(q.QtipError) as e:
+            q.qtip_rht(*args, **kw)
+        assert e.value.code == -1
+
+
+@pytest.mark.parametrize("name", binding._GPU_ENTRIES)
+def test_wrong_arguments_raise(name):
+    f = getattr(q, name)
+    with pytest.raises(TypeError, match="missing required argument"):
+        f(stream=0)
+    with pytest.raises(TypeError, match="unexpected keyword"):
+        f(nonsense=1)
+    with pytest.raises(TypeError, match="at most"):
+        f(*[None] * 20)
+    with pytest.raises(TypeError, match="multiple values"):
+        f(None, **{{"qtip_rht": "x", "qtip_rht_f32": "x", "qtip_decode_states": "states", "qtip_quantize_gpu": "W",
+                    "qtip_block_ldl": "H", "qtip_quantize_ldlq": "W"}.get(name, "codes"): None})
+    with pytest.raises((TypeError, AttributeError)):
+        f(*[object()] * 7, stream=0)
