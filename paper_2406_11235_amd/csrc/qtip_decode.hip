@@ -157,8 +157,8 @@ __device__ __forceinline__ int reduce_over_tile_groups(float (&acc)[RPL], int la
 
 // FUSED: x is the untransformed activation and the workgroup first computes the input-side
 // random Hadamard transform V (S .* x) of Section 2.1 into LDS itself (every workgroup the
-// whole vector: at most 8192 values, about 2 us, against a kernel launch and the gap to
-// the next dependent kernel, which cost more for layers this small), with the arithmetic
+// whole vector, at most 8192 values, against a kernel launch and the gap to the next
+// dependent kernel, which cost more for layers this small), with the device function
 // of the stand-alone transform, so that the result is the same bit for bit.
 constexpr int FUSED_MAX_N = 8192;
 
@@ -181,26 +181,7 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     __shared__ __attribute__((aligned(16))) uint32_t s_lut[code_lds_words(CODE, SPREAD)];
     __shared__ float s_part[NW][16];
     __shared__ __attribute__((aligned(16))) half_t s_x[FUSED ? FUSED_MAX_N : 8];
-    // room for FUSED_MAX_N values in blocks of any size, each block with its padding
-    __shared__ float s_v[FUSED ? FUSED_MAX_N + FUSED_MAX_N / 32 + FUSED_MAX_N / 16 : 1];
-    if constexpr (FUSED) {
-        // groups of threads take one block each (a thread holds 16 values per round)
-        const int b = 1 << log2_block, n = 16 * tn;
-        const int gthreads = min(NW * 64, b >> 4);
-        const int groups = min(NW * 64 / gthreads, FUSED_MAX_N / b);  // what s_v holds
-        const int group = threadIdx.x / gthreads, gtid = threadIdx.x % gthreads;
-        for (int o0 = 0; o0 < n; o0 += groups * b) {
-            const int o = o0 + group * b;
-            const bool active = group < groups && o < n;
-            half_t *dst = s_x + (active ? o : 0);
-            rht_block<half_t, 0>(x + (active ? o : 0), signs + (active ? o : 0), log2_block, 0,
-                                 s_v + (active ? group : 0) * rht_lds_floats(b), gtid, gthreads, active,
-                                 [dst](int idx, half_t v) { dst[idx] = v; });
-        }
-    }
-    stage_code_table<CODE, SPREAD>(lut, s_lut, NW * 64);
-    typename RowDotFor<K, CODE, SPREAD>::type rd;
-    rd.init(s_lut);
+    __shared__ __attribute__((aligned(16))) float s_v[FUSED ? RHT_LDS_FLOATS : 1];
     const int I = blockIdx.x;
     // the wave's number as a scalar: its tile range and the loop over it then live in scalar
     // registers and the loop control costs no vector instructions
@@ -211,21 +192,17 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     const int Jend = min(tn, J0 + chunk);
     // this tile row's words: a uniform base, so that a lane's address is base + 32-bit offset
     const uint32_t *__restrict__ row_codes = codes + (size_t)I * tn * (8 * K);
-    float acc[RPL];
-#pragma unroll
-    for (int rr = 0; rr < RPL; rr++) acc[rr] = 0.f;
-
-    // Software pipeline: the loads of step i+1 are in flight while step i is decoded.
-    // Two operand sets alternate (the loop body is two steps), so nothing is copied
-    // (3-4 % on the computed codes, measured against the copying form on one box).
     struct Operands {
         WordsN<WPL> w;
         uint4 xa, xb;
     };
-    auto issue = [&](Operands &o, int Jb) {
+    auto issue_words = [&](Operands &o, int Jb) {
         const uint32_t Jc = min(Jb + g, Jend - 1);  // lanes past the end re-read the last tile
         // (byte offsets in 32 bits from uniform bases: the loads take them as they are)
         o.w = load_words_at<WPL>(row_codes, Jc * (32 * K) + q * (4 * WPL));
+    };
+    auto issue_x = [&](Operands &o, int Jb) {
+        const uint32_t Jc = min(Jb + g, Jend - 1);
         if constexpr (FUSED) {
             const uint4 *xp = reinterpret_cast<const uint4 *>(s_x + 16 * Jc);
             o.xa = xp[0];
@@ -236,6 +213,61 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
             o.xb = xp[1];
         }
     };
+    auto issue = [&](Operands &o, int Jb) {
+        issue_words(o, Jb);
+        issue_x(o, Jb);
+    };
+    Operands opA, opB;
+    if constexpr (FUSED) {
+        constexpr int N = 16 / NW, NCH = NW == 16 ? 2 : 1;  // (fewer waves: a row of less than 4096 values)
+        const int n = 16 * tn;
+        half4_t v[NCH][N];
+        uint32_t sg[NCH][N];
+#pragma unroll
+        for (int c = 0; c < NCH; c++)
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                const int at = min(c * RHT_CHUNK + rht_in_index(wave + NW * i, lane), n - 4);
+                v[c][i] = *reinterpret_cast<const half4_t *>(x + at);
+                sg[c][i] = *reinterpret_cast<const uint32_t *>(signs + at);
+            }
+        // the first step's words, from memory, arrive while the input is transformed
+        if (J0 < Jend) issue_words(opA, J0);
+        RhtMatrix M;
+        M.init(lane);
+        float4_t sum[NCH][N];
+#pragma unroll
+        for (int c = 0; c < NCH; c++) {
+            if (c * RHT_CHUNK >= n) break;
+#pragma unroll
+            for (int i = 0; i < N; i++) v[c][i] = rht_signed(v[c][i], sg[c][i]);
+            if (c > 0) __syncthreads();
+            rht_chunk<NW>(v[c], M, log2_block, (n - c * RHT_CHUNK + 255) >> 8, s_v, wave, lane, sum[c]);
+        }
+        if (log2_block == 13) rht_between_chunks<NCH, N>(sum);
+        const float unit = rht_scale(log2_block);
+#pragma unroll
+        for (int c = 0; c < NCH; c++)
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                const int to = c * RHT_CHUNK + rht_out_index(wave + NW * i, lane);
+                if (to < n) *reinterpret_cast<half4_t *>(s_x + to) = rht_round(sum[c][i], unit);
+            }
+        if constexpr (code_lds_words(CODE) == 1) __syncthreads();
+    } else {
+        // (ahead of the table, so that they are under way while it is filled)
+        if (J0 < Jend) issue(opA, J0);
+    }
+    stage_code_table<CODE, SPREAD>(lut, s_lut, NW * 64);
+    typename RowDotFor<K, CODE, SPREAD>::type rd;
+    rd.init(s_lut);
+    float acc[RPL];
+#pragma unroll
+    for (int rr = 0; rr < RPL; rr++) acc[rr] = 0.f;
+
+    // Software pipeline: the loads of step i+1 are in flight while step i is decoded.
+    // Two operand sets alternate (the loop body is two steps), so nothing is copied
+    // (3-4 % on the computed codes, measured against the copying form on one box).
     auto compute = [&](const Operands &o, int Jb) {
         uint32_t w[WPL + 1];
 #pragma unroll
@@ -248,8 +280,9 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
             rd.run_tile(w, xv, acc);
         }
     };
-    Operands opA, opB;
-    if (J0 < Jend) issue(opA, J0);
+    if constexpr (FUSED) {
+        if (J0 < Jend) issue_x(opA, J0);
+    }
     for (int Jb = J0; Jb < Jend; Jb += 2 * TPI) {
         if (Jb + TPI < Jend) issue(opB, Jb + TPI);
         compute(opA, Jb);
