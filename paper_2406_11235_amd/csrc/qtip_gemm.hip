@@ -1,0 +1,465 @@
+// Decode + batched product for prompts and large batches: Y = X W~^T with the weights decoded on the way
+// into the matrix cores.
+//
+// v_mfma_f32_32x32x16_f16 with the activations as A (32 batch rows) and the decoded weights as B (32
+// outputs), so that a result register holds 32 neighbouring outputs of one batch row and is stored as whole
+// cache lines.  A step is 16 inputs, one tile J: lane l decodes eight neighbouring weights of output l % 32,
+// inputs 8 (l / 32) .. + 7 of the tile, straight into the B operand.
+//
+// What bounds it.  Decoding eight weights costs a wave about 40 vector instructions, a matrix instruction
+// keeps its unit busy for 32 cycles: a decoded operand has to meet eight batch groups (256 batch rows)
+// before the matrix cores are the slower side.  So a wave owns RB groups of 32 outputs and all NBB groups of 32
+// batch rows of its workgroup, and no weight is decoded twice in a workgroup.  Its loop interleaves the matrix
+// instructions of a step with the decoding of the next step's weights, one piece after every matrix
+// instruction, which leaves both units busy from one wave.
+//
+// The activations go from memory into LDS without passing through registers, KS tiles (KS * 32 bytes per batch row)
+// at a time and one such stage ahead, and are shared by the WM waves that own different outputs; WK waves
+// (or groups of WM) split the inputs instead where there are few outputs, and add up through LDS at the end.
+// In LDS a row's 16-byte pieces are permuted by the row's number, so that the 16-byte reads of
+// neighbouring rows fall on different banks; the copy into LDS fetches them in that order.
+#include <type_traits>
+
+#include "qtip_device.h"
+#include "qtip_internal.h"
+
+namespace qtip {
+namespace {
+
+typedef float float16_t __attribute__((ext_vector_type(16)));
+
+// Where the eight weights of lane (i = output within its group of 32, h) of step J are: word index of the
+// first and bit offset in it.  16 x 16 tiles: row i % 16 of the tile in tile row i / 16 of the group, second half
+// of the row if h.  Lookup-only code: row i of block 2 J + h.
+template <int K, int CODE>
+__device__ __forceinline__ int first_bit(int i, int h) {
+    return CODE == CODE_LUT ? 8 * K * i : 16 * K * (i & 15) + 8 * K * h;
+}
+
+// Sum of a 3INST word's halves into the low or the high half of a packed pair.  A register half-written by one
+// of these may not be read by the very next instruction; the callers keep other instructions in between.
+__device__ __forceinline__ void add_halves_low(uint32_t y, uint32_t &p) {
+    asm("v_add_f16_sdwa %0, %1, %1 dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1" : "=v"(p) : "v"(y));
+}
+__device__ __forceinline__ void add_halves_high(uint32_t y, uint32_t &p) {
+    asm("v_add_f16_sdwa %0, %1, %1 dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:WORD_0 src1_sel:WORD_1" : "+v"(p) : "v"(y));
+}
+__device__ __forceinline__ void add_halves_last(uint32_t y0, uint32_t y1, uint32_t &p) {
+    asm("v_add_f16_sdwa %0, %1, %1 dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1\n\t"
+        "s_nop 0\n\t"
+        "v_add_f16_sdwa %0, %2, %2 dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:WORD_0 src1_sel:WORD_1\n\t"
+        "s_nop 0"
+        : "=&v"(p)
+        : "v"(y0), "v"(y1));
+}
+
+// Eight weights from the 64 bits at their first one, one per call of step<c>, as four packed pairs.
+template <int K, int CODE> struct EightWeights {
+    uint64_t b64;
+    uint32_t mm, lane4;
+    const uint32_t *lut;  // LDS
+    uint32_t w[2], t[4];
+    __device__ __forceinline__ void init(const uint32_t *lds_lut) {
+        lut = lds_lut;
+        lane4 = (threadIdx.x & 31u) << 2;
+        b64 = CODE == CODE_3INST ? INST_B : MAD_B;
+        mm = INST_MM;
+        asm volatile("" : "+v"(b64), "+v"(mm));
+    }
+    // w0, w1: two neighbouring words of the stream; selector: the bytes of (w0, w1) that start at the first bit
+    __device__ __forceinline__ void start(uint32_t w0, uint32_t w1, uint32_t selector, uint32_t shift) {
+        if constexpr (K == 4) {
+            w[0] = w0;
+            w[1] = w1;
+        } else {
+            w[0] = __builtin_amdgcn_perm(w0, w1, selector);
+            w[1] = K == 2 ? 0u : w1 << shift;
+        }
+    }
+    template <int c> __device__ __forceinline__ void step(uint32_t (&h)[4]) {
+        if constexpr (CODE == CODE_3INST) {
+            // (four vector instructions per call: a weight's sum of halves goes behind the next one's multiply-add,
+            // which needs a wait state before its result is read)
+            const uint32_t Z = lcg_mad64(window16(w, c * K), INST_A, b64);
+            if constexpr (c % 2 == 1 && c < 7) add_halves_low(t[0], h[c / 2]);
+            if constexpr (c % 2 == 0 && c > 0) add_halves_high(t[1], h[c / 2 - 1]);
+            t[c & 1] = (Z & INST_MASK) ^ mm;
+            if constexpr (c == 7) add_halves_last(t[0], t[1], h[3]);
+        } else if constexpr (CODE == CODE_1MAD) {
+            const uint32_t X = lcg_mad64(window16(w, c * K), MAD_A, b64);
+            const uint32_t s = __builtin_amdgcn_sad_u8(X, 0u, 0x4B000000u);  // float 2^23 + s
+            t[c & 1] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(float, s) - 8389118.0f) * MAD_INV_SCALE);
+            if constexpr (c & 1)
+                h[c / 2] = as_u32(half2_t{(half_t)__builtin_bit_cast(float, t[0]), (half_t)__builtin_bit_cast(float, t[1])});
+        } else if constexpr (code_is_hyb(CODE)) {
+            if constexpr ((c & 1) == 0) {
+                const uint32_t st = window16(w, c * K);
+                const uint32_t X = st * st + st;
+                h[c / 2] = hyb_signed_lookup(lut, (X >> 4) & 0xFFCu);
+                if constexpr (CODE == CODE_HYB2) h[c / 2] ^= (X >> 16) & 0x8000u;
+            }
+        } else if constexpr (CODE == CODE_HYB1) {
+            const uint32_t st = window16(w, c * K);
+            const uint32_t X = st * st + st;
+            t[c & 1] = hyb_signed_lookup(lut, ((X >> 2) & 0x3F80u) | lane4);
+            if constexpr (c & 1) h[c / 2] = hyb1_pair(t[0], t[1]);
+        } else {
+            // 14 state bits to bits 14..1
+            const uint32_t off = c * K < 17 ? (w[0] >> (17 - c * K)) & 0x7FFEu : window32(w, c * K - 17) & 0x7FFEu;
+            t[c & 1] = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(lut) + off);
+            if constexpr (c & 1) h[c / 2] = t[0] | (t[1] << 16);
+        }
+    }
+};
+
+// s_waitcnt that waits until at most n memory loads are outstanding, and for nothing else.
+constexpr int vmcnt_only(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
+
+// A buffer of `bytes` bytes: what is read behind its end is 0.
+__device__ __forceinline__ u32x4_t buffer_of(const void *p, size_t bytes) {
+    const uint64_t at = reinterpret_cast<uintptr_t>(p);
+    return u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(bytes < 0xFFFFFFFFu ? bytes : 0xFFFFFFFFu)),
+                   0x00020000u};
+}
+// 16 bytes per lane from byte `lane_offset` + `offset` of a buffer into LDS at `to`, lane by lane.  (Written
+// out, because the compiler makes every later read of LDS wait for the copy, whatever it reads.  The kernel
+// waits for its copies itself; the compiler's own waits only become longer by loads it does not count.)
+__device__ __forceinline__ void copy_to_lds(u32x4_t buffer, uint32_t lane_offset, uint32_t offset, const char *to) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)to;
+    asm volatile("s_mov_b32 m0, %3\n\t"
+                 "s_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %1, %2 offen lds"
+                 :
+                 : "v"(lane_offset), "s"(buffer), "s"(offset), "s"(at)
+                 : "memory");
+}
+
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, F, I + 1>(static_cast<F &&>(f));
+    }
+}
+
+// Sizes of a workgroup's LDS.
+template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS> struct GemmLds {
+    static constexpr bool LUT = CODE == CODE_LUT;
+    static constexpr int SLICE = 32 * NBB * KS * 32;                       // activations of a stage
+    static constexpr int STEP_BYTES = (LUT ? 8 : 4) * 8 * K;               // code words of a tile row and step
+    static constexpr int CODE_ROW = KS * STEP_BYTES, CODE_ROWS = LUT ? RB : 2 * RB;  // of a wave and stage
+    static constexpr int CODE_COPIES = (CODE_ROWS * CODE_ROW + 1023) / 1024, CODE_STAGE = CODE_COPIES * 1024;
+    static constexpr int TABLE_WORDS = LUT ? 1 << 13 : code_lds_words(CODE);
+    // batch groups whose partial sums are in LDS at the same time, in the room of the activations
+    static constexpr int SUM_BYTES = WM * WK * RB * 4096;
+    static constexpr int SUMS = WK == 1 ? 0 : NBB * SUM_BYTES <= 2 * WK * SLICE ? NBB : (2 * WK * SLICE) / SUM_BYTES;
+    static constexpr int BYTES = 2 * WK * SLICE + WM * WK * 2 * CODE_STAGE + 4 * TABLE_WORDS;
+    static_assert(WK == 1 || (SUMS >= 1 && NBB % SUMS == 0), "whole rounds of partial sums");
+};
+
+template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS>
+__global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
+    const uint32_t *__restrict__ codes, const uint32_t *__restrict__ lut, int m, int n, const half_t *__restrict__ X,
+    int B, const half_t *__restrict__ scale, float *__restrict__ Y) {
+    constexpr bool LUT = CODE == CODE_LUT;
+    constexpr int NWORDS = 8 * K, NT = WM * WK * 64;
+    constexpr int BT = 32 * NBB, ROW = KS * 32;       // batch rows of a workgroup; bytes of a row per stage
+    constexpr int UNITS = KS * 2, RPI = 64 / UNITS;   // 16-byte pieces of a row; rows per copy instruction
+    using Lds = GemmLds<K, CODE, RB, NBB, WM, WK, KS>;
+    constexpr int SLICE = Lds::SLICE, NCOPY = BT / RPI / WM;  // bytes of a stage; copy instructions per wave
+    constexpr int SUMS_AT_ONCE = Lds::SUMS;
+    constexpr int AHEAD = 3, GROUPS = KS * NBB * RB;  // a group: one matrix instruction and what goes with it
+    constexpr int STEP_BYTES = Lds::STEP_BYTES, CODE_ROW = Lds::CODE_ROW, CODE_ROWS = Lds::CODE_ROWS;
+    constexpr int CODE_COPIES = Lds::CODE_COPIES, CODE_STAGE = Lds::CODE_STAGE;
+    constexpr int COPIES = CODE_COPIES + NCOPY;
+    constexpr auto copy_group = [](int c) { return c * (GROUPS / 2) / COPIES; };
+    static_assert(KS >= 2 && COPIES <= 60, "a stage holds the step after the next; the count of a wait");
+    static_assert(BT % (RPI * WM) == 0, "whole copies");
+    __shared__ __attribute__((aligned(16))) uint32_t s_lut[Lds::TABLE_WORDS];
+    __shared__ __attribute__((aligned(1024))) char s_x[2 * WK * SLICE];
+    __shared__ __attribute__((aligned(1024))) char s_codes[WM * WK * 2 * CODE_STAGE];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wm = wave % WM, wk = wave / WM;
+    const int i = lane & 31, h = lane >> 5;
+    const int o0 = (blockIdx.x * WM + wm) * (32 * RB);  // first output
+    const int b0 = blockIdx.y * BT;
+    const int tn = (n + 15) / 16;                         // steps
+    const int per = (tn + WK * KS - 1) / (WK * KS) * KS;  // of a slice
+    const int J0 = wk * per, Jend = min(tn, J0 + per);
+    const int stages = per / KS;
+
+    // The wave's code words of a stage: the KS tiles of a tile row lie one after the other, so whole pieces of 16
+    // bytes are copied into LDS as they are.  (Behind a row's last tile comes the next row, behind the buffer
+    // zeros: any weights do there, their inputs are zeros.)
+    constexpr int r_first = LUT ? 32 : 16;
+    const size_t line = (size_t)(LUT ? n / 8 : n / 16) * (4 * NWORDS);  // bytes of a tile row
+    const int I_base = min(o0, m - 1) / r_first;
+    const u32x4_t code_buffer =
+        buffer_of(reinterpret_cast<const char *>(codes) + (size_t)I_base * line, ((size_t)(m / r_first) - I_base) * line);
+    char *const my_codes = s_codes + wave * (2 * CODE_STAGE);
+    uint32_t coff[CODE_COPIES];
+#pragma unroll
+    for (int q = 0; q < CODE_COPIES; q++) {
+        const int at = (64 * q + lane) * 16, r = min(at / CODE_ROW, CODE_ROWS - 1);
+        const int I = min(o0 + r * r_first, m - 1) / r_first - I_base;  // (beyond m: any row)
+        coff[q] = (uint32_t)I * (uint32_t)line + at % CODE_ROW;
+    }
+    const int bit = first_bit<K, CODE>(i, h);
+    const int w0 = bit >> 5, w1 = (w0 + 1) % NWORDS;  // (wraps inside a tile: tail-biting)
+    const uint32_t selector = 0x07060504u - (uint32_t)((bit & 31) >> 3) * 0x01010101u, shift = bit & 31;
+    const char *const code_words = my_codes + (LUT ? h * 4 * NWORDS : (i >> 4) * CODE_ROW);
+    auto copy_codes = [&](auto qc, int J, int buffer) {
+        constexpr int q = decltype(qc)::value;
+        copy_to_lds(code_buffer, coff[q], min(J, tn - 1) * STEP_BYTES, my_codes + buffer * CODE_STAGE + q * 1024);
+    };
+    // copies into LDS: lane = (row within the instruction, place of the piece)
+    auto swizzle = [](int row) { return (row / (16 / UNITS)) & (UNITS - 1); };
+    const int crow = lane / UNITS;
+    char *const slice = s_x + wk * (2 * SLICE);
+    const int rows = min(BT, B - b0), pieces = min(2 * Jend, n / 8);
+    uint32_t xoff[NCOPY];
+    int piece[NCOPY];
+#pragma unroll
+    for (int q = 0; q < NCOPY; q++) {
+        const int b = (wm * NCOPY + q) * RPI + crow;
+        piece[q] = (lane % UNITS) ^ swizzle(q * RPI + crow) ^ (NCOPY % 2 ? swizzle(wm * NCOPY * RPI) : 0);
+        xoff[q] = (uint32_t)min(b, rows - 1) * (uint32_t)(2 * n) + 16 * piece[q];
+    }
+    const char *const xbase = reinterpret_cast<const char *>(X + (size_t)b0 * n);
+    const u32x4_t x_buffer = buffer_of(xbase, (size_t)rows * 2 * n);
+    auto copy_x = [&](auto qc, int J, int buffer) {
+        constexpr int q = decltype(qc)::value;
+        // Pieces beyond the slice's end are asked for beyond the buffer's end, so that zeros arrive: the weights of
+        // their steps are the last tile's again.
+        // (the uniform offset stays inside the buffer: the check subtracts it from the buffer's size)
+        copy_to_lds(x_buffer, 2 * J + piece[q] < pieces ? xoff[q] : 0xFFFFFF00u, 32 * min(J, tn - 1),
+                    slice + buffer * SLICE + (wm * NCOPY + q) * 1024);
+    };
+    // a lane's place in a buffer: row i, piece 2 j + h
+    const uint32_t xread = (uint32_t)i * ROW + (uint32_t)((h ^ swizzle(i)) << 4);
+
+    if (J0 < Jend) {
+        static_for<CODE_COPIES>([&](auto q) { copy_codes(q, J0, 0); });
+        static_for<NCOPY>([&](auto q) { copy_x(q, J0, 0); });
+    }
+    if constexpr (LUT) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(lut);
+        uint4 *dst = reinterpret_cast<uint4 *>(s_lut);
+        for (int e = threadIdx.x; e < 2048; e += NT) dst[e] = src[e];
+        __syncthreads();
+    } else {
+        stage_code_table<CODE>(lut, s_lut, NT);
+    }
+    EightWeights<K, CODE> dec[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++) dec[rb].init(s_lut);
+    float16_t acc[RB][NBB];
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+        for (int nb = 0; nb < NBB; nb++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[rb][nb][e] = 0.f;
+
+    uint32_t wnext[RB][4];  // the decoded weights of the next step
+    uint32_t cw[RB][2];  // the two words that the next eight weights start in
+    auto read_codes = [&](int step, int buffer) {
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+            const char *p = code_words + buffer * CODE_STAGE + rb * (CODE_ROWS / RB) * CODE_ROW + step * STEP_BYTES;
+            cw[rb][0] = *reinterpret_cast<const uint32_t *>(p + 4 * w0);
+            cw[rb][1] = *reinterpret_cast<const uint32_t *>(p + 4 * w1);
+        }
+    };
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));  // the first stage is there
+    __syncthreads();
+    if (J0 < Jend) {
+        read_codes(0, 0);
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+            dec[rb].start(cw[rb][0], cw[rb][1], selector, shift);
+            static_for<8>([&](auto c) { dec[rb].template step<decltype(c)::value>(wnext[rb]); });
+        }
+        read_codes(1, 0);
+    }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int mine = J0 < Jend ? (Jend - J0 + KS - 1) / KS : 0;
+    for (int s = 0; s < mine; s++) {
+        const int J = J0 + s * KS;
+        const char *const buf = slice + (s & 1) * SLICE;
+        // the activations of a stage, KS * NBB operands, are read from LDS AHEAD operands before their use
+        half8_t xv[AHEAD + 1];
+        auto read_x = [&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            xv[r % (AHEAD + 1)] = *reinterpret_cast<const half8_t *>(buf + (xread ^ (r / NBB << 5)) + r % NBB * 32 * ROW);
+        };
+        static_for<AHEAD>([&](auto r) { read_x(r); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<KS>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            half8_t wv[RB];
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++) {
+                wv[rb] = __builtin_bit_cast(half8_t, u32x4{wnext[rb][0], wnext[rb][1], wnext[rb][2], wnext[rb][3]});
+                dec[rb].start(cw[rb][0], cw[rb][1], selector, shift);
+            }
+            static_for<NBB>([&](auto nbc) {
+                constexpr int nb = decltype(nbc)::value, r = j * NBB + nb;
+                if constexpr (r + AHEAD < KS * NBB) read_x(std::integral_constant<int, r + AHEAD>{});
+                static_for<RB>([&](auto rbc) {
+                    constexpr int rb = decltype(rbc)::value, group = r * RB + rb;
+                    acc[rb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xv[r % (AHEAD + 1)], wv[rb], acc[rb][nb], 0, 0, 0);
+                    // the next stage's copies, spread over the first part of this one: a wave that issues several in a
+                    // row waits for the memory pipeline, and the matrix cores with it
+                    static_for<COPIES>([&](auto cc) {
+                        constexpr int c = decltype(cc)::value;
+                        if constexpr (copy_group(c) == group) {
+                            if constexpr (c < CODE_COPIES)
+                                copy_codes(std::integral_constant<int, c>{}, J + KS, (s + 1) & 1);
+                            else
+                                copy_x(std::integral_constant<int, c - CODE_COPIES>{}, J + KS, (s + 1) & 1);
+                        }
+                    });
+                    static_for<8 / NBB>([&](auto pc) {
+                        dec[rb].template step<nb * (8 / NBB) + decltype(pc)::value>(wnext[rb]);
+                    });
+                    // the words of the step after the next: of this stage, or, at its last steps, of the next
+                    if constexpr (nb == NBB / 2 && rb == 0) {
+                        if constexpr (j + 2 < KS) {
+                            read_codes(j + 2, s & 1);
+                        } else {
+                            if constexpr (j + 2 == KS) __builtin_amdgcn_s_waitcnt(vmcnt_only(COPIES - CODE_COPIES));
+                            read_codes(j + 2 - KS, (s + 1) & 1);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+        });
+        // The copies of this stage have landed, everywhere.
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+    for (int s = mine; s < stages; s++) __builtin_amdgcn_s_barrier();  // (a slice with less or nothing to do)
+    __syncthreads();
+
+    // D element e of a lane: batch row 8 (e / 4) + 4 h + e % 4, output i
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+            const int o = o0 + 32 * rb + i;
+            if (o >= m) continue;
+            const float sc = scale ? (float)scale[o] : 1.f;
+#pragma unroll
+            for (int nb = 0; nb < NBB; nb++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const int b = b0 + 32 * nb + 8 * (e / 4) + 4 * h + e % 4;
+                    if (b < B) Y[(size_t)b * m + o] = acc[rb][nb][e] * sc;
+                }
+        }
+    } else {
+        float *const sums = reinterpret_cast<float *>(s_x);  // [wk][wm][rb][nb of this round][e][lane]
+        constexpr int BLOCKS = WM * RB * SUMS_AT_ONCE, PARTS = BLOCKS * 16;
+#pragma unroll
+        for (int nb0 = 0; nb0 < NBB; nb0 += SUMS_AT_ONCE) {
+            if (nb0 > 0) __syncthreads();
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                for (int nb = 0; nb < SUMS_AT_ONCE; nb++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++)
+                        sums[(((wk * WM + wm) * RB + rb) * SUMS_AT_ONCE + nb) * 1024 + e * 64 + lane] = acc[rb][nb0 + nb][e];
+            __syncthreads();
+            for (int part = wave; part < PARTS; part += WM * WK) {
+                const int e = part % 16, block = part / 16;
+                const int nb = nb0 + block % SUMS_AT_ONCE, rb = block / SUMS_AT_ONCE % RB, mw = block / SUMS_AT_ONCE / RB;
+                float v = 0.f;
+#pragma unroll
+                for (int kk = 0; kk < WK; kk++) v += sums[kk * (BLOCKS * 1024) + block * 1024 + e * 64 + lane];
+                const int o = (blockIdx.x * WM + mw) * (32 * RB) + 32 * rb + i;
+                const int b = b0 + 32 * nb + 8 * (e / 4) + 4 * h + e % 4;
+                if (o < m && b < B) Y[(size_t)b * m + o] = scale ? v * (float)scale[o] : v;
+            }
+        }
+    }
+}
+
+}  // namespace
+
+// ------------------------------------------------------------------ launcher
+
+// The ways a product is split: outputs and batch rows of a workgroup, and the time of a round of 256 workgroups
+// (one per CU), `first` once and `round` for each, measured at 4096 inputs (us, 2-bit 3INST; only their ratios matter
+// here).  A large tile decodes a weight once for more batch rows; a small one leaves no CU idle where outputs
+// or batch rows are few, and splits the inputs between its waves.
+struct GemmSplit {
+    int outputs, rows;
+    float first, round;
+};
+static constexpr GemmSplit GEMM_SPLITS[] = {{256, 256, 0.f, 105.f}, {128, 128, 0.f, 42.f}, {64, 128, 2.f, 25.f},
+                                            {64, 64, 5.f, 15.f},    {32, 64, 2.f, 11.3f},  {32, 32, 4.5f, 5.5f}};
+
+// Kernels of the splits, in their order.
+#define QTIP_GEMM_SPLITS(GO) \
+    GO(0, 1, 8, 8, 1) GO(1, 1, 4, 4, 2) GO(2, 1, 4, 2, 4) GO(3, 1, 2, 2, 4) GO(4, 1, 2, 1, 8) GO(5, 1, 1, 1, 8)
+
+template <int K, int CODE>
+static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int m, int n, const void *X, int B,
+                                const void *scale, float *Y, hipStream_t st) {
+    int best = -1;
+    float least = 0.f;
+#define QTIP_GEMM_FITS(I, RB, NBB, WM, WK) GemmLds<K, CODE, RB, NBB, WM, WK, 4>::BYTES <= 160 * 1024,
+    constexpr bool fits[] = {QTIP_GEMM_SPLITS(QTIP_GEMM_FITS)};
+    for (int i = 0; i < 6; i++) {
+        const GemmSplit &s = GEMM_SPLITS[i];
+        const long gx = (m + s.outputs - 1) / s.outputs, gy = (B + s.rows - 1) / s.rows;
+        if (!fits[i] || gy > 65535) continue;
+        const float t = s.first + s.round * (float)((gx * gy + 255) / 256);
+        if (best < 0 || t < least) best = i, least = t;
+    }
+    const dim3 grid((m + GEMM_SPLITS[best].outputs - 1) / GEMM_SPLITS[best].outputs,
+                    (B + GEMM_SPLITS[best].rows - 1) / GEMM_SPLITS[best].rows);
+#define QTIP_GEMM_GO(I, RB, NBB, WM, WK)                                                                        \
+    if constexpr (fits[I])                                                                                      \
+        if (best == I) {                                                                                        \
+            static_assert(32 * RB * WM == GEMM_SPLITS[I].outputs && 32 * NBB == GEMM_SPLITS[I].rows, "order"); \
+            hipLaunchKernelGGL((gemm_kernel<K, CODE, RB, NBB, WM, WK, 4>), grid, dim3(WM * WK * 64), 0, st, codes, \
+                               lut, m, n, (const half_t *)X, B, (const half_t *)scale, Y);                      \
+        }
+    QTIP_GEMM_SPLITS(QTIP_GEMM_GO)
+#undef QTIP_GEMM_GO
+#undef QTIP_GEMM_FITS
+    return hipGetLastError();
+}
+
+// (a tile row and the activations of 256 batch rows are addressed with 32-bit byte offsets)
+bool gemm_takes(int n) { return n <= 1 << 22; }
+
+hipError_t launch_gemm(int k, int code_id, const uint32_t *codes, const void *lut, int m, int n, const void *X, int B,
+                       const void *scale, float *Y, hipStream_t st) {
+    const uint32_t *tab = (const uint32_t *)lut;
+#define QTIP_GEMM_CODE(CODE)                                                                    \
+    case CODE:                                                                                  \
+        if (k == 2) return launch_gemm_t<2, CODE>(codes, tab, m, n, X, B, scale, Y, st);        \
+        if (k == 3) return launch_gemm_t<3, CODE>(codes, tab, m, n, X, B, scale, Y, st);        \
+        return launch_gemm_t<4, CODE>(codes, tab, m, n, X, B, scale, Y, st);
+    switch (code_id) {
+        QTIP_GEMM_CODE(CODE_1MAD)
+        QTIP_GEMM_CODE(CODE_3INST)
+        QTIP_GEMM_CODE(CODE_HYB)
+        QTIP_GEMM_CODE(CODE_HYB2)
+        QTIP_GEMM_CODE(CODE_HYB1)
+        default: break;
+        QTIP_GEMM_CODE(CODE_LUT)
+    }
+#undef QTIP_GEMM_CODE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace qtip

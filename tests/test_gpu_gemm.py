@@ -1,0 +1,72 @@
+"""The product for more than 16 batch rows at the sizes where its splits can go wrong: every split of outputs, batch rows
+and inputs (by sizes that the launcher's rule gives to it), edges of tiles, odd numbers of steps, the smallest of
+everything, for every code, against the decoded matrix times the activations in binary64."""
+import pytest
+
+from qtip_synth import CODE_1MAD, CODE_3INST, CODE_HYB, CODE_HYB1, CODE_HYB2, CODE_LUT
+
+pytestmark = pytest.mark.gpu
+
+CODES = {CODE_1MAD: (16, 1, 0), CODE_3INST: (16, 1, 0), CODE_HYB: (16, 2, 1024), CODE_HYB2: (16, 2, 1024),
+         CODE_LUT: (14, 1, 1 << 14), CODE_HYB1: (16, 1, 64)}
+# m, n, B: 32 x 32, 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 256 x 256 outputs x batch rows of a workgroup
+SHAPES = [(32, 16, 17), (96, 208, 33), (544, 1056, 40), (8192, 80, 49), (8224, 48, 64), (16384, 144, 100),
+          (8224, 112, 200), (16416, 80, 1000), (16384, 272, 769)]
+
+
+@pytest.fixture(scope="module")
+def q():
+    import paper_2406_11235_amd as q
+    q.lib()
+    return q
+
+
+def check(q, code, k, m, n, B, scaled, seed=0):
+    import torch
+    L, V, entries = CODES[code]
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    codes = torch.randint(-2**31, 2**31, (m * n // 256, 8 * k), dtype=torch.int32, device="cuda", generator=g)
+    lut = torch.randn(entries, device="cuda", generator=g).half() if entries else None
+    X = torch.randn(B, n, device="cuda", generator=g).half()
+    sc = (torch.rand(m, device="cuda", generator=g) + 0.5).half() if scaled else None
+    # a guard behind Y, and nothing left from before in it
+    buf = torch.full((B * m + 4096,), float("nan"), device="cuda")
+    q.qtip_decode_matmat(codes, L, k, V, code, lut, m, n, X, B, sc, buf)
+    W = torch.empty(m, n, dtype=torch.float16, device="cuda")
+    q.qtip_dequantize(codes, L, k, V, code, lut, m, n, W)
+    ref = X.double() @ W.double().T.contiguous()
+    if scaled:
+        ref = ref * sc.double()
+    Y = buf[:B * m].view(B, m).double()
+    torch.cuda.synchronize()
+    assert torch.isfinite(Y).all() and torch.isnan(buf[B * m:]).all()
+    err = float((Y - ref).abs().max() / ref.abs().max())
+    assert err <= 1e-5, (code, k, m, n, B, err)
+
+
+@pytest.mark.parametrize("code", list(CODES))
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_splits(q, code, k):
+    for i, (m, n, B) in enumerate(SHAPES):
+        check(q, code, k, m, n, B, scaled=i % 2 == 0, seed=i)
+
+
+def test_half_a_step_of_the_lookup_only_code(q):
+    for n in (8, 24, 8 * 65, 8 * 129):
+        for m, B in ((32, 18), (64, 70), (4128, 300), (16416, 700)):
+            check(q, CODE_LUT, 2 + n % 3, m, n, B, scaled=False)
+
+
+def test_a_batch_row_meets_nothing_but_itself(q):
+    """An infinity in one batch row leaves the others finite; rows of a last, partly filled tile included."""
+    import torch
+    m, n, B = 64, 80, 37
+    codes = torch.randint(-2**31, 2**31, (m * n // 256, 16), dtype=torch.int32, device="cuda")
+    X = torch.randn(B, n, device="cuda").half()
+    X[5, 3] = float("inf")
+    Y = torch.empty(B, m, device="cuda")
+    q.qtip_decode_matmat(codes, 16, 2, 1, CODE_3INST, None, m, n, X, B, None, Y)
+    torch.cuda.synchronize()
+    ok = torch.ones(B, dtype=torch.bool, device="cuda")
+    ok[5] = False
+    assert torch.isfinite(Y[ok]).all() and not torch.isfinite(Y[5]).any()
