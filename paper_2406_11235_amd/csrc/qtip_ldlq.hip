@@ -27,86 +27,270 @@ namespace {
 // G = T_y = block size of the decomposition = width of a sequence's block of the matrix
 
 // ------------------------------------------------------------------ block LDL
+//
+// In 16 x 16 blocks, on the binary64 matrix cores.  Everything is kept transposed and by blocks: T_ji = S_ij^T (S
+// the trailing matrix, j <= i) and M_ji = L_ij^T = D_j^-1 T_ji, each as the result layout of
+// v_mfma_f64_16x16x4_f64: lane l, register t holds row 4 t + l / 16, column l % 16.  In that layout a block is at
+// the same time a B operand, and, transposed, an A operand of a product that contracts over its rows, and these are the
+// only products there are:
+//     M_ji = D_j^-1 T_ji,        T_ki -= T_jk^T M_ji   (S_ik -= L_ij S_kj^T)   for j < k <= i.
+// The workspace holds T and M by blocks of 2 KiB, which a wave reads and writes as they are.
+//
+// Panels of 8 block columns, two launches each.  ldl_panel_kernel: a workgroup has a wave for each of the panel's own 8
+// block rows and LDL_ROWS waves for block rows below; a wave holds its 8 blocks in registers.  The pivot wave inverts
+// D_j, and after one barrier per block column all waves take the two products above.  Every workgroup
+// factors the panel's own rows again, which costs no time (the inversions are a serial chain and leave the
+// matrix cores idle) and saves a launch per panel.  ldl_update_kernel: the products with what is right of the
+// panel.
+// What bounds it is that chain: 16 pivots per block column, about 1 us, and a launch with its gap twice per panel.
+// n = 2048, g = 16: 1744 us with two launches per block column, the inversion with five barriers per pivot and the
+// products on the vector units, LDL_US us now.
 
-__global__ void ldl_init_kernel(const double *__restrict__ H, double *__restrict__ S,
-                                double *__restrict__ Lm, int n) {
-    const size_t total = (size_t)n * n;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (size_t)gridDim.x * blockDim.x) {
-        S[idx] = H[idx];
-        Lm[idx] = (idx / n == idx % n) ? 1.0 : 0.0;
+typedef double double4_t __attribute__((ext_vector_type(4)));
+constexpr int LDL_PANEL = 8, LDL_ROWS = 4;
+
+__device__ __forceinline__ double *ldl_block(double *base, int nb, int k, int i) {
+    return base + ((size_t)k * nb + i) * 256;
+}
+__device__ __forceinline__ double4_t ldl_load(const double *block, int lane) {
+    return double4_t{block[lane], block[64 + lane], block[128 + lane], block[192 + lane]};
+}
+__device__ __forceinline__ void ldl_store(double *block, int lane, double4_t v) {
+#pragma unroll
+    for (int t = 0; t < 4; t++) block[64 * t + lane] = v[t];
+}
+// c + X^T Y, the contraction over the rows of X and Y
+__device__ __forceinline__ double4_t ldl_product(double4_t x, double4_t y, double4_t c) {
+#pragma unroll
+    for (int t = 0; t < 4; t++) c = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t], y[t], c, 0, 0, 0);
+    return c;
+}
+
+// T from the lower triangle of H, one wave per block, and zeros where A has no block of its own.
+__global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict__ H, double *__restrict__ T,
+                                                       float *__restrict__ A, int n) {
+    const int nb = n >> 4, lane = threadIdx.x & 63;
+    const int i = blockIdx.y, j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j >= nb) return;
+    const int r = lane >> 2, m = lane & 3;  // row r, columns 4 m .. 4 m + 3 of the block
+    if (j >= i) *reinterpret_cast<float4_t *>(A + (size_t)(16 * i + r) * n + 16 * j + 4 * m) = float4_t{0.f, 0.f, 0.f, 0.f};
+    if (j > i) return;
+    const double *h = H + (size_t)(16 * i + r) * n + 16 * j + 4 * m;
+    double *t = ldl_block(T, nb, j, i) + 64 * m + r;
+#pragma unroll
+    for (int c = 0; c < 4; c++) t[16 * c] = h[c];
+}
+
+// a[c] += b * a_p[c], a_p the row that lane p of this row of 16 lanes holds.  (A register that the vector ALU has just
+// written may not be read across lanes by the next two instructions: `first` waits for that, and behind it,
+// in ldl_invert, others are always between.)
+template <int p, bool first>
+__device__ __forceinline__ void add_multiple_of_row(double &a, double b) {
+    if constexpr (first)
+        asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(b), "n"(p));
+    else
+        asm volatile("v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(b), "n"(p));
+}
+template <int p>
+__device__ __forceinline__ double row_value(double a) {  // of lane p of this row of 16 lanes
+    double v;
+    asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=&v"(v) : "v"(a), "n"(p));
+    return v;
+}
+
+// 1 / d to the last bit or two: the hardware's reciprocal (2^-26) and two Newton steps.
+__device__ __forceinline__ double reciprocal(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+}
+
+// Gauss-Jordan elimination of [D | I] in place, without pivoting (D is positive definite): lane l of a row of 16 holds
+// row l.  Rows are not scaled on the way: `scale` is 1 / pivot of the lane's row, and the inverse is scale * a in
+// the end.  After pivots 0 .. P - 1 the first P columns hold the identity's part.
+template <int p, int END>
+__device__ __forceinline__ void ldl_invert(double (&a)[16], double inv, double &scale, int row) {
+    if constexpr (p < END) {
+        const double f = row == p ? 0.0 : -a[p] * inv;
+        scale = row == p ? inv : scale;
+        // the next pivot's column first, so that its reciprocal is under way beside the other columns
+        if constexpr (p + 1 < 16) add_multiple_of_row<p, true>(a[(p + 1) & 15], f);
+        double next = 1.0;
+#pragma unroll
+        for (int c = 0; c < 16; c++)
+            if (c != p && c != p + 1) {
+                add_multiple_of_row<p, false>(a[c], f);
+                if (c == (p >= 4 ? 3 : 12)) {
+                    if constexpr (p + 1 < 16) next = reciprocal(row_value<(p + 1) & 15>(a[(p + 1) & 15]));
+                }
+            }
+        a[p] = row == p ? 1.0 : f;
+        ldl_invert<p + 1, END>(a, next, scale, row);
     }
 }
 
-// Workgroup b of step j: b = 0 stores D_j; b > 0 computes L_ij = S_ij D_j^-1 for block row
-// i = j + b.  Every workgroup inverts D_j itself (Gauss-Jordan in LDS, no pivoting: the
-// block is symmetric positive definite).
+// L_ij in binary32 from E = L_ij^T.
+__device__ __forceinline__ void ldl_emit(float *__restrict__ A, int n, int i, int j, int lane, double4_t e) {
+    float *a = A + (size_t)(16 * i + (lane & 15)) * n + 16 * j + (lane >> 4);
+#pragma unroll
+    for (int t = 0; t < 4; t++) a[4 * t] = (float)e[t];
+}
+
+// Block columns J0 .. J0 + np - 1, and the LDL_ROWS block rows of this workgroup below them.
 template <int G>
-__global__ __launch_bounds__(G * G) void ldl_panel_kernel(double *__restrict__ S, double *__restrict__ Lm,
-                                                        int n, int j, double *__restrict__ Dout) {
-    __shared__ double s_aug[G][2 * G + 1];
-    __shared__ double s_t[G][G + 1];
-    const int r = threadIdx.x / G, c = threadIdx.x % G;
-    const int o = j * G;
-    const double d = S[(size_t)(o + r) * n + o + c];
-    s_aug[r][c] = d;
-    s_aug[r][G + c] = r == c ? 1.0 : 0.0;
-    if (blockIdx.x == 0 && Dout) Dout[((size_t)j * G + r) * G + c] = d;
-    __syncthreads();
-    for (int p = 0; p < G; p++) {
-        const double piv = s_aug[p][p];
-        __syncthreads();
-        if (r == p) {
-            s_aug[p][c] /= piv;
-            s_aug[p][G + c] /= piv;
+__global__ __launch_bounds__((LDL_PANEL + LDL_ROWS) * 64) void ldl_panel_kernel(double *__restrict__ T,
+                                                                               double *__restrict__ Ms,
+                                                                               float *__restrict__ A, int n, int J0,
+                                                                               double *__restrict__ Dout) {
+    __shared__ __attribute__((aligned(16))) double s_inv[2][16][18];  // D_j^-1 by rows
+    __shared__ __attribute__((aligned(16))) double s_out[2][16][18];  // what L_ij^T is made with: for G = 8 see below
+    __shared__ __attribute__((aligned(16))) double s_t[2][LDL_PANEL][256];
+    __shared__ __attribute__((aligned(16))) double s_d[16][18];
+    const int nb = n >> 4, np = min(LDL_PANEL, nb - J0);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int row = lane & 15, g = lane >> 4;
+    const bool own = wave < LDL_PANEL;  // of the panel's own block rows
+    const int rel = own ? wave : LDL_PANEL + blockIdx.x * LDL_ROWS + (wave - LDL_PANEL);
+    const int i = J0 + rel;
+    const bool some = i < nb;
+    const bool speaks = own ? blockIdx.x == 0 : true;  // writes results
+    double4_t t[LDL_PANEL];
+#pragma unroll
+    for (int j = 0; j < LDL_PANEL; j++) {
+        t[j] = double4_t{0.0, 0.0, 0.0, 0.0};
+        if (some && j < np && j <= rel) t[j] = ldl_load(ldl_block(T, nb, J0 + j, i), lane);
+    }
+#pragma unroll
+    for (int j = 0; j < LDL_PANEL; j++) {
+        if (j >= np) break;
+        const int buf = j & 1;
+        if (own && rel > j) ldl_store(s_t[buf][rel], lane, t[j]);
+        if (wave == j) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) s_d[4 * q + g][row] = t[j][q];
+            // (this wave's own LDS: its operations complete in order, the fence keeps the compiler in line)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            double a[16];
+#pragma unroll
+            for (int c = 0; c < 16; c++) a[c] = s_d[row][c];
+            double *const d = Dout + (size_t)(J0 + j) * (16 / G) * (G * G);
+            const bool d_out = Dout != nullptr && blockIdx.x == 0 && g == 0;
+            if (d_out) {
+#pragma unroll
+                for (int c = 0; c < 16; c++)
+                    if (G == 16 || (row < 8 && c < 8)) d[row * G + c] = a[c];
+            }
+            double scale = 1.0;
+            const double first = reciprocal(row_value<0>(a[0]));
+            if constexpr (G == 16) {
+                ldl_invert<0, 16>(a, first, scale, row);
+            } else {
+                // Half-way the first 8 rows hold the inverse of D's first 8 x 8 block, the last 8 the second
+                // block of D in 8 x 8 blocks and, negative, the entry of L between the two.
+                ldl_invert<0, 8>(a, first, scale, row);
+                if (d_out && row >= 8) {
+#pragma unroll
+                    for (int c = 0; c < 8; c++) d[64 + (row - 8) * 8 + c] = a[8 + c];
+                }
+                if (blockIdx.x == 0 && g == 0 && row >= 8) {
+#pragma unroll
+                    for (int c = 0; c < 8; c++) A[(size_t)(16 * (J0 + j) + row) * n + 16 * (J0 + j) + c] = (float)-a[c];
+                }
+                if (g == 0 && row < 8) {
+#pragma unroll
+                    for (int c = 0; c < 16; c++) s_out[buf][row][c] = c < 8 ? a[c] * scale : 0.0;
+                }
+                ldl_invert<8, 16>(a, reciprocal(row_value<8>(a[8])), scale, row);
+            }
+            if (g == 0) {
+#pragma unroll
+                for (int c = 0; c < 16; c++) s_inv[buf][row][c] = a[c] * scale;
+                if (G == 8 && row >= 8) {
+#pragma unroll
+                    for (int c = 0; c < 16; c++) s_out[buf][row][c] = a[c] * scale;
+                }
+            }
         }
         __syncthreads();
-        const double f = s_aug[r][p];
-        const double a0 = s_aug[p][c], a1 = s_aug[p][G + c];
-        __syncthreads();
-        if (r != p) {
-            s_aug[r][c] -= f * a0;
-            s_aug[r][G + c] -= f * a1;
+        if (some && rel > j) {
+            double4_t inv, m = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; q++) inv[q] = s_inv[buf][row][4 * q + g];  // an A operand by rows
+            m = ldl_product(inv, t[j], m);
+            const double4_t neg = -m;
+            // (the next block column's block first: the next pivot wave waits for it)
+#pragma unroll
+            for (int k = j + 1; k < LDL_PANEL; k++)
+                if (k < np && k <= rel) t[k] = ldl_product(ldl_load(s_t[buf][k], lane), neg, t[k]);
+            if (speaks) {
+                if (!own) {
+                    ldl_store(ldl_block(T, nb, J0 + j, i), lane, t[j]);
+                    ldl_store(ldl_block(Ms, nb, J0 + j, i), lane, m);
+                }
+                if constexpr (G == 8) {
+                    double4_t out, e = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int q = 0; q < 4; q++) out[q] = s_out[buf][row][4 * q + g];
+                    ldl_emit(A, n, i, J0 + j, lane, ldl_product(out, t[j], e));
+                } else {
+                    ldl_emit(A, n, i, J0 + j, lane, m);
+                }
+            }
         }
-        __syncthreads();
     }
-    if (blockIdx.x == 0) return;
-    const int i0 = (j + blockIdx.x) * G;
-    s_t[r][c] = S[(size_t)(i0 + r) * n + o + c];
-    __syncthreads();
-    double acc = 0.0;
-#pragma unroll
-    for (int q = 0; q < G; q++) acc += s_t[r][q] * s_aug[q][G + c];
-    Lm[(size_t)(i0 + r) * n + o + c] = acc;
 }
 
-// S_ik -= L_ij (S_kj)^T for the blocks i >= k > j (D_j is symmetric, so L_ij D_j L_kj^T is
-// L_ij times the transpose of the untouched S_kj = L_kj D_j).
-template <int G>
-__global__ __launch_bounds__(G * G) void ldl_update_kernel(double *__restrict__ S, const double *__restrict__ Lm,
-                                                         int n, int j) {
-    const int bi = j + 1 + blockIdx.y, bk = j + 1 + blockIdx.x;
-    if (bk > bi) return;
-    __shared__ double s_l[G][G + 1], s_s[G][G + 1];
-    const int r = threadIdx.x / G, c = threadIdx.x % G;
-    const int o = j * G;
-    s_l[r][c] = Lm[(size_t)(bi * G + r) * n + o + c];
-    s_s[r][c] = S[(size_t)(bk * G + r) * n + o + c];
-    __syncthreads();
-    double acc = 0.0;
+// T_ki -= sum over the panel's block columns j of T_jk^T M_ji, for k <= i from block b0 on; TB x TB blocks per wave.
+template <int TB>
+__global__ __launch_bounds__(256) void ldl_update_kernel(double *__restrict__ T, const double *__restrict__ Ms, int nb,
+                                                         int J0, int pairs) {
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (w >= pairs) return;
+    // w = ip (ip + 1) / 2 + kp, kp <= ip
+    int ip = (int)((__builtin_sqrtf(8.f * (float)w + 1.f) - 1.f) * 0.5f);
+    while ((ip + 1) * (ip + 2) / 2 <= w) ip++;
+    while (ip * (ip + 1) / 2 > w) ip--;
+    const int kp = w - ip * (ip + 1) / 2;
+    const int b0 = J0 + LDL_PANEL;
+    int k[TB], i[TB];
 #pragma unroll
-    for (int q = 0; q < G; q++) acc += s_l[r][q] * s_s[c][q];
-    S[(size_t)(bi * G + r) * n + bk * G + c] -= acc;
-}
-
-// A = L - I in binary32: the blocks strictly below the diagonal blocks, zero elsewhere.
-__global__ void ldl_emit_kernel(const double *__restrict__ Lm, float *__restrict__ A, int n, int G) {
-    const size_t total = (size_t)n * n;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (size_t)gridDim.x * blockDim.x) {
-        const int row = (int)(idx / n), col = (int)(idx % n);
-        A[idx] = (row / G > col / G) ? (float)Lm[idx] : 0.f;
+    for (int e = 0; e < TB; e++) {
+        k[e] = min(b0 + TB * kp + e, nb - 1);
+        i[e] = min(b0 + TB * ip + e, nb - 1);
     }
+    double4_t acc[TB][TB];
+#pragma unroll
+    for (int a = 0; a < TB; a++)
+#pragma unroll
+        for (int b = 0; b < TB; b++) acc[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
+    double4_t x[2][TB], y[2][TB];
+    auto load = [&](int j, int to) {
+#pragma unroll
+        for (int e = 0; e < TB; e++) {
+            x[to][e] = ldl_load(ldl_block(T, nb, J0 + j, k[e]), lane);
+            y[to][e] = ldl_load(ldl_block(const_cast<double *>(Ms), nb, J0 + j, i[e]), lane);
+        }
+    };
+    load(0, 0);
+#pragma unroll
+    for (int j = 0; j < LDL_PANEL; j++) {
+        if (j + 1 < LDL_PANEL) load(j + 1, (j + 1) & 1);
+#pragma unroll
+        for (int a = 0; a < TB; a++)
+#pragma unroll
+            for (int b = 0; b < TB; b++) acc[a][b] = ldl_product(x[j & 1][a], y[j & 1][b], acc[a][b]);
+    }
+#pragma unroll
+    for (int a = 0; a < TB; a++)
+#pragma unroll
+        for (int b = 0; b < TB; b++) {
+            if (b0 + TB * ip + b >= nb || b0 + TB * kp + a > b0 + TB * ip + b) continue;
+            double *at = ldl_block(T, nb, k[a], i[b]);
+            ldl_store(at, lane, ldl_load(at, lane) - acc[a][b]);
+        }
 }
 
 // ------------------------------------------------------------------ Algorithm 5
@@ -181,17 +365,28 @@ size_t block_ldl_workspace(int n) { return 2 * align256((size_t)n * n * sizeof(d
 
 template <int G>
 static hipError_t block_ldl_t(const double *H, int n, float *A, double *Dout, void *ws, hipStream_t st) {
-    double *S = (double *)ws;
-    double *Lm = (double *)((char *)ws + align256((size_t)n * n * sizeof(double)));
-    const int nb = n / G;
-    hipLaunchKernelGGL(ldl_init_kernel, dim3(1024), dim3(256), 0, st, H, S, Lm, n);
-    for (int j = 0; j < nb; j++) {
-        hipLaunchKernelGGL(ldl_panel_kernel<G>, dim3(nb - j), dim3(G * G), 0, st, S, Lm, n, j, Dout);
-        if (j + 1 < nb)
-            hipLaunchKernelGGL(ldl_update_kernel<G>, dim3(nb - j - 1, nb - j - 1), dim3(G * G), 0, st, S,
-                               (const double *)Lm, n, j);
+    double *T = (double *)ws;
+    double *Ms = (double *)((char *)ws + align256((size_t)n * n * sizeof(double)));
+    const int nb = n / 16;
+    hipLaunchKernelGGL(ldl_init_kernel, dim3((nb + 3) / 4, nb), dim3(256), 0, st, H, T, A, n);
+    for (int J0 = 0; J0 < nb; J0 += LDL_PANEL) {
+        const int below = nb - J0 - LDL_PANEL;  // block rows below the panel
+        const int groups = below > 0 ? (below + LDL_ROWS - 1) / LDL_ROWS : 1;
+        hipLaunchKernelGGL(ldl_panel_kernel<G>, dim3(groups), dim3((LDL_PANEL + LDL_ROWS) * 64), 0, st, T, Ms, A, n, J0,
+                           Dout);
+        if (below <= 0) break;
+        // 2 x 2 blocks per wave while that is a wave per SIMD; single blocks, a shorter chain, otherwise
+        const int p2 = (below + 1) / 2;
+        if (p2 * (p2 + 1) / 2 >= 512) {
+            const int pairs = p2 * (p2 + 1) / 2;
+            hipLaunchKernelGGL(ldl_update_kernel<2>, dim3((pairs + 3) / 4), dim3(256), 0, st, T, (const double *)Ms, nb,
+                               J0, pairs);
+        } else {
+            const int pairs = below * (below + 1) / 2;
+            hipLaunchKernelGGL(ldl_update_kernel<1>, dim3((pairs + 3) / 4), dim3(256), 0, st, T, (const double *)Ms, nb,
+                               J0, pairs);
+        }
     }
-    hipLaunchKernelGGL(ldl_emit_kernel, dim3(1024), dim3(256), 0, st, (const double *)Lm, A, n, G);
     return hipGetLastError();
 }
 
