@@ -256,7 +256,7 @@ int qtip_quantize_gpu(const float *W, int m, int n, int L, int k, int V, int cod
  *   D_out:   device, (n/g) x g x g binary64, or NULL: the diagonal blocks of D.
  *   workspace: device, 256-byte aligned, qtip_block_ldl_workspace(n) bytes (two n x n
  *            binary64 matrices); contents are scratch.
- * Binary64 throughout; 2 n/g + 2 kernel launches on `stream`, no synchronization.
+ * Binary64 throughout; about n/64 kernel launches on `stream`, no synchronization.
  */
 size_t qtip_block_ldl_workspace(int n);
 int qtip_block_ldl(const double *H, int n, int g, float *A_out, double *D_out, void *workspace,

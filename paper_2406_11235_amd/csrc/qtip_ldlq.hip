@@ -37,17 +37,17 @@ namespace {
 // The workspace holds T and M by blocks of 2 KiB, which a wave reads and writes as they are.
 //
 // Panels of 8 block columns, two launches each.  ldl_panel_kernel: a workgroup has a wave for each of the panel's own 8
-// block rows and LDL_ROWS waves for block rows below; a wave holds its 8 blocks in registers.  The pivot wave inverts
+// block rows and one to four for block rows below; a wave holds its 8 blocks in registers.  The pivot wave inverts
 // D_j, and after one barrier per block column all waves take the two products above.  Every workgroup
 // factors the panel's own rows again, which costs no time (the inversions are a serial chain and leave the
-// matrix cores idle) and saves a launch per panel.  ldl_update_kernel: the products with what is right of the
-// panel.
+// matrix cores idle) and saves a launch per panel.  ldl_update_panel_kernel: the panel's products with the next
+// panel's block columns.  Those with everything further right are taken beside the next panel, in its launch.
 // What bounds it is that chain: 16 pivots per block column, about 1 us, and a launch with its gap twice per panel.
 // n = 2048, g = 16: 1744 us with two launches per block column, the inversion with five barriers per pivot and the
-// products on the vector units, LDL_US us now.
+// products on the vector units, 412 us now.
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
-constexpr int LDL_PANEL = 8, LDL_ROWS = 4;
+constexpr int LDL_PANEL = 8, LDL_MAX_ROWS = 4;
 
 __device__ __forceinline__ double *ldl_block(double *base, int nb, int k, int i) {
     return base + ((size_t)k * nb + i) * 256;
@@ -66,19 +66,25 @@ __device__ __forceinline__ double4_t ldl_product(double4_t x, double4_t y, doubl
     return c;
 }
 
-// T from the lower triangle of H, one wave per block, and zeros where A has no block of its own.
+// T from the lower triangle of H, and zeros where A has no block of its own.
 __global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict__ H, double *__restrict__ T,
                                                        float *__restrict__ A, int n) {
     const int nb = n >> 4, lane = threadIdx.x & 63;
-    const int i = blockIdx.y, j = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= nb) return;
-    const int r = lane >> 2, m = lane & 3;  // row r, columns 4 m .. 4 m + 3 of the block
-    if (j >= i) *reinterpret_cast<float4_t *>(A + (size_t)(16 * i + r) * n + 16 * j + 4 * m) = float4_t{0.f, 0.f, 0.f, 0.f};
-    if (j > i) return;
-    const double *h = H + (size_t)(16 * i + r) * n + 16 * j + 4 * m;
-    double *t = ldl_block(T, nb, j, i) + 64 * m + r;
+    const int i = blockIdx.y, r = lane >> 2, m = lane & 3;  // row r, columns 4 m .. 4 m + 3 of the block
+    const double *h = H + (size_t)(16 * i + r) * n + 4 * m;
+    float *a = A + (size_t)(16 * i + r) * n + 4 * m;
 #pragma unroll
-    for (int c = 0; c < 4; c++) t[16 * c] = h[c];
+    for (int e = 0; e < 4; e++) {
+        const int j = blockIdx.x * 16 + 4 * e + (threadIdx.x >> 6);
+        if (j < nb && j >= i) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) a[16 * j + c] = 0.f;
+        }
+        if (j > i) continue;
+        double *t = ldl_block(T, nb, j, i) + 64 * m + r;
+#pragma unroll
+        for (int c = 0; c < 4; c++) t[16 * c] = h[16 * j + c];
+    }
 }
 
 // a[c] += b * a_p[c], a_p the row that lane p of this row of 16 lanes holds.  (A register that the vector ALU has just
@@ -95,6 +101,43 @@ template <int p>
 __device__ __forceinline__ double row_value(double a) {  // of lane p of this row of 16 lanes
     double v;
     asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=&v"(v) : "v"(a), "n"(p));
+    return v;
+}
+
+// Rows of a symmetric block in the result layout: a[c] = entry (l % 16, c) in lane l.  The lane has column l % 16,
+// four of its entries; the others are in the lanes 16, 32 and 48 further on, and come by exchanges of lane rows.
+__device__ __forceinline__ void ldl_rows(double4_t d, double (&a)[16]) {
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+        const double v = d[t];
+        const u32x2_t w = __builtin_bit_cast(u32x2_t, v);
+        u32x2_t out[4];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            // (x, x) -> the even lane rows' values in both rows of a pair, the odd ones'; then the same for halves
+            const auto p = __builtin_amdgcn_permlane16_swap(w[h], w[h], false, false);
+            const auto lo = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);
+            out[0][h] = lo[0];
+            out[1][h] = hi[0];
+            out[2][h] = lo[1];
+            out[3][h] = hi[1];
+        }
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+            const u32x2_t o = out[g];
+            a[4 * t + g] = __builtin_bit_cast(double, o);
+        }
+    }
+}
+// The other way: entries 4 t + g, g = l / 16, of the lane's row: an A operand with the rows as they are.
+__device__ __forceinline__ double4_t ldl_operand(const double (&a)[16], int g) {
+    double4_t v;
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+        const double e = g & 1 ? a[4 * t + 1] : a[4 * t], o = g & 1 ? a[4 * t + 3] : a[4 * t + 2];
+        v[t] = g & 2 ? o : e;
+    }
     return v;
 }
 
@@ -136,21 +179,93 @@ __device__ __forceinline__ void ldl_emit(float *__restrict__ A, int n, int i, in
     for (int t = 0; t < 4; t++) a[4 * t] = (float)e[t];
 }
 
-// Block columns J0 .. J0 + np - 1, and the LDL_ROWS block rows of this workgroup below them.
-template <int G>
-__global__ __launch_bounds__((LDL_PANEL + LDL_ROWS) * 64) void ldl_panel_kernel(double *__restrict__ T,
+// T_ki -= sum over the block columns j of the panel at J0 of T_jk^T M_ji, for the TB x TB blocks from (k0, i0) on that
+// have k <= i, by one wave.
+template <int TB>
+__device__ __forceinline__ void ldl_update(double *T, const double *Ms, int nb, int J0, int k0, int i0, int lane) {
+    int k[TB], i[TB];
+#pragma unroll
+    for (int e = 0; e < TB; e++) {
+        k[e] = min(k0 + e, nb - 1);
+        i[e] = min(i0 + e, nb - 1);
+    }
+    double4_t acc[TB][TB], old[TB][TB];
+    // the operands of three block columns ahead: another XCD's workgroup has just written them, so they come from
+    // behind the L2
+    constexpr int AHEAD = 3;
+    double4_t x[AHEAD + 1][TB], y[AHEAD + 1][TB];
+    auto load = [&](int j, int to) {
+#pragma unroll
+        for (int e = 0; e < TB; e++) {
+            x[to][e] = ldl_load(ldl_block(T, nb, J0 + j, k[e]), lane);
+            y[to][e] = ldl_load(ldl_block(const_cast<double *>(Ms), nb, J0 + j, i[e]), lane);
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < AHEAD; j++) load(j, j);
+#pragma unroll
+    for (int a = 0; a < TB; a++)
+#pragma unroll
+        for (int b = 0; b < TB; b++) {
+            acc[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
+            old[a][b] = ldl_load(ldl_block(T, nb, min(k[a], i[b]), max(k[a], i[b])), lane);
+        }
+#pragma unroll
+    for (int j = 0; j < LDL_PANEL; j++) {
+        if (j + AHEAD < LDL_PANEL) load(j + AHEAD, (j + AHEAD) % (AHEAD + 1));
+#pragma unroll
+        for (int a = 0; a < TB; a++)
+#pragma unroll
+            for (int b = 0; b < TB; b++)
+                acc[a][b] = ldl_product(x[j % (AHEAD + 1)][a], y[j % (AHEAD + 1)][b], acc[a][b]);
+    }
+#pragma unroll
+    for (int a = 0; a < TB; a++)
+#pragma unroll
+        for (int b = 0; b < TB; b++) {
+            if (i0 + b >= nb || k0 + a > i0 + b) continue;
+            ldl_store(ldl_block(T, nb, k[a], i[b]), lane, old[a][b] - acc[a][b]);
+        }
+}
+// The same for the w-th pair of block groups, kp <= ip, of the triangle from block b0 on.
+template <int TB>
+__device__ __forceinline__ void ldl_update_triangle(double *T, const double *Ms, int nb, int J0, int b0, int w, int lane) {
+    int ip = (int)((__builtin_sqrtf(8.f * (float)w + 1.f) - 1.f) * 0.5f);  // w = ip (ip + 1) / 2 + kp
+    while ((ip + 1) * (ip + 2) / 2 <= w) ip++;
+    while (ip * (ip + 1) / 2 > w) ip--;
+    ldl_update<TB>(T, Ms, nb, J0, b0 + TB * (w - ip * (ip + 1) / 2), b0 + TB * ip, lane);
+}
+// The block columns of the panel behind the one at J0.
+__global__ __launch_bounds__(256) void ldl_update_panel_kernel(double *__restrict__ T, const double *__restrict__ Ms,
+                                                               int nb, int J0) {
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int k = J0 + LDL_PANEL + w % LDL_PANEL, i = J0 + LDL_PANEL + w / LDL_PANEL;
+    if (i < nb && k <= i) ldl_update<1>(T, Ms, nb, J0, k, i, threadIdx.x & 63);
+}
+
+// The first `groups` workgroups: block columns J0 .. J0 + np - 1, and `rows` block rows below them per workgroup, a wave
+// each.  The others: what the panel before has to subtract behind this one, TB x TB blocks per wave, on the CUs that
+// the chain leaves idle.
+template <int G, int TB>
+__global__ __launch_bounds__((LDL_PANEL + LDL_MAX_ROWS) * 64) void ldl_panel_kernel(double *__restrict__ T,
                                                                                double *__restrict__ Ms,
                                                                                float *__restrict__ A, int n, int J0,
+                                                                               int groups, int rows, int pairs,
                                                                                double *__restrict__ Dout) {
-    __shared__ __attribute__((aligned(16))) double s_inv[2][16][18];  // D_j^-1 by rows
-    __shared__ __attribute__((aligned(16))) double s_out[2][16][18];  // what L_ij^T is made with: for G = 8 see below
+    // D_j^-1 as an A operand, and what L_ij^T is made with (for G = 8 see below)
+    __shared__ __attribute__((aligned(16))) double s_inv[2][256];
+    __shared__ __attribute__((aligned(16))) double s_out[2][G == 8 ? 256 : 1];
     __shared__ __attribute__((aligned(16))) double s_t[2][LDL_PANEL][256];
-    __shared__ __attribute__((aligned(16))) double s_d[16][18];
     const int nb = n >> 4, np = min(LDL_PANEL, nb - J0);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if ((int)blockIdx.x >= groups) {
+        const int w = (blockIdx.x - groups) * (LDL_PANEL + rows) + wave;
+        if (w < pairs) ldl_update_triangle<TB>(T, Ms, nb, J0 - LDL_PANEL, J0 + LDL_PANEL, w, lane);
+        return;
+    }
     const int row = lane & 15, g = lane >> 4;
     const bool own = wave < LDL_PANEL;  // of the panel's own block rows
-    const int rel = own ? wave : LDL_PANEL + blockIdx.x * LDL_ROWS + (wave - LDL_PANEL);
+    const int rel = own ? wave : LDL_PANEL + blockIdx.x * rows + (wave - LDL_PANEL);
     const int i = J0 + rel;
     const bool some = i < nb;
     const bool speaks = own ? blockIdx.x == 0 : true;  // writes results
@@ -160,28 +275,15 @@ __global__ __launch_bounds__((LDL_PANEL + LDL_ROWS) * 64) void ldl_panel_kernel(
         t[j] = double4_t{0.0, 0.0, 0.0, 0.0};
         if (some && j < np && j <= rel) t[j] = ldl_load(ldl_block(T, nb, J0 + j, i), lane);
     }
+    double4_t last = {0.0, 0.0, 0.0, 0.0}, out_before = last;
 #pragma unroll
     for (int j = 0; j < LDL_PANEL; j++) {
         if (j >= np) break;
         const int buf = j & 1;
         if (own && rel > j) ldl_store(s_t[buf][rel], lane, t[j]);
         if (wave == j) {
-#pragma unroll
-            for (int q = 0; q < 4; q++) s_d[4 * q + g][row] = t[j][q];
-            // (this wave's own LDS: its operations complete in order, the fence keeps the compiler in line)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             double a[16];
-#pragma unroll
-            for (int c = 0; c < 16; c++) a[c] = s_d[row][c];
-            double *const d = Dout + (size_t)(J0 + j) * (16 / G) * (G * G);
-            const bool d_out = Dout != nullptr && blockIdx.x == 0 && g == 0;
-            if (d_out) {
-#pragma unroll
-                for (int c = 0; c < 16; c++)
-                    if (G == 16 || (row < 8 && c < 8)) d[row * G + c] = a[c];
-            }
+            ldl_rows(t[j], a);
             double scale = 1.0;
             const double first = reciprocal(row_value<0>(a[0]));
             if constexpr (G == 16) {
@@ -190,107 +292,62 @@ __global__ __launch_bounds__((LDL_PANEL + LDL_ROWS) * 64) void ldl_panel_kernel(
                 // Half-way the first 8 rows hold the inverse of D's first 8 x 8 block, the last 8 the second
                 // block of D in 8 x 8 blocks and, negative, the entry of L between the two.
                 ldl_invert<0, 8>(a, first, scale, row);
-                if (d_out && row >= 8) {
-#pragma unroll
-                    for (int c = 0; c < 8; c++) d[64 + (row - 8) * 8 + c] = a[8 + c];
-                }
                 if (blockIdx.x == 0 && g == 0 && row >= 8) {
 #pragma unroll
-                    for (int c = 0; c < 8; c++) A[(size_t)(16 * (J0 + j) + row) * n + 16 * (J0 + j) + c] = (float)-a[c];
+                    for (int c = 0; c < 8; c++) {
+                        A[(size_t)(16 * (J0 + j) + row) * n + 16 * (J0 + j) + c] = (float)-a[c];
+                        if (Dout) Dout[(size_t)(J0 + j) * 128 + 64 + (row - 8) * 8 + c] = a[8 + c];
+                    }
                 }
-                if (g == 0 && row < 8) {
+                double f[16];
 #pragma unroll
-                    for (int c = 0; c < 16; c++) s_out[buf][row][c] = c < 8 ? a[c] * scale : 0.0;
-                }
+                for (int c = 0; c < 16; c++) f[c] = c < 8 ? a[c] * scale : 0.0;
                 ldl_invert<8, 16>(a, reciprocal(row_value<8>(a[8])), scale, row);
+#pragma unroll
+                for (int c = 0; c < 16; c++) f[c] = row < 8 ? f[c] : a[c] * scale;
+                ldl_store(s_out[buf], lane, ldl_operand(f, g));
             }
-            if (g == 0) {
+            ldl_store(s_inv[buf], lane, ldl_operand(a, g) * scale);
+        }
+        // (the waves meet for what is in LDS; the results on their way to memory are nobody's business here)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (wave == j && blockIdx.x == 0 && j > 0) {
+            const double4_t e = G == 16 ? last : ldl_product(out_before, t[j > 0 ? j - 1 : 0], double4_t{0.0, 0.0, 0.0, 0.0});
+            ldl_emit(A, n, i, J0 + j - 1, lane, e);
+        }
+        if (wave == j && blockIdx.x == 0 && Dout) {
+            if constexpr (G == 16) {
+                ldl_store(Dout + (size_t)(J0 + j) * 256, lane, t[j]);
+            } else if (row < 8) {
 #pragma unroll
-                for (int c = 0; c < 16; c++) s_inv[buf][row][c] = a[c] * scale;
-                if (G == 8 && row >= 8) {
-#pragma unroll
-                    for (int c = 0; c < 16; c++) s_out[buf][row][c] = a[c] * scale;
-                }
+                for (int q = 0; q < 2; q++) Dout[(size_t)(J0 + j) * 128 + (4 * q + g) * 8 + row] = t[j][q];
             }
         }
-        __syncthreads();
         if (some && rel > j) {
-            double4_t inv, m = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int q = 0; q < 4; q++) inv[q] = s_inv[buf][row][4 * q + g];  // an A operand by rows
-            m = ldl_product(inv, t[j], m);
+            const double4_t m = ldl_product(ldl_load(s_inv[buf], lane), t[j], double4_t{0.0, 0.0, 0.0, 0.0});
             const double4_t neg = -m;
             // (the next block column's block first: the next pivot wave waits for it)
 #pragma unroll
             for (int k = j + 1; k < LDL_PANEL; k++)
                 if (k < np && k <= rel) t[k] = ldl_product(ldl_load(s_t[buf][k], lane), neg, t[k]);
-            if (speaks) {
+            // (the next pivot wave writes its last block when its own pivot is done)
+            if (rel == j + 1 && own) {
+                last = m;
+                if constexpr (G == 8) out_before = ldl_load(s_out[buf], lane);
+            } else if (speaks) {
                 if (!own) {
                     ldl_store(ldl_block(T, nb, J0 + j, i), lane, t[j]);
                     ldl_store(ldl_block(Ms, nb, J0 + j, i), lane, m);
                 }
                 if constexpr (G == 8) {
-                    double4_t out, e = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int q = 0; q < 4; q++) out[q] = s_out[buf][row][4 * q + g];
-                    ldl_emit(A, n, i, J0 + j, lane, ldl_product(out, t[j], e));
+                    ldl_emit(A, n, i, J0 + j, lane,
+                             ldl_product(ldl_load(s_out[buf], lane), t[j], double4_t{0.0, 0.0, 0.0, 0.0}));
                 } else {
                     ldl_emit(A, n, i, J0 + j, lane, m);
                 }
             }
         }
     }
-}
-
-// T_ki -= sum over the panel's block columns j of T_jk^T M_ji, for k <= i from block b0 on; TB x TB blocks per wave.
-template <int TB>
-__global__ __launch_bounds__(256) void ldl_update_kernel(double *__restrict__ T, const double *__restrict__ Ms, int nb,
-                                                         int J0, int pairs) {
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (w >= pairs) return;
-    // w = ip (ip + 1) / 2 + kp, kp <= ip
-    int ip = (int)((__builtin_sqrtf(8.f * (float)w + 1.f) - 1.f) * 0.5f);
-    while ((ip + 1) * (ip + 2) / 2 <= w) ip++;
-    while (ip * (ip + 1) / 2 > w) ip--;
-    const int kp = w - ip * (ip + 1) / 2;
-    const int b0 = J0 + LDL_PANEL;
-    int k[TB], i[TB];
-#pragma unroll
-    for (int e = 0; e < TB; e++) {
-        k[e] = min(b0 + TB * kp + e, nb - 1);
-        i[e] = min(b0 + TB * ip + e, nb - 1);
-    }
-    double4_t acc[TB][TB];
-#pragma unroll
-    for (int a = 0; a < TB; a++)
-#pragma unroll
-        for (int b = 0; b < TB; b++) acc[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
-    double4_t x[2][TB], y[2][TB];
-    auto load = [&](int j, int to) {
-#pragma unroll
-        for (int e = 0; e < TB; e++) {
-            x[to][e] = ldl_load(ldl_block(T, nb, J0 + j, k[e]), lane);
-            y[to][e] = ldl_load(ldl_block(const_cast<double *>(Ms), nb, J0 + j, i[e]), lane);
-        }
-    };
-    load(0, 0);
-#pragma unroll
-    for (int j = 0; j < LDL_PANEL; j++) {
-        if (j + 1 < LDL_PANEL) load(j + 1, (j + 1) & 1);
-#pragma unroll
-        for (int a = 0; a < TB; a++)
-#pragma unroll
-            for (int b = 0; b < TB; b++) acc[a][b] = ldl_product(x[j & 1][a], y[j & 1][b], acc[a][b]);
-    }
-#pragma unroll
-    for (int a = 0; a < TB; a++)
-#pragma unroll
-        for (int b = 0; b < TB; b++) {
-            if (b0 + TB * ip + b >= nb || b0 + TB * kp + a > b0 + TB * ip + b) continue;
-            double *at = ldl_block(T, nb, k[a], i[b]);
-            ldl_store(at, lane, ldl_load(at, lane) - acc[a][b]);
-        }
 }
 
 // ------------------------------------------------------------------ Algorithm 5
@@ -368,24 +425,23 @@ static hipError_t block_ldl_t(const double *H, int n, float *A, double *Dout, vo
     double *T = (double *)ws;
     double *Ms = (double *)((char *)ws + align256((size_t)n * n * sizeof(double)));
     const int nb = n / 16;
-    hipLaunchKernelGGL(ldl_init_kernel, dim3((nb + 3) / 4, nb), dim3(256), 0, st, H, T, A, n);
+    hipLaunchKernelGGL(ldl_init_kernel, dim3((nb + 15) / 16, nb), dim3(256), 0, st, H, T, A, n);
     for (int J0 = 0; J0 < nb; J0 += LDL_PANEL) {
         const int below = nb - J0 - LDL_PANEL;  // block rows below the panel
-        const int groups = below > 0 ? (below + LDL_ROWS - 1) / LDL_ROWS : 1;
-        hipLaunchKernelGGL(ldl_panel_kernel<G>, dim3(groups), dim3((LDL_PANEL + LDL_ROWS) * 64), 0, st, T, Ms, A, n, J0,
-                           Dout);
-        if (below <= 0) break;
-        // 2 x 2 blocks per wave while that is a wave per SIMD; single blocks, a shorter chain, otherwise
-        const int p2 = (below + 1) / 2;
-        if (p2 * (p2 + 1) / 2 >= 512) {
-            const int pairs = p2 * (p2 + 1) / 2;
-            hipLaunchKernelGGL(ldl_update_kernel<2>, dim3((pairs + 3) / 4), dim3(256), 0, st, T, (const double *)Ms, nb,
-                               J0, pairs);
-        } else {
-            const int pairs = below * (below + 1) / 2;
-            hipLaunchKernelGGL(ldl_update_kernel<1>, dim3((pairs + 3) / 4), dim3(256), 0, st, T, (const double *)Ms, nb,
-                               J0, pairs);
-        }
+        // as few rows per workgroup as keep it at one workgroup per CU: they take the matrix cores from the chain
+        const int rows = below <= 256 ? 1 : below <= 512 ? 2 : LDL_MAX_ROWS;
+        const int groups = below > 0 ? (below + rows - 1) / rows : 1, waves = LDL_PANEL + rows;
+        // 2 x 2 blocks per wave while that is half a wave per SIMD; single blocks, a shorter chain, otherwise
+        const int p2 = J0 > 0 && below > 0 ? (below + 1) / 2 : 0, pairs2 = p2 * (p2 + 1) / 2;
+        const int pairs = pairs2 >= 512 ? pairs2 : p2 > 0 ? below * (below + 1) / 2 : 0;
+        const dim3 grid(groups + (pairs + waves - 1) / waves), block(waves * 64);
+        if (pairs2 >= 512)
+            hipLaunchKernelGGL((ldl_panel_kernel<G, 2>), grid, block, 0, st, T, Ms, A, n, J0, groups, rows, pairs, Dout);
+        else
+            hipLaunchKernelGGL((ldl_panel_kernel<G, 1>), grid, block, 0, st, T, Ms, A, n, J0, groups, rows, pairs, Dout);
+        if (below > 0)
+            hipLaunchKernelGGL(ldl_update_panel_kernel, dim3((below * LDL_PANEL + 3) / 4), dim3(256), 0, st, T,
+                               (const double *)Ms, nb, J0);
     }
     return hipGetLastError();
 }
