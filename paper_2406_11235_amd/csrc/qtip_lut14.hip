@@ -110,44 +110,57 @@ __global__ void lut_decode_states_kernel(const uint32_t *__restrict__ states, in
 
 // ------------------------------------------------------- decode + matvec (B = 1)
 
-template <int K, int NW>
-__global__ __launch_bounds__(NW * 64) void lut_matvec_kernel(const uint32_t *__restrict__ codes,
-                                                             const uint16_t *__restrict__ lut, int tn,
-                                                             const half_t *__restrict__ x,
-                                                             const half_t *__restrict__ scale,
-                                                             float *__restrict__ y) {
-    constexpr int WPL = Geo<K>::WPL, LPT = Geo<K>::LPT;
+// A workgroup has 32 / S rows of a block row.  The random reads of the table are the bound (one 64-lane read takes the
+// LDS about 8 cycles for bank conflicts), so what counts is that all CUs have the same number of them: a block row is
+// given to S workgroups where a whole one each would leave CUs idle (see pick_lut_split).
+// k = 2: 4128 x 14464, 129 block rows, 28.2 us at S = 1, 25.3 at S = 4; 4096 x 4096 10.4 at S = 1, 7.1 at S = 2;
+// k = 3: 2048 x 8192 15.8 at S = 1, 6.8 at S = 4.
+template <int K, int S, int NW>
+__global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint32_t *__restrict__ codes,
+                                                                     const uint16_t *__restrict__ lut, int tm, int tn,
+                                                                     const half_t *__restrict__ x,
+                                                                     const half_t *__restrict__ scale,
+                                                                     float *__restrict__ y) {
+    constexpr int WPL = Geo<K>::WPL, NWORDS = 8 * K;
     constexpr int WL = WPL * 32 / K, RL = WL / LUT_TY;  // weights and block rows per lane
+    constexpr int ROWS = LUT_TX / S, LPT = ROWS / RL;   // rows of the workgroup; lanes of a block
     constexpr int TPI = 64 / LPT;                       // blocks per wave per step
+    static_assert(LPT >= 1, "whole lanes");
     __shared__ __attribute__((aligned(16))) uint16_t s_tab[LUT_STATES];
-    __shared__ float s_part[NW][LUT_TX];
-    stage_table(lut, s_tab, NW * 64);
-    __syncthreads();
-    const int I = blockIdx.x;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ float s_part[NW][ROWS];
+    // Workgroups go round the eight XCDs; those of one block row, which read the same cache lines, stay on one.
+    const int local = blockIdx.x >> 3;
+    const int I = local / S * 8 + (blockIdx.x & 7), part = local % S;
+    if (I >= tm) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int g = lane / LPT, q = lane & (LPT - 1);
     const int chunk = ((tn + NW * TPI - 1) / (NW * TPI)) * TPI;
     const int J0 = wave * chunk;
     const int Jend = min(tn, J0 + chunk);
+    const uint32_t *__restrict__ row_codes = codes + (size_t)I * tn * NWORDS;
+    const uint32_t w0 = (part * LPT + q) * WPL, w_next = (w0 + WPL) % NWORDS;  // (the stream is cyclic: tail-biting)
     float acc[RL];
 #pragma unroll
     for (int rr = 0; rr < RL; rr++) acc[rr] = 0.f;
 
     // software pipeline over two alternating operand sets, as in the 16 x 16 kernel
     struct Operands {
-        Words<K> w;
+        WordsN<WPL> w;
+        uint32_t next;
         uint4 xv;
     };
     auto issue = [&](Operands &o, int Jb) {
-        const int Jc = min(Jb + g, Jend - 1);  // lanes past the end re-read the last block
-        o.w = load_words<K>(codes, (size_t)I * tn + Jc, q);
-        o.xv = *reinterpret_cast<const uint4 *>(x + LUT_TY * Jc);
+        const uint32_t Jc = min(Jb + g, Jend - 1);  // lanes past the end re-read the last block
+        o.w = load_words_at<WPL>(row_codes, (Jc * NWORDS + w0) * 4);
+        o.next = stream_load(reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(row_codes) +
+                                                                (size_t)((Jc * NWORDS + w_next) * 4)));
+        o.xv = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(x) + (size_t)(Jc * 16u));
     };
     auto compute = [&](const Operands &o, int Jb) {
         uint32_t w[WPL + 1];
 #pragma unroll
         for (int i = 0; i < WPL; i++) w[i] = o.w.v[i];
-        w[WPL] = __shfl(w[0], (lane & ~(LPT - 1)) | ((q + 1) & (LPT - 1)), 64);  // tail-biting wrap
+        w[WPL] = o.next;
         if (Jb + g < Jend) {
             const uint32_t xv[4] = {o.xv.x, o.xv.y, o.xv.z, o.xv.w};
             uint32_t off[WL];
@@ -162,7 +175,9 @@ __global__ __launch_bounds__(NW * 64) void lut_matvec_kernel(const uint32_t *__r
         }
     };
     Operands opA, opB;
-    if (J0 < Jend) issue(opA, J0);
+    if (J0 < Jend) issue(opA, J0);  // (ahead of the table, so that they are under way while it is filled)
+    stage_table(lut, s_tab, NW * 64);
+    __syncthreads();
     for (int Jb = J0; Jb < Jend; Jb += 2 * TPI) {
         if (Jb + TPI < Jend) issue(opB, Jb + TPI);
         compute(opA, Jb);
@@ -181,11 +196,11 @@ __global__ __launch_bounds__(NW * 64) void lut_matvec_kernel(const uint32_t *__r
         for (int rr = 0; rr < RL; rr++) s_part[wave][q * RL + rr] = acc[rr];
     }
     __syncthreads();
-    if (threadIdx.x < LUT_TX) {
+    if (threadIdx.x < ROWS) {
         float s = 0.f;
 #pragma unroll
         for (int wv = 0; wv < NW; wv++) s += s_part[wv][threadIdx.x];
-        const int row = LUT_TX * I + threadIdx.x;
+        const int row = LUT_TX * I + ROWS * part + threadIdx.x;
         if (scale) s *= (float)scale[row];
         y[row] = s;
     }
@@ -331,19 +346,35 @@ hipError_t launch_lut_decode_states(const uint32_t *states, int count, const voi
     return hipGetLastError();
 }
 
+// Workgroups per block row for the batch-1 kernel.  A CU's share of workgroups, each 1 us for its copy of the table and
+// 32 n / S reads of the table, 8 cycles per 64: the smallest, over the shares that S = 1, 2 and 4 make.
+static int pick_lut_split(int tm, int n) {
+    int best = 1;
+    float least = 0.f;
+    for (int s = 1; s <= 4; s *= 2) {
+        const float t = (float)((tm * s + 255) / 256) * (1.f + (float)n / s * (4.f / 2400.f));
+        if (s == 1 || t < least) best = s, least = t;
+    }
+    return best;
+}
+
 template <int K>
 static hipError_t lut_matvec_t(const uint32_t *codes, const uint16_t *tab, int m, int n, const void *x,
                                const void *scale, float *y, hipStream_t st) {
-    constexpr int TPI = 64 / Geo<K>::LPT;
-    const int tm = m / LUT_TX, tn = n / LUT_TY;
-    const int steps = (tn + TPI - 1) / TPI;
-    // every workgroup first copies the table (32 KiB), so few large workgroups
-    if (steps >= 32)
-        hipLaunchKernelGGL((lut_matvec_kernel<K, 16>), dim3(tm), dim3(1024), 0, st, codes, tab, tn,
-                           (const half_t *)x, (const half_t *)scale, y);
-    else
-        hipLaunchKernelGGL((lut_matvec_kernel<K, 8>), dim3(tm), dim3(512), 0, st, codes, tab, tn,
-                           (const half_t *)x, (const half_t *)scale, y);
+    const int tm = m / LUT_TX, tn = n / LUT_TY, s = pick_lut_split(tm, n);
+    const dim3 grid((tm + 7) / 8 * 8 * s);
+#define QTIP_LUT_MV(S, NW)                                                                              \
+    hipLaunchKernelGGL((lut_matvec_kernel<K, S, NW>), grid, dim3(NW * 64), 0, st, codes, tab, tm, tn, \
+                       (const half_t *)x, (const half_t *)scale, y)
+    // (every workgroup first copies the table, so few large ones; a wave needs a few steps to itself)
+    constexpr int TPI = Geo<K>::LPT == 4 ? 16 : 8;
+    const bool wide = tn >= 32 * TPI * s;
+    if (s == 1 && wide) QTIP_LUT_MV(1, 16);
+    else if (s == 1) QTIP_LUT_MV(1, 8);
+    else if (s == 2 && wide) QTIP_LUT_MV(2, 16);
+    else if (s == 2) QTIP_LUT_MV(2, 8);
+    else QTIP_LUT_MV(4, 8);
+#undef QTIP_LUT_MV
     return hipGetLastError();
 }
 
