@@ -327,18 +327,26 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
 // activations line by line (8 lanes = the 128 bytes that one batch row has under the
 // four tiles of a step) and transposes them through a private piece of LDS.
 
-// The words that hold tile row i (16 K bits from bit 16 K i) and the 16 - K V bits
-// after it, brought to bit offset 0; indices wrap inside the tile (tail-biting).
+// The words that hold tile row i (16 K bits from bit 16 K i) and the 16 - K V bits after it, brought to bit offset 0;
+// words behind a row's own wrap inside the tile (tail-biting).  At k = 2 and 4 a row is one or two whole words and
+// the word behind it is the first one of the next row, which the next lane of a row of 16 lanes has: one load per row.
 template <int K>
-__device__ __forceinline__ void load_row_words(const uint32_t *__restrict__ tile, int i,
-                                               uint32_t (&w)[3]) {
+__device__ __forceinline__ void load_row_words(const uint32_t *__restrict__ tile, int i, uint32_t (&w)[3]) {
     constexpr int NWORDS = 8 * K;
-    const int bit = 16 * K * i;
-    const int w0 = bit >> 5;
-    w[0] = stream_load(tile + w0);
-    w[1] = stream_load(tile + (w0 + 1) % NWORDS);
-    w[2] = (K == 2) ? 0u : stream_load(tile + (w0 + 2) % NWORDS);
+    if constexpr (K == 2) {
+        w[0] = stream_load(tile + i);
+    } else if constexpr (K == 4) {
+        const u32x2_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(tile + 2 * i));
+        w[0] = t.x;
+        w[1] = t.y;
+    } else {
+        const int w0 = (16 * K * i) >> 5;
+        w[0] = stream_load(tile + w0);
+        w[1] = stream_load(tile + (w0 + 1) % NWORDS);
+        w[2] = stream_load(tile + (w0 + 2) % NWORDS);
+    }
 }
+// (every lane of the wave makes the call)
 template <int K>
 __device__ __forceinline__ void align_row_words(int i, uint32_t (&w)[3]) {
     if constexpr (K == 3) {
@@ -347,18 +355,19 @@ __device__ __forceinline__ void align_row_words(int i, uint32_t (&w)[3]) {
             w[1] = __builtin_amdgcn_alignbit(w[1], w[2], 16);
             w[2] <<= 16;
         }
+    } else {
+        w[K / 2] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[0], 0x12F, 0xF, 0xF, false);  // row rotate by 15
     }
 }
 
 // SPREAD: the HYB table in 16 copies, as in the batch-1 kernel (64 KiB: only next to the
 // small partial-sum buffer of NB = 1).
-template <int K, int V, int CODE, int NB, int NW, bool STAGE, bool SPREAD = false>
+template <int K, int V, int CODE, int R, int NB, int NW, bool STAGE, bool SPREAD = false>
 __global__ __launch_bounds__(NW * 64) void matmat_kernel(const uint32_t *__restrict__ codes,
                                                          const uint32_t *__restrict__ lut,
                                                          int tm, int tn, const half_t *__restrict__ X,
                                                          int B, const half_t *__restrict__ scale,
                                                          float *__restrict__ Y) {
-    constexpr int R = 2;
     constexpr int NWORDS = 8 * K;
     __shared__ __attribute__((aligned(16))) uint32_t s_lut[code_lds_words(CODE, SPREAD)];
     // one buffer, used twice: in the loop each wave's staging region (SR batch rows at a
@@ -381,7 +390,9 @@ __global__ __launch_bounds__(NW * 64) void matmat_kernel(const uint32_t *__restr
     const int chunk = ((tn + NW * 4 - 1) / (NW * 4)) * 4;
     const int J0 = wave * chunk;
     const int Jend = min(tn, J0 + chunk);
-    const bool row_ok[R] = {true, I0 + 1 < tm};
+    bool row_ok[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) row_ok[r] = I0 + r < tm;
 
     float4_t acc[R][NB];
 #pragma unroll
@@ -598,27 +609,34 @@ template <int K, int V, int CODE>
 static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, int m, int n,
                                   const void *X, int B, const void *scale, float *Y,
                                   hipStream_t st) {
-    constexpr int NW = 8;
-    const int groups = (B + 15) / 16;
+    const int groups = (B + 15) / 16;  // more than one only where the large-batch kernel does not reach
     const int tm = m / 16, tn = n / 16;
-    const dim3 block(NW * 64);
     const half_t *Xh = (const half_t *)X, *sc = (const half_t *)scale;
     constexpr bool HYB = CODE == CODE_HYB;
     // (measured: the 16 table copies pay at 9 to 16 batch rows, 8192 x 8192 13.1 -> 12.3 us and
     // 8192 x 28672 35 -> 31 us, and make no difference below)
-    const bool spread = HYB && pick_hyb_spread(CODE, n);
-    if (groups == 1 && B <= 8) {  // few distinct batch rows: load the B operand directly
-        hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, NW, false>), dim3((tm + 1) / 2, 1), block, 0,
-                           st, codes, lut, tm, tn, Xh, B, sc, Y);
-    } else {  // (several groups only where the large-batch kernel does not reach)
-        const dim3 grid((tm + 1) / 2, groups);
-        if (spread)
-            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, NW, true, HYB>), grid, block, 0, st, codes, lut, tm, tn,
-                               Xh, B, sc, Y);
-        else
-            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, NW, true>), grid, block, 0, st, codes, lut, tm, tn, Xh,
-                               B, sc, Y);
+    const bool spread = HYB && pick_hyb_spread(CODE, n) && B > 8;
+    // Two tile rows per workgroup share what is loaded of X; one where that gives a CU less to do: matrices of
+    // at most 4096 rows, which would fill half of the CUs (then with 16 waves: 4 rows, 4096 x 14336 2-bit 3INST
+    // 22.3 -> 14.1 us, 4096 x 4096 8.4 -> 5.9), and row counts between the rounds (10240: 37.2 -> 33.8).
+#define QTIP_MM(R, NW, STAGE, SPREAD)                                                                              \
+    hipLaunchKernelGGL((matmat_kernel<K, V, CODE, R, 1, NW, STAGE, SPREAD>), dim3((tm + R - 1) / R, groups),      \
+                       dim3(NW * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y)
+#define QTIP_MM_BATCH(R, NW)                                    \
+    if (B <= 8) QTIP_MM(R, NW, false, false); /* few distinct batch rows: load the B operand directly */ \
+    else if (spread) QTIP_MM(R, NW, true, HYB);                 \
+    else QTIP_MM(R, NW, true, false)
+    if (tm <= 256) {
+        QTIP_MM_BATCH(1, 16);
+    } else if ((tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256)) {
+        QTIP_MM_BATCH(1, 8);
+    } else if (tm <= 512) {  // (at most one per CU: 16 waves, 8192 x 8192 4-bit HYB 12.9 -> 11.6 us)
+        QTIP_MM_BATCH(2, 16);
+    } else {
+        QTIP_MM_BATCH(2, 8);
     }
+#undef QTIP_MM_BATCH
+#undef QTIP_MM
     return hipGetLastError();
 }
 

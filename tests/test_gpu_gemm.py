@@ -70,3 +70,12 @@ def test_a_batch_row_meets_nothing_but_itself(q):
     ok = torch.ones(B, dtype=torch.bool, device="cuda")
     ok[5] = False
     assert torch.isfinite(Y[ok]).all() and not torch.isfinite(Y[5]).any()
+
+
+@pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
+@pytest.mark.parametrize("B", [2, 8, 9, 16])
+def test_splits_of_small_batches(q, code, B):
+    """At most 16 batch rows: one and two tile rows per workgroup, a last pair that is not full, both wave counts."""
+    for k in (2, 3, 4):
+        for m, n in ((16, 16), (4080, 48), (4112, 80), (8208, 1040), (10240, 16)):
+            check(q, code, k, m, n, B, scaled=True, seed=B)
