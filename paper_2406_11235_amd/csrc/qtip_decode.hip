@@ -133,7 +133,7 @@ template <int N> __device__ __forceinline__ float add_row_ror(float v) {
 // that belong to g.
 template <int LPT, int RPL>
 __device__ __forceinline__ int reduce_over_tile_groups(float (&acc)[RPL], int lane) {
-    static_assert((LPT == 4 && RPL == 4) || (LPT == 8 && RPL == 2), "tile geometries of Geo<K>");
+    static_assert((LPT <= 4 && RPL == 4) || (LPT == 8 && RPL == 2), "tile geometries of MvGeo");
     const bool b5 = lane & 32, b4 = lane & 16;
     float v;
     if constexpr (RPL == 4) {
@@ -144,6 +144,8 @@ __device__ __forceinline__ int reduce_over_tile_groups(float (&acc)[RPL], int la
         v = (b4 ? v1 : v0) + lane_xor(b4 ? v0 : v1, lane, 16);
         v = add_row_ror<8>(v);
         v = add_row_ror<4>(v);
+        if constexpr (LPT <= 2) v = add_row_ror<2>(v);
+        if constexpr (LPT <= 1) v = add_row_ror<1>(v);
         acc[0] = v;
         return (b5 ? 2 : 0) + (b4 ? 1 : 0);
     } else {
@@ -169,20 +171,25 @@ constexpr int FUSED_MAX_N = 8192;
 // (The V = 1 hash code keeps a whole tile's table reads in flight and needs more registers; the
 // kernel that transforms its own input runs with at most one workgroup per CU, four waves per
 // SIMD, and may take the registers that leaves it.)
-template <int K, int V, int CODE, int NW, bool FUSED, bool SPREAD = false, bool WIDE = false>
+// S: workgroups per tile row, 16 / S rows each (the launcher splits a tile row where whole ones leave CUs idle).
+template <int K, int V, int CODE, int S, int NW, bool FUSED, bool SPREAD = false, bool WIDE = false>
 __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void matvec_kernel(const uint32_t *__restrict__ codes,
                                                          const uint32_t *__restrict__ lut,
-                                                         int tn, const half_t *__restrict__ x,
+                                                         int tm, int tn, const half_t *__restrict__ x,
                                                          const int8_t *__restrict__ signs, int log2_block,
                                                          const half_t *__restrict__ scale,
                                                          float *__restrict__ y) {
-    constexpr int WPL = MvGeo<K, WIDE>::WPL, LPT = MvGeo<K, WIDE>::LPT, RPL = MvGeo<K, WIDE>::RPL;
+    constexpr int WPL = MvGeo<K, WIDE>::WPL, LPT = MvGeo<K, WIDE>::LPT / S, RPL = MvGeo<K, WIDE>::RPL;
+    constexpr int ROWS = 16 / S;
     constexpr int TPI = 64 / LPT;  // tiles per wave per iteration
     __shared__ __attribute__((aligned(16))) uint32_t s_lut[code_lds_words(CODE, SPREAD)];
-    __shared__ float s_part[NW][16];
+    __shared__ float s_part[NW][ROWS];
     __shared__ __attribute__((aligned(16))) half_t s_x[FUSED ? FUSED_MAX_N : 8];
     __shared__ __attribute__((aligned(16))) float s_v[FUSED ? RHT_LDS_FLOATS : 1];
-    const int I = blockIdx.x;
+    // Workgroups go round the eight XCDs; those of one tile row, which read the same cache lines, stay on one.
+    const int I = S == 1 ? blockIdx.x : (blockIdx.x >> 3) / S * 8 + (blockIdx.x & 7);
+    const int part = S == 1 ? 0 : (blockIdx.x >> 3) % S;
+    if (S > 1 && I >= tm) return;
     // the wave's number as a scalar: its tile range and the loop over it then live in scalar
     // registers and the loop control costs no vector instructions
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -194,12 +201,16 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     const uint32_t *__restrict__ row_codes = codes + (size_t)I * tn * (8 * K);
     struct Operands {
         WordsN<WPL> w;
+        uint32_t next;  // S > 1: the word behind them
         uint4 xa, xb;
     };
     auto issue_words = [&](Operands &o, int Jb) {
         const uint32_t Jc = min(Jb + g, Jend - 1);  // lanes past the end re-read the last tile
         // (byte offsets in 32 bits from uniform bases: the loads take them as they are)
-        o.w = load_words_at<WPL>(row_codes, Jc * (32 * K) + q * (4 * WPL));
+        o.w = load_words_at<WPL>(row_codes, Jc * (32 * K) + (part * LPT + q) * (4 * WPL));
+        if constexpr (S > 1)
+            o.next = stream_load(reinterpret_cast<const uint32_t *>(
+                reinterpret_cast<const char *>(row_codes) + (size_t)(Jc * (32 * K) + ((part * LPT + q + 1) * WPL) % (8 * K) * 4)));
     };
     auto issue_x = [&](Operands &o, int Jb) {
         const uint32_t Jc = min(Jb + g, Jend - 1);
@@ -219,7 +230,7 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     };
     Operands opA, opB;
     if constexpr (FUSED) {
-        constexpr int N = 16 / NW, NCH = NW == 16 ? 2 : 1;  // (fewer waves: a row of less than 4096 values)
+        constexpr int N = 16 / NW, NCH = NW == 16 || S > 1 ? 2 : 1;  // (else a row of less than 4096 values)
         const int n = 16 * tn;
         half4_t v[NCH][N];
         uint32_t sg[NCH][N];
@@ -273,7 +284,8 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
 #pragma unroll
         for (int i = 0; i < WPL; i++) w[i] = o.w.v[i];
         // first word of the next lane of the same tile, cyclically (tail-biting wrap)
-        w[WPL] = __shfl(w[0], (lane & ~(LPT - 1)) | ((q + 1) & (LPT - 1)), 64);
+        if constexpr (S > 1) w[WPL] = o.next;
+        else w[WPL] = __shfl(w[0], (lane & ~(LPT - 1)) | ((q + 1) & (LPT - 1)), 64);
         if (Jb + g < Jend) {
             uint32_t xv[8] = {o.xa.x, o.xa.y, o.xa.z, o.xa.w, o.xb.x, o.xb.y, o.xb.z, o.xb.w};
             rd.prep_x(xv);
@@ -296,11 +308,11 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     const int rr_mine = reduce_over_tile_groups<LPT, RPL>(acc, lane);
     if ((g & (16 / LPT - 1)) == 0) s_part[wave][q * RPL + rr_mine] = acc[0];
     __syncthreads();
-    if (threadIdx.x < 16) {
+    if (threadIdx.x < ROWS) {
         float s = 0.f;
 #pragma unroll
         for (int wv = 0; wv < NW; wv++) s += s_part[wv][threadIdx.x];
-        const int row = 16 * I + threadIdx.x;
+        const int row = 16 * I + ROWS * part + threadIdx.x;
         if (scale) s *= (float)scale[row];
         y[row] = s;
     }
@@ -561,6 +573,22 @@ static bool pick_hyb_spread(int code, int n) {
     return code == CODE_HYB && n >= 8192;
 }
 
+// Workgroups per tile row: the share of a CU, workgroups of about 0.8 us each and the time of their rows (0.5 us per
+// 1000 inputs of a whole tile row), is smallest; a split leaves at least two steps.  (2-bit 3INST: 1280 x 26624
+// 18.1 -> 12.1 us, 2048 x 8192 6.6 -> 4.4, 1024 x 4096 4.1 -> 3.0, with its transform 5.7 -> 4.7.  Matrices of 4096 rows
+// and more gain nothing: a whole tile row per CU fills its issue slots.  The choice depends on the sizes alone, so
+// that the kernel that transforms its own input makes the same one.)
+static int pick_matvec_split(int tm, int tn) {
+    int best = 1;
+    float least = 0.f;
+    for (int s = 1; s <= 4; s *= 2) {
+        if (s > 1 && tn < 2 * 16 * s) break;
+        const float t = (float)((tm * (long)s + 255) / 256) * (0.8f + (float)tn * (0.008f / s));
+        if (s == 1 || t < least) best = s, least = t;
+    }
+    return best;
+}
+
 template <int K, int V, int CODE>
 static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, int m, int n,
                                   const void *x, const int8_t *signs, int log2_block, const void *scale,
@@ -570,17 +598,32 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
     const int steps = (tn + TPI - 1) / TPI;
     const int nw = pick_matvec_waves(steps);
     const bool spread = pick_hyb_spread(CODE, n);
+    const int split = pick_matvec_split(tm, tn);
+    const dim3 grid(split == 1 ? tm : (tm + 7) / 8 * 8 * split);
     // signs != null: x is untransformed and the kernel transforms it itself (n <= FUSED_MAX_N)
-#define QTIP_MV_LAUNCH4(NW, FUSED, SPREAD, WIDE)                                                            \
-    hipLaunchKernelGGL((matvec_kernel<K, V, CODE, NW, FUSED, SPREAD, WIDE>), dim3(tm), dim3(NW * 64), 0, st, \
-                       codes, lut, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y)
-#define QTIP_MV_LAUNCH(NW, WIDE)                                \
-    if (signs)                                                  \
-        QTIP_MV_LAUNCH4(NW, true, false, WIDE);                 \
-    else if (code_is_hyb(CODE) && spread)                       \
-        QTIP_MV_LAUNCH4(NW, false, code_is_hyb(CODE), WIDE);    \
-    else                                                        \
-        QTIP_MV_LAUNCH4(NW, false, false, WIDE)
+#define QTIP_MV_LAUNCH4(S, NW, FUSED, SPREAD, WIDE)                                                           \
+    hipLaunchKernelGGL((matvec_kernel<K, V, CODE, S, NW, FUSED, SPREAD, WIDE>), grid, dim3(NW * 64), 0, st, \
+                       codes, lut, tm, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y)
+#define QTIP_MV_LAUNCH(S, NW, WIDE)                                \
+    if (signs)                                                     \
+        QTIP_MV_LAUNCH4(S, NW, true, false, WIDE);                 \
+    else if (code_is_hyb(CODE) && spread)                          \
+        QTIP_MV_LAUNCH4(S, NW, false, code_is_hyb(CODE), WIDE);    \
+    else                                                           \
+        QTIP_MV_LAUNCH4(S, NW, false, false, WIDE)
+    // (a lane has four tile rows of a tile at every k where a tile row is split)
+    if (split > 1) {
+        const int ssteps = (tn + 16 * split - 1) / (16 * split);
+        constexpr bool WIDE = K != 2;
+        if (split == 2) {
+            if (ssteps >= 16) QTIP_MV_LAUNCH(2, 16, WIDE);
+            else QTIP_MV_LAUNCH(2, 8, WIDE);
+        } else {
+            if (ssteps >= 16) QTIP_MV_LAUNCH(4, 16, WIDE);
+            else QTIP_MV_LAUNCH(4, 8, WIDE);
+        }
+        return hipGetLastError();
+    }
     // Four rows per lane at k = 3 and 4 (MvGeo<K, true>: steps of 16 tiles) where 16 waves still have a
     // step each and the row splits into such steps as evenly as into the narrow ones (measured, k = 4:
     // 14336 x 4096 12.44 -> 11.38 us, 8192 x 8192 HYB 10.64 -> 10.38; 4096 x 14336, 896 tiles = 3.5 wide
@@ -590,15 +633,15 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
         constexpr int WTPI = 64 / MvGeo<K, true>::LPT;
         const int wsteps = (tn + WTPI - 1) / WTPI;
         if (wsteps >= 16 && 2 * ((wsteps + 15) / 16) <= (steps + nw - 1) / nw) {
-            QTIP_MV_LAUNCH(16, true);
+            QTIP_MV_LAUNCH(1, 16, true);
             return hipGetLastError();
         }
     }
     switch (nw) {
-        case 2: QTIP_MV_LAUNCH(2, false); break;
-        case 4: QTIP_MV_LAUNCH(4, false); break;
-        case 16: QTIP_MV_LAUNCH(16, false); break;
-        default: QTIP_MV_LAUNCH(8, false); break;
+        case 2: QTIP_MV_LAUNCH(1, 2, false); break;
+        case 4: QTIP_MV_LAUNCH(1, 4, false); break;
+        case 16: QTIP_MV_LAUNCH(1, 16, false); break;
+        default: QTIP_MV_LAUNCH(1, 8, false); break;
     }
 #undef QTIP_MV_LAUNCH
 #undef QTIP_MV_LAUNCH4
