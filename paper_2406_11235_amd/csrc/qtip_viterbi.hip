@@ -20,13 +20,21 @@
 // Instead `best` itself is written to HBM every J steps, and the walk back recomputes what it
 // needs: of the states J steps before a known state only 2^(kV J) can lead to it, a tree that
 // one wave evaluates from the stored `best` in a few hundred instructions.
-//   Measured, 2048 x 2048, 2-bit 3INST (16384 tiles): see viterbi_forward_kernel.
+//   What bounds it is the issue of those instructions: 2.8 cycles for the subtraction and 2.9 for the
+// fused multiply-add, 4.35 for a minimum are 2020 cycles a step at kV = 2 and V = 1, 1950 measured.
+// 2048 x 2048, 2-bit 3INST: 69.7 ms with back-pointers, 36.1 now (37.5 on another card).  (The subtractions on the matrix cores, one
+// v_mfma_f32_16x16x1 for 16 registers, bit for bit the same: 34.7 ms, but BlockLDLQ's 128
+// sequences 48.4 -> 48.8: its 32 cycles are not hidden behind other waves' vector instructions.)
 //
 // Walk back.  One wave per sequence and J steps at a time: it reads the 2^(kV J) stored minima
 // below the current state (one contiguous run: `best` is stored with the state's low bits, which
 // are fixed there, as the major index), and repeats the recursion level by level with the
 // arguments kept; ties go to the lowest predecessor.  The same operations in the same order
 // give the same bits as the forward kernel, so the walk is the one its minima imply.
+// Where there are few sequences four waves share a tree, one p_1 (or a quarter of them) each, and
+// compare their roots: BlockLDLQ of 2048 x 1024, 128 sequences at a time, 48.4 -> 46.0 ms.
+// The copies go through the caches as they come: written and read with the non-temporal hint the same
+// case takes 46.4 ms, and thousands of sequences the same.
 // Algorithm 4 is forward / walk to the middle / constrained forward / full walk.
 //
 // Arithmetic (fixed, so that a CPU reference can repeat every decision): binary32,
@@ -70,6 +78,13 @@ struct VitGeo {
     static constexpr int LOWB = LB - KV * (J + 1);  // low prefix bits, fixed within one tree
     static constexpr int NSEG = (G - 1 + J - 1) / J;  // trees of a whole walk; the last one
     static constexpr int LAST = (G - 1) - (NSEG - 1) * J;  // has LAST levels and starts at step 0
+    // Up to this many sequences a walk has four waves: a tree is a serial chain (leaves from memory,
+    // about 1 us, then J levels), and four waves have a quarter of the leaves each.  Not at J < 3, where a
+    // wave's share of the chain is no shorter than the exchange at the root (HYB k = 2, 256 tiles: 1009 us
+    // with one wave, 1023 with four); and not where all SIMDs have walks enough to hide the chains
+    // (3INST k = 2, us with one wave | four: 256 tiles 888 | 840, 1024 2555 | 2531, 2048 4634 | 4691;
+    // lookup-only code, whose forward pass is a quarter as long: 256 456 | 431, 512 515 | 510, 1024 767 | 824).
+    static constexpr int FEW = J < 3 ? 0 : LB == 16 ? 1024 : 512;
     static constexpr int MID = G / 2 - 1;           // the step the first walk goes down to
     static constexpr int NSEG_MID = (G - 1 - MID + J - 1) / J;
     static_assert(LOWB >= 0, "a tree's leaves are distinct states");
@@ -257,7 +272,7 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
                 float *dst = store_base + (size_t)(c_now - c_lo) * NP;
 #pragma unroll
                 for (int i = 0; i < NB; i++)
-                    __builtin_nontemporal_store(best[i], dst + Geo::stored((uint32_t)(my_hi + i)));
+                    dst[Geo::stored((uint32_t)(my_hi + i))] = best[i];
             }
             c_now--;
         }
@@ -304,25 +319,46 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
 
 // ------------------------------------------------------------------- walk back
 
+// x from the lane whose index differs in bit BIT alone.
+template <int BIT>
+__device__ __forceinline__ uint32_t other_lane(uint32_t x) {
+    if constexpr (BIT == 0) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);        // quad_perm [1, 0, 3, 2]
+    else if constexpr (BIT == 1) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+    else if constexpr (BIT == 3) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);  // row_ror:8
+    else return __shfl_xor(x, 1 << BIT, 64);
+}
+
+// What the waves of a sequence tell each other at the root of a tree: value and leaf of the best walk
+// of each, twice, so that one barrier per tree is enough.
+struct WalkRoot {
+    float value[2][4];
+    uint32_t leaf[2][4];
+};
+
 // One tree of JJ levels below state y at step t, whose leaves are the states of step t - JJ.
 // Leaf l = (p_JJ ... p_1), digit p_j being the top kV bits of the state j steps back, is state
-// (l << (L - kV JJ)) | (y >> kV JJ); the low six bits of l are the lane, the others a register.
-// Level j takes the minimum over p_j and moves one step forward.  On return digit[j] = p_j of the
-// best walk (the same in all lanes).
-template <int KV, int V, int CODE, int JJ>
+// (l << (L - kV JJ)) | (y >> kV JJ); the low WB bits of l are the wave, the next six the lane, the
+// others a register.  Level j takes the minimum over p_j and moves one step forward; the wave's bits, of
+// p_1, come last, at the root.  On return digit[j] = p_j of the best walk (the same in all lanes).
+template <int KV, int V, int CODE, int JJ, int WB>
 struct WalkTree {
     using Geo = VitGeo<KV, V, code_state_bits(CODE)>;
     static constexpr int LB = code_state_bits(CODE);
-    static constexpr int regs(int bits) { return bits > 6 ? 1 << (bits - 6) : 1; }
+    static constexpr int LREG = WB + 6;  // the first bit of a leaf that is a register's
+    static constexpr int regs(int bits) { return bits > LREG ? 1 << (bits - LREG) : 1; }
+    static_assert(WB <= KV, "the wave is a part of the last digit");
 
     uint32_t y;
-    int t, lane;
+    int t, lane, wave;
     const uint32_t *lut;
     const float *seq;  // LDS
+    WalkRoot *root;    // LDS
+    float best;        // of the wave, at the root
     uint32_t args[JJ + 1];  // args[j]: kV bits per register of level j - 1
 
     __device__ __forceinline__ uint32_t node_state(int j, int m) const {  // level j, register m
-        const uint32_t l = KV * j >= 6 ? (uint32_t)(m * 64 + lane) : (uint32_t)lane & ((1u << (KV * j)) - 1u);
+        const uint32_t own = (uint32_t)(m << LREG) | (uint32_t)(lane << WB) | (uint32_t)wave;
+        const uint32_t l = KV * j >= LREG ? own : own & ((1u << (KV * j)) - 1u);
         return ((l << (LB - KV * j)) | (y >> (KV * j))) & ((1u << LB) - 1u);
     }
     __device__ __forceinline__ float node_value(int j, int m, float b) const {
@@ -333,10 +369,13 @@ struct WalkTree {
     template <int j>
     __device__ __forceinline__ void reduce(float (&v)[regs(KV * JJ)]) {
         constexpr int M = regs(KV * j), M1 = regs(KV * (j - 1)), A = M / M1;
-        // digit j: its top bits tell registers apart, its other bits, if any, are lane bits
-        constexpr int LANE_LO = KV * (j - 1), LANE_HI = KV * j < 6 ? KV * j : 6;
+        // digit j: its top bits tell registers apart, the next ones, if any, are lane bits, and the low
+        // ones of digit 1 the wave
+        constexpr int WAVE = j == 1 ? WB : 0;
+        constexpr int LANE_LO = KV * (j - 1) + WAVE - WB, LANE_HI = (KV * j < LREG ? KV * j : LREG) - WB;
         constexpr int LBITS = LANE_HI > LANE_LO ? LANE_HI - LANE_LO : 0;
-        const uint32_t mine = LBITS ? ((uint32_t)lane >> LANE_LO) & ((1u << LBITS) - 1u) : 0u;
+        const uint32_t mine = ((LBITS ? ((uint32_t)lane >> LANE_LO) & ((1u << LBITS) - 1u) : 0u) << WAVE) |
+                              (WAVE ? (uint32_t)wave : 0u);
         uint32_t packed = 0;
 #pragma unroll
         for (int m = 0; m < M1; m++) {
@@ -346,32 +385,42 @@ struct WalkTree {
             for (int a = 1; a < A; a++) {
                 const bool lt = v[a * M1 + m] < bv;
                 bv = lt ? v[a * M1 + m] : bv;
-                bp = lt ? ((uint32_t)a << LBITS) | mine : bp;
+                bp = lt ? ((uint32_t)a << (LBITS + WAVE)) | mine : bp;
             }
-#pragma unroll
-            for (int b = 0; b < LBITS; b++) {
-                const float ov = __shfl_xor(bv, 1 << (LANE_LO + b), 64);
-                const uint32_t op = __shfl_xor(bp, 1 << (LANE_LO + b), 64);
-                const bool take = ov < bv || (ov == bv && op < bp);
-                bv = take ? ov : bv;
-                bp = take ? op : bp;
-            }
+            auto meet = [&](auto bit) {
+                constexpr int BIT = decltype(bit)::value;
+                if constexpr (BIT < LBITS) {
+                    const float ov = __builtin_bit_cast(float, other_lane<LANE_LO + BIT>(__builtin_bit_cast(uint32_t, bv)));
+                    const uint32_t op = other_lane<LANE_LO + BIT>(bp);
+                    const bool take = ov < bv || (ov == bv && op < bp);
+                    bv = take ? ov : bv;
+                    bp = take ? op : bp;
+                }
+            };
+            meet(std::integral_constant<int, 0>{});
+            meet(std::integral_constant<int, 1>{});
+            meet(std::integral_constant<int, 2>{});
+            meet(std::integral_constant<int, 3>{});
+            meet(std::integral_constant<int, 4>{});
+            meet(std::integral_constant<int, 5>{});
             packed |= bp << (m * KV);
             if constexpr (j > 1) v[m] = node_value(j - 1, m, bv);
+            else best = bv;
         }
         args[j] = packed;
         if constexpr (j > 1) reduce<j - 1>(v);
     }
 
     // stored: best at step t - JJ, or null for step 0 (0, or INF off the forced prefix)
-    __device__ __forceinline__ void run(const float *__restrict__ stored, bool constrained, uint32_t O,
+    // turn: which of root's two places
+    __device__ __forceinline__ void run(const float *__restrict__ stored, bool constrained, uint32_t O, int turn,
                                         uint32_t (&digit)[JJ + 1]) {
         constexpr int M = regs(KV * JJ);
         float v[M];
 #pragma unroll
         for (int m = 0; m < M; m++) {
             const uint32_t hi = node_state(JJ, m) >> KV;
-            v[m] = stored ? __builtin_nontemporal_load(stored + Geo::stored(hi))
+            v[m] = stored ? stored[Geo::stored(hi)]
                           : (constrained && hi != O) ? __builtin_inff() : 0.f;
         }
 #pragma unroll
@@ -380,20 +429,40 @@ struct WalkTree {
         uint32_t l = 0;  // (p_{j-1} ... p_1)
 #pragma unroll
         for (int j = 1; j <= JJ; j++) {
-            const uint32_t word = __builtin_amdgcn_readlane(args[j], l & 63u);
-            const uint32_t m = KV * (j - 1) > 6 ? l >> 6 : 0u;
+            const uint32_t word = __builtin_amdgcn_readlane(args[j], (l >> WB) & 63u);
+            const uint32_t m = KV * (j - 1) > LREG ? l >> LREG : 0u;
             digit[j] = (word >> (m * KV)) & ((1u << KV) - 1u);
             l |= digit[j] << (KV * (j - 1));
+        }
+        if constexpr (WB > 0) {
+            if (lane == 0) {
+                root->value[turn][wave] = best;
+                root->leaf[turn][wave] = l;
+            }
+            __syncthreads();
+            float bv = root->value[turn][0];
+            l = root->leaf[turn][0];
+#pragma unroll
+            for (int w = 1; w < 1 << WB; w++) {
+                const float ov = root->value[turn][w];
+                const uint32_t ol = root->leaf[turn][w];
+                const bool take = ov < bv || (ov == bv && (ol & ((1u << KV) - 1u)) < (l & ((1u << KV) - 1u)));
+                bv = take ? ov : bv;
+                l = take ? ol : l;
+            }
+            l = __builtin_amdgcn_readfirstlane(l);
+#pragma unroll
+            for (int j = 1; j <= JJ; j++) digit[j] = (l >> (KV * (j - 1))) & ((1u << KV) - 1u);
         }
     }
 };
 
-// One wave per sequence.  pass 1: from the final state down to step G/2 - 1, whose low L-kV bits are
+// One wave per sequence, or four (WB = 2) where there are few.  pass 1: from the final state down to step G/2 - 1, whose low L-kV bits are
 // the overlap of Algorithm 4.  pass 2: the whole walk; step t contributes the top kV bits of its
 // state as stream bits t kV .. (t+1) kV - 1 (first bit = most significant bit of word 0).  The
 // trees c_lo .. c_hi - 1 of the walk are done; where the workspace holds too few copies of `best`
 // for the whole walk, the state it got to waits in final_state and the next launch adds its bits.
-template <int KV, int V, int CODE>
+template <int KV, int V, int CODE, int WB>
 __global__ __launch_bounds__(256) void viterbi_walk_kernel(
     const float *__restrict__ W, int n, int tn, long tile0, const uint32_t *__restrict__ lut, int pass,
     const float *__restrict__ store, long slots, int c_lo, int c_hi, uint32_t *__restrict__ final_state,
@@ -404,8 +473,10 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
     constexpr int NWORDS = KV * G / 32;
     __shared__ float s_seq[4][VT_T];
     __shared__ uint32_t s_sym[4][VT_T / 4];  // one byte per step
+    __shared__ WalkRoot s_root;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slot = blockIdx.x * 4 + wave;
+    const int slot = WB ? blockIdx.x : blockIdx.x * 4 + wave;
+    const bool first = WB == 0 || wave == 0;  // (all waves of a sequence know all of its walk)
     if (slot >= count) return;
     float *const seq = s_seq[wave];
     uint8_t *const sym = reinterpret_cast<uint8_t *>(s_sym[wave]);
@@ -428,26 +499,28 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
     auto tree = [&](auto jj, int c) {
         constexpr int JJ = decltype(jj)::value;
         const int t = G - 1 - J * c;
-        WalkTree<KV, V, CODE, JJ> w;
+        WalkTree<KV, V, CODE, JJ, WB> w;
         w.y = y;
         w.t = t;
         w.lane = lane;
+        w.wave = WB ? wave : 0;
+        w.root = &s_root;
         w.lut = lut;
         w.seq = seq;
         uint32_t digit[JJ + 1];
-        w.run(t > JJ ? my_store + (size_t)(c - c_lo) * NP : nullptr, constrained, O, digit);
+        w.run(t > JJ ? my_store + (size_t)(c - c_lo) * NP : nullptr, constrained, O, c & 1, digit);
 #pragma unroll
         for (int j = 1; j <= JJ; j++) {
             y = (digit[j] << OV) | (y >> KV);
             if (lane == 0) sym[t - j] = (uint8_t)digit[j];
-            if (pass == 1 && t - j == Geo::MID && lane == 0) overlap[slot] = y & (uint32_t)(NP - 1);
+            if (first && pass == 1 && t - j == Geo::MID && lane == 0) overlap[slot] = y & (uint32_t)(NP - 1);
         }
     };
     for (int c = c_lo; c < c_hi; c++) {
         if (c == NSEG - 1) tree(std::integral_constant<int, Geo::LAST>{}, c);
         else tree(std::integral_constant<int, J>{}, c);
     }
-    if (pass == 1 && c_hi >= Geo::NSEG_MID) return;
+    if (!first || (pass == 1 && c_hi >= Geo::NSEG_MID)) return;
     wave_sync();
     if (c_hi < NSEG && lane == 0) final_state[slot] = y;
     if (pass == 1) return;
@@ -541,6 +614,7 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
     float *store = (float *)((char *)ws + head_bytes(cap));
     for (long tile0 = 0; tile0 < ntiles; tile0 += cap) {
         const int cnt = (int)(ntiles - tile0 < cap ? ntiles - tile0 : cap);
+        const bool few = cnt <= Geo::FEW;
         for (int pass = 1; pass <= 2; pass++) {
             const int nseg = pass == 1 ? Geo::NSEG_MID : Geo::NSEG;
             for (int c_lo = 0; c_lo < nseg; c_lo += plan.slots) {
@@ -552,9 +626,10 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
                     hipLaunchKernelGGL((viterbi_forward_kernel<KV, V, CODE>), dim3(cnt), dim3(Geo::NT), 0, st, W, ld,
                                        tn, tile0, lut, pass == 1, pass == 1 ? (const uint32_t *)nullptr : overlap,
                                        store, (long)plan.slots, c_lo, c_hi, t_end, final_state, final_value);
-                hipLaunchKernelGGL((viterbi_walk_kernel<KV, V, CODE>), dim3((cnt + 3) / 4), dim3(256), 0, st, W, ld,
-                                   tn, tile0, lut, pass, (const float *)store, (long)plan.slots, c_lo, c_hi,
-                                   final_state, (const float *)final_value, cnt, overlap, codes, tile_err);
+                hipLaunchKernelGGL((few ? viterbi_walk_kernel<KV, V, CODE, Geo::FEW ? 2 : 0> : viterbi_walk_kernel<KV, V, CODE, 0>),
+                                   dim3(few ? cnt : (cnt + 3) / 4), dim3(256), 0, st, W, ld, tn, tile0, lut, pass,
+                                   (const float *)store, (long)plan.slots, c_lo, c_hi, final_state,
+                                   (const float *)final_value, cnt, overlap, codes, tile_err);
                 if (c_hi == nseg) break;
             }
         }
