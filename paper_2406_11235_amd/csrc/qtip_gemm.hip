@@ -160,7 +160,7 @@ template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS> struct GemmL
 };
 
 template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS>
-__global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
+__global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
     const uint32_t *__restrict__ codes, const uint32_t *__restrict__ lut, int m, int n, const half_t *__restrict__ X,
     int B, const half_t *__restrict__ scale, float *__restrict__ Y) {
     constexpr bool LUT = CODE == CODE_LUT;
@@ -170,6 +170,12 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
     using Lds = GemmLds<K, CODE, RB, NBB, WM, WK, KS>;
     constexpr int SLICE = Lds::SLICE, NCOPY = BT / RPI / WM;  // bytes of a stage; copy instructions per wave
     constexpr int SUMS_AT_ONCE = Lds::SUMS;
+    // Stages that are summed in the matrix cores before the sums go to totals of their own: the rounding error of a long
+    // chain grows with it (997 x 4096 x 14336, against binary64: 4.1e-7 in one chain of 256 matrix instructions,
+    // 1.3e-7 in chains of 16, 1.6e-7 with eight waves that split the inputs).  With eight slices of the inputs the
+    // chains are short.  The totals take as many registers as the running sums: at 256 batch rows a workgroup is
+    // four waves with a SIMD's registers each (115 -> 149 us; up to 128 batch rows it costs 1 to 4 %).
+    constexpr int CHAIN = WK == 8 ? 0 : 16 / KS;
     constexpr int AHEAD = 3, GROUPS = KS * NBB * RB;  // a group: one matrix instruction and what goes with it
     constexpr int STEP_BYTES = Lds::STEP_BYTES, CODE_ROW = Lds::CODE_ROW, CODE_ROWS = Lds::CODE_ROWS;
     constexpr int CODE_COPIES = Lds::CODE_COPIES, CODE_STAGE = Lds::CODE_STAGE;
@@ -255,13 +261,19 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
     EightWeights<K, CODE> dec[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; rb++) dec[rb].init(s_lut);
-    float16_t acc[RB][NBB];
+    float16_t acc[RB][NBB], total[RB][NBB];
 #pragma unroll
     for (int rb = 0; rb < RB; rb++)
 #pragma unroll
         for (int nb = 0; nb < NBB; nb++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) acc[rb][nb][e] = 0.f;
+            for (int e = 0; e < 16; e++) acc[rb][nb][e] = 0.f, total[rb][nb][e] = 0.f;
+    auto add_up = [&] {
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+            for (int nb = 0; nb < NBB; nb++) total[rb][nb] += acc[rb][nb];
+    };
 
     uint32_t wnext[RB][4];  // the decoded weights of the next step
     uint32_t cw[RB][2];  // the two words that the next eight weights start in
@@ -286,7 +298,8 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
     }
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const int mine = J0 < Jend ? (Jend - J0 + KS - 1) / KS : 0;
-    for (int s = 0; s < mine; s++) {
+    // fresh: the running sums start again
+    auto stage = [&](int s, auto fresh) {
         const int J = J0 + s * KS;
         const char *const buf = slice + (s & 1) * SLICE;
         // the activations of a stage, KS * NBB operands, are read from LDS AHEAD operands before their use
@@ -310,7 +323,8 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
                 if constexpr (r + AHEAD < KS * NBB) read_x(std::integral_constant<int, r + AHEAD>{});
                 static_for<RB>([&](auto rbc) {
                     constexpr int rb = decltype(rbc)::value, group = r * RB + rb;
-                    acc[rb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xv[r % (AHEAD + 1)], wv[rb], acc[rb][nb], 0, 0, 0);
+                    acc[rb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xv[r % (AHEAD + 1)], wv[rb],
+                                                                         decltype(fresh)::value && j == 0 ? float16_t{} : acc[rb][nb], 0, 0, 0);
                     // the next stage's copies, spread over the first part of this one: a wave that issues several in a
                     // row waits for the memory pipeline, and the matrix cores with it
                     static_for<COPIES>([&](auto cc) {
@@ -343,7 +357,20 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+    };
+    if constexpr (CHAIN == 0) {
+        for (int s = 0; s < mine; s++) stage(s, std::false_type{});
+    } else {
+        for (int s = 0; s < mine;) {
+            stage(s++, std::true_type{});
+            for (int c = 1; c < CHAIN && s < mine; c++) stage(s++, std::false_type{});
+            add_up();
+        }
     }
+    const auto &sum = [&]() -> auto & {
+        if constexpr (CHAIN == 0) return acc;
+        else return total;
+    }();
     for (int s = mine; s < stages; s++) __builtin_amdgcn_s_barrier();  // (a slice with less or nothing to do)
     __syncthreads();
 
@@ -359,7 +386,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
                     const int b = b0 + 32 * nb + 8 * (e / 4) + 4 * h + e % 4;
-                    if (b < B) Y[(size_t)b * m + o] = acc[rb][nb][e] * sc;
+                    if (b < B) Y[(size_t)b * m + o] = sum[rb][nb][e] * sc;
                 }
         }
     } else {
@@ -374,7 +401,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 8 ? 1 : 2) void gemm_kernel(
                 for (int nb = 0; nb < SUMS_AT_ONCE; nb++)
 #pragma unroll
                     for (int e = 0; e < 16; e++)
-                        sums[(((wk * WM + wm) * RB + rb) * SUMS_AT_ONCE + nb) * 1024 + e * 64 + lane] = acc[rb][nb0 + nb][e];
+                        sums[(((wk * WM + wm) * RB + rb) * SUMS_AT_ONCE + nb) * 1024 + e * 64 + lane] = sum[rb][nb0 + nb][e];
             __syncthreads();
             for (int part = wave; part < PARTS; part += WM * WK) {
                 const int e = part % 16, block = part / 16;
@@ -402,12 +429,12 @@ struct GemmSplit {
     int outputs, rows;
     float first, round;
 };
-static constexpr GemmSplit GEMM_SPLITS[] = {{256, 256, 0.f, 105.f}, {128, 128, 0.f, 42.f}, {64, 128, 2.f, 25.f},
+static constexpr GemmSplit GEMM_SPLITS[] = {{128, 256, 0.f, 74.f}, {128, 128, 0.f, 42.f}, {64, 128, 2.f, 25.f},
                                             {64, 64, 5.f, 15.f},    {32, 64, 2.f, 11.3f},  {32, 32, 4.5f, 5.5f}};
 
 // Kernels of the splits, in their order.
 #define QTIP_GEMM_SPLITS(GO) \
-    GO(0, 1, 8, 8, 1) GO(1, 1, 4, 4, 2) GO(2, 1, 4, 2, 4) GO(3, 1, 2, 2, 4) GO(4, 1, 2, 1, 8) GO(5, 1, 1, 1, 8)
+    GO(0, 1, 8, 4, 1) GO(1, 1, 4, 4, 2) GO(2, 1, 4, 2, 4) GO(3, 1, 2, 2, 4) GO(4, 1, 2, 1, 8) GO(5, 1, 1, 1, 8)
 
 template <int K, int CODE>
 static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int m, int n, const void *X, int B,

@@ -6,9 +6,8 @@
 // tile with the GPU Viterbi quantizer and feeds the error of every finished block forward.
 //
 // Block LDL (H = L D L^T, L unit block lower triangular, D block diagonal, A = L - I) runs
-// in binary64 on the device, right-looking, two launches per block column: a panel kernel
-// (invert the 16x16 diagonal block, scale the column below it) and a trailing update on the
-// lower triangle.  It is a one-off of n^3/3 multiply-adds per layer.
+// in binary64 on the device, right-looking, in panels of 8 block columns with two launches each.
+// It is a one-off of n^3/3 multiply-adds per layer.
 //
 // The feedback sum is written so that a CPU reference can repeat it bit for bit, because
 // what it feeds is a quantizer, whose decisions are not continuous: binary32, one fused
@@ -44,7 +43,7 @@ namespace {
 // panel's block columns.  Those with everything further right are taken beside the next panel, in its launch.
 // What bounds it is that chain: 16 pivots per block column, about 1 us, and a launch with its gap twice per panel.
 // n = 2048, g = 16: 1744 us with two launches per block column, the inversion with five barriers per pivot and the
-// products on the vector units, 412 us now.
+// products on the vector units, 394 us now.
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 constexpr int LDL_PANEL = 8, LDL_MAX_ROWS = 4;
