@@ -224,7 +224,7 @@ int qtip_quantize(const float *W, int m, int n, int L, int k, int V, int code_id
  *               search for each tile = its squared reconstruction error, as
  *               accumulated in binary32.
  *   workspace:  device, 256-byte aligned, workspace_bytes long; holds the
- *               back-pointers of the tiles in flight.  Any size from
+ *               stored minima of the tiles in flight.  Any size from
  *               qtip_quantize_gpu_workspace(k, V, 1) up works; tiles are processed
  *               in batches of as many as fit, so give it
  *               qtip_quantize_gpu_workspace(k, V, t) for t of a few thousand (about

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 CODES = {CODE_1MAD: (16, 1, 0), CODE_3INST: (16, 1, 0), CODE_HYB: (16, 2, 1024), CODE_HYB2: (16, 2, 1024),
          CODE_LUT: (14, 1, 1 << 14), CODE_HYB1: (16, 1, 64)}
-# m, n, B: 32 x 32, 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 256 x 256 outputs x batch rows of a workgroup
+# m, n, B: 32 x 32, 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 128 x 256 outputs x batch rows of a workgroup
 SHAPES = [(32, 16, 17), (96, 208, 33), (544, 1056, 40), (8192, 80, 49), (8224, 48, 64), (16384, 144, 100),
           (8224, 112, 200), (16416, 80, 1000), (16384, 272, 769)]
 
@@ -79,3 +79,20 @@ def test_splits_of_small_batches(q, code, B):
     for k in (2, 3, 4):
         for m, n in ((16, 16), (4080, 48), (4112, 80), (8208, 1040), (10240, 16)):
             check(q, code, k, m, n, B, scaled=True, seed=B)
+
+
+@pytest.mark.parametrize("m,n,B", [(14304, 4112, 997), (4096, 4112, 500), (8192, 8208, 100)])
+def test_long_rows_are_not_one_chain_of_sums(q, m, n, B):
+    """Chains of 16 matrix instructions whose sums are added up: 1.2e-7 to 1.3e-7 of the result's 2-norm is rounding
+    (binary32's half unit is 6e-8, and an error of a random sign per addition grows with the root of the chain);
+    one chain over 4096 inputs has 2.1e-7 or more with four slices of the inputs, and 4.1e-7 with one."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(m)
+    codes = torch.randint(-2**31, 2**31, (m * n // 256, 16), dtype=torch.int32, device="cuda", generator=g)
+    X = torch.randn(B, n, device="cuda", generator=g).half()
+    Y = torch.empty(B, m, device="cuda")
+    W = torch.empty(m, n, dtype=torch.float16, device="cuda")
+    q.qtip_decode_matmat(codes, 16, 2, 1, CODE_3INST, None, m, n, X, B, None, Y)
+    q.qtip_dequantize(codes, 16, 2, 1, CODE_3INST, None, m, n, W)
+    ref = X.double() @ W.double().T.contiguous()
+    assert (Y.double() - ref).norm() <= 1.8e-7 * ref.norm()
