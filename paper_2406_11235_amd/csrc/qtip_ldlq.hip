@@ -65,7 +65,9 @@ __device__ __forceinline__ double4_t ldl_product(double4_t x, double4_t y, doubl
     return c;
 }
 
-// T from the lower triangle of H, and zeros where A has no block of its own.
+// T from the lower triangle of H, a diagonal block's upper half from its lower one (what H holds above its diagonal is
+// nobody's to read, the blocks between the two 8 x 8 blocks of a g = 8 pivot included), and zeros where A has no block of
+// its own.
 __global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict__ H, double *__restrict__ T,
                                                        float *__restrict__ A, int n) {
     const int nb = n >> 4, lane = threadIdx.x & 63;
@@ -82,7 +84,8 @@ __global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict_
         if (j > i) continue;
         double *t = ldl_block(T, nb, j, i) + 64 * m + r;
 #pragma unroll
-        for (int c = 0; c < 4; c++) t[16 * c] = h[16 * j + c];
+        for (int c = 0; c < 4; c++)
+            t[16 * c] = j < i || 4 * m + c <= r ? h[16 * j + c] : H[(size_t)(16 * i + 4 * m + c) * n + 16 * i + r];
     }
 }
 

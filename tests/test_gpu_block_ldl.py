@@ -1,6 +1,6 @@
 """The block LDL decomposition at the sizes where its panels and its triangle of updates can go wrong: one block, less than
-a panel, panels and one block more, both forms of the update, both group sizes.  L D L^T gives the matrix back, A is
-zero where it has no block, D symmetric."""
+a panel, panels and one block more, both forms of the update, both group sizes.  H has nothing above its diagonal;
+L D L^T gives the matrix back, A is zero where it has no block, D symmetric."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -15,13 +15,8 @@ def test_reconstructs(n, g):
     X = torch.randn(3 * n, n, dtype=torch.float64, device="cuda", generator=gen)
     X = 0.8 * X[:, :1] + 0.2 * X
     H = X.T.contiguous() @ X / (3 * n) + 1e-3 * torch.eye(n, dtype=torch.float64, device="cuda")
-    Hin = torch.tril(H)
-    for i in range(0, n, g):  # only blocks on and below the diagonal are read
-        Hin[i:i + g, i:i + g] = H[i:i + g, i:i + g]
-        Hin[i:i + g, (i // 16 + 1) * 16:] = float("nan")
-    if g == 8:
-        for i in range(0, n, 16):
-            Hin[i:i + 16, i:i + 16] = H[i:i + 16, i:i + 16]
+    # only the lower triangle is read
+    Hin = torch.where(torch.ones_like(H, dtype=torch.bool).tril(), H, float("nan"))
     A = torch.full((n, n), float("nan"), device="cuda")
     D = torch.full((n // g, g, g), float("nan"), dtype=torch.float64, device="cuda")
     size = q.qtip_block_ldl_workspace(n)
@@ -39,3 +34,34 @@ def test_reconstructs(n, g):
     q.qtip_block_ldl(Hin, n, g, A2, None, ws, size)
     torch.cuda.synchronize()
     assert torch.equal(A, A2)
+
+
+@pytest.mark.parametrize("g", [8, 16])
+@pytest.mark.parametrize("filled", ["lower triangle", "g x g blocks", "everything"])
+def test_what_stands_above_the_diagonal_does_not_matter(g, filled):
+    """H filled in with zeros above its diagonal, above its diagonal blocks of g, and whole: the same A and D."""
+    import torch
+    import paper_2406_11235_amd as q
+    n = 176
+    gen = torch.Generator(device="cuda").manual_seed(g)
+    X = torch.randn(3 * n, n, dtype=torch.float64, device="cuda", generator=gen)
+    H = X.T.contiguous() @ X / (3 * n)
+    H = torch.tril(H) + torch.tril(H, -1).T
+    Hin = torch.tril(H) if filled != "everything" else H.clone()
+    if filled == "g x g blocks":
+        for i in range(0, n, g):
+            Hin[i:i + g, i:i + g] = H[i:i + g, i:i + g]
+    size = q.qtip_block_ldl_workspace(n)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    A, D = torch.empty(n, n, device="cuda"), torch.empty(n // g, g, g, dtype=torch.float64, device="cuda")
+    q.qtip_block_ldl(Hin, n, g, A, D, ws, size)
+    torch.cuda.synchronize()
+    # the definition, in binary64 on the host: L_ij D_j = S_ij, S_ik -= L_ij S_kj^T
+    S, L = H.cpu(), torch.eye(n, dtype=torch.float64)
+    for j in range(0, n, g):
+        Dj = S[j:j + g, j:j + g].clone()
+        assert float((D[j // g].cpu() - Dj).norm() / Dj.norm()) < 1e-11, j
+        L[j + g:, j:j + g] = torch.linalg.solve(Dj, S[j + g:, j:j + g].T).T
+        S[j + g:, j + g:] -= L[j + g:, j:j + g] @ S[j + g:, j:j + g].T
+    ref = L - torch.eye(n, dtype=torch.float64)
+    assert float((A.cpu().double() - ref).norm() / ref.norm()) < 1e-7  # (half a unit of binary32: 6e-8)
