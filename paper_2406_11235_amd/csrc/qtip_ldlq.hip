@@ -89,18 +89,10 @@ __global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict_
     }
 }
 
-// a[c] += b * a_p[c], a_p the row that lane p of this row of 16 lanes holds.  (A register that the vector ALU has just
-// written may not be read across lanes by the next two instructions: `first` waits for that, and behind it,
-// in ldl_invert, others are always between.)
-template <int p, bool first>
-__device__ __forceinline__ void add_multiple_of_row(double &a, double b) {
-    if constexpr (first)
-        asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(b), "n"(p));
-    else
-        asm volatile("v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(b), "n"(p));
-}
+// The value that lane p of this row of 16 lanes has.  (What reads across lanes may not follow the vector instruction that
+// wrote its register within two wait states, which is left to whoever writes it as text: it begins with them.)
 template <int p>
-__device__ __forceinline__ double row_value(double a) {  // of lane p of this row of 16 lanes
+__device__ __forceinline__ double row_value(double a) {
     double v;
     asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=&v"(v) : "v"(a), "n"(p));
     return v;
@@ -150,27 +142,44 @@ __device__ __forceinline__ double reciprocal(double d) {
     return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
 }
 
+// The other columns of pivot p: a[c] += f * a_p[c], c != p, a_p the row that lane p of this row of 16 lanes holds; returns
+// the reciprocal of the next pivot (reciprocal() of lane p + 1's a[p + 1]), whose chain runs between the columns.  One
+// piece of text, so that the waits are in it and nothing can come in between: two wait states before the first read
+// across lanes, two columns between the next pivot's column and its broadcast, one behind the hardware's reciprocal.
+// (Column by column, with the waits left to what stood between, the compiler put an exchange of lane rows one instruction
+// before the read of its result.)
+template <int p>
+__device__ __forceinline__ double ldl_eliminate(double (&a)[16], double f) {
+    double d, r, e;
+#define COLUMN(C) "v_fmac_f64_dpp %" #C ", %" #C ", %[f] row_newbcast:%[p] row_mask:0xf bank_mask:0xf\n\t"
+    asm volatile("s_nop 1\n\t" COLUMN(0) COLUMN(1) COLUMN(2)
+                 "v_mov_b64_dpp %[d], %0 row_newbcast:%[next] row_mask:0xf bank_mask:0xf\n\t" COLUMN(3)
+                 "v_rcp_f64_e32 %[r], %[d]\n\t" COLUMN(4) COLUMN(5) COLUMN(6)
+                 "v_fma_f64 %[e], -%[d], %[r], 1.0\n\t" COLUMN(7) COLUMN(8)
+                 "v_fma_f64 %[r], %[e], %[r], %[r]\n\t" COLUMN(9) COLUMN(10)
+                 "v_fma_f64 %[e], -%[d], %[r], 1.0\n\t" COLUMN(11) COLUMN(12)
+                 "v_fma_f64 %[r], %[e], %[r], %[r]\n\t" COLUMN(13) COLUMN(14)
+                 : "+v"(a[(p + 1) & 15]), "+v"(a[(p + 2) & 15]), "+v"(a[(p + 3) & 15]), "+v"(a[(p + 4) & 15]),
+                   "+v"(a[(p + 5) & 15]), "+v"(a[(p + 6) & 15]), "+v"(a[(p + 7) & 15]), "+v"(a[(p + 8) & 15]),
+                   "+v"(a[(p + 9) & 15]), "+v"(a[(p + 10) & 15]), "+v"(a[(p + 11) & 15]), "+v"(a[(p + 12) & 15]),
+                   "+v"(a[(p + 13) & 15]), "+v"(a[(p + 14) & 15]), "+v"(a[(p + 15) & 15]), [d] "=&v"(d), [r] "=&v"(r),
+                   [e] "=&v"(e)
+                 : [f] "v"(f), [p] "n"(p), [next] "n"((p + 1) & 15));
+#undef COLUMN
+    return r;
+}
+
 // Gauss-Jordan elimination of [D | I] in place, without pivoting (D is positive definite): lane l of a row of 16 holds
 // row l.  Rows are not scaled on the way: `scale` is 1 / pivot of the lane's row, and the inverse is scale * a in
-// the end.  After pivots 0 .. P - 1 the first P columns hold the identity's part.
+// the end.  After pivots 0 .. P - 1 the first P columns hold the identity's part, and `inv` is 1 / pivot P.
 template <int p, int END>
-__device__ __forceinline__ void ldl_invert(double (&a)[16], double inv, double &scale, int row) {
+__device__ __forceinline__ void ldl_invert(double (&a)[16], double &inv, double &scale, int row) {
     if constexpr (p < END) {
         const double f = row == p ? 0.0 : -a[p] * inv;
         scale = row == p ? inv : scale;
-        // the next pivot's column first, so that its reciprocal is under way beside the other columns
-        if constexpr (p + 1 < 16) add_multiple_of_row<p, true>(a[(p + 1) & 15], f);
-        double next = 1.0;
-#pragma unroll
-        for (int c = 0; c < 16; c++)
-            if (c != p && c != p + 1) {
-                add_multiple_of_row<p, false>(a[c], f);
-                if (c == (p >= 4 ? 3 : 12)) {
-                    if constexpr (p + 1 < 16) next = reciprocal(row_value<(p + 1) & 15>(a[(p + 1) & 15]));
-                }
-            }
+        inv = ldl_eliminate<p>(a, f);
         a[p] = row == p ? 1.0 : f;
-        ldl_invert<p + 1, END>(a, next, scale, row);
+        ldl_invert<p + 1, END>(a, inv, scale, row);
     }
 }
 
@@ -287,13 +296,13 @@ __global__ __launch_bounds__((LDL_PANEL + LDL_MAX_ROWS) * 64) void ldl_panel_ker
             double a[16];
             ldl_rows(t[j], a);
             double scale = 1.0;
-            const double first = reciprocal(row_value<0>(a[0]));
+            double inv = reciprocal(row_value<0>(a[0]));
             if constexpr (G == 16) {
-                ldl_invert<0, 16>(a, first, scale, row);
+                ldl_invert<0, 16>(a, inv, scale, row);
             } else {
                 // Half-way the first 8 rows hold the inverse of D's first 8 x 8 block, the last 8 the second
                 // block of D in 8 x 8 blocks and, negative, the entry of L between the two.
-                ldl_invert<0, 8>(a, first, scale, row);
+                ldl_invert<0, 8>(a, inv, scale, row);
                 if (blockIdx.x == 0 && g == 0 && row >= 8) {
 #pragma unroll
                     for (int c = 0; c < 8; c++) {
@@ -304,7 +313,7 @@ __global__ __launch_bounds__((LDL_PANEL + LDL_MAX_ROWS) * 64) void ldl_panel_ker
                 double f[16];
 #pragma unroll
                 for (int c = 0; c < 16; c++) f[c] = c < 8 ? a[c] * scale : 0.0;
-                ldl_invert<8, 16>(a, reciprocal(row_value<8>(a[8])), scale, row);
+                ldl_invert<8, 16>(a, inv, scale, row);
 #pragma unroll
                 for (int c = 0; c < 16; c++) f[c] = row < 8 ? f[c] : a[c] * scale;
                 ldl_store(s_out[buf], lane, ldl_operand(f, g));
