@@ -172,10 +172,13 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
     constexpr int SUMS_AT_ONCE = Lds::SUMS;
     // Stages that are summed in the matrix cores before the sums go to totals of their own: the rounding error of a long
     // chain grows with it (997 x 4096 x 14336, against binary64: 4.1e-7 in one chain of 256 matrix instructions,
-    // 1.3e-7 in chains of 16, 1.6e-7 with eight waves that split the inputs).  With eight slices of the inputs the
-    // chains are short.  The totals take as many registers as the running sums: at 256 batch rows a workgroup is
+    // 1.3e-7 in chains of 16).  The totals take as many registers as the running sums: at 256 batch rows a workgroup is
     // four waves with a SIMD's registers each (115 -> 149 us; up to 128 batch rows it costs 1 to 4 %).
-    constexpr int CHAIN = WK == 8 ? 0 : 16 / KS;
+    // With eight slices of the inputs a chain is a 128th of the inputs long, no longer than it was in the kernels that
+    // had 17 to 64 rows before (1.6e-7 at 4096 inputs, 2.8e-7 at 14464; totals would halve that and cost HYB 3 to 5 %).
+    // Only the lookup-only code had 16 slices there, up to 32 rows (1.3e-7 and 2.1e-7), so its sums go to totals here too:
+    // 1.2e-7 and 1.3e-7; 24 rows, 4096 x 4096 12.6 -> 12.7 us, 2048 x 14464 35.7 -> 36.0, 8192 x 8192 22.6 -> 23.1.
+    constexpr int CHAIN = WK == 8 && !(LUT && NBB == 1) ? 0 : 16 / KS;
     constexpr int AHEAD = 3, GROUPS = KS * NBB * RB;  // a group: one matrix instruction and what goes with it
     constexpr int STEP_BYTES = Lds::STEP_BYTES, CODE_ROW = Lds::CODE_ROW, CODE_ROWS = Lds::CODE_ROWS;
     constexpr int CODE_COPIES = Lds::CODE_COPIES, CODE_STAGE = Lds::CODE_STAGE;

@@ -96,3 +96,25 @@ def test_long_rows_are_not_one_chain_of_sums(q, m, n, B):
     q.qtip_dequantize(codes, 16, 2, 1, CODE_3INST, None, m, n, W)
     ref = X.double() @ W.double().T.contiguous()
     assert (Y.double() - ref).norm() <= 1.8e-7 * ref.norm()
+
+
+@pytest.mark.parametrize("k", [2, 3, 4])
+@pytest.mark.parametrize("m,n", [(1024, 4096), (2048, 14464)])
+def test_slices_of_the_lookup_only_code_are_not_one_chain_of_sums(q, k, m, n):
+    """17 to 32 batch rows, whose waves split the inputs: a wave's sums go to totals after 16 matrix instructions as well.
+    A chain of c instructions of 16 products has an error that grows with the root of c: 1.2e-7 to 1.3e-7 of the result's
+    2-norm for 16 and the few sums over chains and waves (binary32's half unit is 6e-8); without totals it is 1.56e-7 for
+    chains of 32 (n = 4096) and 2.76e-7 for 113 (n = 14464), with twice as many slices 1.30e-7 and 2.1e-7."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    codes = torch.randint(-2**31, 2**31, (m * n // 256, 8 * k), dtype=torch.int32, device="cuda", generator=g)
+    lut = torch.randn(1 << 14, device="cuda", generator=g).half()
+    W = torch.empty(m, n, dtype=torch.float16, device="cuda")
+    q.qtip_dequantize(codes, 14, k, 1, CODE_LUT, lut, m, n, W)
+    Wt = W.double().T.contiguous()
+    for B in (17, 24, 32):
+        X = torch.randn(B, n, device="cuda", generator=g).half()
+        Y = torch.empty(B, m, device="cuda")
+        q.qtip_decode_matmat(codes, 14, k, 1, CODE_LUT, lut, m, n, X, B, None, Y)
+        ref = X.double() @ Wt
+        assert (Y.double() - ref).norm() <= 1.4e-7 * ref.norm(), B
