@@ -6,6 +6,7 @@ integer device pointers) and enqueue on torch's current stream unless a stream i
 given.  There is no fallback: if the library is missing, loading raises.
 """
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -155,35 +156,72 @@ def _load_call():
     return _call
 
 
-def _entry(name):
-    """The callable for one entry point; a stand-in that looks for it when called where nothing is built yet."""
+def _entry(signature):
+    """The callable for one entry point, which looks like the function it is written as below; a stand-in that looks for
+    it when called where nothing is built yet or what is there is from before (it has to be importable to be built)."""
     try:
-        return getattr(_load_call(), name)
-    except FileNotFoundError:
+        return functools.update_wrapper(getattr(_load_call(), signature.__name__), signature)
+    except (FileNotFoundError, AttributeError):
         def entry(*args, **kwargs):
-            return getattr(_load_call(), name)(*args, **kwargs)
-        entry.__name__ = name
-        return entry
+            return getattr(_load_call(), signature.__name__)(*args, **kwargs)
+        return functools.update_wrapper(entry, signature)
 
 
-qtip_rht = _entry("qtip_rht")  # (x, signs, n, block, batch, side, out, stream=None)
-qtip_rht_f32 = _entry("qtip_rht_f32")  # (x, signs, n, block, batch, side, out, stream=None)
-# (codes, L, k, V, code_id, lut, m, n, x, y, stream=None)
-qtip_decode_matvec = _entry("qtip_decode_matvec")
-# (codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y, xt_scratch=None, stream=None)
-qtip_rht_decode_matvec = _entry("qtip_rht_decode_matvec")
-# (codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y, stream=None)
-qtip_rht_decode_matvec_noalloc = _entry("qtip_rht_decode_matvec_noalloc")
-# (codes, L, k, V, code_id, lut, m, n, X, B, row_scale, Y, stream=None)
-qtip_decode_matmat = _entry("qtip_decode_matmat")
-# (codes, L, k, V, code_id, lut, m, n, W, stream=None)
-qtip_dequantize = _entry("qtip_dequantize")
-qtip_decode_states = _entry("qtip_decode_states")  # (states, count, L, V, code_id, lut, out, stream=None)
-# (W, m, n, L, k, V, code_id, lut, codes_out, tile_err, workspace, workspace_bytes, stream=None)
-qtip_quantize_gpu = _entry("qtip_quantize_gpu")
-qtip_block_ldl = _entry("qtip_block_ldl")  # (H, n, g, A_out, D_out, workspace, workspace_bytes, stream=None)
-# (W, A, m, n, L, k, V, code_id, lut, codes_out, What_out, tile_err, workspace, workspace_bytes, stream=None)
-qtip_quantize_ldlq = _entry("qtip_quantize_ldlq")
+@_entry
+def qtip_rht(x, signs, n, block, batch, side, out, stream=None):
+    """Random Hadamard transform of fp16 activations: side 0 is V (S .* x), side 1 is S .* (V^T x)."""
+
+
+@_entry
+def qtip_rht_f32(x, signs, n, block, batch, side, out, stream=None):
+    """qtip_rht of fp32 values; the result is fp16."""
+
+
+@_entry
+def qtip_decode_matvec(codes, L, k, V, code_id, lut, m, n, x, y, stream=None):
+    """y = W~ x, the weights decoded on the way."""
+
+
+@_entry
+def qtip_rht_decode_matvec(codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y, xt_scratch=None,
+                           stream=None):
+    """y = row_scale .* (W~ (V (S_n .* x))): the input side of a layer."""
+
+
+@_entry
+def qtip_rht_decode_matvec_noalloc(codes, L, k, V, code_id, lut, m, n, x, signs_n, block, row_scale, y, stream=None):
+    """qtip_rht_decode_matvec with the library's own scratch (n at most 65536)."""
+
+
+@_entry
+def qtip_decode_matmat(codes, L, k, V, code_id, lut, m, n, X, B, row_scale, Y, stream=None):
+    """Y[b] = row_scale .* (W~ X[b]) for B rows."""
+
+
+@_entry
+def qtip_dequantize(codes, L, k, V, code_id, lut, m, n, W, stream=None):
+    """The weights of a code stream as an m x n fp16 matrix."""
+
+
+@_entry
+def qtip_decode_states(states, count, L, V, code_id, lut, out, stream=None):
+    """The values of a list of states."""
+
+
+@_entry
+def qtip_quantize_gpu(W, m, n, L, k, V, code_id, lut, codes_out, tile_err, workspace, workspace_bytes, stream=None):
+    """A weight matrix to code streams, block by block."""
+
+
+@_entry
+def qtip_block_ldl(H, n, g, A_out, D_out, workspace, workspace_bytes, stream=None):
+    """The block LDL decomposition of a proxy Hessian."""
+
+
+@_entry
+def qtip_quantize_ldlq(W, A, m, n, L, k, V, code_id, lut, codes_out, What_out, tile_err, workspace, workspace_bytes,
+                       stream=None):
+    """A weight matrix to code streams with feedback (BlockLDLQ)."""
 
 
 def qtip_version():

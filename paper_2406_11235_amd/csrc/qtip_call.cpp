@@ -7,7 +7,9 @@
 // object and 1.6 the marshalling; through here it costs 2.9.
 //
 // The objects know nothing of a library file: connect() hands them the addresses of the
-// entry points of the one that binding.py loaded.
+// entry points of the one that binding.py loaded.  Otherwise they are to a program what a function of binding.py is:
+// they take attributes (binding.py gives them name, module, documentation and signature), weak references, pickle and
+// copy by name and bind to an instance.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -37,6 +39,7 @@ struct Entry {
     int count, required;
     Kind kind[MAX_ARGS];
     PyObject *keyword[MAX_ARGS];
+    PyObject *dict, *weak_references;
 };
 
 bool as_integer(PyObject *o, unsigned long long &out) {
@@ -141,24 +144,51 @@ PyObject *entry_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObj
 
 void entry_dealloc(PyObject *self) {
     Entry *e = reinterpret_cast<Entry *>(self);
+    PyObject_GC_UnTrack(self);
+    if (e->weak_references) PyObject_ClearWeakRefs(self);
+    Py_XDECREF(e->dict);
     for (int i = 0; i < e->count; i++) Py_XDECREF(e->keyword[i]);
     Py_TYPE(self)->tp_free(self);
+}
+int entry_traverse(PyObject *self, visitproc visit, void *arg) {
+    Py_VISIT(reinterpret_cast<Entry *>(self)->dict);
+    return 0;
+}
+int entry_clear(PyObject *self) {
+    Py_CLEAR(reinterpret_cast<Entry *>(self)->dict);
+    return 0;
 }
 PyObject *entry_repr(PyObject *self) {
     return PyUnicode_FromFormat("<entry point %s>", reinterpret_cast<Entry *>(self)->name);
 }
-PyObject *entry_name(PyObject *self, void *) { return PyUnicode_FromString(reinterpret_cast<Entry *>(self)->name); }
-PyGetSetDef entry_attributes[] = {{"__name__", entry_name, nullptr, nullptr, nullptr}, {}};
+PyObject *entry_get(PyObject *self, PyObject *instance, PyObject *) {
+    if (instance && instance != Py_None) return PyMethod_New(self, instance);
+    Py_INCREF(self);
+    return self;
+}
+// (a name: pickle and copy look it up in __module__)
+PyObject *entry_reduce(PyObject *self, PyObject *) {
+    return PyUnicode_FromString(reinterpret_cast<Entry *>(self)->name);
+}
+PyMethodDef entry_methods[] = {{"__reduce__", entry_reduce, METH_NOARGS, nullptr}, {}};
+PyGetSetDef entry_attributes[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr}, {}};
 
 PyTypeObject EntryType = [] {
     PyTypeObject t = {PyVarObject_HEAD_INIT(nullptr, 0)};
     t.tp_name = "paper_2406_11235_amd._call.Entry";
     t.tp_basicsize = sizeof(Entry);
-    t.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
+    t.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL | Py_TPFLAGS_HAVE_GC;
     t.tp_vectorcall_offset = offsetof(Entry, call);
     t.tp_call = PyVectorcall_Call;
     t.tp_dealloc = entry_dealloc;
     t.tp_repr = entry_repr;
+    t.tp_traverse = entry_traverse;
+    t.tp_clear = entry_clear;
+    t.tp_free = PyObject_GC_Del;
+    t.tp_dictoffset = offsetof(Entry, dict);
+    t.tp_weaklistoffset = offsetof(Entry, weak_references);
+    t.tp_descr_get = entry_get;
+    t.tp_methods = entry_methods;
     t.tp_getset = entry_attributes;
     return t;
 }();
@@ -187,7 +217,7 @@ template <class F>
 bool add_entry(PyObject *module, const char *name, int required, std::initializer_list<const char *> names) {
     using S = Signature<F>;
     static_assert(S::COUNT <= MAX_ARGS, "room for the arguments");
-    Entry *e = PyObject_New(Entry, &EntryType);
+    Entry *e = PyObject_GC_New(Entry, &EntryType);
     if (!e) return false;
     e->call = entry_call;
     e->name = name;
@@ -195,9 +225,11 @@ bool add_entry(PyObject *module, const char *name, int required, std::initialize
     e->invoke = S::invoke;
     e->count = 0;
     e->required = required;
+    e->dict = e->weak_references = nullptr;
     S::kinds(e->kind);
     e->kind[S::COUNT - 1] = STREAM;
     for (const char *n : names) e->keyword[e->count++] = PyUnicode_InternFromString(n);
+    PyObject_GC_Track(reinterpret_cast<PyObject *>(e));
     if (e->count != S::COUNT) {
         PyErr_Format(PyExc_SystemError, "%s: %d names for %d arguments", name, e->count, S::COUNT);
         return false;

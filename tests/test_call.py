@@ -31,3 +31,36 @@ def test_wrong_arguments_raise(name):
                     "qtip_block_ldl": "H", "qtip_quantize_ldlq": "W"}.get(name, "codes"): None})
     with pytest.raises((TypeError, AttributeError)):
         f(*[object()] * 7, stream=0)
+
+
+@pytest.mark.parametrize("name", binding._GPU_ENTRIES)
+def test_entry_points_are_like_functions(name):
+    import copy
+    import inspect
+    import pickle
+    import weakref
+    f = getattr(q, name)
+    assert (f.__name__, f.__qualname__, f.__module__) == (name, name, binding.__name__) and f.__doc__
+    assert pickle.loads(pickle.dumps(f)) is f and copy.copy(f) is f and copy.deepcopy(f) is f
+    assert weakref.ref(f)() is f
+    f.note = "kept"
+    assert f.note == "kept" and vars(f)["note"] == "kept"
+    del f.note
+    assert not hasattr(f, "note")
+
+    class Holder:
+        method = f
+    held = Holder()
+    assert Holder.method is f and held.method.__self__ is held and held.method.__func__ is f
+    # the signature is the one the call has: every name is taken, what has no default is needed
+    parameters = inspect.signature(f).parameters
+    needed = [p.name for p in parameters.values() if p.default is p.empty]
+    assert {p.default for p in parameters.values()} <= {inspect.Parameter.empty, None} and "stream" in parameters
+    for given in (list(parameters), needed + ["stream"]):
+        with pytest.raises(q.QtipError):
+            f(**{p: 0 for p in given})
+    for p in needed:
+        with pytest.raises(TypeError, match=f"missing required argument '{p}'"):
+            f(**{o: 0 for o in parameters if o != p})
+    with pytest.raises(q.QtipError):
+        f(*[0] * len(parameters))
