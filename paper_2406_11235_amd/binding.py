@@ -105,7 +105,13 @@ def _ptr(t):
 def _stream(stream):
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        current = torch.cuda.current_stream().cuda_stream  # (initializes torch's GPU state where nothing has yet)
+        # from here on _call asks torch's own getters of the current device and of its current stream as an integer,
+        # where this torch has them
+        device, raw = (getattr(torch._C, name, None) for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+        if _call is not None and device is not None and raw is not None:
+            _call.hooks(_ptr, _stream, _check, _connect, device, raw)
+        return current
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -127,17 +133,7 @@ _call = None
 
 def _connect():
     """Give the entry points of _call the addresses of the loaded library's functions."""
-    import torch
     L = lib()
-    # torch's own getters of the current device and of its current stream as an integer; without
-    # them (or without a GPU) _stream() asks the public interface
-    device = getattr(torch._C, "_cuda_getDevice", None)
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if device is None or raw is None or not torch.cuda.is_available():
-        device = raw = None
-    else:
-        torch.cuda.init()
-    _call.hooks(_ptr, _stream, _check, _connect, device, raw)
     for name in _GPU_ENTRIES:
         _call.connect(getattr(_call, name), ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
 

@@ -64,3 +64,34 @@ def test_entry_points_are_like_functions(name):
             f(**{o: 0 for o in parameters if o != p})
     with pytest.raises(q.QtipError):
         f(*[0] * len(parameters))
+
+
+def test_calls_that_name_their_stream_leave_torch_alone():
+    """torch's GPU state is not looked at, and not initialized, by calls that say where they go (a child process,
+    because the library is connected once)."""
+    import subprocess
+    import sys
+    program = """
+import torch
+def asked(*args): raise AssertionError("asked")
+torch.cuda.init = torch.cuda.is_available = torch.cuda._lazy_init = torch.cuda.current_stream = asked
+import paper_2406_11235_amd as q
+for stream in (0, 64, type("Stream", (), {"cuda_stream": 0})()):
+    assert q.qtip_decode_states(64, 0, 16, 1, 0, None, 64, stream) == 0  # nothing to do: no launch
+    try:
+        q.qtip_rht(0, 0, 64, 64, 1, 0, 0, stream=stream)
+    except q.QtipError:
+        continue
+    raise SystemExit("not refused")
+try:
+    q.qtip_decode_states(64, 0, 16, 1, 0, None, 64)
+except AssertionError:
+    raise SystemExit(0)
+raise SystemExit("the current stream came from nowhere")
+"""
+    subprocess.run([sys.executable, "-c", program], check=True, cwd=build_root())
+
+
+def build_root():
+    import os
+    return os.path.dirname(os.path.dirname(os.path.abspath(q.__file__)))
