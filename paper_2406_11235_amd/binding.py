@@ -138,6 +138,11 @@ def _connect():
         _call.connect(getattr(_call, name), ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
 
 
+def _ask_torch():
+    """Have _call come to _stream() for the current stream."""
+    _call.hooks(_ptr, _stream, _check, _connect, None, None)
+
+
 def _load_call():
     global _call
     if _call is None:
@@ -148,7 +153,9 @@ def _load_call():
             raise FileNotFoundError(
                 f"the _call extension of {__package__} is missing ({e}): run `python -m paper_2406_11235_amd.build`"
             ) from e
-        _call.hooks(_ptr, _stream, _check, _connect, None, None)
+        _ask_torch()
+        # (torch refuses GPU work in a forked child of a process that has done some; its getters alone would not)
+        os.register_at_fork(after_in_child=_ask_torch)
     return _call
 
 

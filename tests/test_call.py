@@ -92,6 +92,35 @@ raise SystemExit("the current stream came from nowhere")
     subprocess.run([sys.executable, "-c", program], check=True, cwd=build_root())
 
 
+def test_a_forked_child_asks_torch_again():
+    """torch.cuda.current_stream() raises in the forked child of a process that has used the GPU, and so does a call
+    without a stream, although the parent has torch's getters at hand."""
+    import subprocess
+    import sys
+    program = """
+import os
+import torch
+import paper_2406_11235_amd as q
+from paper_2406_11235_amd import binding
+def refused(): raise RuntimeError("forked")
+def call(): return q.qtip_decode_states(64, 0, 16, 1, 0, None, 64)  # nothing to do: no launch
+q.qtip_decode_states(64, 0, 16, 1, 0, None, 64, 0)
+binding._call.hooks(binding._ptr, binding._stream, binding._check, binding._connect, lambda: 0, lambda device: 0)
+torch.cuda.current_stream = refused
+assert call() == 0
+child = os.fork()
+if child == 0:
+    try:
+        call()
+    except RuntimeError as e:
+        os._exit(0 if str(e) == "forked" else 2)
+    os._exit(1)
+assert os.waitstatus_to_exitcode(os.waitpid(child, 0)[1]) == 0
+assert call() == 0
+"""
+    subprocess.run([sys.executable, "-c", program], check=True, cwd=build_root())
+
+
 def build_root():
     import os
     return os.path.dirname(os.path.dirname(os.path.abspath(q.__file__)))
