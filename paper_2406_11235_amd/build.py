@@ -7,7 +7,8 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqtip.so")
-CALL = os.path.join(HERE, "_call.so")
+# (with the interpreter's tag: _call is built for one Python, and another one may not load it)
+CALL = os.path.join(HERE, "_call" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 CALL_SOURCE = os.path.join(CSRC, "qtip_call.cpp")
 SOURCES = ["qtip_api.hip", "qtip_decode.hip", "qtip_lut14.hip", "qtip_gemm.hip", "qtip_rht.hip", "qtip_viterbi.hip", "qtip_ldlq.hip", "qtip_quantize.cpp"]
 HEADERS = ["qtip_device.h", "qtip_rht_device.h", "qtip_internal.h", os.path.join("..", "..", "include", "qtip.h")]
@@ -27,17 +28,20 @@ def is_stale():
 
 
 def build_call(verbose=False):
-    """Compile paper_2406_11235_amd/_call.so, the Python side of the entry points."""
+    """Compile paper_2406_11235_amd/_call, the Python side of the entry points."""
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-I" + sysconfig.get_paths()["include"], CALL_SOURCE, "-o", CALL]
     if verbose:
         print(" ".join(cmd), file=sys.stderr)
     subprocess.run(cmd, check=True)
+    untagged = os.path.join(HERE, "_call.so")  # as older builds named it
+    if CALL != untagged and os.path.exists(untagged):
+        os.remove(untagged)
 
 
 def build(force=True, extra_flags=(), verbose=False, out=None, jobs=None):
     """Compile every source into paper_2406_11235_amd/libqtip.so (or `out`): one hipcc
-    process per source file, a few at a time, then one link.  Without `out` also _call.so."""
+    process per source file, a few at a time, then one link.  Without `out` also _call."""
     if out is None and not force and not is_stale():
         return LIB
     if out is None:

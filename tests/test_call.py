@@ -121,6 +121,18 @@ assert call() == 0
     subprocess.run([sys.executable, "-c", program], check=True, cwd=build_root())
 
 
+def test_the_extension_is_this_pythons_own():
+    """Built under the interpreter's tag, so that no other one finds it, and nothing untagged beside it."""
+    import importlib.machinery
+    import os
+    import sysconfig
+    from paper_2406_11235_amd import build
+    tag = sysconfig.get_config_var("EXT_SUFFIX")
+    assert binding._load_call().__file__ == build.CALL and build.CALL.endswith(tag) and sysconfig.get_config_var("SOABI") in tag
+    found = [f for f in os.listdir(os.path.dirname(build.CALL)) if f.startswith("_call") and f.endswith(".so")]
+    assert "_call.so" not in found and tag in importlib.machinery.EXTENSION_SUFFIXES
+
+
 def build_root():
     import os
     return os.path.dirname(os.path.dirname(os.path.abspath(q.__file__)))
