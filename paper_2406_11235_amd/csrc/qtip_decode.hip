@@ -655,6 +655,18 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     const int groups = (B + 15) / 16;  // more than one only where the large-batch kernel does not reach
     const int tm = m / 16, tn = n / 16;
     const half_t *Xh = (const half_t *)X, *sc = (const half_t *)scale;
+    // There a workgroup decodes a weight for 16 batch rows while that makes at most two workgroups per CU, and for 32
+    // or 64 otherwise (2^22 inputs, 2-bit 3INST, ms for 16 and for 32 or 64: 1024 outputs 64 rows 3.8 and 8.7, 128 rows
+    // 7.2 and 8.8, 200 rows 13.4 and 8.9; 4096 outputs 24 rows 6.8 and 6.8, 48 rows 10.0 and 8.7, 200 rows 39.8 and 21.7).
+    if (groups > 1 && (long)tm * groups > 512) {
+        if (groups == 2)
+            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 2, 8, true>), dim3((tm + 1) / 2), dim3(8 * 64), 0, st, codes,
+                               lut, tm, tn, Xh, B, sc, Y);
+        else
+            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 4, 8, true>), dim3((tm + 1) / 2, (groups + 3) / 4),
+                               dim3(8 * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y);
+        return hipGetLastError();
+    }
     constexpr bool HYB = CODE == CODE_HYB;
     // (measured: the 16 table copies pay at 9 to 16 batch rows, 8192 x 8192 13.1 -> 12.3 us and
     // 8192 x 28672 35 -> 31 us, and make no difference below)
@@ -735,7 +747,7 @@ hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32
                          hipStream_t st) {
     // (17 to 32 rows: as fast or up to 10 % faster than two groups of 16 here; 64 rows, 4096 x 4096 2-bit 3INST: 14.6 ->
     // 10.7 us, 8192 x 8192 4-bit HYB 28.1 -> 24.6; 997 rows, 14336 x 4096: 311 -> 116 us)
-    if (B > 16 && gemm_takes(n)) return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
+    if (B > 16 && gemm_takes(code_id, n, B)) return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
     if (code_id == CODE_LUT) return launch_lut_matmat(k, codes, lut, m, n, X, B, scale, Y, st);
     QTIP_DISPATCH(launch_matmat_t, codes, lut, m, n, X, B, scale, Y, st);
 }

@@ -435,6 +435,10 @@ struct GemmSplit {
 static constexpr GemmSplit GEMM_SPLITS[] = {{128, 256, 0.f, 74.f}, {128, 128, 0.f, 42.f}, {64, 128, 2.f, 25.f},
                                             {64, 64, 5.f, 15.f},    {32, 64, 2.f, 11.3f},  {32, 32, 4.5f, 5.5f}};
 
+// A workgroup addresses its batch rows and its wave's tile rows (16 bytes an input at most, less than 32 batch rows) with
+// 32-bit byte offsets from uniform bases, kept within 2^31.
+static bool offsets_fit(const GemmSplit &s, int n) { return (long)s.rows * 2 * n <= 1L << 31; }
+
 // Kernels of the splits, in their order.
 #define QTIP_GEMM_SPLITS(GO) \
     GO(0, 1, 8, 4, 1) GO(1, 1, 4, 4, 2) GO(2, 1, 4, 2, 4) GO(3, 1, 2, 2, 4) GO(4, 1, 2, 1, 8) GO(5, 1, 1, 1, 8)
@@ -449,7 +453,7 @@ static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int 
     for (int i = 0; i < 6; i++) {
         const GemmSplit &s = GEMM_SPLITS[i];
         const long gx = (m + s.outputs - 1) / s.outputs, gy = (B + s.rows - 1) / s.rows;
-        if (!fits[i] || gy > 65535) continue;
+        if (!fits[i] || gy > 65535 || !offsets_fit(s, n)) continue;
         const float t = s.first + s.round * (float)((gx * gy + 255) / 256);
         if (best < 0 || t < least) best = i, least = t;
     }
@@ -468,8 +472,14 @@ static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int 
     return hipGetLastError();
 }
 
-// (a tile row and the activations of 256 batch rows are addressed with 32-bit byte offsets)
-bool gemm_takes(int n) { return n <= 1 << 22; }
+// Rows of up to 2^22 inputs fit every split.  Longer rows are megabytes apart, which the copies into LDS bear badly (2^22
+// inputs, 64 outputs and 64 rows, where nothing but the copies takes long: 9.5 ms; the 16-row kernel 3.1).  There the 16 x 16
+// codes' own kernels are faster (4096 outputs, 2-bit HYB, 24 rows: 7.7 against 5.4 ms), the lookup-only code's are not (24 rows
+// 9.3 against 11.8 ms, 200 rows 18 against 54), so its rows go on as long as the smallest split's offsets fit
+// (and its grid takes the batch).
+bool gemm_takes(int code_id, int n, int B) {
+    return n <= 1 << 22 || (code_id == CODE_LUT && n <= 1 << 25 && B <= 32 * 65535);
+}
 
 hipError_t launch_gemm(int k, int code_id, const uint32_t *codes, const void *lut, int m, int n, const void *X, int B,
                        const void *scale, float *Y, hipStream_t st) {

@@ -11,8 +11,8 @@ hipError_t launch_matvec(int k, int code_id, const uint32_t *codes, const uint32
                          int n, const void *x, const void *scale, float *y, hipStream_t st);
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                          int n, const void *X, int B, const void *scale, float *Y, hipStream_t st);
-// The product for more than 16 batch rows (qtip_gemm.hip), any code, where gemm_takes(n).
-bool gemm_takes(int n);
+// The product for more than 16 batch rows (qtip_gemm.hip), where gemm_takes() the sizes.
+bool gemm_takes(int code_id, int n, int B);
 hipError_t launch_gemm(int k, int code_id, const uint32_t *codes, const void *lut, int m, int n, const void *X, int B,
                        const void *scale, float *Y, hipStream_t st);
 // decode + matvec that computes the input-side transform V (S .* x) itself; n at most

@@ -118,3 +118,44 @@ def test_slices_of_the_lookup_only_code_are_not_one_chain_of_sums(q, k, m, n):
         q.qtip_decode_matmat(codes, 14, k, 1, CODE_LUT, lut, m, n, X, B, None, Y)
         ref = X.double() @ Wt
         assert (Y.double() - ref).norm() <= 1.4e-7 * ref.norm(), B
+
+
+def check_sparse(q, code, m, n, rows):
+    """All but about 1200 inputs, the first, the last and some everywhere, are zeros, so that a single wrong tile shows: a
+    wave's running sum changes in at most 400 of its additions, each of which is off by at most a unit of the sum, 2^-23."""
+    import torch
+    L, V, entries = CODES[code]
+    k = 2 + code % 3
+    g = torch.Generator(device="cuda").manual_seed(code)
+    codes = torch.randint(-2**31, 2**31, (m * n // 256, 8 * k), dtype=torch.int32, device="cuda", generator=g)
+    lut = torch.randn(entries, device="cuda", generator=g).half() if entries else None
+    sc = (torch.rand(m, device="cuda", generator=g) + 0.5).half()
+    some = torch.randint(0, n, (1000,), device="cuda", generator=g)
+    some = torch.cat([torch.arange(40, device="cuda"), some, torch.arange(n - 120, n, device="cuda")]).unique()
+    X = torch.zeros(max(rows), n, dtype=torch.float16, device="cuda")
+    X[:, some] = torch.randn(max(rows), len(some), device="cuda", generator=g).half()
+    W = torch.empty(m, n, dtype=torch.float16, device="cuda")
+    q.qtip_dequantize(codes, L, k, V, code, lut, m, n, W)
+    ref = (X[:, some].double() @ W[:, some].double().T.contiguous()) * sc.double()
+    for B in rows:
+        buf = torch.full((B * m + 4096,), float("nan"), device="cuda")
+        q.qtip_decode_matmat(codes, L, k, V, code, lut, m, n, X, B, sc, buf)
+        Y = buf[:B * m].view(B, m).double()
+        torch.cuda.synchronize()
+        assert torch.isnan(buf[B * m:]).all()
+        assert (Y - ref[:B]).norm() <= 400 * 2.0**-23 * ref[:B].norm(), (code, B)
+
+
+@pytest.mark.parametrize("code", list(CODES))
+@pytest.mark.parametrize("n", [2**22 + 80, 2**25, 2**25 + 80])
+def test_very_long_rows(q, code, n):
+    """Lengths at which the larger splits' 32-bit offsets, and then every split's, do not reach."""
+    check_sparse(q, code, 32 if code == CODE_LUT else 48, n, (17, 32, 33, 65))
+
+
+@pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
+def test_very_long_rows_decoded_for_more_than_16_rows_at_once(q, code):
+    """More than 512 tile rows times groups of 16 rows: weights decoded for 32 rows and for 64, a last pair of tile rows
+    that is not full."""
+    check_sparse(q, code, 16 * 171, 2**22 + 16, (48, 50, 64, 65, 97))
+    check_sparse(q, code, 16 * 257, 2**22 + 16, (17, 32))
