@@ -216,7 +216,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint3
 //   32 I + 8 (e / 4) + 4 (l / 32) + e % 4 for batch row b0 + l % 32.
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
-template <int K, int NB, int NW>
+template <int K, int NW>
 __global__ __launch_bounds__(NW * 64) void lut_matmat_kernel(const uint32_t *__restrict__ codes,
                                                              const uint16_t *__restrict__ lut, int tn,
                                                              int m, const half_t *__restrict__ X, int B,
@@ -224,13 +224,13 @@ __global__ __launch_bounds__(NW * 64) void lut_matmat_kernel(const uint32_t *__r
                                                              float *__restrict__ Y) {
     constexpr int NWORDS = 8 * K;
     __shared__ __attribute__((aligned(16))) uint16_t s_tab[LUT_STATES];
-    __shared__ float s_part[NW - 1][NB][16][64];
+    __shared__ float s_part[NW - 1][16][64];
     stage_table(lut, s_tab, NW * 64);
     __syncthreads();
     const int I = blockIdx.x;
-    const int b0 = blockIdx.y * (32 * NB);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int i = lane & 31, s = lane >> 5;
+    const int b = blockIdx.y * 32 + i;
     const size_t n = (size_t)tn * LUT_TY;
     const int chunk = ((tn + NW * 2 - 1) / (NW * 2)) * 2;
     const int J0 = wave * chunk;
@@ -238,83 +238,62 @@ __global__ __launch_bounds__(NW * 64) void lut_matmat_kernel(const uint32_t *__r
     // block row i starts 8 K i bits into the block; its 8 K + 14 - K bits lie in two words
     const int bit = 8 * K * i, w0 = bit >> 5, sh = bit & 31;
 
-    float16_t acc[NB];
+    float16_t acc;
 #pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) acc[nb][e] = 0.f;
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
 
     uint32_t wn[2];
-    half8_t xn[NB];
+    half8_t xn;
     auto issue = [&](int Jb) {
         const int J = min(Jb + s, Jend - 1);  // a half past the end re-reads the last block
         const uint32_t *tile = codes + ((size_t)I * tn + J) * NWORDS;
         wn[0] = stream_load(tile + w0);
         wn[1] = stream_load(tile + (w0 + 1) % NWORDS);  // wraps inside the block (tail-biting)
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++) {
-            const int b = b0 + 32 * nb + i;
-            xn[nb] = *reinterpret_cast<const half8_t *>(X + (size_t)min(b, B - 1) * n + LUT_TY * J);
-        }
+        xn = *reinterpret_cast<const half8_t *>(X + (size_t)min(b, B - 1) * n + LUT_TY * J);
     };
     // Three stages in flight: the stream words and activations of step t + 2 are being loaded,
     // the table reads of step t + 1 are issued before the matrix-core instruction of step t,
     // so that the LDS and the matrix cores work at the same time inside one wave.
-    auto decode = [&](half8_t &a, half8_t (&xb)[NB], int Jb) {
+    auto decode = [&](half8_t &a, half8_t &xb, int Jb) {
         const uint64_t both = (((uint64_t)wn[0] << 32) | wn[1]) << sh;
         const uint32_t w[2] = {(uint32_t)(both >> 32), (uint32_t)both};
-        const bool live = Jb + s < Jend;
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++) {
-            xb[nb] = xn[nb];
-            if (!live || b0 + 32 * nb + i >= B) xb[nb] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};  // dead half / batch row
-        }
+        xb = xn;
+        if (Jb + s >= Jend || b >= B) xb = half8_t{0, 0, 0, 0, 0, 0, 0, 0};  // dead half / batch row
         if (Jb + 2 < Jend) issue(Jb + 2);
 #pragma unroll
         for (int c = 0; c < 8; c++) a[c] = table_at(s_tab, table_offset(w, c * K));
     };
-    half8_t a1, x1[NB];
+    half8_t a1, x1;
     if (J0 < Jend) {
         issue(J0);
         decode(a1, x1, J0);
     }
     for (int Jb = J0; Jb < Jend; Jb += 2) {
-        const half8_t a = a1;
-        half8_t xb[NB];
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++) xb[nb] = x1[nb];
+        const half8_t a = a1, xb = x1;
         if (Jb + 2 < Jend) decode(a1, x1, Jb + 2);
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, xb[nb], acc[nb], 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, xb, acc, 0, 0, 0);
     }
     if (wave > 0) {
 #pragma unroll
-        for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) s_part[wave - 1][nb][e][lane] = acc[nb][e];
+        for (int e = 0; e < 16; e++) s_part[wave - 1][e][lane] = acc[e];
     }
     __syncthreads();
-    if (wave == 0) {
+    if (wave == 0 && b < B) {
 #pragma unroll
-        for (int nb = 0; nb < NB; nb++) {
-            const int b = b0 + 32 * nb + i;
-            if (b >= B) continue;
+        for (int e4 = 0; e4 < 4; e4++) {
+            float4_t v;
 #pragma unroll
-            for (int e4 = 0; e4 < 4; e4++) {
-                float4_t v;
+            for (int e = 0; e < 4; e++) {
+                v[e] = acc[4 * e4 + e];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    v[e] = acc[nb][4 * e4 + e];
-#pragma unroll
-                    for (int wv = 0; wv < NW - 1; wv++) v[e] += s_part[wv][nb][4 * e4 + e][lane];
-                }
-                const int orow = LUT_TX * I + 8 * e4 + 4 * s;
-                if (scale) {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) v[e] *= (float)scale[orow + e];
-                }
-                *reinterpret_cast<float4_t *>(Y + (size_t)b * m + orow) = v;
+                for (int wv = 0; wv < NW - 1; wv++) v[e] += s_part[wv][4 * e4 + e][lane];
             }
+            const int orow = LUT_TX * I + 8 * e4 + 4 * s;
+            if (scale) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] *= (float)scale[orow + e];
+            }
+            *reinterpret_cast<float4_t *>(Y + (size_t)b * m + orow) = v;
         }
     }
 }
@@ -391,7 +370,7 @@ static hipError_t lut_matmat_t(const uint32_t *codes, const uint16_t *tab, int m
                                const void *scale, float *Y, hipStream_t st) {
     const int tm = m / LUT_TX, tn = n / LUT_TY;
     // a workgroup owns 32 outputs, so there are few workgroups: many waves each
-    hipLaunchKernelGGL((lut_matmat_kernel<K, 1, 16>), dim3(tm, (B + 31) / 32), dim3(1024), 0, st, codes, tab, tn, m,
+    hipLaunchKernelGGL((lut_matmat_kernel<K, 16>), dim3(tm, (B + 31) / 32), dim3(1024), 0, st, codes, tab, tn, m,
                        (const half_t *)X, B, (const half_t *)scale, Y);
     return hipGetLastError();
 }
