@@ -130,10 +130,11 @@ int qtip_decode_matvec(const uint32_t *codes, int L, int k, int V, int code_id,
  * X_f16: device, B x n row-major fp16.  Y: device, B x m row-major fp32,
  * overwritten.  row_scale_f16: device, m fp16, or NULL for no scale.  B >= 1.
  * B = 1 runs the batch-1 kernel on the vector ALUs (for QTIP_CODE_1MAD with the unrounded
- * quotient, as qtip_decode_matvec); every B >= 2 runs on the matrix cores
- * (MFMA) with the decoded 16x16 tile as one operand (Section 4: T_x = T_y = 16 matches a
+ * quotient, as qtip_decode_matvec); every B >= 2 runs on the matrix cores (MFMA): up to 16
+ * rows with the decoded 16x16 tile as one operand (Section 4: T_x = T_y = 16 matches a
  * 16x16 matrix-multiply tile; with QTIP_CODE_LUT two neighbouring 32 x 8 blocks are the
- * 32 x 16 operand of the 32x32x16 instruction).  Y must be 16-byte aligned (and m a multiple
+ * 32 x 16 operand of the 32x32x16 instruction), more rows with 32 outputs x 16 inputs, decoded
+ * once for 32 to 256 batch rows, as the operand of that instruction.  Y must be 16-byte aligned (and m a multiple
  * of 16, as everywhere): outputs are stored four at a time.
  */
 int qtip_decode_matmat(const uint32_t *codes, int L, int k, int V, int code_id,
@@ -145,13 +146,13 @@ int qtip_decode_matmat(const uint32_t *codes, int L, int k, int V, int code_id,
  * i.e. qtip_rht(side 0, batch 1) followed by the batch-1 product, with the same
  * arithmetic and therefore the same y bit for bit.  For n <= 8192 and m <= 4096 it is ONE
  * kernel launch: every workgroup transforms x itself, in LDS, before it starts on its tile
- * row (about 2 us of redundant work per workgroup against a kernel launch plus the gap
- * before a dependent kernel, which is what bounds layers of this size: 4096 x 4096 goes
- * from 14.9 to 8.9 us per call).  Larger layers have several workgroups per CU and would
- * redo the transform too often: there the call enqueues the two kernels and needs
- * xt_scratch (device, n fp16, 16-byte aligned; may be NULL otherwise) for the transformed
- * vector (QTIP_CODE_LUT always takes this two-kernel form: its workgroups fill their LDS
- * with the table).  Together with qtip_rht_f32(side 1) on y a small layer is two launches.
+ * row, beside its first code words (in a stream of calls 1024 x 1024 takes 3.5 us against
+ * 5.8 for the two kernels, 4096 x 4096 5.6 against 7.3, 4096 x 8192 9.05 against 9.6).
+ * Larger layers have several workgroups per CU and would redo the transform too often: there
+ * the call enqueues the two kernels and needs xt_scratch (device, n fp16, 16-byte aligned;
+ * may be NULL otherwise) for the transformed vector (QTIP_CODE_LUT always takes this
+ * two-kernel form: its workgroups fill their LDS with the table).  Together with
+ * qtip_rht_f32(side 1) on y a small layer is two launches.
  *   x_f16: device, n fp16, untransformed.  signs_n: device, n int8 in {+1,-1}.
  *   block: Hadamard block (as qtip_rht).  row_scale_f16: device m fp16 or NULL.
  */
@@ -214,8 +215,8 @@ int qtip_quantize(const float *W, int m, int n, int L, int k, int V, int code_id
  * GPU quantizer: the same problem as qtip_quantize -- every 16x16 tile of W
  * quantized as one sequence by the Viterbi algorithm on the bitshift trellis
  * (Section 2.3), made tail-biting by Algorithm 4, under squared error against the
- * code's values (Algorithms 1-3) -- run on the device, one workgroup per tile with
- * the 2^16-entry value function held in registers.  (QTIP_CODE_LUT: every 32 x 8 block,
+ * code's values (Algorithms 1-3) -- run on the device, one workgroup per tile: the code's
+ * 2^16 values in registers, the minima that pass from step to step in LDS.  (QTIP_CODE_LUT: every 32 x 8 block,
  * 2^14 states; read 32 x 8 for 16 x 16 below.)
  *   W:          device, m x n row-major fp32.
  *   lut_f16:    device table of the code (NULL for the computed codes).

@@ -41,9 +41,12 @@ namespace {
 // factors the panel's own rows again, which costs no time (the inversions are a serial chain and leave the
 // matrix cores idle) and saves a launch per panel.  ldl_update_panel_kernel: the panel's products with the next
 // panel's block columns.  Those with everything further right are taken beside the next panel, in its launch.
-// What bounds it is that chain: 16 pivots per block column, about 1 us, and a launch with its gap twice per panel.
-// n = 2048, g = 16: 1744 us with two launches per block column, the inversion with five barriers per pivot and the
-// products on the vector units, 394 us now.
+// What bounds it is the chain of block columns: a panel kernel takes 18 to 22 us, 2.2 to 2.8 us per block column, of which the
+// gather and the 16 pivots are 1.2 us (a second inversion beside the first costs that) and the barrier and two dependent
+// products the rest; and the launch between two panels, 4.8 us.  n = 2048, g = 16: 1744 us with two launches
+// per block column, the inversion with five barriers per pivot and the products on the vector units, 388 us now: 16 panels
+// 313, 15 updates 72.  g = 8: 475 us; its pivot wave holds three arrays of 16, of which 144 bytes a lane lie in private memory
+// (24 accesses per block column).
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 constexpr int LDL_PANEL = 8, LDL_MAX_ROWS = 4;
