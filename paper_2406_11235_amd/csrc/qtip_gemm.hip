@@ -37,7 +37,8 @@ __device__ __forceinline__ int first_bit(int i, int h) {
 }
 
 // Sum of a 3INST word's halves into the low or the high half of a packed pair.  A register half-written by one
-// of these may not be read by the very next instruction; the callers keep other instructions in between.
+// of these may not be read by the very next instruction: the compiler puts a wait there, around such text too (unlike a read
+// across lanes), which the callers make unnecessary with other instructions in between.
 __device__ __forceinline__ void add_halves_low(uint32_t y, uint32_t &p) {
     asm("v_add_f16_sdwa %0, %1, %1 dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1" : "=v"(p) : "v"(y));
 }
