@@ -177,9 +177,10 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
     // four waves with a SIMD's registers each (115 -> 149 us; up to 128 batch rows it costs 1 to 4 %).
     // With eight slices of the inputs a chain is a 128th of the inputs long, no longer than it was in the kernels that
     // had 17 to 64 rows before (1.6e-7 at 4096 inputs, 2.8e-7 at 14464; totals would halve that and cost HYB 3 to 5 %).
-    // Only the lookup-only code had 16 slices there, up to 32 rows (1.3e-7 and 2.1e-7), so its sums go to totals here too:
-    // 1.2e-7 and 1.3e-7; 24 rows, 4096 x 4096 12.6 -> 12.7 us, 2048 x 14464 35.7 -> 36.0, 8192 x 8192 22.6 -> 23.1.
-    constexpr int CHAIN = WK == 8 && !(LUT && NBB == 1) ? 0 : 16 / KS;
+    // Only the lookup-only code had more, 16 slices up to 32 rows (1.3e-7 and 2.1e-7) and four with totals up to 64, so its
+    // sums go to totals here too: 1.2e-7 and 1.3e-7; 24 rows, 4096 x 4096 12.6 -> 12.7 us, 2048 x 14464 35.7 -> 36.0, 8192 x
+    // 8192 22.6 -> 23.1.
+    constexpr int CHAIN = WK == 8 && !LUT ? 0 : 16 / KS;
     constexpr int AHEAD = 3, GROUPS = KS * NBB * RB;  // a group: one matrix instruction and what goes with it
     constexpr int STEP_BYTES = Lds::STEP_BYTES, CODE_ROW = Lds::CODE_ROW, CODE_ROWS = Lds::CODE_ROWS;
     constexpr int CODE_COPIES = Lds::CODE_COPIES, CODE_STAGE = Lds::CODE_STAGE;
@@ -356,11 +357,15 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
                 });
             });
         });
-        // The copies of this stage have landed, everywhere.
+        // The copies of this stage have landed, everywhere.  Where waves own different inputs (WM = 1) each reads only what
+        // it copied, and waits for nothing else: in step they all decoded and all used the matrix cores at the same time
+        // (8192 x 8192, 4-bit HYB, 64 rows 24.8 -> 21.0 us, 32 rows 17.8 -> 16.9).
         __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        if constexpr (WM > 1) {
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
     };
     if constexpr (CHAIN == 0) {
         for (int s = 0; s < mine; s++) stage(s, std::false_type{});
@@ -375,7 +380,8 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
         if constexpr (CHAIN == 0) return acc;
         else return total;
     }();
-    for (int s = mine; s < stages; s++) __builtin_amdgcn_s_barrier();  // (a slice with less or nothing to do)
+    if constexpr (WM > 1)
+        for (int s = mine; s < stages; s++) __builtin_amdgcn_s_barrier();  // (a slice with less or nothing to do)
     __syncthreads();
 
     // D element e of a lane: batch row 8 (e / 4) + 4 h + e % 4, output i
@@ -444,16 +450,19 @@ static constexpr GemmSplit GEMM_SPLITS[] = {{128, 256, 0.f, 74.f}, {128, 128, 0.
 // 32-bit byte offsets from uniform bases, kept within 2^31.
 static bool offsets_fit(const GemmSplit &s, int n) { return (long)s.rows * 2 * n <= 1L << 31; }
 
-// Kernels of the splits, in their order.
-#define QTIP_GEMM_SPLITS(GO) \
-    GO(0, 1, 8, 4, 1) GO(1, 1, 4, 4, 2) GO(2, 1, 4, 2, 4) GO(3, 1, 2, 2, 4) GO(4, 1, 2, 1, 8) GO(5, 1, 1, 1, 8)
+// Kernels of the splits, in their order.  A stage is four tiles, 128 bytes of every batch row, which is what the memory
+// pipeline likes (two tiles, 8192 x 8192, 4-bit HYB, 64 rows: 21 -> 27 us); two where four leave no room for the lookup-only
+// code's table, at 32 x 64 (8192 x 8192, 48 rows, against 64 x 64, which leaves half of the CUs idle: 44 -> 26 us).
+#define QTIP_GEMM_SPLITS(GO)                                             \
+    GO(0, 1, 8, 4, 1, 4) GO(1, 1, 4, 4, 2, 4) GO(2, 1, 4, 2, 4, 4)       \
+    GO(3, 1, 2, 2, 4, 4) GO(4, 1, 2, 1, 8, (CODE == CODE_LUT ? 2 : 4)) GO(5, 1, 1, 1, 8, 4)
 
 template <int K, int CODE>
 static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int m, int n, const void *X, int B,
                                 const void *scale, float *Y, hipStream_t st) {
     int best = -1;
     float least = 0.f;
-#define QTIP_GEMM_FITS(I, RB, NBB, WM, WK) GemmLds<K, CODE, RB, NBB, WM, WK, 4>::BYTES <= 160 * 1024,
+#define QTIP_GEMM_FITS(I, RB, NBB, WM, WK, KS) GemmLds<K, CODE, RB, NBB, WM, WK, KS>::BYTES <= 160 * 1024,
     constexpr bool fits[] = {QTIP_GEMM_SPLITS(QTIP_GEMM_FITS)};
     for (int i = 0; i < 6; i++) {
         const GemmSplit &s = GEMM_SPLITS[i];
@@ -464,11 +473,11 @@ static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int 
     }
     const dim3 grid((m + GEMM_SPLITS[best].outputs - 1) / GEMM_SPLITS[best].outputs,
                     (B + GEMM_SPLITS[best].rows - 1) / GEMM_SPLITS[best].rows);
-#define QTIP_GEMM_GO(I, RB, NBB, WM, WK)                                                                        \
+#define QTIP_GEMM_GO(I, RB, NBB, WM, WK, KS)                                                                        \
     if constexpr (fits[I])                                                                                      \
         if (best == I) {                                                                                        \
             static_assert(32 * RB * WM == GEMM_SPLITS[I].outputs && 32 * NBB == GEMM_SPLITS[I].rows, "order"); \
-            hipLaunchKernelGGL((gemm_kernel<K, CODE, RB, NBB, WM, WK, 4>), grid, dim3(WM * WK * 64), 0, st, codes, \
+            hipLaunchKernelGGL((gemm_kernel<K, CODE, RB, NBB, WM, WK, KS>), grid, dim3(WM * WK * 64), 0, st, codes, \
                                lut, m, n, (const half_t *)X, B, (const half_t *)scale, Y);                      \
         }
     QTIP_GEMM_SPLITS(QTIP_GEMM_GO)

@@ -120,6 +120,27 @@ def test_slices_of_the_lookup_only_code_are_not_one_chain_of_sums(q, k, m, n):
         assert (Y.double() - ref).norm() <= 1.4e-7 * ref.norm(), B
 
 
+@pytest.mark.parametrize("k", [2, 3, 4])
+@pytest.mark.parametrize("m,n,B", [(4128, 8, 33), (8192, 24, 64), (4160, 264, 50), (4096, 4104, 47)])
+def test_stages_of_two_tiles(q, k, m, n, B):
+    """33 to 64 batch rows of the lookup-only code in tiles of 32 x 64, whose stages are two tiles: half a tile, one and a
+    half, one more half than whole stages; the long rows' sums within the bound of the test above."""
+    import torch
+    check(q, CODE_LUT, k, m, n, B, scaled=k == 3, seed=n)
+    if n < 4096:
+        return
+    g = torch.Generator(device="cuda").manual_seed(n)
+    codes = torch.randint(-2**31, 2**31, (m * n // 256, 8 * k), dtype=torch.int32, device="cuda", generator=g)
+    lut = torch.randn(1 << 14, device="cuda", generator=g).half()
+    X = torch.randn(B, n, device="cuda", generator=g).half()
+    Y = torch.empty(B, m, device="cuda")
+    W = torch.empty(m, n, dtype=torch.float16, device="cuda")
+    q.qtip_decode_matmat(codes, 14, k, 1, CODE_LUT, lut, m, n, X, B, None, Y)
+    q.qtip_dequantize(codes, 14, k, 1, CODE_LUT, lut, m, n, W)
+    ref = X.double() @ W.double().T.contiguous()
+    assert (Y.double() - ref).norm() <= 1.4e-7 * ref.norm()
+
+
 def check_sparse(q, code, m, n, rows):
     """All but about 1200 inputs, the first, the last and some everywhere, are zeros, so that a single wrong tile shows: a
     wave's running sum changes in at most 400 of its additions, each of which is off by at most a unit of the sum, 2^-23."""
