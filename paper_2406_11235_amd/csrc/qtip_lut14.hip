@@ -115,11 +115,16 @@ __global__ void lut_decode_states_kernel(const uint32_t *__restrict__ states, in
 // given to S workgroups where a whole one each would leave CUs idle (see pick_lut_split).
 // k = 2: 4128 x 14464, 129 block rows, 28.2 us at S = 1, 25.3 at S = 4; 4096 x 4096 10.4 at S = 1, 7.1 at S = 2;
 // k = 3: 2048 x 8192 15.8 at S = 1, 6.8 at S = 4.
-template <int K, int S, int NW>
+// Where that leaves a last round nearly empty, the block rows of whole rounds (tm of them) are split so, and the rows of the
+// others, the tail, go round the same workgroups one by one: all waves of a workgroup on a row, a lane eight weights of
+// a block, so that the CUs' shares differ by one row.  4128 x 14464, 256 workgroups and 32 rows over, 25.5 -> 19.5 us (4096 x
+// 14464: 18.0); 8224 x 4096 15.1 -> 12.1; 4128 x 28672 41.1 -> 30.5.
+constexpr int LUT_MAX_TAIL = 8;  // tail rows of a workgroup
+template <int K, int S, int NW, bool TAIL>
 __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint32_t *__restrict__ codes,
                                                                      const uint16_t *__restrict__ lut, int tm, int tn,
                                                                      const half_t *__restrict__ x,
-                                                                     const half_t *__restrict__ scale,
+                                                                     const half_t *__restrict__ scale, int tail_rows,
                                                                      float *__restrict__ y) {
     constexpr int WPL = Geo<K>::WPL, NWORDS = 8 * K;
     constexpr int WL = WPL * 32 / K, RL = WL / LUT_TY;  // weights and block rows per lane
@@ -128,6 +133,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint3
     static_assert(LPT >= 1, "whole lanes");
     __shared__ __attribute__((aligned(16))) uint16_t s_tab[LUT_STATES];
     __shared__ float s_part[NW][ROWS];
+    __shared__ float s_tail[TAIL ? NW : 1][LUT_MAX_TAIL];
     // Workgroups go round the eight XCDs; those of one block row, which read the same cache lines, stay on one.
     const int local = blockIdx.x >> 3;
     const int I = local / S * 8 + (blockIdx.x & 7), part = local % S;
@@ -174,7 +180,57 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint3
                 }
         }
     };
+    // The tail: rows 32 tm + blockIdx.x + e gridDim.x, e < mine, in steps of 64 NW blocks, the first two steps' loads under
+    // way during the last of the block row.
+    const int mine = TAIL && tail_rows > (int)blockIdx.x ? (tail_rows - 1 - blockIdx.x) / gridDim.x + 1 : 0;
+    const int tail_steps = (tn + NW * 64 - 1) / (NW * 64);
+    struct TailOperands {
+        uint32_t w[2];
+        uint4 xv;
+    };
+    auto tail_block = [&](int step) { return (step % tail_steps * NW + wave) * 64 + lane; };
+    auto tail_bit = [&](int step) { return 8 * K * (int)((blockIdx.x + step / tail_steps * gridDim.x) % LUT_TX); };
+    auto issue_tail = [&](TailOperands &o, int step) {
+        const uint32_t Jc = min(tail_block(step), tn - 1);
+        const uint32_t *const row =
+            codes + (size_t)(tm + (blockIdx.x + step / tail_steps * gridDim.x) / LUT_TX) * tn * NWORDS;
+        // (one load of four-byte alignment: every lane is on a line of its own, which is what these loads cost)
+        const int v = tail_bit(step) >> 5;
+        if (v + 1 < NWORDS) {
+            __builtin_memcpy(o.w, row + Jc * NWORDS + v, 8);
+        } else {
+            o.w[0] = row[Jc * NWORDS + v];
+            o.w[1] = row[Jc * NWORDS];
+        }
+        o.xv = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(x) + (size_t)(Jc * 16u));
+    };
+    float tail_acc = 0.f;
+    auto compute_tail = [&](const TailOperands &o, int step) {
+        if (tail_block(step) < tn) {
+            // (the eight states are within 64 bits of the first word, whatever bit they start at)
+            const uint64_t b = ((uint64_t)o.w[0] << 32 | o.w[1]) << (tail_bit(step) & 31);
+            const uint32_t w[2] = {(uint32_t)(b >> 32), (uint32_t)b};
+            const uint32_t xv[4] = {o.xv.x, o.xv.y, o.xv.z, o.xv.w};
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const half2_t p = {table_at(s_tab, table_offset(w, 2 * c * K)), table_at(s_tab, table_offset(w, (2 * c + 1) * K))};
+                tail_acc = __builtin_amdgcn_fdot2(p, as_half2(xv[c]), tail_acc, false);
+            }
+        }
+        if ((step + 1) % tail_steps == 0) {
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) tail_acc += __shfl_xor(tail_acc, off, 64);
+            if (lane == 0) s_tail[wave][step / tail_steps] = tail_acc;
+            tail_acc = 0.f;
+        }
+    };
+    const int tail_end = mine * tail_steps;
     Operands opA, opB;
+    TailOperands tailA, tailB;
+    auto begin_tail = [&] {
+        if (tail_end > 0) issue_tail(tailA, 0);
+        if (tail_end > 1) issue_tail(tailB, 1);
+    };
     if (J0 < Jend) issue(opA, J0);  // (ahead of the table, so that they are under way while it is filled)
     stage_table(lut, s_tab, NW * 64);
     __syncthreads();
@@ -183,8 +239,18 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint3
         compute(opA, Jb);
         if (Jb + TPI < Jend) {
             if (Jb + 2 * TPI < Jend) issue(opA, Jb + 2 * TPI);
+            if (TAIL && Jb + 2 * TPI >= Jend) begin_tail();
             compute(opB, Jb + TPI);
+        } else if (TAIL) {
+            begin_tail();
         }
+    }
+    if (TAIL && J0 >= Jend) begin_tail();
+    for (int step = 0; step < tail_end; step += 2) {
+        compute_tail(tailA, step);
+        if (step + 2 < tail_end) issue_tail(tailA, step + 2);
+        if (step + 1 < tail_end) compute_tail(tailB, step + 1);
+        if (step + 3 < tail_end) issue_tail(tailB, step + 3);
     }
     // lanes with equal q hold partial sums of the same rows: add over g
 #pragma unroll
@@ -201,6 +267,14 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint3
 #pragma unroll
         for (int wv = 0; wv < NW; wv++) s += s_part[wv][threadIdx.x];
         const int row = LUT_TX * I + ROWS * part + threadIdx.x;
+        if (scale) s *= (float)scale[row];
+        y[row] = s;
+    }
+    if (TAIL && wave == NW - 1 && lane < mine) {
+        float s = 0.f;
+#pragma unroll
+        for (int wv = 0; wv < NW; wv++) s += s_tail[TAIL ? wv : 0][lane];
+        const int row = LUT_TX * tm + blockIdx.x + lane * gridDim.x;
         if (scale) s *= (float)scale[row];
         y[row] = s;
     }
@@ -325,14 +399,26 @@ hipError_t launch_lut_decode_states(const uint32_t *states, int count, const voi
     return hipGetLastError();
 }
 
-// Workgroups per block row for the batch-1 kernel.  A CU's share of workgroups, each 1 us for its copy of the table and
-// 32 n / S reads of the table, 8 cycles per 64: the smallest, over the shares that S = 1, 2 and 4 make.
-static int pick_lut_split(int tm, int n) {
-    int best = 1;
+// Workgroups per block row for the batch-1 kernel, and the block rows that are split so; the rows of the others are the
+// tail.  A CU's share of workgroups, each 1 us for its copy of the table and 32 n / S reads of the table, 8 cycles per 64, and
+// of tail rows, each half a microsecond (a line of memory per lane, a sum over all waves) and its reads (measured: 0.7 us at
+// 4096 inputs, 1.4 at 14464, 2.0 at 28672): the smallest, over what S = 1, 2 and 4 make with a last round that is not full,
+// and without it.
+struct LutSplit {
+    int s, tm;
+};
+static LutSplit pick_lut_split(int tm, int n) {
+    LutSplit best{1, tm};
     float least = 0.f;
     for (int s = 1; s <= 4; s *= 2) {
-        const float t = (float)((tm * s + 255) / 256) * (1.f + (float)n / s * (4.f / 2400.f));
-        if (s == 1 || t < least) best = s, least = t;
+        const float block_row = (float)n * (4.f / 2400.f);  // us
+        const int rounds = (tm * s + 255) / 256, full = tm * s / 256;
+        const float t = (float)rounds * (1.f + block_row / s);
+        if (s == 1 || t < least) best = {s, tm}, least = t;
+        if (full == 0 || full == rounds) continue;
+        const int each = ((tm - full * (256 / s)) * LUT_TX + 256 * full - 1) / (256 * full);
+        const float folded = (float)full * (1.f + block_row / s + each * (0.5f + 1.05f * block_row / LUT_TX));
+        if (each <= LUT_MAX_TAIL && folded < least) best = {s, full * (256 / s)}, least = folded;
     }
     return best;
 }
@@ -340,20 +426,32 @@ static int pick_lut_split(int tm, int n) {
 template <int K>
 static hipError_t lut_matvec_t(const uint32_t *codes, const uint16_t *tab, int m, int n, const void *x,
                                const void *scale, float *y, hipStream_t st) {
-    const int tm = m / LUT_TX, tn = n / LUT_TY, s = pick_lut_split(tm, n);
+    const int tn = n / LUT_TY;
+    const auto [s, tm] = pick_lut_split(m / LUT_TX, n);
+    const int tail_rows = m - LUT_TX * tm;  // (with a tail every workgroup of the grid has a part of a block row)
     const dim3 grid((tm + 7) / 8 * 8 * s);
-#define QTIP_LUT_MV(S, NW)                                                                              \
-    hipLaunchKernelGGL((lut_matvec_kernel<K, S, NW>), grid, dim3(NW * 64), 0, st, codes, tab, tm, tn, \
-                       (const half_t *)x, (const half_t *)scale, y)
+#define QTIP_LUT_MV2(S, NW, TAIL)                                                                             \
+    hipLaunchKernelGGL((lut_matvec_kernel<K, S, NW, TAIL>), grid, dim3(NW * 64), 0, st, codes, tab, tm, tn, \
+                       (const half_t *)x, (const half_t *)scale, tail_rows, y)
+#define QTIP_LUT_MV(S, NW)                     \
+    if (tail_rows > 0) QTIP_LUT_MV2(S, NW, true); \
+    else QTIP_LUT_MV2(S, NW, false)
     // (every workgroup first copies the table, so few large ones; a wave needs a few steps to itself)
     constexpr int TPI = Geo<K>::LPT == 4 ? 16 : 8;
     const bool wide = tn >= 32 * TPI * s;
-    if (s == 1 && wide) QTIP_LUT_MV(1, 16);
-    else if (s == 1) QTIP_LUT_MV(1, 8);
-    else if (s == 2 && wide) QTIP_LUT_MV(2, 16);
-    else if (s == 2) QTIP_LUT_MV(2, 8);
-    else QTIP_LUT_MV(4, 8);
+    if (s == 1 && wide) {
+        QTIP_LUT_MV(1, 16);
+    } else if (s == 1) {
+        QTIP_LUT_MV(1, 8);
+    } else if (s == 2 && wide) {
+        QTIP_LUT_MV(2, 16);
+    } else if (s == 2) {
+        QTIP_LUT_MV(2, 8);
+    } else {
+        QTIP_LUT_MV(4, 8);
+    }
 #undef QTIP_LUT_MV
+#undef QTIP_LUT_MV2
     return hipGetLastError();
 }
 

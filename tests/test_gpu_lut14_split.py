@@ -10,8 +10,10 @@ from qtip_synth import CODE_LUT
 pytestmark = pytest.mark.gpu
 
 
+# (the last five: rows over whole rounds of workgroups, one or several for each, with one and with several steps of a row)
 @pytest.mark.parametrize("k", [2, 3, 4])
-@pytest.mark.parametrize("m,n", [(32, 8), (32, 1032), (288, 136), (4096, 520), (4128, 264), (8224, 72), (8192, 4104)])
+@pytest.mark.parametrize("m,n", [(32, 8), (32, 1032), (288, 136), (4096, 520), (4128, 264), (8224, 72), (8192, 4104),
+                                 (8224, 8), (8704, 40), (2080, 14464), (4160, 20480), (8288, 8200)])
 def test_every_split(k, m, n):
     import torch
     import paper_2406_11235_amd as q
