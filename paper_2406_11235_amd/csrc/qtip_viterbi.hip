@@ -35,7 +35,8 @@
 // arguments kept; ties go to the lowest predecessor.  The same operations in the same order
 // give the same bits as the forward kernel, so the walk is the one its minima imply.
 // Where there are few sequences four waves share a tree, one p_1 (or a quarter of them) each, and
-// compare their roots: BlockLDLQ of 2048 x 1024, 128 sequences at a time, 48.4 -> 46.0 ms.
+// compare their roots: BlockLDLQ of 2048 x 1024, 128 sequences at a time, 48.4 -> 46.0 ms; and with at most one
+// sequence per CU one kernel does all of Algorithm 4 (viterbi_few_kernel).
 // The copies go through the caches as they come: written and read with the non-temporal hint the same
 // case takes 46.4 ms, and thousands of sequences the same.
 // Algorithm 4 is forward / walk to the middle / constrained forward / full walk.
@@ -163,6 +164,39 @@ __device__ __forceinline__ float sequence_element(const float *__restrict__ W, i
     return W[(size_t)(TX * I + (s >> LTY)) * n + TY * J + (s & (TY - 1))];
 }
 
+// A thread's minima of one step from `best` of its states (in LDS), for prefixes whose predecessors it owns (kV <= 4).
+template <int KV, int V, int LB>
+__device__ __forceinline__ void thread_minima(const float *__restrict__ in, const uint32_t (&cr)[VT_REGS], float s0, float s1,
+                                              int tid, float (&best)[VitGeo<KV, V, LB>::NB]) {
+    using Geo = VitGeo<KV, V, LB>;
+    constexpr int NC = Geo::NC, NB = Geo::NB, BSTEP = Geo::OV - KV;
+    if constexpr (KV == 2) {
+        float4_t b[NC];
+#pragma unroll
+        for (int p = 0; p < NC; p++) b[p] = *reinterpret_cast<const float4_t *>(in + Geo::place((p << BSTEP) + 4 * tid));
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+            float v[NC];
+#pragma unroll
+            for (int p = 0; p < NC; p++) v[p] = state_value<V>(cr[i * NC + p], s0, s1, b[p][i >> 2]);
+            best[i] = min3(min2(v[0], v[1]), v[2], v[3]);
+        }
+    } else {
+        float b[NC];
+#pragma unroll
+        for (int p = 0; p < NC; p++) b[p] = in[Geo::place((p << BSTEP) + (NB * tid >> KV))];
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+            float m = state_value<V>(cr[i * NC], s0, s1, b[0]);
+#pragma unroll
+            for (int p = 1; p + 1 < NC; p += 2)
+                m = min3(m, state_value<V>(cr[i * NC + p], s0, s1, b[p]),
+                         state_value<V>(cr[i * NC + p + 1], s0, s1, b[p + 1]));
+            best[i] = min2(m, state_value<V>(cr[i * NC + NC - 1], s0, s1, b[NC - 1]));
+        }
+    }
+}
+
 // Steps 0 .. t_end - 1 of sequence tile0 + blockIdx.x, with `best` stored after every J steps
 // counted from the last (copies c_lo .. c_hi - 1, copy c at step G - 1 - J (c + 1)), and, when
 // t_end = G - 1, the best final state.  overlap != null: the first state's top L-kV bits and the
@@ -207,8 +241,6 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
     }
     __syncthreads();
 
-    // best entry that register r's state hangs on: (p << (OV-KV)) | (hi >> KV)
-    constexpr int BSTEP = OV - KV;
     float *store_base = store + (size_t)slot * slots * NP;
     int until = (G - 1) % J;  // steps to the next one that is a multiple of J from the last
     if (until == 0) until = J;
@@ -219,31 +251,8 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
         // (the next step's samples are read ahead of the barrier)
         const float n0 = s_seq[V * (t + 1)], n1 = V == 2 ? s_seq[V * (t + 1) + 1] : 0.f;
         float best[NB];
-        if constexpr (KV == 2) {
-            float4_t b[NC];
-#pragma unroll
-            for (int p = 0; p < NC; p++)
-                b[p] = *reinterpret_cast<const float4_t *>(in + Geo::place((p << BSTEP) + 4 * tid));
-#pragma unroll
-            for (int i = 0; i < NB; i++) {
-                float v[NC];
-#pragma unroll
-                for (int p = 0; p < NC; p++) v[p] = state_value<V>(cr[i * NC + p], s0, s1, b[p][i >> 2]);
-                best[i] = min3(min2(v[0], v[1]), v[2], v[3]);
-            }
-        } else if constexpr (KV <= 4) {
-            float b[NC];
-#pragma unroll
-            for (int p = 0; p < NC; p++) b[p] = in[Geo::place((p << BSTEP) + (my_hi >> KV))];
-#pragma unroll
-            for (int i = 0; i < NB; i++) {
-                float m = state_value<V>(cr[i * NC], s0, s1, b[0]);
-#pragma unroll
-                for (int p = 1; p + 1 < NC; p += 2)
-                    m = min3(m, state_value<V>(cr[i * NC + p], s0, s1, b[p]),
-                             state_value<V>(cr[i * NC + p + 1], s0, s1, b[p + 1]));
-                best[i] = min2(m, state_value<V>(cr[i * NC + NC - 1], s0, s1, b[NC - 1]));
-            }
+        if constexpr (KV <= 4) {
+            thread_minima<KV, V, code_state_bits(CODE)>(in, cr, s0, s1, tid, best);
         } else {
             // the 64 entries are one row of 68 floats, the same for the whole wave (kV = 6) or for
             // sixteen lanes (kV = 8)
@@ -273,9 +282,13 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
             until = J;
             if (c_now >= c_lo && c_now < c_hi && (Geo::WHOLE || lane < 16)) {
                 float *dst = store_base + (size_t)(c_now - c_lo) * NP;
+                // (where a thread's prefixes differ in the low bits alone, its places are a uniform distance apart: one
+                // address and scalar additions)
 #pragma unroll
-                for (int i = 0; i < NB; i++)
-                    dst[Geo::stored((uint32_t)(my_hi + i))] = best[i];
+                for (int i = 0; i < NB; i++) {
+                    if constexpr (NB <= 1 << Geo::LOWB) (dst + (i << (KV * J)))[Geo::stored((uint32_t)my_hi)] = best[i];
+                    else dst[Geo::stored((uint32_t)(my_hi + i))] = best[i];
+                }
             }
             c_now--;
         }
@@ -322,13 +335,21 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
 
 // ------------------------------------------------------------------- walk back
 
-// x from the lane whose index differs in bit BIT alone.
+// x from the lane whose index differs in bit BIT alone, without LDS.
 template <int BIT>
 __device__ __forceinline__ uint32_t other_lane(uint32_t x) {
     if constexpr (BIT == 0) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);        // quad_perm [1, 0, 3, 2]
     else if constexpr (BIT == 1) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+    else if constexpr (BIT == 2)  // lane ^ 7 (row_half_mirror), then ^ 3 (quad_perm [3, 2, 1, 0])
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
     else if constexpr (BIT == 3) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);  // row_ror:8
-    else return __shfl_xor(x, 1 << BIT, 64);
+    else if constexpr (BIT == 4) {  // rows 0 and 2 of the second result are rows 1 and 3 of x, and the other way round
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return threadIdx.x & 16 ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return threadIdx.x & 32 ? r[0] : r[1];
+    }
 }
 
 // What the waves of a sequence tell each other at the root of a tree: value and leaf of the best walk
@@ -540,6 +561,359 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
     if (tile_err && lane == 0) tile_err[tile0 + slot] = final_value[slot];
 }
 
+// --------------------------------------------------- few sequences: all of Algorithm 4 in one workgroup
+
+// With at most a few sequences per CU both the walks, serial chains of trees, and the parts of forward passes that are
+// repeated where the workspace has no room for every copy are a large part of the time.  Here a workgroup keeps its code
+// values in registers through both passes, and all of it walks back: a copy of `best` (each thread reads back what it stored,
+// and has the next one under way while a segment is walked) is taken F steps forward by the same code as in the forward
+// pass, and the last T steps of a segment are a tree of 4096 leaves, T levels: a thread per node of level T - 1, then one
+// wave.  F is what the number of copies asks for: `nseg` segments of T + F steps, lengths differing by one at most.
+// The last forward step of a segment is only taken for the prefixes that the tree hangs on, a few of each thread.
+//   What bounds it is still the issue of the forward steps: 255 of 2043 cycles in each pass (kV = 2, V = 1); the walks, 16 and 33
+// segments, are 132 and 306 thousand cycles, of 9100 each at that size (copy put back 1093, a forward step 1850, the last one
+// 960, level T 944 and its wait 1431, levels across lanes 1349, digits of the forward steps 1084).  128 sequences of 2-bit 3INST
+// with half of a walk's copies: 737 us -> 671; 3-bit, 1.6 forward passes before, 1023 -> 693; BlockLDLQ of 2048 x 1024 46.1 ms ->
+// 41.9, of 3-bit 1024 x 256 16.0 -> 10.8.
+template <int KV, int V> struct FewGeo : VitGeo<KV, V, 16> {
+    static constexpr int T = KV == 2 ? 6 : KV == 3 ? 4 : 3;    // levels of a tree
+    static constexpr int NODES = 1 << (KV * (T - 1));          // of level T - 1
+    static constexpr int FIXED = 4 - KV;                       // low bits that the prefixes of a tree's leaves share
+    static constexpr int ARRAYS = KV == 3 ? 4 : 2;             // room for `best` of consecutive steps
+    static constexpr int LONGEST = T + ARRAYS;                 // segment
+    static constexpr int D1 = VitGeo<KV, V, 16>::G - 1 - VitGeo<KV, V, 16>::MID, D2 = VitGeo<KV, V, 16>::G - 1;  // steps walked
+    static_assert(16 - KV * T == 4 && NODES <= 1024, "4096 leaves");
+    static_assert(D1 > LONGEST, "two segments at least, so one copy");
+    static constexpr bool fits(int d, int nseg) { return nseg > 0 && (d + nseg - 1) / nseg <= LONGEST; }
+};
+
+template <int KV, int V, int CODE>
+__global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__restrict__ W, int n, int tn,
+                                                              const uint32_t *__restrict__ lut, float *__restrict__ store,
+                                                              long slots, int nseg1, int nseg2, uint32_t *__restrict__ codes,
+                                                              float *__restrict__ tile_err) {
+    using Geo = FewGeo<KV, V>;
+    constexpr int NP = Geo::NP, NC = Geo::NC, NB = Geo::NB, OV = Geo::OV, G = Geo::G, T = Geo::T, NODES = Geo::NODES;
+    constexpr int NWORDS = KV * G / 32, LB = 16;
+    static_assert(Geo::NT == 1024 && Geo::BEST_FLOATS == NP && NB % 4 == 0, "kV = 2 to 4");
+    __shared__ __attribute__((aligned(16))) float s_best[Geo::ARRAYS][NP];
+    __shared__ __attribute__((aligned(16))) float s_leaf[4096];  // `best` under a tree's leaves
+    __shared__ __attribute__((aligned(16))) uint2 s_node[NODES];
+    __shared__ uint2 s_four[KV == 2 ? 256 : 1];  // nodes of level 4
+    __shared__ float s_seq[VT_T];
+    __shared__ uint32_t s_sym[VT_T / 4];  // one byte per step
+    __shared__ float s_rv[16];
+    __shared__ uint32_t s_ry[16], s_state;
+    int tid = threadIdx.x, my_hi = NB * tid;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), slot = blockIdx.x;
+    const float INF = __builtin_inff();
+    uint8_t *const sym = reinterpret_cast<uint8_t *>(s_sym);
+    // (a thread's minima are stored four at a time, threads side by side)
+    float4_t *const my_store = reinterpret_cast<float4_t *>(store + (size_t)slot * slots * NP);
+
+    if (tid < VT_T) s_seq[tid] = sequence_element<CODE>(W, n, tn, slot, tid, 0);
+    if (tid < VT_T / 4) s_sym[tid] = 0;
+    uint32_t cr[VT_REGS];
+#pragma unroll
+    for (int r = 0; r < VT_REGS; r++) {
+        cr[r] = code_register<CODE>(((uint32_t)(r % NC) << OV) | (uint32_t)(my_hi + r / NC), lut);
+        asm volatile("" : "+v"(cr[r]));  // (as in the forward kernel)
+    }
+
+    uint32_t O = 0;
+    for (int pass = 1; pass <= 2; pass++) {
+        const bool constrained = pass == 2;
+        const int rotate = pass == 1 ? VT_T / 2 : 0;
+        const int nseg = pass == 1 ? nseg1 : nseg2, D = pass == 1 ? Geo::D1 : Geo::D2;
+        const int base = D / nseg, longer = D % nseg, copies = pass == 1 ? nseg : nseg - 1;
+        auto sample = [&](int t, int e) { return s_seq[(V * t + e + rotate) & (VT_T - 1)]; };
+        // the step that copy c, under segment c from the end, belongs to
+        auto step_of = [&](int c) { return G - 1 - (c + 1) * base - min(c + 1, longer); };
+        auto put = [&](float *to, const float *best) {
+#pragma unroll
+            for (int i = 0; i < NB; i += 4)
+                *reinterpret_cast<float4_t *>(to + Geo::place(my_hi + i)) =
+                    float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
+        };
+        auto put_first = [&](float *to) {  // step 0
+            float best[NB];
+#pragma unroll
+            for (int i = 0; i < NB; i++) best[i] = constrained && (uint32_t)(my_hi + i) != O ? INF : 0.f;
+            put(to, best);
+        };
+        put_first(s_best[0]);
+        __syncthreads();
+        int c_now = copies - 1, t_next = step_of(c_now);
+        float s0 = sample(0, 0), s1 = V == 2 ? sample(0, 1) : 0.f;
+        auto step = [&](const float *in, float *out, int t) {
+            // (the next step's samples are read ahead of the barrier)
+            const float n0 = sample(t + 1, 0), n1 = V == 2 ? sample(t + 1, 1) : 0.f;
+            float best[NB];
+            thread_minima<KV, V, LB>(in, cr, s0, s1, tid, best);
+            s0 = n0;
+            s1 = n1;
+            put(out, best);
+            if (t + 1 == t_next) {
+                float4_t *const to = my_store + (size_t)c_now * (NP / 4);
+#pragma unroll
+                for (int i = 0; i < NB; i += 4) to[(uint32_t)(256 * i + tid)] = float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
+                c_now--;
+                t_next = c_now >= 0 ? step_of(c_now) : -1;
+            }
+            __syncthreads();
+        };
+        for (int t = 0; t + 1 < G - 1; t += 2) {
+            step(s_best[0], s_best[1], t);
+            step(s_best[1], s_best[0], t + 1);
+        }
+        static_assert((G - 1) % 2 == 1, "one step over");
+        step(s_best[0], s_best[1], G - 2);
+
+        // the best allowed final state, lowest state on ties
+        float bv = INF;
+        uint32_t by = 0xFFFFFFFFu;
+        auto take_better = [&](bool ok, float v, uint32_t y) {
+            const bool take = ok & ((v < bv) | ((v == bv) & (y < by)));
+            bv = take ? v : bv;
+            by = take ? y : by;
+        };
+#pragma unroll
+        for (int r = 0; r < VT_REGS; r++) {
+            const uint32_t y = ((uint32_t)(r % NC) << OV) | (uint32_t)(my_hi + r / NC);
+            take_better(!constrained | ((y & (uint32_t)(NP - 1)) == O),
+                        state_value<V>(cr[r], s0, s1, s_best[1][Geo::place((int)(y >> KV))]), y);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) take_better(true, __shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
+        if (lane == 0) s_rv[wave] = bv, s_ry[wave] = by;
+        // (the segment's copy; the rest is under way)
+        float pre[NB];
+        auto fetch = [&](int c) {  // (whether there is one or not: else the last one would have to be kept meanwhile)
+            const float4_t *const from = my_store + (size_t)min(c, copies - 1) * (NP / 4);
+#pragma unroll
+            for (int i = 0; i < NB; i += 4) {
+                const float4_t four = from[(uint32_t)(256 * i + tid)];
+#pragma unroll
+                for (int e = 0; e < 4; e++) pre[i + e] = four[e];
+            }
+        };
+        fetch(0);
+        __syncthreads();
+        bv = INF;
+        by = 0xFFFFFFFFu;
+        for (int w = 0; w < 16; w++) take_better(true, s_rv[w], s_ry[w]);
+        uint32_t y = __builtin_amdgcn_readfirstlane(by) & 0xFFFFu;
+        if (pass == 2 && tid == 0) {
+            sym[G - 1] = (uint8_t)(y >> OV);
+            if (tile_err) tile_err[slot] = bv;
+        }
+
+        int t = G - 1;
+        for (int c = 0; c < nseg; c++) {
+            const int length = base + (c < longer), forward = length - T, u = t - length;
+            // (nothing that depends on these is worth a register across segments: it would be one of the spilled ones)
+            asm volatile("" : "+v"(tid), "+v"(my_hi));
+            const int lane = tid & 63;
+            if (c < copies) put(s_best[0], pre);
+            else put_first(s_best[0]);
+            __syncthreads();
+            for (int k = 0; k + 1 < forward; k++) {
+                float best[NB];
+                thread_minima<KV, V, LB>(s_best[k], cr, sample(u + k, 0), V == 2 ? sample(u + k, 1) : 0.f, tid, best);
+                put(s_best[k + 1], best);
+                __syncthreads();
+            }
+            const uint32_t under = (y >> (KV * T)) & 15u;  // low bits of the leaves
+            const int fixed = __builtin_amdgcn_readfirstlane(under >> KV);
+            if (forward > 0) {
+                const float *const in = s_best[forward - 1];
+                const float s0 = sample(u + forward - 1, 0), s1 = V == 2 ? sample(u + forward - 1, 1) : 0.f;
+                // prefix my_hi + (a << FIXED) + fixed is leaf 4 tid + a's
+                auto some = [&](auto fc) {
+                    constexpr int f = decltype(fc)::value;
+                    float b[NC][KV == 2 ? 4 : 1];
+#pragma unroll
+                    for (int p = 0; p < NC; p++) {
+                        if constexpr (KV == 2) {
+                            const float4_t four = *reinterpret_cast<const float4_t *>(in + Geo::place((p << (OV - KV)) + 4 * tid));
+#pragma unroll
+                            for (int a = 0; a < 4; a++) b[p][a] = four[a];
+                        } else {
+                            b[p][0] = in[Geo::place((p << (OV - KV)) + (my_hi >> KV))];
+                        }
+                    }
+                    float4_t best;
+#pragma unroll
+                    for (int a = 0; a < 4; a++) {
+                        const int i = (a << Geo::FIXED) + f;
+                        float m = min2(state_value<V>(cr[i * NC], s0, s1, b[0][KV == 2 ? a : 0]),
+                                       state_value<V>(cr[i * NC + 1], s0, s1, b[1][KV == 2 ? a : 0]));
+#pragma unroll
+                        for (int p = 2; p < NC; p += 2)
+                            m = min3(m, state_value<V>(cr[i * NC + p], s0, s1, b[p][KV == 2 ? a : 0]),
+                                     state_value<V>(cr[i * NC + p + 1], s0, s1, b[p + 1][KV == 2 ? a : 0]));
+                        best[a] = m;
+                    }
+                    *reinterpret_cast<float4_t *>(s_leaf + 4 * tid) = best;
+                };
+                if constexpr (Geo::FIXED == 0) {
+                    some(std::integral_constant<int, 0>{});
+                } else if constexpr (Geo::FIXED == 1) {
+                    if (fixed == 0) some(std::integral_constant<int, 0>{});
+                    else some(std::integral_constant<int, 1>{});
+                } else {
+                    if (fixed == 0) some(std::integral_constant<int, 0>{});
+                    else if (fixed == 1) some(std::integral_constant<int, 1>{});
+                    else if (fixed == 2) some(std::integral_constant<int, 2>{});
+                    else some(std::integral_constant<int, 3>{});
+                }
+                __syncthreads();
+            }
+
+            // Leaf l = (p_T ... p_1), digit p_j being the top kV bits of the state j steps back; node (p_j ... p_1) of level j is
+            // state (node << (16 - kV j)) | (y >> kV j).  A node carries its value and the digits of its best walk.
+            auto node_state = [&](int j, uint32_t node) { return ((node << (LB - KV * j)) | (y >> (KV * j))) & 0xFFFFu; };
+            // A node's code and samples, read and formed before what its value waits for.
+            struct Node {
+                uint32_t code;
+                float s0, s1;
+                __device__ __forceinline__ float value(float b) const { return state_value<V>(code, s0, s1, b); }
+            };
+            auto uniform = [](float v) {
+                return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+            };
+            auto node_of = [&](uint32_t state, int step) {
+                return Node{code_register<CODE>(state, lut), uniform(sample(step, 0)), V == 2 ? uniform(sample(step, 1)) : 0.f};
+            };
+            // the minimum over the top digit of the nodes above `node`, and their walks with that digit behind
+            auto best_below = [&](const uint2 *nodes, int count, uint32_t node, float &v, uint32_t &walk) {
+                uint2 e[NC];
+#pragma unroll
+                for (int p = 0; p < NC; p++) e[p] = nodes[(uint32_t)(p * count) + node];
+#pragma unroll
+                for (int p = 0; p < NC; p++) {
+                    const float ev = __builtin_bit_cast(float, e[p].x);
+                    const bool lt = p == 0 || ev < v;
+                    v = lt ? ev : v;
+                    walk = lt ? (e[p].y << KV) | (uint32_t)p : walk;
+                }
+            };
+            if (tid < NODES) {
+                Node leaf[NC];
+                float b[NC];
+#pragma unroll
+                for (int p = 0; p < NC; p++) {
+                    const uint32_t l = (uint32_t)(p * NODES + tid);
+                    b[p] = forward > 0 ? s_leaf[l] : s_best[0][Geo::place((int)(l << Geo::FIXED) | fixed)];
+                    leaf[p] = node_of(node_state(T, l), t - T);
+                }
+                const Node own = node_of(node_state(T - 1, (uint32_t)tid), t - T + 1);
+                float m = INF;
+                uint32_t digit = 0;
+#pragma unroll
+                for (int p = 0; p < NC; p++) {
+                    const float v = leaf[p].value(b[p]);
+                    const bool lt = p == 0 || v < m;
+                    m = lt ? v : m;
+                    digit = lt ? (uint32_t)p : digit;
+                }
+                s_node[tid] = uint2{__builtin_bit_cast(uint32_t, own.value(m)), digit};
+            }
+            // (here, where few registers are in use: ahead of the steps above these would be spilled as they arrive)
+            fetch(c + 1);
+            // levels whose nodes are the lanes of wave 0
+            constexpr int ROOTS = KV == 2 ? 3 : KV == 3 ? 2 : 1;
+            const uint32_t me = (uint32_t)lane & ((1u << (KV * ROOTS)) - 1u);
+            Node four{};
+            if constexpr (KV == 2) {
+                if (wave < 4) four = node_of(node_state(4, (uint32_t)tid), t - 4);
+            }
+            __syncthreads();
+            if constexpr (KV == 2) {  // level 4: 256 nodes
+                if (wave < 4) {
+                    float m = INF;
+                    uint32_t walk = 0;
+                    best_below(s_node, 256, (uint32_t)tid, m, walk);
+                    s_four[tid] = uint2{__builtin_bit_cast(uint32_t, four.value(m)), walk};
+                }
+                __syncthreads();
+            }
+            if (wave == 0) {
+                Node root[ROOTS + 1];
+#pragma unroll
+                for (int j = 1; j <= ROOTS; j++) root[j] = node_of(node_state(j, me & ((1u << (KV * j)) - 1u)), t - j);
+                float m = INF;
+                uint32_t walk = 0;
+                best_below(KV == 2 ? s_four : s_node, 1 << (KV * ROOTS), me, m, walk);
+                // levels ROOTS to 1 across lanes: the lane's bits kV (j - 1) .. are digit j
+                auto across = [&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    const uint32_t digit = (me >> (KV * (j - 1))) & (uint32_t)(NC - 1);
+                    m = root[j].value(m);
+                    walk = (walk << KV) | digit;
+                    auto meet = [&](auto bit) {
+                        constexpr int BIT = decltype(bit)::value;
+                        if constexpr (BIT < KV) {
+                            const float ov = __builtin_bit_cast(float, other_lane<KV * (j - 1) + BIT>(__builtin_bit_cast(uint32_t, m)));
+                            const uint32_t ow = other_lane<KV * (j - 1) + BIT>(walk);
+                            const bool take = ov < m || (ov == m && (ow & (uint32_t)(NC - 1)) < (walk & (uint32_t)(NC - 1)));
+                            m = take ? ov : m;
+                            walk = take ? ow : walk;
+                        }
+                    };
+                    meet(std::integral_constant<int, 0>{});
+                    meet(std::integral_constant<int, 1>{});
+                    meet(std::integral_constant<int, 2>{});
+                    meet(std::integral_constant<int, 3>{});
+                };
+                if constexpr (ROOTS >= 3) across(std::integral_constant<int, 3>{});
+                if constexpr (ROOTS >= 2) across(std::integral_constant<int, 2>{});
+                across(std::integral_constant<int, 1>{});
+                walk = __builtin_amdgcn_readfirstlane(walk);
+                if (lane < T) sym[t - 1 - lane] = (uint8_t)((walk >> (KV * lane)) & (uint32_t)(NC - 1));
+                uint32_t z = (walk << 4) | under;
+                // and the steps that were taken forward
+                for (int k = forward - 1; k >= 0; k--) {
+                    const uint32_t p = (uint32_t)lane & (uint32_t)(NC - 1), state = (p << OV) | (z >> KV);
+                    float v = node_of(state, u + k).value(s_best[k][Geo::place((int)(state >> KV))]);
+                    uint32_t digit = p;
+                    auto meet = [&](auto bit) {
+                        constexpr int BIT = decltype(bit)::value;
+                        if constexpr (BIT < KV) {
+                            const float ov = __builtin_bit_cast(float, other_lane<BIT>(__builtin_bit_cast(uint32_t, v)));
+                            const uint32_t od = other_lane<BIT>(digit);
+                            const bool take = ov < v || (ov == v && od < digit);
+                            v = take ? ov : v;
+                            digit = take ? od : digit;
+                        }
+                    };
+                    meet(std::integral_constant<int, 0>{});
+                    meet(std::integral_constant<int, 1>{});
+                    meet(std::integral_constant<int, 2>{});
+                    meet(std::integral_constant<int, 3>{});
+                    digit = __builtin_amdgcn_readfirstlane(digit);
+                    if (lane == 0) sym[u + k] = (uint8_t)digit;
+                    z = (digit << OV) | (z >> KV);
+                }
+                if (lane == 0) s_state = z;
+            }
+            __syncthreads();
+            y = __builtin_amdgcn_readfirstlane(s_state);
+            t = u;
+        }
+        O = y & (uint32_t)(NP - 1);  // (after the first pass: of step MID)
+    }
+    if (tid < NWORDS) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int b = 0; b < 32; b++) {
+            const int pos = 32 * tid + b;
+            word = (word << 1) | ((sym[pos / KV] >> (KV - 1 - pos % KV)) & 1u);
+        }
+        codes[(size_t)slot * NWORDS + tid] = word;
+    }
+}
+
 // ------------------------------------------------------------------- launchers
 
 // Words of a sequence in flight besides its copies of `best`: final state, overlap, final value.
@@ -607,6 +981,26 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
     constexpr int TY = 1 << code_log2_ty(CODE), TX = VT_T / TY;
     const int tn = n / TY;
     const long ntiles = (long)(m / TX) * tn;
+    // One launch for at most one sequence per CU; two at kV = 3, where walks and forward pass repeat the most steps.  (us, with
+    // the workspace callers are told to bring, 128 | 256 | 512 sequences, several launches and one: 3INST k = 2 749 682 | 819
+    // 754 | 1340 1467, k = 3 982 660 | 1072 728 | 2041 1415, k = 4 765 624 | 819 675 | 1386 1358, HYB k = 2 949 853 | 965 871 |
+    // 1539 1660.  With room for every copy k = 2 takes 655 651 | 727 791 and HYB 769 786, so there the launches stay apart.)
+    if constexpr (KV <= 4 && code_state_bits(CODE) == 16) {
+        using Few = FewGeo<KV, V>;
+        if (ntiles <= (KV == 3 ? 512 : 256)) {
+            const size_t copy_bytes = (size_t)ntiles * Geo::NP * sizeof(float);
+            const size_t room = ws_bytes > head_bytes(ntiles) ? (ws_bytes - head_bytes(ntiles)) / copy_bytes : 0;
+            const long slots = (long)(room < (size_t)VT_T ? room : (size_t)VT_T);
+            constexpr bool ALWAYS = V == 1 && KV > 2;
+            const int nseg1 = (int)(slots < Few::D1 / Few::T ? slots : Few::D1 / Few::T);
+            const int nseg2 = (int)(slots + 1 < Few::D2 / Few::T ? slots + 1 : Few::D2 / Few::T);
+            if ((ALWAYS || slots < Geo::NSEG - 1) && Few::fits(Few::D1, nseg1) && Few::fits(Few::D2, nseg2)) {
+                hipLaunchKernelGGL((viterbi_few_kernel<KV, V, CODE>), dim3((unsigned)ntiles), dim3(1024), 0, st, W, ld, tn,
+                                   lut, (float *)((char *)ws + head_bytes(ntiles)), slots, nseg1, nseg2, codes, tile_err);
+                return hipGetLastError();
+            }
+        }
+    }
     const size_t sized_for = quantize_gpu_workspace(KV / V, V, 1) - head_bytes(1);
     const Plan plan = make_plan<Geo>(ntiles, ws_bytes, sized_for);
     const long cap = plan.tiles;
