@@ -164,35 +164,44 @@ __device__ __forceinline__ float sequence_element(const float *__restrict__ W, i
     return W[(size_t)(TX * I + (s >> LTY)) * n + TY * J + (s & (TY - 1))];
 }
 
-// A thread's minima of one step from `best` of its states (in LDS), for prefixes whose predecessors it owns (kV <= 4).
+// For prefixes whose predecessors a thread owns (kV <= 4): the entries of `best` (in LDS) that its states hang on, and the minima
+// of a step from them.  Prefix i's predecessor p hangs on entry `under(i, p)`.
+template <int KV> struct Hang {
+    static constexpr int COUNT = KV == 2 ? 16 : 1 << KV;
+    __host__ __device__ static constexpr int under(int i, int p) { return KV == 2 ? 4 * p + (i >> 2) : p; }
+};
 template <int KV, int V, int LB>
-__device__ __forceinline__ void thread_minima(const float *__restrict__ in, const uint32_t (&cr)[VT_REGS], float s0, float s1,
-                                              int tid, float (&best)[VitGeo<KV, V, LB>::NB]) {
+__device__ __forceinline__ void thread_reads(const float *__restrict__ in, int tid, float (&b)[Hang<KV>::COUNT]) {
     using Geo = VitGeo<KV, V, LB>;
-    constexpr int NC = Geo::NC, NB = Geo::NB, BSTEP = Geo::OV - KV;
-    if constexpr (KV == 2) {
-        float4_t b[NC];
+    constexpr int BSTEP = Geo::OV - KV;
 #pragma unroll
-        for (int p = 0; p < NC; p++) b[p] = *reinterpret_cast<const float4_t *>(in + Geo::place((p << BSTEP) + 4 * tid));
+    for (int p = 0; p < Geo::NC; p++) {
+        if constexpr (KV == 2) {
+            const float4_t four = *reinterpret_cast<const float4_t *>(in + Geo::place((p << BSTEP) + 4 * tid));
 #pragma unroll
-        for (int i = 0; i < NB; i++) {
+            for (int a = 0; a < 4; a++) b[4 * p + a] = four[a];
+        } else {
+            b[p] = in[Geo::place((p << BSTEP) + (Geo::NB * tid >> KV))];
+        }
+    }
+}
+template <int KV, int V, int LB>
+__device__ __forceinline__ void thread_minima(const float (&b)[Hang<KV>::COUNT], const uint32_t (&cr)[VT_REGS], float s0,
+                                              float s1, float (&best)[VitGeo<KV, V, LB>::NB]) {
+    constexpr int NC = VitGeo<KV, V, LB>::NC;
+#pragma unroll
+    for (int i = 0; i < VitGeo<KV, V, LB>::NB; i++) {
+        auto value = [&](int p) { return state_value<V>(cr[i * NC + p], s0, s1, b[Hang<KV>::under(i, p)]); };
+        if constexpr (KV == 2) {
             float v[NC];
 #pragma unroll
-            for (int p = 0; p < NC; p++) v[p] = state_value<V>(cr[i * NC + p], s0, s1, b[p][i >> 2]);
+            for (int p = 0; p < NC; p++) v[p] = value(p);
             best[i] = min3(min2(v[0], v[1]), v[2], v[3]);
-        }
-    } else {
-        float b[NC];
+        } else {
+            float m = value(0);
 #pragma unroll
-        for (int p = 0; p < NC; p++) b[p] = in[Geo::place((p << BSTEP) + (NB * tid >> KV))];
-#pragma unroll
-        for (int i = 0; i < NB; i++) {
-            float m = state_value<V>(cr[i * NC], s0, s1, b[0]);
-#pragma unroll
-            for (int p = 1; p + 1 < NC; p += 2)
-                m = min3(m, state_value<V>(cr[i * NC + p], s0, s1, b[p]),
-                         state_value<V>(cr[i * NC + p + 1], s0, s1, b[p + 1]));
-            best[i] = min2(m, state_value<V>(cr[i * NC + NC - 1], s0, s1, b[NC - 1]));
+            for (int p = 1; p + 1 < NC; p += 2) m = min3(m, value(p), value(p + 1));
+            best[i] = min2(m, value(NC - 1));
         }
     }
 }
@@ -252,7 +261,9 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
         const float n0 = s_seq[V * (t + 1)], n1 = V == 2 ? s_seq[V * (t + 1) + 1] : 0.f;
         float best[NB];
         if constexpr (KV <= 4) {
-            thread_minima<KV, V, code_state_bits(CODE)>(in, cr, s0, s1, tid, best);
+            float b[Hang<KV>::COUNT];
+            thread_reads<KV, V, code_state_bits(CODE)>(in, tid, b);
+            thread_minima<KV, V, code_state_bits(CODE)>(b, cr, s0, s1, best);
         } else {
             // the 64 entries are one row of 68 floats, the same for the whole wave (kV = 6) or for
             // sixteen lanes (kV = 8)
@@ -565,16 +576,16 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
 
 // With at most a few sequences per CU both the walks, serial chains of trees, and the parts of forward passes that are
 // repeated where the workspace has no room for every copy are a large part of the time.  Here a workgroup keeps its code
-// values in registers through both passes, and all of it walks back: a copy of `best` (each thread reads back what it stored,
-// and has the next one under way while a segment is walked) is taken F steps forward by the same code as in the forward
-// pass, and the last T steps of a segment are a tree of 4096 leaves, T levels: a thread per node of level T - 1, then one
-// wave.  F is what the number of copies asks for: `nseg` segments of T + F steps, lengths differing by one at most.
-// The last forward step of a segment is only taken for the prefixes that the tree hangs on, a few of each thread.
-//   What bounds it is still the issue of the forward steps: 255 of 2043 cycles in each pass (kV = 2, V = 1); the walks, 16 and 33
-// segments, are 132 and 306 thousand cycles, of 9100 each at that size (copy put back 1093, a forward step 1850, the last one
-// 960, level T 944 and its wait 1431, levels across lanes 1349, digits of the forward steps 1084).  128 sequences of 2-bit 3INST
-// with half of a walk's copies: 737 us -> 671; 3-bit, 1.6 forward passes before, 1023 -> 693; BlockLDLQ of 2048 x 1024 46.1 ms ->
-// 41.9, of 3-bit 1024 x 256 16.0 -> 10.8.
+// values in registers through both passes, and all of it walks back: each thread has its part of the next copy of `best` under
+// way while a segment is walked; a copy is taken F steps forward by the same code as in the forward pass, and the last T steps
+// of a segment are a tree of 4096 leaves, T levels: a thread per node of level T, then one wave.  F is what the number of
+// copies asks for: `nseg` segments of T + F steps, lengths differing by one at most.
+// The last forward step of a segment is only taken for the prefixes that the tree hangs on, a few of each thread; with F = 0
+// level T takes entries and codes from the registers they arrive in.
+//   What bounds it is still the issue of the forward steps: 255 of 2043 cycles in each pass (kV = 2, V = 1), 453 of 635 us.  (us,
+// several launches | here, 128 sequences, the workspace callers are told to bring: 3INST k = 2 732 | 635, k = 3 993 | 641, k = 4
+// 777 | 635, HYB 928 | 800; BlockLDLQ of 2048 x 256 11.44 ms | 10.01, of 3-bit 1024 x 256 15.94 | 10.34.  With every copy through
+// LDS and all of a tree's codes formed anew: 3INST 671, 693, 648, HYB 821.)
 template <int KV, int V> struct FewGeo : VitGeo<KV, V, 16> {
     static constexpr int T = KV == 2 ? 6 : KV == 3 ? 4 : 3;    // levels of a tree
     static constexpr int NODES = 1 << (KV * (T - 1));          // of level T - 1
@@ -587,6 +598,14 @@ template <int KV, int V> struct FewGeo : VitGeo<KV, V, 16> {
     static constexpr bool fits(int d, int nseg) { return nseg > 0 && (d + nseg - 1) / nseg <= LONGEST; }
 };
 
+// f(integral_constant) of the one of 0 .. COUNT - 1 that the wave-uniform `which` is.
+template <int COUNT, int FIRST = 0, class F>
+__device__ __forceinline__ void one_of(uint32_t which, F f) {
+    if constexpr (COUNT == 1) f(std::integral_constant<int, FIRST>{});
+    else if (which & (uint32_t)(COUNT / 2)) one_of<COUNT / 2, FIRST + COUNT / 2>(which, f);
+    else one_of<COUNT / 2, FIRST>(which, f);
+}
+
 template <int KV, int V, int CODE>
 __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__restrict__ W, int n, int tn,
                                                               const uint32_t *__restrict__ lut, float *__restrict__ store,
@@ -594,7 +613,8 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                                                               float *__restrict__ tile_err) {
     using Geo = FewGeo<KV, V>;
     constexpr int NP = Geo::NP, NC = Geo::NC, NB = Geo::NB, OV = Geo::OV, G = Geo::G, T = Geo::T, NODES = Geo::NODES;
-    constexpr int NWORDS = KV * G / 32, LB = 16;
+    constexpr int NWORDS = KV * G / 32, LB = 16, COUNT = Hang<KV>::COUNT, AHEAD = KV == 4 ? NB : COUNT;
+    constexpr bool CODES_KEPT = KV < 4 || CODE == CODE_HYB1 || V == 2;  // level T takes its leaves' codes from registers
     static_assert(Geo::NT == 1024 && Geo::BEST_FLOATS == NP && NB % 4 == 0, "kV = 2 to 4");
     __shared__ __attribute__((aligned(16))) float s_best[Geo::ARRAYS][NP];
     __shared__ __attribute__((aligned(16))) float s_leaf[4096];  // `best` under a tree's leaves
@@ -608,8 +628,7 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), slot = blockIdx.x;
     const float INF = __builtin_inff();
     uint8_t *const sym = reinterpret_cast<uint8_t *>(s_sym);
-    // (a thread's minima are stored four at a time, threads side by side)
-    float4_t *const my_store = reinterpret_cast<float4_t *>(store + (size_t)slot * slots * NP);
+    float *const my_store = store + (size_t)slot * slots * NP;
 
     if (tid < VT_T) s_seq[tid] = sequence_element<CODE>(W, n, tn, slot, tid, 0);
     if (tid < VT_T / 4) s_sym[tid] = 0;
@@ -635,30 +654,48 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 *reinterpret_cast<float4_t *>(to + Geo::place(my_hi + i)) =
                     float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
         };
-        auto put_first = [&](float *to) {  // step 0
+        // (entry `hi` of step 0)
+        auto first = [&](int hi) { return constrained && (uint32_t)hi != O ? INF : 0.f; };
+        {
             float best[NB];
 #pragma unroll
-            for (int i = 0; i < NB; i++) best[i] = constrained && (uint32_t)(my_hi + i) != O ? INF : 0.f;
-            put(to, best);
-        };
-        put_first(s_best[0]);
+            for (int i = 0; i < NB; i++) best[i] = first(my_hi + i);
+            put(s_best[0], best);
+        }
         __syncthreads();
         int c_now = copies - 1, t_next = step_of(c_now);
         float s0 = sample(0, 0), s1 = V == 2 ? sample(0, 1) : 0.f;
+        auto next_copy = [&] {
+            c_now--;
+            t_next = c_now >= 0 ? step_of(c_now) : -1;
+        };
         auto step = [&](const float *in, float *out, int t) {
             // (the next step's samples are read ahead of the barrier)
             const float n0 = sample(t + 1, 0), n1 = V == 2 ? sample(t + 1, 1) : 0.f;
-            float best[NB];
-            thread_minima<KV, V, LB>(in, cr, s0, s1, tid, best);
+            float b[COUNT], best[NB];
+            thread_reads<KV, V, LB>(in, tid, b);
+            // A copy of step t_next is stored as it will be read, coalesced both times.
+            if constexpr (KV == 2) {
+                if (t == t_next) {
+                    float4_t *const to = reinterpret_cast<float4_t *>(my_store + (size_t)c_now * NP);
+#pragma unroll
+                    for (int p = 0; p < NC; p++)
+                        (to + 1024 * p)[(uint32_t)tid] = float4_t{b[4 * p], b[4 * p + 1], b[4 * p + 2], b[4 * p + 3]};
+                    next_copy();
+                }
+            }
+            thread_minima<KV, V, LB>(b, cr, s0, s1, best);
             s0 = n0;
             s1 = n1;
             put(out, best);
-            if (t + 1 == t_next) {
-                float4_t *const to = my_store + (size_t)c_now * (NP / 4);
+            if constexpr (KV > 2) {
+                if (t + 1 == t_next) {
+                    float4_t *const to = reinterpret_cast<float4_t *>(my_store + (size_t)c_now * NP);
 #pragma unroll
-                for (int i = 0; i < NB; i += 4) to[(uint32_t)(256 * i + tid)] = float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
-                c_now--;
-                t_next = c_now >= 0 ? step_of(c_now) : -1;
+                    for (int i = 0; i < NB; i += 4)
+                        to[(uint32_t)(NB / 4 * tid + i / 4)] = float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
+                    next_copy();
+                }
             }
             __syncthreads();
         };
@@ -686,15 +723,20 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) take_better(true, __shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
         if (lane == 0) s_rv[wave] = bv, s_ry[wave] = by;
-        // (the segment's copy; the rest is under way)
-        float pre[NB];
+        // (a segment's copy, on the way while the one before is walked)
+        float pre[AHEAD];
         auto fetch = [&](int c) {  // (whether there is one or not: else the last one would have to be kept meanwhile)
-            const float4_t *const from = my_store + (size_t)min(c, copies - 1) * (NP / 4);
+            const float *const from = my_store + (size_t)min(c, copies - 1) * NP;
+            if constexpr (KV == 3) {
 #pragma unroll
-            for (int i = 0; i < NB; i += 4) {
-                const float4_t four = from[(uint32_t)(256 * i + tid)];
+                for (int p = 0; p < NC; p++) pre[p] = (from + (p << (OV - KV)))[(uint32_t)tid];
+            } else {
 #pragma unroll
-                for (int e = 0; e < 4; e++) pre[i + e] = four[e];
+                for (int i = 0; i < AHEAD; i += 4) {
+                    const float4_t four = (reinterpret_cast<const float4_t *>(from) + 256 * i)[(uint32_t)tid];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) pre[i + e] = four[e];
+                }
             }
         };
         fetch(0);
@@ -714,59 +756,63 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             // (nothing that depends on these is worth a register across segments: it would be one of the spilled ones)
             asm volatile("" : "+v"(tid), "+v"(my_hi));
             const int lane = tid & 63;
-            if (c < copies) put(s_best[0], pre);
-            else put_first(s_best[0]);
-            __syncthreads();
-            for (int k = 0; k + 1 < forward; k++) {
-                float best[NB];
-                thread_minima<KV, V, LB>(s_best[k], cr, sample(u + k, 0), V == 2 ? sample(u + k, 1) : 0.f, tid, best);
-                put(s_best[k + 1], best);
+            // The entries of step u that the thread's states hang on.  (At kV = 4 four threads have the same sixteen, as many
+            // loads from memory for a few bytes: there they go through LDS.)
+            float through_lds[KV == 4 ? COUNT : 1];
+            float(&b)[COUNT] = [&]() -> float(&)[COUNT] {
+                if constexpr (KV == 4) return through_lds;
+                else return pre;
+            }();
+            if constexpr (KV == 4) {
+                if (c == copies) {
+#pragma unroll
+                    for (int i = 0; i < NB; i++) pre[i] = first(my_hi + i);
+                }
+                put(s_best[0], pre);
                 __syncthreads();
+            } else if (c == copies) {
+#pragma unroll
+                for (int p = 0; p < NC; p++) {
+#pragma unroll
+                    for (int a = 0; a < COUNT / NC; a++)
+                        pre[COUNT / NC * p + a] = first((p << (OV - KV)) + COUNT / NC * tid + a);
+                }
             }
             const uint32_t under = (y >> (KV * T)) & 15u;  // low bits of the leaves
-            const int fixed = __builtin_amdgcn_readfirstlane(under >> KV);
             if (forward > 0) {
-                const float *const in = s_best[forward - 1];
-                const float s0 = sample(u + forward - 1, 0), s1 = V == 2 ? sample(u + forward - 1, 1) : 0.f;
-                // prefix my_hi + (a << FIXED) + fixed is leaf 4 tid + a's
-                auto some = [&](auto fc) {
-                    constexpr int f = decltype(fc)::value;
-                    float b[NC][KV == 2 ? 4 : 1];
+                if constexpr (KV == 4) {
+                    thread_reads<KV, V, LB>(s_best[0], tid, b);
+                } else {  // (LDS has step u for the way down)
 #pragma unroll
                     for (int p = 0; p < NC; p++) {
-                        if constexpr (KV == 2) {
-                            const float4_t four = *reinterpret_cast<const float4_t *>(in + Geo::place((p << (OV - KV)) + 4 * tid));
-#pragma unroll
-                            for (int a = 0; a < 4; a++) b[p][a] = four[a];
-                        } else {
-                            b[p][0] = in[Geo::place((p << (OV - KV)) + (my_hi >> KV))];
-                        }
+                        if constexpr (KV == 2)
+                            *reinterpret_cast<float4_t *>(s_best[0] + Geo::place((p << (OV - KV)) + 4 * tid)) =
+                                float4_t{b[4 * p], b[4 * p + 1], b[4 * p + 2], b[4 * p + 3]};
+                        else s_best[0][Geo::place((p << (OV - KV)) + tid)] = b[p];
                     }
+                }
+                for (int k = 0; k + 1 < forward; k++) {
+                    float best[NB];
+                    thread_minima<KV, V, LB>(b, cr, sample(u + k, 0), V == 2 ? sample(u + k, 1) : 0.f, best);
+                    put(s_best[k + 1], best);
+                    __syncthreads();
+                    thread_reads<KV, V, LB>(s_best[k + 1], tid, b);
+                }
+                const float s0 = sample(u + forward - 1, 0), s1 = V == 2 ? sample(u + forward - 1, 1) : 0.f;
+                // prefix my_hi + (a << FIXED) + (under >> KV) is leaf 4 tid + a's
+                one_of<1 << Geo::FIXED>(under >> KV, [&](auto fc) {
                     float4_t best;
 #pragma unroll
                     for (int a = 0; a < 4; a++) {
-                        const int i = (a << Geo::FIXED) + f;
-                        float m = min2(state_value<V>(cr[i * NC], s0, s1, b[0][KV == 2 ? a : 0]),
-                                       state_value<V>(cr[i * NC + 1], s0, s1, b[1][KV == 2 ? a : 0]));
+                        const int i = (a << Geo::FIXED) + decltype(fc)::value;
+                        auto value = [&](int p) { return state_value<V>(cr[i * NC + p], s0, s1, b[Hang<KV>::under(i, p)]); };
+                        float m = min2(value(0), value(1));
 #pragma unroll
-                        for (int p = 2; p < NC; p += 2)
-                            m = min3(m, state_value<V>(cr[i * NC + p], s0, s1, b[p][KV == 2 ? a : 0]),
-                                     state_value<V>(cr[i * NC + p + 1], s0, s1, b[p + 1][KV == 2 ? a : 0]));
+                        for (int p = 2; p < NC; p += 2) m = min3(m, value(p), value(p + 1));
                         best[a] = m;
                     }
                     *reinterpret_cast<float4_t *>(s_leaf + 4 * tid) = best;
-                };
-                if constexpr (Geo::FIXED == 0) {
-                    some(std::integral_constant<int, 0>{});
-                } else if constexpr (Geo::FIXED == 1) {
-                    if (fixed == 0) some(std::integral_constant<int, 0>{});
-                    else some(std::integral_constant<int, 1>{});
-                } else {
-                    if (fixed == 0) some(std::integral_constant<int, 0>{});
-                    else if (fixed == 1) some(std::integral_constant<int, 1>{});
-                    else if (fixed == 2) some(std::integral_constant<int, 2>{});
-                    else some(std::integral_constant<int, 3>{});
-                }
+                });
                 __syncthreads();
             }
 
@@ -787,37 +833,66 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             };
             // the minimum over the top digit of the nodes above `node`, and their walks with that digit behind
             auto best_below = [&](const uint2 *nodes, int count, uint32_t node, float &v, uint32_t &walk) {
-                uint2 e[NC];
+                constexpr int AT_A_TIME = NC < 8 ? NC : 8;
 #pragma unroll
-                for (int p = 0; p < NC; p++) e[p] = nodes[(uint32_t)(p * count) + node];
+                for (int p0 = 0; p0 < NC; p0 += AT_A_TIME) {
+                    uint2 e[AT_A_TIME];
 #pragma unroll
-                for (int p = 0; p < NC; p++) {
-                    const float ev = __builtin_bit_cast(float, e[p].x);
-                    const bool lt = p == 0 || ev < v;
-                    v = lt ? ev : v;
-                    walk = lt ? (e[p].y << KV) | (uint32_t)p : walk;
+                    for (int p = 0; p < AT_A_TIME; p++) e[p] = nodes[(uint32_t)((p0 + p) * count) + node];
+#pragma unroll
+                    for (int p = 0; p < AT_A_TIME; p++) {
+                        const float ev = __builtin_bit_cast(float, e[p].x);
+                        const bool lt = p0 + p == 0 || ev < v;
+                        v = lt ? ev : v;
+                        walk = lt ? (e[p].y << KV) | (uint32_t)(p0 + p) : walk;
+                    }
+                    asm volatile("" : "+v"(v), "+v"(walk));
                 }
             };
-            if (tid < NODES) {
-                Node leaf[NC];
-                float b[NC];
-#pragma unroll
-                for (int p = 0; p < NC; p++) {
-                    const uint32_t l = (uint32_t)(p * NODES + tid);
-                    b[p] = forward > 0 ? s_leaf[l] : s_best[0][Geo::place((int)(l << Geo::FIXED) | fixed)];
-                    leaf[p] = node_of(node_state(T, l), t - T);
-                }
-                const Node own = node_of(node_state(T - 1, (uint32_t)tid), t - T + 1);
+            // Level T's node is what the forward step calls a prefix, number `under` (its low bits) of the thread that has its
+            // predecessors' codes, and where the copy is of this very step also their entries, in registers.  At kV = 4 that is
+            // every fourth thread: computed codes are formed anew by 256 side by side, table codes would be as many reads.
+            auto level_t = [&](int node, bool active, const uint32_t (&leaf)[NC], const float (&entry)[NC]) {
+                const Node own = node_of(node_state(T - 1, (uint32_t)node), t - T + 1);
+                const float s0 = sample(t - T, 0), s1 = V == 2 ? sample(t - T, 1) : 0.f;
                 float m = INF;
                 uint32_t digit = 0;
 #pragma unroll
                 for (int p = 0; p < NC; p++) {
-                    const float v = leaf[p].value(b[p]);
+                    const float v = state_value<V>(leaf[p], s0, s1, entry[p]);
                     const bool lt = p == 0 || v < m;
                     m = lt ? v : m;
                     digit = lt ? (uint32_t)p : digit;
                 }
-                s_node[tid] = uint2{__builtin_bit_cast(uint32_t, own.value(m)), digit};
+                if (active) s_node[node] = uint2{__builtin_bit_cast(uint32_t, own.value(m)), digit};
+            };
+            if constexpr (CODES_KEPT) {
+                const int node = tid >> (KV - 2);
+                uint32_t leaf[NC];
+                float entry[NC];
+                one_of<NB>(under & (uint32_t)(NB - 1), [&](auto ic) {
+#pragma unroll
+                    for (int p = 0; p < NC; p++) {
+                        leaf[p] = cr[decltype(ic)::value * NC + p];
+                        entry[p] = KV == 4 ? 0.f : b[Hang<KV>::under(decltype(ic)::value, p)];
+                        // (else the cases become one with an index, and the arrays go to memory)
+                        asm("; %2" : "+v"(leaf[p]), "+v"(entry[p]) : "i"(decltype(ic)::value));
+                    }
+                });
+                if (KV == 4 || forward > 0) {
+#pragma unroll
+                    for (int p = 0; p < NC; p++) entry[p] = (forward > 0 ? s_leaf : s_best[0])[p * NODES + node];
+                }
+                level_t(node, (uint32_t)(tid & ((1 << (KV - 2)) - 1)) == under >> (6 - KV), leaf, entry);
+            } else if (tid < NODES) {
+                uint32_t leaf[NC];
+                float entry[NC];
+#pragma unroll
+                for (int p = 0; p < NC; p++) {
+                    entry[p] = (forward > 0 ? s_leaf : s_best[0])[p * NODES + tid];
+                    leaf[p] = code_register<CODE>(node_state(T, (uint32_t)(p * NODES + tid)), lut);
+                }
+                level_t(tid, true, leaf, entry);
             }
             // (here, where few registers are in use: ahead of the steps above these would be spilled as they arrive)
             fetch(c + 1);
@@ -827,6 +902,11 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             Node four{};
             if constexpr (KV == 2) {
                 if (wave < 4) four = node_of(node_state(4, (uint32_t)tid), t - 4);
+            }
+            Node root[ROOTS + 1];
+            if (wave == 0) {
+#pragma unroll
+                for (int j = 1; j <= ROOTS; j++) root[j] = node_of(node_state(j, me & ((1u << (KV * j)) - 1u)), t - j);
             }
             __syncthreads();
             if constexpr (KV == 2) {  // level 4: 256 nodes
@@ -839,9 +919,6 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 __syncthreads();
             }
             if (wave == 0) {
-                Node root[ROOTS + 1];
-#pragma unroll
-                for (int j = 1; j <= ROOTS; j++) root[j] = node_of(node_state(j, me & ((1u << (KV * j)) - 1u)), t - j);
                 float m = INF;
                 uint32_t walk = 0;
                 best_below(KV == 2 ? s_four : s_node, 1 << (KV * ROOTS), me, m, walk);
@@ -981,20 +1058,22 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
     constexpr int TY = 1 << code_log2_ty(CODE), TX = VT_T / TY;
     const int tn = n / TY;
     const long ntiles = (long)(m / TX) * tn;
-    // One launch for at most one sequence per CU; two at kV = 3, where walks and forward pass repeat the most steps.  (us, with
-    // the workspace callers are told to bring, 128 | 256 | 512 sequences, several launches and one: 3INST k = 2 749 682 | 819
-    // 754 | 1340 1467, k = 3 982 660 | 1072 728 | 2041 1415, k = 4 765 624 | 819 675 | 1386 1358, HYB k = 2 949 853 | 965 871 |
-    // 1539 1660.  With room for every copy k = 2 takes 655 651 | 727 791 and HYB 769 786, so there the launches stay apart.)
+    // One launch for at most one sequence per CU; three at kV = 3, where walks and forward passes repeat the most steps.  (us, with
+    // the workspace callers are told to bring, 128 | 256 | 512 sequences, several launches and one: 3INST k = 2 742 663 | 806
+    // 736 | 1332 1381, k = 3 976 628 | 1075 687 | 2035 1325, k = 4 767 630 | 835 681 | 1382 1333, HYB k = 2 954 822 | 983 842 |
+    // 1553 1594; k = 3 of 768 2062 1967, of 1024 2742 2668.  With room for every copy k = 2 650 619 | 709 768, k = 3 722 553 |
+    // 765 615 | 1430 1229 and of 768 1949 1820, k = 4 659 593 | 709 627 | 1179 1218, HYB 777 756 | 802 773 | 1438 1491: at kV = 2
+    // the launches stay apart there if more than half of the CUs have a sequence, all of them storing every copy.)
     if constexpr (KV <= 4 && code_state_bits(CODE) == 16) {
         using Few = FewGeo<KV, V>;
-        if (ntiles <= (KV == 3 ? 512 : 256)) {
+        if (ntiles <= (KV == 3 ? 768 : 256)) {
             const size_t copy_bytes = (size_t)ntiles * Geo::NP * sizeof(float);
             const size_t room = ws_bytes > head_bytes(ntiles) ? (ws_bytes - head_bytes(ntiles)) / copy_bytes : 0;
             const long slots = (long)(room < (size_t)VT_T ? room : (size_t)VT_T);
-            constexpr bool ALWAYS = V == 1 && KV > 2;
+            const bool pays = KV > 2 || ntiles <= 128 || slots < Geo::NSEG - 1;
             const int nseg1 = (int)(slots < Few::D1 / Few::T ? slots : Few::D1 / Few::T);
             const int nseg2 = (int)(slots + 1 < Few::D2 / Few::T ? slots + 1 : Few::D2 / Few::T);
-            if ((ALWAYS || slots < Geo::NSEG - 1) && Few::fits(Few::D1, nseg1) && Few::fits(Few::D2, nseg2)) {
+            if (pays && Few::fits(Few::D1, nseg1) && Few::fits(Few::D2, nseg2)) {
                 hipLaunchKernelGGL((viterbi_few_kernel<KV, V, CODE>), dim3((unsigned)ntiles), dim3(1024), 0, st, W, ld, tn,
                                    lut, (float *)((char *)ws + head_bytes(ntiles)), slots, nseg1, nseg2, codes, tile_err);
                 return hipGetLastError();

@@ -1,4 +1,4 @@
-"""Up to 256 sequences (512 at k = 3) go through Algorithm 4 in one launch where the workspace asks for it: the same streams
+"""Up to 256 sequences (768 at k = 3) go through Algorithm 4 in one launch where the workspace asks for it: the same streams
 and errors, bit for bit, as from several launches, for every number of copies that the workspace can hold."""
 import pytest
 
@@ -12,7 +12,7 @@ TREE = {2: 6, 3: 4, 4: 3}
 
 @pytest.mark.parametrize("code_id,k", [(CODE_3INST, 2), (CODE_3INST, 3), (CODE_1MAD, 4), (CODE_HYB1, 2), (CODE_HYB, 2),
                                        (CODE_HYB2, 2)])
-@pytest.mark.parametrize("m,n", [(16, 16), (48, 80), (16, 4096), (32, 2064)])
+@pytest.mark.parametrize("m,n", [(16, 16), (48, 80), (16, 4096), (32, 2064), (16, 12288)])
 def test_one_launch_equals_several(code_id, k, m, n):
     import torch
 
@@ -39,7 +39,7 @@ def test_one_launch_equals_several(code_id, k, m, n):
         return codes, err
 
     # several launches: among more sequences than one launch takes
-    many = torch.cat([W, torch.randn(m, 16 * -(-513 // (m // 16)), device="cuda", generator=g)], dim=1)
+    many = torch.cat([W, torch.randn(m, 16 * -(-769 // (m // 16)), device="cuda", generator=g)], dim=1)
     want = [x.view(m // 16, many.shape[1] // 16, -1)[:, :n // 16].reshape(tiles, -1)
             for x in quantize(many, q.qtip_quantize_gpu_workspace(k, V, many.numel() // 256))]
     longest = {2: 8, 3: 8, 4: 5}[kv]
