@@ -171,25 +171,17 @@ constexpr int FUSED_MAX_N = 8192;
 // (The V = 1 hash code keeps a whole tile's table reads in flight and needs more registers; the
 // kernel that transforms its own input runs with at most one workgroup per CU, four waves per
 // SIMD, and may take the registers that leaves it.)
-// S: workgroups per tile row, 16 / S rows each (the launcher splits a tile row where whole ones leave CUs idle).
-template <int K, int V, int CODE, int S, int NW, bool FUSED, bool SPREAD = false, bool WIDE = false>
-__global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void matvec_kernel(const uint32_t *__restrict__ codes,
-                                                         const uint32_t *__restrict__ lut,
-                                                         int tm, int tn, const half_t *__restrict__ x,
-                                                         const int8_t *__restrict__ signs, int log2_block,
-                                                         const half_t *__restrict__ scale,
-                                                         float *__restrict__ y) {
+// S: workgroups per tile row, 16 / S rows each (the launcher splits a tile row where whole ones leave CUs idle): this one
+// does part `part` of tile row I.
+template <int K, int V, int CODE, int S, int NW, bool FUSED, bool SPREAD, bool WIDE, bool ROUNDS = false>
+__device__ __forceinline__ void matvec_tile_row(int I, int Iend, int part, bool staged, const uint32_t *__restrict__ codes,
+                                                const uint32_t *__restrict__ lut, int tn, const half_t *__restrict__ x,
+                                                const int8_t *__restrict__ signs, int log2_block,
+                                                const half_t *__restrict__ scale, float *__restrict__ y,
+                                                uint32_t *s_lut, float (*s_part)[16], half_t *s_x, float *s_v) {
     constexpr int WPL = MvGeo<K, WIDE>::WPL, LPT = MvGeo<K, WIDE>::LPT / S, RPL = MvGeo<K, WIDE>::RPL;
     constexpr int ROWS = 16 / S;
     constexpr int TPI = 64 / LPT;  // tiles per wave per iteration
-    __shared__ __attribute__((aligned(16))) uint32_t s_lut[code_lds_words(CODE, SPREAD)];
-    __shared__ float s_part[NW][ROWS];
-    __shared__ __attribute__((aligned(16))) half_t s_x[FUSED ? FUSED_MAX_N : 8];
-    __shared__ __attribute__((aligned(16))) float s_v[FUSED ? RHT_LDS_FLOATS : 1];
-    // Workgroups go round the eight XCDs; those of one tile row, which read the same cache lines, stay on one.
-    const int I = S == 1 ? blockIdx.x : (blockIdx.x >> 3) / S * 8 + (blockIdx.x & 7);
-    const int part = S == 1 ? 0 : (blockIdx.x >> 3) % S;
-    if (S > 1 && I >= tm) return;
     // the wave's number as a scalar: its tile range and the loop over it then live in scalar
     // registers and the loop control costs no vector instructions
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -198,7 +190,7 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     const int J0 = wave * chunk;
     const int Jend = min(tn, J0 + chunk);
     // this tile row's words: a uniform base, so that a lane's address is base + 32-bit offset
-    const uint32_t *__restrict__ row_codes = codes + (size_t)I * tn * (8 * K);
+    const uint32_t *row_codes = codes + (size_t)I * tn * (8 * K);
     struct Operands {
         WordsN<WPL> w;
         uint32_t next;  // S > 1: the word behind them
@@ -269,7 +261,7 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
         // (ahead of the table, so that they are under way while it is filled)
         if (J0 < Jend) issue(opA, J0);
     }
-    stage_code_table<CODE, SPREAD>(lut, s_lut, NW * 64);
+    if (!staged) stage_code_table<CODE, SPREAD>(lut, s_lut, NW * 64);
     typename RowDotFor<K, CODE, SPREAD>::type rd;
     rd.init(s_lut);
     float acc[RPL];
@@ -295,6 +287,49 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     if constexpr (FUSED) {
         if (J0 < Jend) issue_x(opA, J0);
     }
+    auto finish_row = [&](int buf) {
+        rd.finish(acc);
+        const int rr_mine = reduce_over_tile_groups<LPT, RPL>(acc, lane);
+        float(*const part_sums)[16] = s_part + buf * NW;
+        if ((g & (16 / LPT - 1)) == 0) part_sums[wave][q * RPL + rr_mine] = acc[0];
+        __syncthreads();
+        if (threadIdx.x < ROWS) {
+            float s = 0.f;
+#pragma unroll
+            for (int wv = 0; wv < NW; wv++) s += part_sums[wv][threadIdx.x];
+            const int row = 16 * I + ROWS * part + threadIdx.x;
+            if (scale) s *= (float)scale[row];
+            y[row] = s;
+        }
+    };
+    if constexpr (ROUNDS) {
+        const int J1 = J0 + max(1, (Jend - J0 + TPI - 1) / TPI) * TPI;
+        if (J0 >= Jend) issue(opA, J0);
+        int Jb = J0, buf = 0;
+        // one step: the next one's operands into `other`, decode, and the row's end; false after the last
+        auto step = [&](Operands &o, Operands &other) {
+            int Jn = Jb + TPI, In = I;
+            if (Jn >= J1) {
+                Jn = J0;
+                In = I + (int)gridDim.x;
+                row_codes = codes + (size_t)In * tn * (8 * K);
+            }
+            if (In < Iend) issue(other, Jn);
+            compute(o, Jb);
+            if (Jn == J0) {
+                finish_row(buf);
+                buf ^= 1;
+#pragma unroll
+                for (int rr = 0; rr < RPL; rr++) acc[rr] = 0.f;
+                rd.init(s_lut);
+            }
+            Jb = Jn;
+            I = In;
+            return I < Iend;
+        };
+        while (step(opA, opB) && step(opB, opA)) {}
+        return;
+    }
     for (int Jb = J0; Jb < Jend; Jb += 2 * TPI) {
         if (Jb + TPI < Jend) issue(opB, Jb + TPI);
         compute(opA, Jb);
@@ -303,19 +338,51 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
             compute(opB, Jb + TPI);
         }
     }
-    rd.finish(acc);
-    // lanes with equal q hold partial sums of the same rows: add over g
-    const int rr_mine = reduce_over_tile_groups<LPT, RPL>(acc, lane);
-    if ((g & (16 / LPT - 1)) == 0) s_part[wave][q * RPL + rr_mine] = acc[0];
-    __syncthreads();
-    if (threadIdx.x < ROWS) {
-        float s = 0.f;
-#pragma unroll
-        for (int wv = 0; wv < NW; wv++) s += s_part[wv][threadIdx.x];
-        const int row = 16 * I + ROWS * part + threadIdx.x;
-        if (scale) s *= (float)scale[row];
-        y[row] = s;
+    finish_row(0);
+}
+// TAIL 2 or 4: the tile rows from `whole` on are split into as many parts, by workgroups behind those of the whole ones (ahead
+// of them, or the whole rows in a loop over at most 512 workgroups, is slower: 3INST 14336 x 4096 10.44, 10.85 and 10.52 us,
+// 1MAD 5120 x 8192 8.45, 9.51, 11.5).  ROUNDS, for the V = 1 hash code, of which one workgroup fits a CU, so that nothing is decoded
+// while another one begins and ends: the whole rows in rounds over at most 256 workgroups that keep their table and
+// have the next row's words under way, then the others' parts, if any (k = 4, 14336 x 4096 19.0 -> 15.2 us).
+template <int K, int V, int CODE, int S, int NW, bool FUSED, bool SPREAD = false, bool WIDE = false, int TAIL = 0,
+          bool ROUNDS = false>
+__global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void matvec_kernel(const uint32_t *__restrict__ codes,
+                                                         const uint32_t *__restrict__ lut,
+                                                         int tm, int tn, const half_t *__restrict__ x,
+                                                         const int8_t *__restrict__ signs, int log2_block,
+                                                         const half_t *__restrict__ scale,
+                                                         float *__restrict__ y, int whole) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_lut[code_lds_words(CODE, SPREAD)];
+    __shared__ float s_part[ROUNDS ? 2 * NW : NW][16];
+    __shared__ __attribute__((aligned(16))) half_t s_x[FUSED ? FUSED_MAX_N : 8];
+    __shared__ __attribute__((aligned(16))) float s_v[FUSED ? RHT_LDS_FLOATS : 1];
+    // Workgroups go round the eight XCDs; those of one tile row, which read the same cache lines, stay on one.
+    const int b = blockIdx.x;
+    auto tail_part = [&](int t, bool staged) {
+        const int I = whole + (t >> 3) / TAIL * 8 + (t & 7);
+        if (I >= tm) return;
+        if (staged) __syncthreads();
+        matvec_tile_row<K, V, CODE, TAIL ? TAIL : 1, NW, FUSED, SPREAD, K != 2>(I, I + 1, (t >> 3) % TAIL, staged, codes, lut, tn, x,
+                                                                                signs, log2_block, scale, y, s_lut, s_part, s_x, s_v);
+    };
+    if constexpr (ROUNDS) {
+        if (b >= whole) return;  // (the grid has no more)
+        matvec_tile_row<K, V, CODE, 1, NW, FUSED, SPREAD, WIDE, true>(b, whole, 0, false, codes, lut, tn, x, signs, log2_block, scale,
+                                                                      y, s_lut, s_part, s_x, s_v);
+        if constexpr (TAIL > 0) {
+            for (int t = b; t < (tm - whole + 7) / 8 * 8 * TAIL; t += gridDim.x) tail_part(t, true);
+        }
+        return;
     }
+    if constexpr (TAIL > 0) {
+        if (b >= whole) return tail_part(b - whole, false);
+    }
+    const int I = S == 1 ? b : (b >> 3) / S * 8 + (b & 7);
+    const int part = S == 1 ? 0 : (b >> 3) % S;
+    if (S > 1 && I >= tm) return;
+    matvec_tile_row<K, V, CODE, S, NW, FUSED, SPREAD, WIDE>(I, I + 1, part, false, codes, lut, tn, x, signs, log2_block, scale, y, s_lut,
+                                                            s_part, s_x, s_v);
 }
 
 // ------------------------------------------- decode + batched product on MFMA
@@ -578,13 +645,23 @@ static bool pick_hyb_spread(int code, int n) {
 // 18.1 -> 12.1 us, 2048 x 8192 6.6 -> 4.4, 1024 x 4096 4.1 -> 3.0, with its transform 5.7 -> 4.7.  Matrices of 4096 rows
 // and more gain nothing: a whole tile row per CU fills its issue slots.  The choice depends on the sizes alone, so
 // that the kernel that transforms its own input makes the same one.)
-static int pick_matvec_split(int tm, int tn) {
-    int best = 1;
-    float least = 0.f;
-    for (int s = 1; s <= 4; s *= 2) {
-        if (s > 1 && tn < 2 * 16 * s) break;
-        const float t = (float)((tm * (long)s + 255) / 256) * (0.8f + (float)tn * (0.008f / s));
-        if (s == 1 || t < least) best = s, least = t;
+// With more tile rows than CUs the ones behind the last whole round may be split alone, by the same measure, if the row is
+// long enough for 16 waves (us, all rows whole and so: 1MAD k = 3 14336 x 4096 10.9 10.3, 6144 x 4096 6.06 5.44, 5120 x 8192 10.4
+// 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6).
+struct MatvecSplit {
+    int s, whole, tail;  // rows from `whole` on: `tail` workgroups each
+};
+static MatvecSplit pick_matvec_split(int tm, int tn) {
+    auto time = [&](int rows, int s) { return (float)((rows * (long)s + 255) / 256) * (0.8f + (float)tn * (0.008f / (float)s)); };
+    MatvecSplit best{1, tm, 0};
+    float least = time(tm, 1);
+    for (int s = 2; s <= 4 && tn >= 2 * 16 * s; s *= 2) {
+        if (time(tm, s) < least) best = {s, tm, 0}, least = time(tm, s);
+        const int whole = tm / 256 * 256;
+        if (whole > 0 && whole < tm && tn >= 256) {
+            const float t = time(whole, 1) + time(tm - whole, s);
+            if (t < least) best = {1, whole, s}, least = t;
+        }
     }
     return best;
 }
@@ -598,12 +675,32 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
     const int steps = (tn + TPI - 1) / TPI;
     const int nw = pick_matvec_waves(steps);
     const bool spread = pick_hyb_spread(CODE, n);
-    const int split = pick_matvec_split(tm, tn);
-    const dim3 grid(split == 1 ? tm : (tm + 7) / 8 * 8 * split);
+    const MatvecSplit pick = pick_matvec_split(tm, tn);
+    const int split = pick.s, tails = pick.tail ? (tm - pick.whole + 7) / 8 * 8 * pick.tail : 0;
+    const bool rounds = CODE == CODE_HYB1 && split == 1 && tm > 256 && nw == 16;
+    // (in rounds every workgroup begins with a whole row)
+    const dim3 grid(split > 1 ? (tm + 7) / 8 * 8 * split : rounds ? std::min(256, pick.whole) : pick.whole + tails);
     // signs != null: x is untransformed and the kernel transforms it itself (n <= FUSED_MAX_N)
-#define QTIP_MV_LAUNCH4(S, NW, FUSED, SPREAD, WIDE)                                                           \
-    hipLaunchKernelGGL((matvec_kernel<K, V, CODE, S, NW, FUSED, SPREAD, WIDE>), grid, dim3(NW * 64), 0, st, \
-                       codes, lut, tm, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y)
+#define QTIP_MV_LAUNCH6(S, NW, FUSED, SPREAD, WIDE, TAIL, ROUNDS)                                                           \
+    hipLaunchKernelGGL((matvec_kernel<K, V, CODE, S, NW, FUSED, SPREAD, WIDE, TAIL, ROUNDS>), grid, dim3(NW * 64), 0, st, codes, \
+                       lut, tm, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y, pick.whole)
+#define QTIP_MV_LAUNCH4(S, NW, FUSED, SPREAD, WIDE) QTIP_MV_LAUNCH6(S, NW, FUSED, SPREAD, WIDE, 0, false)
+// (more rows than one per CU: never with the transform)
+#define QTIP_MV_LAUNCH_MANY(TAIL, WIDE)                                    \
+    if (code_is_hyb(CODE) && spread)                                       \
+        QTIP_MV_LAUNCH6(1, 16, false, code_is_hyb(CODE), WIDE, TAIL, false); \
+    else                                                                   \
+        QTIP_MV_LAUNCH6(1, 16, false, false, WIDE, TAIL, CODE == CODE_HYB1)
+#define QTIP_MV_LAUNCH_WHOLE(WIDE)                    \
+    if (pick.tail == 2) {                             \
+        QTIP_MV_LAUNCH_MANY(2, WIDE);                 \
+    } else if (pick.tail == 4) {                      \
+        QTIP_MV_LAUNCH_MANY(4, WIDE);                 \
+    } else if (rounds) {                              \
+        if constexpr (CODE == CODE_HYB1) QTIP_MV_LAUNCH_MANY(0, WIDE); \
+    } else {                                          \
+        QTIP_MV_LAUNCH(1, 16, WIDE);                  \
+    }
 #define QTIP_MV_LAUNCH(S, NW, WIDE)                                \
     if (signs)                                                     \
         QTIP_MV_LAUNCH4(S, NW, true, false, WIDE);                 \
@@ -633,18 +730,21 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
         constexpr int WTPI = 64 / MvGeo<K, true>::LPT;
         const int wsteps = (tn + WTPI - 1) / WTPI;
         if (wsteps >= 16 && 2 * ((wsteps + 15) / 16) <= (steps + nw - 1) / nw) {
-            QTIP_MV_LAUNCH(1, 16, true);
+            QTIP_MV_LAUNCH_WHOLE(true);
             return hipGetLastError();
         }
     }
     switch (nw) {
         case 2: QTIP_MV_LAUNCH(1, 2, false); break;
         case 4: QTIP_MV_LAUNCH(1, 4, false); break;
-        case 16: QTIP_MV_LAUNCH(1, 16, false); break;
+        case 16: QTIP_MV_LAUNCH_WHOLE(false); break;
         default: QTIP_MV_LAUNCH(1, 8, false); break;
     }
 #undef QTIP_MV_LAUNCH
+#undef QTIP_MV_LAUNCH_WHOLE
+#undef QTIP_MV_LAUNCH_MANY
 #undef QTIP_MV_LAUNCH4
+#undef QTIP_MV_LAUNCH6
     return hipGetLastError();
 }
 
