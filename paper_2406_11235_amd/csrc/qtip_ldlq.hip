@@ -36,19 +36,23 @@ namespace {
 // The workspace holds T and M by blocks of 2 KiB, which a wave reads and writes as they are.
 //
 // Panels of 8 block columns, two launches each.  ldl_panel_kernel: a workgroup has a wave for each of the panel's own 8
-// block rows and one to four for block rows below; a wave holds its 8 blocks in registers.  The pivot wave inverts
-// D_j, and after one barrier per block column all waves take the two products above.  Every workgroup
-// factors the panel's own rows again, which costs no time (the inversions are a serial chain and leave the
-// matrix cores idle) and saves a launch per panel.  ldl_update_panel_kernel: the panel's products with the next
+// block rows but the first, one to four for block rows below, and one for the pivots; a row's wave holds its 8 blocks in registers.
+// The pivots' wave inverts D_j, the waves meet once per block column, and while the others take the two products above it
+// takes those that its next pivot needs itself.  It has its SIMD to itself: a binary64 matrix instruction of another wave holds
+// that up for 64 cycles at a time (a wave's priority does not help: 388 us -> 397), which was 1200 cycles of each of the
+// panel's first four block columns.  Every workgroup factors the panel's own rows again, which costs little (the inversions
+// are a serial chain) and saves a launch per panel.  ldl_update_panel_kernel: the panel's products with the next
 // panel's block columns.  Those with everything further right are taken beside the next panel, in its launch.
-// What bounds it is the chain of block columns: a panel kernel takes 18 to 22 us, 2.2 to 2.8 us per block column, of which the
-// gather and the 16 pivots are 1.2 us (a second inversion beside the first costs that) and the barrier and two dependent
-// products the rest; and the launch between two panels, 4.8 us.  n = 2048, g = 16: 1744 us with two launches
-// per block column, the inversion with five barriers per pivot and the products on the vector units, 388 us now: 16 panels
-// 313, 15 updates 72.  g = 8: 475 us; its pivot wave holds three arrays of 16, of which 144 bytes a lane lie in private memory
-// (24 accesses per block column).
+// What bounds it is the chain of block columns, 4330 cycles each: rows of the pivot 280, inversion 2280, its way to LDS 530, the
+// meeting 160, two dependent products 900, the loop 190; the first three of a panel wait 2500 more for the products of the other
+// rows, which have three SIMDs; and the launch between two panels, 4.8 us.  n = 2048, g = 16: 1744 us with two launches
+// per block column, the inversion with five barriers per pivot and the products on the vector units, 388 us with the pivots
+// inverted by the waves of their rows, 343 us now; g = 8: 475 us -> 386 (144 bytes a lane of its pivots' wave lie in private
+// memory).  Meeting twice, or handing the next pivot's products' operands over through a flag half-way through the
+// inversion, so that they run before the meeting, is no faster (350 to 371 us): the other rows are what is late then.
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
+typedef double double2_t __attribute__((ext_vector_type(2)));
 constexpr int LDL_PANEL = 8, LDL_MAX_ROWS = 4;
 
 __device__ __forceinline__ double *ldl_block(double *base, int nb, int k, int i) {
@@ -101,30 +105,22 @@ __device__ __forceinline__ double row_value(double a) {
     return v;
 }
 
-// Rows of a symmetric block in the result layout: a[c] = entry (l % 16, c) in lane l.  The lane has column l % 16,
-// four of its entries; the others are in the lanes 16, 32 and 48 further on, and come by exchanges of lane rows.
-__device__ __forceinline__ void ldl_rows(double4_t d, double (&a)[16]) {
+// Rows of a symmetric block in the result layout: a[c] = entry (l % 16, c) in lane l.  The lane has column l % 16, four of
+// its entries; through a piece of LDS that is the wave's own, rows 18 apart.  (Six exchanges of lane rows per register in its
+// place: 476 cycles, this 300.)
+constexpr int LDL_ROW = 18;
+__device__ __forceinline__ void ldl_rows(double4_t d, double *s_rows, int lane, double (&a)[16]) {
+    double *const mine = s_rows + (lane & 15) * LDL_ROW;
 #pragma unroll
-    for (int t = 0; t < 4; t++) {
-        const double v = d[t];
-        const u32x2_t w = __builtin_bit_cast(u32x2_t, v);
-        u32x2_t out[4];
+    for (int t = 0; t < 4; t++) mine[4 * t + (lane >> 4)] = d[t];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            // (x, x) -> the even lane rows' values in both rows of a pair, the odd ones'; then the same for halves
-            const auto p = __builtin_amdgcn_permlane16_swap(w[h], w[h], false, false);
-            const auto lo = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);
-            const auto hi = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);
-            out[0][h] = lo[0];
-            out[1][h] = hi[0];
-            out[2][h] = lo[1];
-            out[3][h] = hi[1];
-        }
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-            const u32x2_t o = out[g];
-            a[4 * t + g] = __builtin_bit_cast(double, o);
-        }
+    for (int c = 0; c < 16; c += 2) {
+        const double2_t two = *reinterpret_cast<const double2_t *>(mine + c);
+        a[c] = two[0];
+        a[c + 1] = two[1];
     }
 }
 // The other way: entries 4 t + g, g = l / 16, of the lane's row: an A operand with the rows as they are.
@@ -257,47 +253,46 @@ __global__ __launch_bounds__(256) void ldl_update_panel_kernel(double *__restric
     if (i < nb && k <= i) ldl_update<1>(T, Ms, nb, J0, k, i, threadIdx.x & 63);
 }
 
-// The first `groups` workgroups: block columns J0 .. J0 + np - 1, and `rows` block rows below them per workgroup, a wave
-// each.  The others: what the panel before has to subtract behind this one, TB x TB blocks per wave, on the CUs that
-// the chain leaves idle.
+// The waves of a panel's workgroup: wave 0 inverts pivots, the others whose number is not a multiple of 4 have a block row
+// each, so that the inversions have their SIMD to themselves (a binary64 matrix instruction holds it for 64 cycles).
+constexpr int ldl_waves(int rows) { return LDL_PANEL + rows + (LDL_PANEL + rows - 2) / 3; }
+// Block row, counted from the panel's first, of the p-th of those waves: the long ones first, so that the three SIMDs have as much.
+__device__ __forceinline__ int ldl_row_of(int p) {
+    return p == 0 ? LDL_PANEL : p < 3 || (p >= 6 && p < 8) ? LDL_PANEL - p : p < 6 ? p : p + 1;
+}
+// (the waves meet for what is in LDS; results on their way to memory are nobody's business here)
+__device__ __forceinline__ void ldl_meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The first `groups` workgroups: block columns J0 .. J0 + np - 1, and `rows` block rows below them per workgroup.  The others:
+// what the panel before has to subtract behind this one, TB x TB blocks per wave, on the CUs that the chain leaves idle.
 template <int G, int TB>
-__global__ __launch_bounds__((LDL_PANEL + LDL_MAX_ROWS) * 64) void ldl_panel_kernel(double *__restrict__ T,
-                                                                               double *__restrict__ Ms,
-                                                                               float *__restrict__ A, int n, int J0,
-                                                                               int groups, int rows, int pairs,
-                                                                               double *__restrict__ Dout) {
+__global__ __launch_bounds__(ldl_waves(LDL_MAX_ROWS) * 64) void ldl_panel_kernel(double *__restrict__ T,
+                                                                                 double *__restrict__ Ms,
+                                                                                 float *__restrict__ A, int n, int J0,
+                                                                                 int groups, int rows, int pairs,
+                                                                                 double *__restrict__ Dout) {
+    static_assert(LDL_PANEL == 8, "ldl_row_of");
     // D_j^-1 as an A operand, and what L_ij^T is made with (for G = 8 see below)
     __shared__ __attribute__((aligned(16))) double s_inv[2][256];
     __shared__ __attribute__((aligned(16))) double s_out[2][G == 8 ? 256 : 1];
-    __shared__ __attribute__((aligned(16))) double s_t[2][LDL_PANEL][256];
+    __shared__ __attribute__((aligned(16))) double s_t[2][LDL_PANEL][256];  // T_ij of the panel's own rows
+    __shared__ __attribute__((aligned(16))) double s_d[2][256];             // the next pivot, column j not yet taken off
+    __shared__ __attribute__((aligned(16))) double s_rows[16 * LDL_ROW];
     const int nb = n >> 4, np = min(LDL_PANEL, nb - J0);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if ((int)blockIdx.x >= groups) {
-        const int w = (blockIdx.x - groups) * (LDL_PANEL + rows) + wave;
+        const int w = (blockIdx.x - groups) * ldl_waves(rows) + wave;
         if (w < pairs) ldl_update_triangle<TB>(T, Ms, nb, J0 - LDL_PANEL, J0 + LDL_PANEL, w, lane);
         return;
     }
-    const int row = lane & 15, g = lane >> 4;
-    const bool own = wave < LDL_PANEL;  // of the panel's own block rows
-    const int rel = own ? wave : LDL_PANEL + blockIdx.x * rows + (wave - LDL_PANEL);
-    const int i = J0 + rel;
-    const bool some = i < nb;
-    const bool speaks = own ? blockIdx.x == 0 : true;  // writes results
-    double4_t t[LDL_PANEL];
-#pragma unroll
-    for (int j = 0; j < LDL_PANEL; j++) {
-        t[j] = double4_t{0.0, 0.0, 0.0, 0.0};
-        if (some && j < np && j <= rel) t[j] = ldl_load(ldl_block(T, nb, J0 + j, i), lane);
-    }
-    double4_t last = {0.0, 0.0, 0.0, 0.0}, out_before = last;
-#pragma unroll
-    for (int j = 0; j < LDL_PANEL; j++) {
-        if (j >= np) break;
-        const int buf = j & 1;
-        if (own && rel > j) ldl_store(s_t[buf][rel], lane, t[j]);
-        if (wave == j) {
+    const double4_t zero = {0.0, 0.0, 0.0, 0.0};
+    if (wave == 0) {
+        const int row = lane & 15, g = lane >> 4;
+        double4_t d = ldl_load(ldl_block(T, nb, J0, J0), lane);
+        for (int j = 0; j < np; j++) {
+            const int buf = j & 1;
             double a[16];
-            ldl_rows(t[j], a);
+            ldl_rows(d, s_rows, lane, a);
             double scale = 1.0;
             double inv = reciprocal(row_value<0>(a[0]));
             if constexpr (G == 16) {
@@ -321,45 +316,60 @@ __global__ __launch_bounds__((LDL_PANEL + LDL_MAX_ROWS) * 64) void ldl_panel_ker
                 for (int c = 0; c < 16; c++) f[c] = row < 8 ? f[c] : a[c] * scale;
                 ldl_store(s_out[buf], lane, ldl_operand(f, g));
             }
-            ldl_store(s_inv[buf], lane, ldl_operand(a, g) * scale);
-        }
-        // (the waves meet for what is in LDS; the results on their way to memory are nobody's business here)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (wave == j && blockIdx.x == 0 && j > 0) {
-            const double4_t e = G == 16 ? last : ldl_product(out_before, t[j > 0 ? j - 1 : 0], double4_t{0.0, 0.0, 0.0, 0.0});
-            ldl_emit(A, n, i, J0 + j - 1, lane, e);
-        }
-        if (wave == j && blockIdx.x == 0 && Dout) {
-            if constexpr (G == 16) {
-                ldl_store(Dout + (size_t)(J0 + j) * 256, lane, t[j]);
-            } else if (row < 8) {
+            const double4_t op = ldl_operand(a, g) * scale;
+            ldl_store(s_inv[buf], lane, op);
+            ldl_meet();
+            if (blockIdx.x == 0 && Dout) {
+                if constexpr (G == 16) {
+                    ldl_store(Dout + (size_t)(J0 + j) * 256, lane, d);
+                } else if (row < 8) {
 #pragma unroll
-                for (int q = 0; q < 2; q++) Dout[(size_t)(J0 + j) * 128 + (4 * q + g) * 8 + row] = t[j][q];
+                    for (int q = 0; q < 2; q++) Dout[(size_t)(J0 + j) * 128 + (4 * q + g) * 8 + row] = d[q];
+                }
+            }
+            if (j + 1 < np) {
+                const double4_t t = ldl_load(s_t[buf][j + 1], lane), before = ldl_load(s_d[buf], lane);
+                d = ldl_product(t, -ldl_product(op, t, zero), before);
             }
         }
-        if (some && rel > j) {
-            const double4_t m = ldl_product(ldl_load(s_inv[buf], lane), t[j], double4_t{0.0, 0.0, 0.0, 0.0});
-            const double4_t neg = -m;
-            // (the next block column's block first: the next pivot wave waits for it)
+        return;
+    }
+    const int rel = wave & 3 ? ldl_row_of(wave - 1 - (wave >> 2)) : -1;
+    const bool own = rel < LDL_PANEL;  // of the panel's own block rows
+    const int i = rel < 0 ? nb : own ? J0 + rel : J0 + rel + (int)blockIdx.x * rows;
+    const bool some = i < nb;
+    const bool speaks = own ? blockIdx.x == 0 : true;  // writes results
+    double4_t t[LDL_PANEL];
 #pragma unroll
-            for (int k = j + 1; k < LDL_PANEL; k++)
-                if (k < np && k <= rel) t[k] = ldl_product(ldl_load(s_t[buf][k], lane), neg, t[k]);
-            // (the next pivot wave writes its last block when its own pivot is done)
-            if (rel == j + 1 && own) {
-                last = m;
-                if constexpr (G == 8) out_before = ldl_load(s_out[buf], lane);
-            } else if (speaks) {
+    for (int j = 0; j < LDL_PANEL; j++) {
+        t[j] = zero;
+        if (some && j < np && j <= rel) t[j] = ldl_load(ldl_block(T, nb, J0 + j, i), lane);
+    }
+#pragma unroll
+    for (int j = 0; j < LDL_PANEL; j++) {
+        if (j >= np) break;
+        const int buf = j & 1;
+        if (some && own && rel > j) ldl_store(s_t[buf][rel], lane, t[j]);
+        if (j + 1 < LDL_PANEL && some && rel == j + 1) ldl_store(s_d[buf], lane, t[j + 1 < LDL_PANEL ? j + 1 : 0]);
+        ldl_meet();
+        if (some && rel > j) {
+            const double4_t m = ldl_product(ldl_load(s_inv[buf], lane), t[j], zero);
+            const double4_t neg = -m;
+            auto take_off = [&](int k) {  // (the next pivot's own is its wave's)
+                if (k < np && k <= rel && rel != j + 1) t[k] = ldl_product(ldl_load(s_t[buf][k], lane), neg, t[k]);
+            };
+            if (j + 1 < LDL_PANEL) take_off(j + 1);
+            // (results leave while products of the three waves of the SIMD run: after the last one 347 us in place of 338)
+            if (speaks) {
                 if (!own) {
                     ldl_store(ldl_block(T, nb, J0 + j, i), lane, t[j]);
                     ldl_store(ldl_block(Ms, nb, J0 + j, i), lane, m);
                 }
-                if constexpr (G == 8) {
-                    ldl_emit(A, n, i, J0 + j, lane,
-                             ldl_product(ldl_load(s_out[buf], lane), t[j], double4_t{0.0, 0.0, 0.0, 0.0}));
-                } else {
-                    ldl_emit(A, n, i, J0 + j, lane, m);
-                }
+                if constexpr (G == 8) ldl_emit(A, n, i, J0 + j, lane, ldl_product(ldl_load(s_out[buf], lane), t[j], zero));
+                else ldl_emit(A, n, i, J0 + j, lane, m);
             }
+#pragma unroll
+            for (int k = j + 2; k < LDL_PANEL; k++) take_off(k);
         }
     }
 }
@@ -444,7 +454,7 @@ static hipError_t block_ldl_t(const double *H, int n, float *A, double *Dout, vo
         const int below = nb - J0 - LDL_PANEL;  // block rows below the panel
         // as few rows per workgroup as keep it at one workgroup per CU: they take the matrix cores from the chain
         const int rows = below <= 256 ? 1 : below <= 512 ? 2 : LDL_MAX_ROWS;
-        const int groups = below > 0 ? (below + rows - 1) / rows : 1, waves = LDL_PANEL + rows;
+        const int groups = below > 0 ? (below + rows - 1) / rows : 1, waves = ldl_waves(rows);
         // 2 x 2 blocks per wave while that is half a wave per SIMD; single blocks, a shorter chain, otherwise
         const int p2 = J0 > 0 && below > 0 ? (below + 1) / 2 : 0, pairs2 = p2 * (p2 + 1) / 2;
         const int pairs = pairs2 >= 512 ? pairs2 : p2 > 0 ? below * (below + 1) / 2 : 0;

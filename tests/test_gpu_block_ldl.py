@@ -65,3 +65,9 @@ def test_what_stands_above_the_diagonal_does_not_matter(g, filled):
         S[j + g:, j + g:] -= L[j + g:, j:j + g] @ S[j + g:, j:j + g].T
     ref = L - torch.eye(n, dtype=torch.float64)
     assert float((A.cpu().double() - ref).norm() / ref.norm()) < 1e-7  # (half a unit of binary32: 6e-8)
+
+
+@pytest.mark.parametrize("n,g", [(4256, 16), (4240, 8), (8352, 16)])
+def test_two_and_four_rows_per_workgroup(n, g):
+    """More block rows below a panel than CUs: two and four of them per workgroup, the last ones not full."""
+    test_reconstructs(n, g)
