@@ -342,9 +342,10 @@ __device__ __forceinline__ void matvec_tile_row(int I, int Iend, int part, bool 
 }
 // TAIL 2 or 4: the tile rows from `whole` on are split into as many parts, by workgroups behind those of the whole ones (ahead
 // of them, or the whole rows in a loop over at most 512 workgroups, is slower: 3INST 14336 x 4096 10.44, 10.85 and 10.52 us,
-// 1MAD 5120 x 8192 8.45, 9.51, 11.5).  ROUNDS, for the V = 1 hash code, of which one workgroup fits a CU, so that nothing is decoded
+// 1MAD 5120 x 8192 8.45, 9.51 and 11.5).  ROUNDS, for the V = 1 hash code, of which one workgroup fits a CU, so that nothing is decoded
 // while another one begins and ends: the whole rows in rounds over at most 256 workgroups that keep their table and
 // have the next row's words under way, then the others' parts, if any (k = 4, 14336 x 4096 19.0 -> 15.2 us).
+// (The arguments are 64 bytes; with one more, `whole`, a launch of the smallest layers cost the host 0.2 us more.)
 template <int K, int V, int CODE, int S, int NW, bool FUSED, bool SPREAD = false, bool WIDE = false, int TAIL = 0,
           bool ROUNDS = false>
 __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void matvec_kernel(const uint32_t *__restrict__ codes,
@@ -352,13 +353,13 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
                                                          int tm, int tn, const half_t *__restrict__ x,
                                                          const int8_t *__restrict__ signs, int log2_block,
                                                          const half_t *__restrict__ scale,
-                                                         float *__restrict__ y, int whole) {
+                                                         float *__restrict__ y) {
     __shared__ __attribute__((aligned(16))) uint32_t s_lut[code_lds_words(CODE, SPREAD)];
     __shared__ float s_part[ROUNDS ? 2 * NW : NW][16];
     __shared__ __attribute__((aligned(16))) half_t s_x[FUSED ? FUSED_MAX_N : 8];
     __shared__ __attribute__((aligned(16))) float s_v[FUSED ? RHT_LDS_FLOATS : 1];
     // Workgroups go round the eight XCDs; those of one tile row, which read the same cache lines, stay on one.
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, whole = TAIL ? tm / 256 * 256 : tm;
     auto tail_part = [&](int t, bool staged) {
         const int I = whole + (t >> 3) / TAIL * 8 + (t & 7);
         if (I >= tm) return;
@@ -649,7 +650,7 @@ static bool pick_hyb_spread(int code, int n) {
 // long enough for 16 waves (us, all rows whole and so: 1MAD k = 3 14336 x 4096 10.9 10.3, 6144 x 4096 6.06 5.44, 5120 x 8192 10.4
 // 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6).
 struct MatvecSplit {
-    int s, whole, tail;  // rows from `whole` on: `tail` workgroups each
+    int s, whole, tail;  // rows from `whole`, the multiple of 256, on: `tail` workgroups each
 };
 static MatvecSplit pick_matvec_split(int tm, int tn) {
     auto time = [&](int rows, int s) { return (float)((rows * (long)s + 255) / 256) * (0.8f + (float)tn * (0.008f / (float)s)); };
@@ -683,7 +684,7 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
     // signs != null: x is untransformed and the kernel transforms it itself (n <= FUSED_MAX_N)
 #define QTIP_MV_LAUNCH6(S, NW, FUSED, SPREAD, WIDE, TAIL, ROUNDS)                                                           \
     hipLaunchKernelGGL((matvec_kernel<K, V, CODE, S, NW, FUSED, SPREAD, WIDE, TAIL, ROUNDS>), grid, dim3(NW * 64), 0, st, codes, \
-                       lut, tm, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y, pick.whole)
+                       lut, tm, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y)
 #define QTIP_MV_LAUNCH4(S, NW, FUSED, SPREAD, WIDE) QTIP_MV_LAUNCH6(S, NW, FUSED, SPREAD, WIDE, 0, false)
 // (more rows than one per CU: never with the transform)
 #define QTIP_MV_LAUNCH_MANY(TAIL, WIDE)                                    \

@@ -1118,8 +1118,8 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
 }  // namespace
 
 // Bytes per sequence in flight that callers are told to bring (at kV = 2 half, at kV = 3 and 4 less,
-// of what a whole walk's copies take: with thousands in flight fewer at a time do as well, with few
-// the forward pass is repeated in part, see Plan).
+// of what a whole walk's copies take: with thousands in flight fewer at a time do as well, with few one launch
+// takes longer segments, and in between the forward pass is repeated in part, see Plan).
 size_t quantize_gpu_workspace(int k, int V, long tiles) {
     size_t per_step;  // words
     switch (k * V) {
