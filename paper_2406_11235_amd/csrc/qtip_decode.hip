@@ -361,11 +361,13 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     // Workgroups go round the eight XCDs; those of one tile row, which read the same cache lines, stay on one.
     const int b = blockIdx.x, whole = TAIL ? tm / 256 * 256 : tm;
     auto tail_part = [&](int t, bool staged) {
-        const int I = whole + (t >> 3) / TAIL * 8 + (t & 7);
-        if (I >= tm) return;
-        if (staged) __syncthreads();
-        matvec_tile_row<K, V, CODE, TAIL ? TAIL : 1, NW, FUSED, SPREAD, K != 2>(I, I + 1, (t >> 3) % TAIL, staged, codes, lut, tn, x,
-                                                                                signs, log2_block, scale, y, s_lut, s_part, s_x, s_v);
+        if constexpr (TAIL > 0) {
+            const int I = whole + (t >> 3) / TAIL * 8 + (t & 7);
+            if (I >= tm) return;
+            if (staged) __syncthreads();
+            matvec_tile_row<K, V, CODE, TAIL, NW, FUSED, SPREAD, K != 2>(I, I + 1, (t >> 3) % TAIL, staged, codes, lut, tn, x, signs,
+                                                                         log2_block, scale, y, s_lut, s_part, s_x, s_v);
+        }
     };
     if constexpr (ROUNDS) {
         if (b >= whole) return;  // (the grid has no more)
@@ -698,7 +700,9 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
     } else if (pick.tail == 4) {                      \
         QTIP_MV_LAUNCH_MANY(4, WIDE);                 \
     } else if (rounds) {                              \
-        if constexpr (CODE == CODE_HYB1) QTIP_MV_LAUNCH_MANY(0, WIDE); \
+        if constexpr (CODE == CODE_HYB1) {            \
+            QTIP_MV_LAUNCH_MANY(0, WIDE);             \
+        }                                             \
     } else {                                          \
         QTIP_MV_LAUNCH(1, 16, WIDE);                  \
     }
