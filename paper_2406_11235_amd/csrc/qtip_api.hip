@@ -158,14 +158,14 @@ int qtip_rht_decode_matvec(const uint32_t *codes, int L, int k, int V, int code_
     hipError_t e;
     // one launch pays while there is at most one workgroup (tile row) per CU; with more, every
     // CU would redo the transform several times over
-    if (!is_lut(code_id) && n <= qtip::fused_rht_matvec_max_n() && m <= 16 * 256) {
+    if (!is_lut(code_id) && n <= qtip::fused_rht_matvec_max_n() && m <= qtip::FUSED_RHT_MATVEC_MAX_M) {
         e = qtip::launch_rht_matvec(k, code_id, codes, (const uint32_t *)lut_f16, m, n, x_f16, signs_n, block,
                                     row_scale_f16, y, (hipStream_t)stream);
     } else {
         if (!xt_scratch_f16 || !aligned(xt_scratch_f16, 16))
             return fail(QTIP_EINVAL,
-                        "%s: n = %d above %d, m = %d above 4096 or the lookup-only code: xt_scratch (n fp16, "
-                        "16-byte aligned) is needed", fn, n, qtip::fused_rht_matvec_max_n(), m);
+                        "%s: n = %d above %d, m = %d above %d or the lookup-only code: xt_scratch (n fp16, "
+                        "16-byte aligned) is needed", fn, n, qtip::fused_rht_matvec_max_n(), m, qtip::FUSED_RHT_MATVEC_MAX_M);
         e = qtip::launch_rht(x_f16, false, signs_n, n, block, 1, 0, xt_scratch_f16, (hipStream_t)stream);
         if (e == hipSuccess)
             e = qtip::launch_matvec(k, code_id, codes, (const uint32_t *)lut_f16, m, n, xt_scratch_f16,

@@ -359,7 +359,7 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
     __shared__ __attribute__((aligned(16))) half_t s_x[FUSED ? FUSED_MAX_N : 8];
     __shared__ __attribute__((aligned(16))) float s_v[FUSED ? RHT_LDS_FLOATS : 1];
     // Workgroups go round the eight XCDs; those of one tile row, which read the same cache lines, stay on one.
-    const int b = blockIdx.x, whole = TAIL ? tm / 256 * 256 : tm;
+    const int b = blockIdx.x, whole = TAIL ? tm / CUS * CUS : tm;
     auto tail_part = [&](int t, bool staged) {
         if constexpr (TAIL > 0) {
             const int I = whole + (t >> 3) / TAIL * 8 + (t & 7);
@@ -652,15 +652,15 @@ static bool pick_hyb_spread(int code, int n) {
 // long enough for 16 waves (us, all rows whole and so: 1MAD k = 3 14336 x 4096 10.9 10.3, 6144 x 4096 6.06 5.44, 5120 x 8192 10.4
 // 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6).
 struct MatvecSplit {
-    int s, whole, tail;  // rows from `whole`, the multiple of 256, on: `tail` workgroups each
+    int s, whole, tail;  // rows from `whole`, the multiple of CUS, on: `tail` workgroups each
 };
 static MatvecSplit pick_matvec_split(int tm, int tn) {
-    auto time = [&](int rows, int s) { return (float)((rows * (long)s + 255) / 256) * (0.8f + (float)tn * (0.008f / (float)s)); };
+    auto time = [&](int rows, int s) { return (float)((rows * (long)s + CUS - 1) / CUS) * (0.8f + (float)tn * (0.008f / (float)s)); };
     MatvecSplit best{1, tm, 0};
     float least = time(tm, 1);
     for (int s = 2; s <= 4 && tn >= 2 * 16 * s; s *= 2) {
         if (time(tm, s) < least) best = {s, tm, 0}, least = time(tm, s);
-        const int whole = tm / 256 * 256;
+        const int whole = tm / CUS * CUS;
         if (whole > 0 && whole < tm && tn >= 256) {
             const float t = time(whole, 1) + time(tm - whole, s);
             if (t < least) best = {1, whole, s}, least = t;
@@ -680,15 +680,15 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
     const bool spread = pick_hyb_spread(CODE, n);
     const MatvecSplit pick = pick_matvec_split(tm, tn);
     const int split = pick.s, tails = pick.tail ? (tm - pick.whole + 7) / 8 * 8 * pick.tail : 0;
-    const bool rounds = CODE == CODE_HYB1 && split == 1 && tm > 256 && nw == 16;
+    const bool rounds = CODE == CODE_HYB1 && split == 1 && tm > CUS && nw == 16;
     // (in rounds every workgroup begins with a whole row)
-    const dim3 grid(split > 1 ? (tm + 7) / 8 * 8 * split : rounds ? std::min(256, pick.whole) : pick.whole + tails);
+    const dim3 grid(split > 1 ? (tm + 7) / 8 * 8 * split : rounds ? std::min(CUS, pick.whole) : pick.whole + tails);
     // signs != null: x is untransformed and the kernel transforms it itself (n <= FUSED_MAX_N)
 #define QTIP_MV_LAUNCH6(S, NW, FUSED, SPREAD, WIDE, TAIL, ROUNDS)                                                           \
     hipLaunchKernelGGL((matvec_kernel<K, V, CODE, S, NW, FUSED, SPREAD, WIDE, TAIL, ROUNDS>), grid, dim3(NW * 64), 0, st, codes, \
                        lut, tm, tn, (const half_t *)x, signs, log2_block, (const half_t *)scale, y)
 #define QTIP_MV_LAUNCH4(S, NW, FUSED, SPREAD, WIDE) QTIP_MV_LAUNCH6(S, NW, FUSED, SPREAD, WIDE, 0, false)
-// (more rows than one per CU: never with the transform)
+// (more rows than one per CU, and so more than launch_rht_matvec takes: never with the transform)
 #define QTIP_MV_LAUNCH_MANY(TAIL, WIDE)                                    \
     if (code_is_hyb(CODE) && spread)                                       \
         QTIP_MV_LAUNCH6(1, 16, false, code_is_hyb(CODE), WIDE, TAIL, false); \
@@ -842,6 +842,8 @@ int fused_rht_matvec_max_n() { return FUSED_MAX_N; }
 hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                              int n, const void *x, const int8_t *signs, int block, const void *scale,
                              float *y, hipStream_t st) {
+    // (beyond these there is no kernel that looks at the signs: QTIP_MV_LAUNCH_MANY)
+    if (m > FUSED_RHT_MATVEC_MAX_M || n > FUSED_MAX_N) return hipErrorInvalidValue;
     int log2_block = 0;
     while ((1 << log2_block) < block) log2_block++;
     QTIP_DISPATCH(launch_matvec_t, codes, lut, m, n, x, signs, log2_block, scale, y, st);

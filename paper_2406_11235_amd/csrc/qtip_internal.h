@@ -5,6 +5,8 @@
 
 namespace qtip {
 
+constexpr int CUS = 256;  // compute units, and so workgroups in a round of one each
+
 hipError_t launch_dequantize(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                              int n, void *W, hipStream_t st);
 hipError_t launch_matvec(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
@@ -16,8 +18,10 @@ bool gemm_takes(int code_id, int n, int B);
 hipError_t launch_gemm(int k, int code_id, const uint32_t *codes, const void *lut, int m, int n, const void *X, int B,
                        const void *scale, float *Y, hipStream_t st);
 // decode + matvec that computes the input-side transform V (S .* x) itself; n at most
-// fused_rht_matvec_max_n().
+// fused_rht_matvec_max_n(), m at most FUSED_RHT_MATVEC_MAX_M (with more than one workgroup, a tile row of 16, per CU
+// each CU would redo the transform several times over); hipErrorInvalidValue beyond.
 int fused_rht_matvec_max_n();
+constexpr int FUSED_RHT_MATVEC_MAX_M = 16 * CUS;
 hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                              int n, const void *x, const int8_t *signs, int block, const void *scale,
                              float *y, hipStream_t st);

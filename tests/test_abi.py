@@ -176,3 +176,17 @@ def test_header_is_plain_c_and_the_library_links_from_c(q, tmp_path):
                     "-Wl,-rpath," + libdir, "-Wl,-rpath,/opt/rocm/lib", "-Wl,--allow-shlib-undefined"], check=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True)
     assert out.stdout.strip() == "ok"
+
+
+@pytest.mark.parametrize("code_id,V", [(0, 1), (1, 1), (2, 2), (3, 2), (5, 1)])
+@pytest.mark.parametrize("m,n", [(4112, 4096), (8192, 4096), (16, 8208)])
+def test_one_launch_layer_refuses_sizes_without_a_kernel_that_transforms(q, code_id, V, m, n):
+    """With more tile rows than CUs the launcher has kernels that take x as transformed already: a call with signs must not
+    get there (hipErrorInvalidValue, before any launch)."""
+    launch = getattr(ctypes.CDLL(q.library_path()),
+                     "_ZN4qtip17launch_rht_matvecEiiPKjS1_iiPKvPKaiS3_PfP12ihipStream_t")
+    launch.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
+                       ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    p = np.zeros(64, dtype=np.uint32).ctypes.data  # (never dereferenced)
+    for k in (2, 3, 4):
+        assert launch(k, code_id, p, p, m, n, p, p, 16, None, p, None) == 1
