@@ -650,21 +650,25 @@ static bool pick_hyb_spread(int code, int n) {
 // that the kernel that transforms its own input makes the same one.)
 // With more tile rows than CUs the ones behind the last whole round may be split alone, by the same measure, if the row is
 // long enough for 16 waves (us, all rows whole and so: 1MAD k = 3 14336 x 4096 10.9 10.3, 6144 x 4096 6.06 5.44, 5120 x 8192 10.4
-// 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6).
+// 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6) and their parts are
+// one workgroup per CU at most.  More of them are slower than whole rows, of which a CU has two at a time (4-bit HYB,
+// 14336 inputs, whole and split: 416 tile rows 13.3 23.1, 448 13.5 24.5, 704 19.9 29.6; 3-bit 1MAD 448 18.3 22.1), but for the
+// 2-bit computed codes behind one round (1MAD, 416 rows: 17.7 16.5).
 struct MatvecSplit {
     int s, whole, tail;  // rows from `whole`, the multiple of CUS, on: `tail` workgroups each
 };
-static MatvecSplit pick_matvec_split(int tm, int tn) {
+static MatvecSplit pick_matvec_split(int k, int code, int tm, int tn) {
     auto time = [&](int rows, int s) { return (float)((rows * (long)s + CUS - 1) / CUS) * (0.8f + (float)tn * (0.008f / (float)s)); };
+    const int whole = tm / CUS * CUS, rest = tm - whole;
+    const bool one_round_of_two_bits = k == 2 && (code == CODE_3INST || code == CODE_1MAD) && whole == CUS;
     MatvecSplit best{1, tm, 0};
     float least = time(tm, 1);
     for (int s = 2; s <= 4 && tn >= 2 * 16 * s; s *= 2) {
         if (time(tm, s) < least) best = {s, tm, 0}, least = time(tm, s);
-        const int whole = tm / CUS * CUS;
-        if (whole > 0 && whole < tm && tn >= 256) {
-            const float t = time(whole, 1) + time(tm - whole, s);
-            if (t < least) best = {1, whole, s}, least = t;
-        }
+        if (whole == 0 || rest == 0 || tn < 256) continue;
+        if (rest * s > CUS && !(one_round_of_two_bits && rest > CUS / 2)) continue;
+        const float t = time(whole, 1) + time(rest, s);
+        if (t < least) best = {1, whole, s}, least = t;
     }
     return best;
 }
@@ -678,7 +682,7 @@ static hipError_t launch_matvec_t(const uint32_t *codes, const uint32_t *lut, in
     const int steps = (tn + TPI - 1) / TPI;
     const int nw = pick_matvec_waves(steps);
     const bool spread = pick_hyb_spread(CODE, n);
-    const MatvecSplit pick = pick_matvec_split(tm, tn);
+    const MatvecSplit pick = pick_matvec_split(K, CODE, tm, tn);
     const int split = pick.s, tails = pick.tail ? (tm - pick.whole + 7) / 8 * 8 * pick.tail : 0;
     const bool rounds = CODE == CODE_HYB1 && split == 1 && tm > CUS && nw == 16;
     // (in rounds every workgroup begins with a whole row)

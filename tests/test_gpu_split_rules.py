@@ -1,0 +1,55 @@
+"""The rules that split batch-1 products over workgroups do not make a matrix slower than one with more rows."""
+import pytest
+
+from qtip_synth import CODE_1MAD, CODE_3INST, CODE_HYB, CODE_HYB1, CODE_HYB2, CODE_LUT
+
+pytestmark = pytest.mark.gpu
+
+TABLE = {CODE_HYB: 1024, CODE_HYB2: 1024, CODE_HYB1: 64, CODE_LUT: 1 << 14}
+
+
+class Product:
+    def __init__(self, code, k, m, n):
+        import torch
+        g = torch.Generator(device="cuda").manual_seed(24061123 + k)
+        self.L, self.V = (14, 1) if code == CODE_LUT else (16, 2 if code in (CODE_HYB, CODE_HYB2) else 1)
+        self.code, self.k, self.m, self.n = code, k, m, n
+        self.codes = torch.randint(-2**31, 2**31, (m * n // 256, 8 * k), dtype=torch.int32, device="cuda", generator=g)
+        self.lut = torch.randn(TABLE[code], device="cuda", generator=g).half() if code in TABLE else None
+        self.x = torch.randn(n, device="cuda", generator=g).half()
+
+    def __call__(self, m):
+        """The first m rows."""
+        import torch
+        import paper_2406_11235_amd as q
+        y = torch.empty(m, device="cuda")
+        q.qtip_decode_matvec(self.codes, self.L, self.k, self.V, self.code, self.lut, m, self.n, self.x, y)
+        return y
+
+    def us(self, m):
+        import torch
+        self(m)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            kept = [self(m) for _ in range(20)]
+        times = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 1e3 / len(kept))
+        return min(times[1:])
+
+
+# (times of the fewer rows over those of the more with the parts of the rows behind whole rounds in more than one round of
+# their own: 1.3 to 1.75)
+@pytest.mark.parametrize("code,k,fewer,more,n", [
+    (CODE_HYB, 4, 7168, 8192, 14336), (CODE_HYB, 3, 11264, 12288, 14336), (CODE_HYB2, 4, 11264, 12288, 14336),
+    (CODE_3INST, 4, 7168, 8192, 14336), (CODE_HYB1, 4, 7168, 8192, 28672)])
+def test_fewer_rows_take_no_longer(code, k, fewer, more, n):
+    product = Product(code, k, more, n)
+    a, b = product.us(fewer), product.us(more)
+    assert a <= 1.15 * b, (a, b)
