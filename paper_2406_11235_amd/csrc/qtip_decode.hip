@@ -653,7 +653,11 @@ static bool pick_hyb_spread(int code, int n) {
 // 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6) and their parts are
 // one workgroup per CU at most.  More of them are slower than whole rows, of which a CU has two at a time (4-bit HYB,
 // 14336 inputs, whole and split: 416 tile rows 13.3 23.1, 448 13.5 24.5, 704 19.9 29.6; 3-bit 1MAD 448 18.3 22.1), but for the
-// 2-bit computed codes behind one round (1MAD, 416 rows: 17.7 16.5).
+// 2-bit computed codes behind one round (1MAD, 416 rows: 17.7 16.5).  And where all rows in two halves were chosen before, halves
+// stay for two kinds of product: the V = 1 hash code's with short rows, whose halves have 8 waves and so go two to a CU (us,
+// last rows in parts and all in halves: k = 2 6144 x 4608 9.13 7.52, 6144 x 4096 7.20 6.55, 10240 x 7168 15.8 14.8; k = 3 5632 x
+// 5120 10.76 10.04, but 6144 inputs 11.1 11.8; k = 4 5632 x 4608 9.71 9.15), and the 2-bit computed codes' behind one round (1MAD
+// 6144 x 4096 5.49 5.19, 5120 inputs 6.98 7.30; 3INST 5.58 5.36, 8192 inputs 9.02 8.85).
 struct MatvecSplit {
     int s, whole, tail;  // rows from `whole`, the multiple of CUS, on: `tail` workgroups each
 };
@@ -661,12 +665,18 @@ static MatvecSplit pick_matvec_split(int k, int code, int tm, int tn) {
     auto time = [&](int rows, int s) { return (float)((rows * (long)s + CUS - 1) / CUS) * (0.8f + (float)tn * (0.008f / (float)s)); };
     const int whole = tm / CUS * CUS, rest = tm - whole;
     const bool one_round_of_two_bits = k == 2 && (code == CODE_3INST || code == CODE_1MAD) && whole == CUS;
+    // (of all rows, than parts of the last ones)
+    auto halves_are_faster = [&](int s) {
+        if (code == CODE_HYB1) return k == 2 ? tn < 512 : whole == CUS && tn <= 320;
+        return one_round_of_two_bits && s == 2 && (code == CODE_3INST || tn < 320);
+    };
     MatvecSplit best{1, tm, 0};
     float least = time(tm, 1);
     for (int s = 2; s <= 4 && tn >= 2 * 16 * s; s *= 2) {
         if (time(tm, s) < least) best = {s, tm, 0}, least = time(tm, s);
         if (whole == 0 || rest == 0 || tn < 256) continue;
         if (rest * s > CUS && !(one_round_of_two_bits && rest > CUS / 2)) continue;
+        if (best.s == 2 && halves_are_faster(s)) continue;
         const float t = time(whole, 1) + time(rest, s);
         if (t < least) best = {1, whole, s}, least = t;
     }
