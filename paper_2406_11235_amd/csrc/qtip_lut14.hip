@@ -401,9 +401,12 @@ hipError_t launch_lut_decode_states(const uint32_t *states, int count, const voi
 
 // Workgroups per block row for the batch-1 kernel, and the block rows that are split so; the rows of the others are the
 // tail.  A CU's share of workgroups, each 1 us for its copy of the table and 32 n / S reads of the table, 8 cycles per 64, and
-// of tail rows, each half a microsecond (a line of memory per lane, a sum over all waves) and its reads (measured: 0.7 us at
-// 4096 inputs, 1.4 at 14464, 2.0 at 28672): the smallest, over what S = 1, 2 and 4 make with a last round that is not full,
-// and without it.
+// of tail rows, 0.3 us for all and each half a microsecond (a line of memory per lane, a sum over all waves) and its reads: the
+// smallest, over what S = 1, 2 and 4 make with a last round that is not full, and without it.  The tail's share is fitted to
+// every split forced in turn, k = 2 to 4, 36 to 688 block rows of 768 to 28672 inputs: no pick is more than 4 % slower than the one
+// made without tails (with half a microsecond and 1.05 times the reads per row it was up to 46 %: 4 bits, 100 block rows of 28672
+// inputs 29.3 -> 42.7 us, 216 of 14464 29.3 -> 42.6; 3 bits, 300 of 2048 9.6 -> 11.1).  Halves of more than two rounds and
+// quarters of more than one are never faster with a tail (4 bits, 216 of 28672: 65 us against 52 whole).
 struct LutSplit {
     int s, tm;
 };
@@ -412,13 +415,13 @@ static LutSplit pick_lut_split(int tm, int n) {
     float least = 0.f;
     for (int s = 1; s <= 4; s *= 2) {
         const float block_row = (float)n * (4.f / 2400.f);  // us
-        const int rounds = (tm * s + 255) / 256, full = tm * s / 256;
+        const int rounds = (tm * s + CUS - 1) / CUS, full = tm * s / CUS;
         const float t = (float)rounds * (1.f + block_row / s);
         if (s == 1 || t < least) best = {s, tm}, least = t;
-        if (full == 0 || full == rounds) continue;
-        const int each = ((tm - full * (256 / s)) * LUT_TX + 256 * full - 1) / (256 * full);
-        const float folded = (float)full * (1.f + block_row / s + each * (0.5f + 1.05f * block_row / LUT_TX));
-        if (each <= LUT_MAX_TAIL && folded < least) best = {s, full * (256 / s)}, least = folded;
+        if (full == 0 || full == rounds || (s > 1 && full * s > 4)) continue;
+        const int each = ((tm - full * (CUS / s)) * LUT_TX + CUS * full - 1) / (CUS * full);
+        const float folded = (float)full * (1.f + block_row / s + each * (0.55f + 1.3f * block_row / LUT_TX)) + 0.3f;
+        if (each <= LUT_MAX_TAIL && folded < least) best = {s, full * (CUS / s)}, least = folded;
     }
     return best;
 }
