@@ -294,10 +294,12 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
             if (c_now >= c_lo && c_now < c_hi && (Geo::WHOLE || lane < 16)) {
                 float *dst = store_base + (size_t)(c_now - c_lo) * NP;
                 // (where a thread's prefixes differ in the low bits alone, its places are a uniform distance apart: one
-                // address and scalar additions)
+                // address and scalar additions; but the 3-bit V = 1 hash code's kernel, which is out of registers, would
+                // spill 36 of them in place of 28: 4096 sequences 9.43 -> 9.57 ms)
+                constexpr bool EVEN = NB <= 1 << Geo::LOWB && !(KV == 3 && CODE == CODE_HYB1);
 #pragma unroll
                 for (int i = 0; i < NB; i++) {
-                    if constexpr (NB <= 1 << Geo::LOWB) (dst + (i << (KV * J)))[Geo::stored((uint32_t)my_hi)] = best[i];
+                    if constexpr (EVEN) (dst + (i << (KV * J)))[Geo::stored((uint32_t)my_hi)] = best[i];
                     else dst[Geo::stored((uint32_t)(my_hi + i))] = best[i];
                 }
             }
