@@ -42,7 +42,8 @@ def test_every_split(code, V, k, m, n, block):
 @pytest.mark.parametrize("m,n", [(4112, 4096), (5392, 4112), (6144, 4096), (8336, 8208), (7936, 4096), (7680, 2048)])
 def test_rows_behind_whole_rounds(code, V, k, m, n):
     """More tile rows than CUs: one behind the last round, a last group of eight that is not full, as many parts as CUs, two
-    rounds before, and too many to split; the first, the last whole and the last ones against the oracle's dequantizer."""
+    rounds before, and too many to split; all of them against the product of the dequantized weights in binary64, and the
+    first, the last whole and the last ones against the oracle's dequantizer as well."""
     import torch
     import paper_2406_11235_amd as q
     w = synth.Workload("mv_tail", 34, 5 * k + code + m % 89, m, n, code, k, V, 16, 16, row_scale=True)
@@ -58,11 +59,17 @@ def test_rows_behind_whole_rounds(code, V, k, m, n):
     torch.cuda.synchronize()
     got = y.cpu().numpy()
     assert np.all(np.isnan(got[m:])) and np.array_equal(got[:m], y2.cpu().numpy()[:m])
+    Wg = torch.empty((m, n), dtype=torch.float16, device="cuda")
+    q.qtip_dequantize(codes, 16, k, V, code, lut, m, n, Wg)
+    all_rows = (Wg.double() @ xt[0].double()) * sc.double()
+    # (the 1MAD loop contracts the unrounded quotient: 2^-12 of a weight)
+    bound = 5e-4 if code == CODE_1MAD else 1e-5
+    assert (y[:m].double() - all_rows).abs().max() <= bound * all_rows.abs().max()
     tm = m // 16
     for I0, I1 in ((0, 2), (tm // 256 * 256 - 1, min(tm, tm // 256 * 256 + 3)), (tm - 3, tm)):
         part = np.ascontiguousarray(inp.codes.reshape(tm, -1)[I0:I1]).reshape(-1, inp.codes.shape[-1])
         W = oracle.dequantize(part, 16, k, V, code, 16 * (I1 - I0), n, inp.lut)
         ref = W.view(np.float16).astype(np.float64) @ xt[0].double().cpu().numpy()
         ref *= inp.row_scale[16 * I0:16 * I1].astype(np.float64)
-        # (as above; the scale is that of all rows)
-        assert np.abs(got[16 * I0:16 * I1] - ref).max() <= (5e-4 if code == CODE_1MAD else 1e-5) * np.abs(got[:m]).max()
+        # (the scale is that of all rows)
+        assert np.abs(got[16 * I0:16 * I1] - ref).max() <= bound * np.abs(got[:m]).max()

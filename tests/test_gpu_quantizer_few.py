@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 TREE = {2: 6, 3: 4, 4: 3}
 
 
-@pytest.mark.parametrize("code_id,k", [(CODE_3INST, 2), (CODE_3INST, 3), (CODE_1MAD, 4), (CODE_HYB1, 2), (CODE_HYB, 2),
+@pytest.mark.parametrize("code_id,k", [(CODE_3INST, 2), (CODE_3INST, 3), (CODE_3INST, 4), (CODE_1MAD, 2), (CODE_1MAD, 3),
+                                       (CODE_1MAD, 4), (CODE_HYB1, 2), (CODE_HYB1, 3), (CODE_HYB1, 4), (CODE_HYB, 2),
                                        (CODE_HYB2, 2)])
 @pytest.mark.parametrize("m,n", [(16, 16), (48, 80), (16, 4096), (32, 2064), (16, 12288)])
 def test_one_launch_equals_several(code_id, k, m, n):
@@ -36,15 +37,19 @@ def test_one_launch_equals_several(code_id, k, m, n):
         codes = torch.zeros(count, 8 * k, dtype=torch.int32, device="cuda")
         err = torch.zeros(count, device="cuda")
         q.qtip_quantize_gpu(W, m, W.shape[1], 16, k, V, code_id, lut, codes, err, ws, size)
-        return codes, err
+        # (only several launches keep the sequences' final states, below 2^16, at the workspace's head)
+        return codes, err, bool((ws[:4 * count].view(torch.int32) == -1).all())
 
     # several launches: among more sequences than one launch takes
     many = torch.cat([W, torch.randn(m, 16 * -(-769 // (m // 16)), device="cuda", generator=g)], dim=1)
     want = [x.view(m // 16, many.shape[1] // 16, -1)[:, :n // 16].reshape(tiles, -1)
-            for x in quantize(many, q.qtip_quantize_gpu_workspace(k, V, many.numel() // 256))]
+            for x in quantize(many, q.qtip_quantize_gpu_workspace(k, V, many.numel() // 256))[:2]]
     longest = {2: 8, 3: 8, 4: 5}[kv]
     least = -(-(steps - 1) // longest) - 1  # copies of the longest segments; the one fewer is several launches too
     every = -(-(steps - 1) // {2: 5, 3: 3, 4: 2}[kv]) - 1
     for copies in [least - 1, least, least + 1, (steps - 1) // TREE[kv] - 1, every - 1, every, every + 7]:
-        codes, err = quantize(W, max(smallest, head + tiles * copies * copy))
+        size = max(smallest, head + tiles * copies * copy)
+        codes, err, one = quantize(W, size)
+        room = (size - head) // (tiles * copy)
+        assert one == (tiles <= (768 if kv == 3 else 256) and room >= least and (kv > 2 or tiles <= 128 or room < every)), copies
         assert torch.equal(codes, want[0]) and torch.equal(err, want[1][:, 0]), copies
