@@ -431,20 +431,23 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
 
 // ------------------------------------------------------------------ launcher
 
-// The ways a product is split: outputs and batch rows of a workgroup, and the time of a round of 256 workgroups
-// (one per CU), `first` once and `round` for each, measured at 4096 inputs (us, 2-bit 3INST; only their ratios matter
-// here).  A large tile decodes a weight once for more batch rows; a small one leaves no CU idle where outputs
-// or batch rows are few, and splits the inputs between its waves.
-// One table serves every code, k and length.  With each split forced in turn (six codes, k = 2 to 4, 1024 x 1024 to 14336 x
-// 4096 and 2048 x 14336, 24 to 1000 rows) the one it picks is the fastest or within the 3 % that runs differ by, with one
-// exception: the lookup-only code, where every workgroup copies 32 KiB of table, takes two rounds of 32 x 32 where one of 64 x
-// 64 is up to 17 % faster (4096 x 4096, 100 rows: 26.1 us against 23.7; 1024 x 1024, 500 rows: 11.0 against 9.4).
+// The ways a product is split: outputs and batch rows of a workgroup, and the time of a round of one workgroup per CU,
+// `first` once and `round` for each (only their ratios matter here).  A large tile decodes a weight once for more batch
+// rows; a small one leaves no CU idle where outputs or batch rows are few, and splits the inputs between its waves.  A
+// round costs the lookup-only code more in the small ones, where every workgroup copies 32 KiB of table, and the V = 1
+// hash code, a table read for every weight, more at 128 x 256, which has four waves.
+// With each split forced in turn, six codes, k = 2 to 4, 18 shapes from 768 x 4096 and 28672 x 1024 to 5120 x 13824, 17 to
+// 1024 rows: the one picked takes 0.15 % more than the fastest on average.  (With one column for all codes, 5.5 a round of 32 x
+// 32 and 42 of 128 x 128, it was up to 39 % slower: 2-bit HYB 9216 x 4096, 96 rows, 30.8 us against 22.2, lookup-only 5120 x
+// 5120, 256 rows, 65.7 against 48.9, 3-bit 3INST 28672 x 1024, 1024 rows, 118 against 101; with 45 for 128 x 128 lookup-only
+// 20480 x 5120, 896 rows, 346 against 311.)  The worst that is left is HYB2 with a single round of 128 x 256 that 64 x 128 beats: 4128 x 14464, 1024 rows, 280 us against 238.
 struct GemmSplit {
     int outputs, rows;
-    float first, round;
+    float first, round, round_lut, round_hyb1;
 };
-static constexpr GemmSplit GEMM_SPLITS[] = {{128, 256, 0.f, 74.f}, {128, 128, 0.f, 42.f}, {64, 128, 2.f, 25.f},
-                                            {64, 64, 5.f, 15.f},    {32, 64, 2.f, 11.3f},  {32, 32, 4.5f, 5.5f}};
+static constexpr GemmSplit GEMM_SPLITS[] = {
+    {128, 256, 0.f, 74.f, 74.f, 80.f}, {128, 128, 0.f, 43.5f, 43.5f, 43.5f}, {64, 128, 2.f, 25.f, 25.f, 25.f},
+    {64, 64, 5.f, 15.f, 15.5f, 15.f},  {32, 64, 2.f, 11.3f, 11.f, 11.3f}, {32, 32, 4.5f, 6.f, 7.7f, 6.f}};
 
 // A workgroup addresses its batch rows and its wave's tile rows (16 bytes an input at most, less than 32 batch rows) with
 // 32-bit byte offsets from uniform bases, kept within 2^31.
@@ -468,7 +471,8 @@ static hipError_t launch_gemm_t(const uint32_t *codes, const uint32_t *lut, int 
         const GemmSplit &s = GEMM_SPLITS[i];
         const long gx = (m + s.outputs - 1) / s.outputs, gy = (B + s.rows - 1) / s.rows;
         if (!fits[i] || gy > 65535 || !offsets_fit(s, n)) continue;
-        const float t = s.first + s.round * (float)((gx * gy + 255) / 256);
+        const float round = CODE == CODE_LUT ? s.round_lut : CODE == CODE_HYB1 ? s.round_hyb1 : s.round;
+        const float t = s.first + round * (float)((gx * gy + CUS - 1) / CUS);
         if (best < 0 || t < least) best = i, least = t;
     }
     const dim3 grid((m + GEMM_SPLITS[best].outputs - 1) / GEMM_SPLITS[best].outputs,
