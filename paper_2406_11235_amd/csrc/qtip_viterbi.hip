@@ -36,7 +36,8 @@
 // give the same bits as the forward kernel, so the walk is the one its minima imply.
 // Where there are few sequences four waves share a tree, one p_1 (or a quarter of them) each, and
 // compare their roots: BlockLDLQ of 2048 x 1024, 128 sequences at a time, 48.4 -> 46.0 ms; and with at most one
-// sequence per CU one kernel does all of Algorithm 4 (viterbi_few_kernel).
+// sequence per CU, at kV = 3 three, one kernel does all of Algorithm 4 (viterbi_few_kernel; not at kV = 6 and 8, HYB with 3 and 4
+// bits, and not for the lookup-only code, which it has no trees for: they take several launches whatever their number).
 // The copies go through the caches as they come: written and read with the non-temporal hint the same
 // case takes 46.4 ms, and thousands of sequences the same.
 // Algorithm 4 is forward / walk to the middle / constrained forward / full walk.
@@ -584,10 +585,10 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
 // copies asks for: `nseg` segments of T + F steps, lengths differing by one at most.
 // The last forward step of a segment is only taken for the prefixes that the tree hangs on, a few of each thread; with F = 0
 // level T takes entries and codes from the registers they arrive in.
-//   What bounds it is still the issue of the forward steps: 255 of 2043 cycles in each pass (kV = 2, V = 1), 453 of 635 us.  (us,
-// several launches | here, 128 sequences, the workspace callers are told to bring: 3INST k = 2 732 | 635, k = 3 993 | 641, k = 4
-// 777 | 635, HYB 928 | 800; BlockLDLQ of 2048 x 256 11.44 ms | 10.01, of 3-bit 1024 x 256 15.94 | 10.34.  With every copy through
-// LDS and all of a tree's codes formed anew: 3INST 671, 693, 648, HYB 821.)
+//   What bounds it is still the issue of the forward steps: 255 of 2043 cycles in each pass (kV = 2, V = 1), 453 of 620 to 635 us.
+// (Several launches and this one are compared where the launcher chooses; BlockLDLQ of 2048 x 256 11.44 | 10.01 ms, of 3-bit
+// 1024 x 256 15.94 | 10.34.  With every copy through LDS and all of a tree's codes formed anew, 128 sequences, against 635,
+// 641, 635 and 800 us on that card: 3INST k = 2 to 4 671, 693, 648, HYB 821.)
 template <int KV, int V> struct FewGeo : VitGeo<KV, V, 16> {
     static constexpr int T = KV == 2 ? 6 : KV == 3 ? 4 : 3;    // levels of a tree
     static constexpr int NODES = 1 << (KV * (T - 1));          // of level T - 1
@@ -1061,18 +1062,19 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
     const int tn = n / TY;
     const long ntiles = (long)(m / TX) * tn;
     // One launch for at most one sequence per CU; three at kV = 3, where walks and forward passes repeat the most steps.  (us, with
-    // the workspace callers are told to bring, 128 | 256 | 512 sequences, several launches and one: 3INST k = 2 742 663 | 806
-    // 736 | 1332 1381, k = 3 976 628 | 1075 687 | 2035 1325, k = 4 767 630 | 835 681 | 1382 1333, HYB k = 2 954 822 | 983 842 |
-    // 1553 1594; k = 3 of 768 2062 1967, of 1024 2742 2668.  With room for every copy k = 2 650 619 | 709 768, k = 3 722 553 |
-    // 765 615 | 1430 1229 and of 768 1949 1820, k = 4 659 593 | 709 627 | 1179 1218, HYB 777 756 | 802 773 | 1438 1491: at kV = 2
-    // the launches stay apart there if more than half of the CUs have a sequence, all of them storing every copy.)
+    // the workspace callers are told to bring, 128 | 256 | 512 sequences, several launches and one: 3INST k = 2 698 619 | 724
+    // 663 | 1272 1307, k = 3 982 644 | 984 650 | 1992 1292, k = 4 761 636 | 762 642 | 1331 1284, HYB k = 2 920 796 | 916 801 |
+    // 1534 1600; k = 3 of 768 2023 1933, of 1024 2695 2579.  With room for every copy k = 2 618 588 | 640 686, k = 3 659 562 |
+    // 675 596 | 1187 1186, of 520 1650 1745 and of 768 1702 1768, k = 4 649 594 | 666 601 | 1153 1192, HYB 756 743 | 767 746 | 1425
+    // 1492: the launches stay apart there, all of them storing every copy, at kV = 2 if more than half of the CUs have a
+    // sequence, at kV = 3 if some have three.)
     if constexpr (KV <= 4 && code_state_bits(CODE) == 16) {
         using Few = FewGeo<KV, V>;
-        if (ntiles <= (KV == 3 ? 768 : 256)) {
+        if (ntiles <= (KV == 3 ? 3 * CUS : CUS)) {
             const size_t copy_bytes = (size_t)ntiles * Geo::NP * sizeof(float);
             const size_t room = ws_bytes > head_bytes(ntiles) ? (ws_bytes - head_bytes(ntiles)) / copy_bytes : 0;
             const long slots = (long)(room < (size_t)VT_T ? room : (size_t)VT_T);
-            const bool pays = KV > 2 || ntiles <= 128 || slots < Geo::NSEG - 1;
+            const bool pays = ntiles <= (KV == 2 ? CUS / 2 : KV == 3 ? 2 * CUS : CUS) || slots < Geo::NSEG - 1;
             const int nseg1 = (int)(slots < Few::D1 / Few::T ? slots : Few::D1 / Few::T);
             const int nseg2 = (int)(slots + 1 < Few::D2 / Few::T ? slots + 1 : Few::D2 / Few::T);
             if (pays && Few::fits(Few::D1, nseg1) && Few::fits(Few::D2, nseg2)) {

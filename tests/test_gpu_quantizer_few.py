@@ -1,4 +1,4 @@
-"""Up to 256 sequences (768 at k = 3) go through Algorithm 4 in one launch where the workspace asks for it: the same streams
+"""Up to 256 sequences (768 at kV = 3) go through Algorithm 4 in one launch where the workspace asks for it: the same streams
 and errors, bit for bit, as from several launches, for every number of copies that the workspace can hold."""
 import pytest
 
@@ -51,5 +51,6 @@ def test_one_launch_equals_several(code_id, k, m, n):
         size = max(smallest, head + tiles * copies * copy)
         codes, err, one = quantize(W, size)
         room = (size - head) // (tiles * copy)
-        assert one == (tiles <= (768 if kv == 3 else 256) and room >= least and (kv > 2 or tiles <= 128 or room < every)), copies
+        assert one == (tiles <= (768 if kv == 3 else 256) and room >= least and
+                       (tiles <= {2: 128, 3: 512, 4: 256}[kv] or room < every)), copies
         assert torch.equal(codes, want[0]) and torch.equal(err, want[1][:, 0]), copies
