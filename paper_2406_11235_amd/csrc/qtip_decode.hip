@@ -341,11 +341,12 @@ __device__ __forceinline__ void matvec_tile_row(int I, int Iend, int part, bool 
     finish_row(0);
 }
 // TAIL 2 or 4: the tile rows from `whole` on are split into as many parts, by workgroups behind those of the whole ones (ahead
-// of them, or the whole rows in a loop over at most 512 workgroups, is slower: 3INST 14336 x 4096 10.44, 10.85 and 10.52 us,
-// 1MAD 5120 x 8192 8.45, 9.51 and 11.5).  ROUNDS, for the V = 1 hash code, of which one workgroup fits a CU, so that nothing is decoded
+// of them, or the whole rows in a loop over at most 512 workgroups, is slower; in this order, on one card: 3INST 14336 x 4096
+// 10.44, 10.85 and 10.52 us, 1MAD 5120 x 8192 8.45, 9.51 and 11.5).  ROUNDS, for the V = 1 hash code, of which one workgroup fits a CU, so that nothing is decoded
 // while another one begins and ends: the whole rows in rounds over at most 256 workgroups that keep their table and
-// have the next row's words under way, then the others' parts, if any (k = 4, 14336 x 4096 19.0 -> 15.2 us).
-// (The arguments are 64 bytes; with one more, `whole`, a launch of the smallest layers cost the host 0.2 us more.)
+// have the next row's words under way, then the others' parts, if any (14336 x 4096 k = 4 19.1 -> 15.5 us, k = 2 16.7 -> 13.3).
+// (The arguments are 64 bytes; with four more, for `whole`, a pass over a 1024 x 1024 layer, this launch and one other, took
+// 8.05 us in place of 7.47.)
 template <int K, int V, int CODE, int S, int NW, bool FUSED, bool SPREAD = false, bool WIDE = false, int TAIL = 0,
           bool ROUNDS = false>
 __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void matvec_kernel(const uint32_t *__restrict__ codes,
@@ -649,9 +650,9 @@ static bool pick_hyb_spread(int code, int n) {
 // and more gain nothing: a whole tile row per CU fills its issue slots.  The choice depends on the sizes alone, so
 // that the kernel that transforms its own input makes the same one.)
 // With more tile rows than CUs the ones behind the last whole round may be split alone, by the same measure, if the row is
-// long enough for 16 waves (us, all rows whole and so: 1MAD k = 3 14336 x 4096 10.9 10.3, 6144 x 4096 6.06 5.44, 5120 x 8192 10.4
-// 8.05, 2-bit 3INST 9216 x 4096 7.95 6.84, 4-bit HYB 10240 x 8192 20.3 14.9, HYB2 5120 x 28672 24.7 18.6) and their parts are
-// one workgroup per CU at most.  More of them are slower than whole rows, of which a CU has two at a time (4-bit HYB,
+// long enough for 16 waves (us, all rows whole and so, codes from memory: 1MAD k = 3 14336 x 4096 11.6 11.4, 6144 x 4096 6.7
+// 6.0, 5120 x 8192 10.8 8.7, 2-bit 3INST 9216 x 4096 8.4 7.6, 4-bit HYB 10240 x 8192 21.6 16.5, HYB2 5120 x 28672 k = 2 25.5 21.0,
+// k = 4 50.7 28.2) and their parts are one workgroup per CU at most.  More of them are slower than whole rows, of which a CU has two at a time (4-bit HYB,
 // 14336 inputs, whole and split: 416 tile rows 13.3 23.1, 448 13.5 24.5, 704 19.9 29.6; 3-bit 1MAD 448 18.3 22.1), but for the
 // 2-bit computed codes behind one round (1MAD, 416 rows: 17.7 16.5).  And where all rows in two halves were chosen before, halves
 // stay for two kinds of product: the V = 1 hash code's with short rows, whose halves have 8 waves and so go two to a CU (us,

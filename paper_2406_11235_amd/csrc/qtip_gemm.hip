@@ -440,7 +440,8 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
 // 1024 rows: the one picked takes 0.15 % more than the fastest on average.  (With one column for all codes, 5.5 a round of 32 x
 // 32 and 42 of 128 x 128, it was up to 39 % slower: 2-bit HYB 9216 x 4096, 96 rows, 30.8 us against 22.2, lookup-only 5120 x
 // 5120, 256 rows, 65.7 against 48.9, 3-bit 3INST 28672 x 1024, 1024 rows, 118 against 101; with 45 for 128 x 128 lookup-only
-// 20480 x 5120, 896 rows, 346 against 311.)  The worst that is left is HYB2 with a single round of 128 x 256 that 64 x 128 beats: 4128 x 14464, 1024 rows, 280 us against 238.
+// 20480 x 5120, 896 rows, 346 against 311.)  The worst that is left is HYB2 with a single round of 128 x 256 that 64 x 128
+// beats: 4128 x 14464, 1024 rows, 280 us against 238.
 struct GemmSplit {
     int outputs, rows;
     float first, round, round_lut, round_hyb1;

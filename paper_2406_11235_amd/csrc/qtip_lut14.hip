@@ -117,8 +117,11 @@ __global__ void lut_decode_states_kernel(const uint32_t *__restrict__ states, in
 // k = 3: 2048 x 8192 15.8 at S = 1, 6.8 at S = 4.
 // Where that leaves a last round nearly empty, the block rows of whole rounds (tm of them) are split so, and the rows of the
 // others, the tail, go round the same workgroups one by one: all waves of a workgroup on a row, a lane eight weights of
-// a block, so that the CUs' shares differ by one row.  4128 x 14464, 256 workgroups and 32 rows over, 25.5 -> 19.5 us (4096 x
-// 14464: 18.0); 8224 x 4096 15.1 -> 12.1; 4128 x 28672 41.1 -> 30.5.
+// a block, so that the CUs' shares differ by one row.  4128 x 14464, 256 workgroups and 32 rows over, 25.0 -> 19.0 us (4096 x
+// 14464: 17.6); 8224 x 4096 15.8 -> 12.4; 4128 x 28672 42.0 -> 32.0.
+// Beside the reads, which take 0.77 us per 1000 inputs of a CU's 16 rows (0.74 at the 7.1 cycles a read that its conflicts
+// cost), there are 4 us (4096 x 4096) to 5.4 (4096 x 14464): launch, filling the table, first words, the sum over waves and
+// the kernel's end, all of them exposed, as one workgroup has the CU to itself.
 constexpr int LUT_MAX_TAIL = 8;  // tail rows of a workgroup
 template <int K, int S, int NW, bool TAIL>
 __global__ __launch_bounds__(NW * 64, NW / 4) void lut_matvec_kernel(const uint32_t *__restrict__ codes,
