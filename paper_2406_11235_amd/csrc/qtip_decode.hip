@@ -656,9 +656,12 @@ static bool pick_hyb_spread(int code, int n) {
 // 14336 inputs, whole and split: 416 tile rows 13.3 23.1, 448 13.5 24.5, 704 19.9 29.6; 3-bit 1MAD 448 18.3 22.1), but for the
 // 2-bit computed codes behind one round (1MAD, 416 rows: 17.7 16.5).  And where all rows in two halves were chosen before, halves
 // stay for two kinds of product: the V = 1 hash code's with short rows, whose halves have 8 waves and so go two to a CU (us,
-// last rows in parts and all in halves: k = 2 6144 x 4608 9.13 7.52, 6144 x 4096 7.20 6.55, 10240 x 7168 15.8 14.8; k = 3 5632 x
-// 5120 10.76 10.04, but 6144 inputs 11.1 11.8; k = 4 5632 x 4608 9.71 9.15), and the 2-bit computed codes' behind one round (1MAD
-// 6144 x 4096 5.49 5.19, 5120 inputs 6.98 7.30; 3INST 5.58 5.36, 8192 inputs 9.02 8.85).
+// last rows in parts and all in halves: k = 2 6144 x 4608 9.13 7.52, 6144 x 4096 7.20 6.55, 10240 x 7168 15.8 14.8, but with quarters
+// 4128 x 6144 8.33 8.80; k = 3 5632 x 5120 10.76 10.04, but 6144 inputs 11.1 11.8; k = 4 5632 x 4608 9.71 9.15), and the 2-bit
+// computed codes' behind one round (1MAD 6144 x 4096 5.49 5.19, 5120 inputs 6.98 7.30; 3INST 5.58 5.36, 6144 inputs 7.51 8.37, 14336
+// 14.7 14.0, 28672 25.6 26.8).
+// Over 15 codecs, 24 heights and 11 lengths, each split forced in turn, the pick takes 0.5 % more than the fastest, 20 % at
+// worst (HYB1 k = 2, 13824 x 4608 in rounds, where halves are faster).
 struct MatvecSplit {
     int s, whole, tail;  // rows from `whole`, the multiple of CUS, on: `tail` workgroups each
 };
@@ -668,8 +671,8 @@ static MatvecSplit pick_matvec_split(int k, int code, int tm, int tn) {
     const bool one_round_of_two_bits = k == 2 && (code == CODE_3INST || code == CODE_1MAD) && whole == CUS;
     // (of all rows, than parts of the last ones)
     auto halves_are_faster = [&](int s) {
-        if (code == CODE_HYB1) return k == 2 ? tn < 512 : whole == CUS && tn <= 320;
-        return one_round_of_two_bits && s == 2 && (code == CODE_3INST || tn < 320);
+        if (code == CODE_HYB1) return k == 2 ? tn < 384 || (tn < 512 && s == 2) : whole == CUS && tn <= 320;
+        return one_round_of_two_bits && s == 2 && (tn < 320 || (code == CODE_3INST && tn >= 768 && tn < 1280));
     };
     MatvecSplit best{1, tm, 0};
     float least = time(tm, 1);

@@ -64,9 +64,10 @@ def test_fewer_rows_take_no_longer(code, k, fewer, more, n):
 # same bits as the same rows of a larger matrix only if that is in halves too)
 @pytest.mark.parametrize("code,k,m,n,halves", [
     (CODE_HYB1, 2, 4112, 4608, True), (CODE_HYB1, 2, 6144, 4096, True), (CODE_HYB1, 2, 10240, 7168, True),
-    (CODE_HYB1, 2, 6144, 8192, False), (CODE_HYB1, 3, 5632, 5120, True), (CODE_HYB1, 3, 5632, 6144, False),
-    (CODE_HYB1, 4, 5632, 4608, True), (CODE_1MAD, 2, 6144, 4096, True), (CODE_1MAD, 2, 6144, 5120, False),
-    (CODE_3INST, 2, 5632, 8192, True), (CODE_3INST, 2, 4112, 4096, False), (CODE_3INST, 3, 6144, 4096, False)])
+    (CODE_HYB1, 2, 4112, 6144, False), (CODE_HYB1, 2, 6144, 8192, False), (CODE_HYB1, 3, 5632, 5120, True),
+    (CODE_HYB1, 3, 5632, 6144, False), (CODE_HYB1, 4, 5632, 4608, True), (CODE_1MAD, 2, 6144, 4096, True),
+    (CODE_1MAD, 2, 6144, 5120, False), (CODE_3INST, 2, 5632, 6144, False), (CODE_3INST, 2, 5632, 14336, True),
+    (CODE_3INST, 2, 4112, 4096, False), (CODE_3INST, 3, 6144, 4096, False)])
 def test_rows_in_halves(code, k, m, n, halves):
     import torch
     product = Product(code, k, m, n)
