@@ -404,26 +404,30 @@ hipError_t launch_lut_decode_states(const uint32_t *states, int count, const voi
 
 // Workgroups per block row for the batch-1 kernel, and the block rows that are split so; the rows of the others are the
 // tail.  A CU's share of workgroups, each 1 us for its copy of the table and 32 n / S reads of the table, 8 cycles per 64, and
-// of tail rows, 0.3 us for all and each half a microsecond (a line of memory per lane, a sum over all waves) and its reads: the
-// smallest, over what S = 1, 2 and 4 make with a last round that is not full, and without it.  The tail's share is fitted to
-// every split forced in turn, k = 2 to 4, 36 to 688 block rows of 768 to 28672 inputs: no pick is more than 4 % slower than the one
-// made without tails (with half a microsecond and 1.05 times the reads per row it was up to 46 %: 4 bits, 100 block rows of 28672
-// inputs 29.3 -> 42.7 us, 216 of 14464 29.3 -> 42.6; 3 bits, 300 of 2048 9.6 -> 11.1).  Halves of more than two rounds and
-// quarters of more than one are never faster with a tail (4 bits, 216 of 28672: 65 us against 52 whole).
+// of tail rows, each half a microsecond (a line of memory per lane, a sum over all waves) and its reads: the smallest, over
+// what S = 1, 2 and 4 make with a last round that is not full, and without it.  At k = 4 a block is a line of 128 bytes, of
+// which a tail row's lane uses 8 and a quarter's lanes 32: both are dearer there.
+// Fitted to every split forced in turn, 16 to 768 block rows of 1024 to 28672 inputs, on the same buffers: the pick takes 1.3 %,
+// 0.3 and 0.2 % more than the fastest at k = 2, 3 and 4, 17 % at worst (k = 2).  (With one price for all k 576 block rows of
+// 28672 inputs at 4 bits went in quarters, 151 us in place of 120, and 704, 184 in place of 140; with a price of tail rows
+// fitted to 2 bits alone 100 of 28672 at 4 bits took 42.7 us in place of 29.3.)  Halves of more than two rounds and quarters of
+// more than one are never faster with a tail (4 bits, 216 of 28672: 65 us against 52 whole).
 struct LutSplit {
     int s, tm;
 };
-static LutSplit pick_lut_split(int tm, int n) {
+static LutSplit pick_lut_split(int k, int tm, int n) {
     LutSplit best{1, tm};
     float least = 0.f;
     for (int s = 1; s <= 4; s *= 2) {
         const float block_row = (float)n * (4.f / 2400.f);  // us
         const int rounds = (tm * s + CUS - 1) / CUS, full = tm * s / CUS;
-        const float t = (float)rounds * (1.f + block_row / s);
+        const float workgroup = k == 4 ? 1.2f + block_row / s * (s == 4 ? 1.15f : 1.f) : 1.f + block_row / s;
+        const float t = (float)rounds * workgroup;
         if (s == 1 || t < least) best = {s, tm}, least = t;
         if (full == 0 || full == rounds || (s > 1 && full * s > 4)) continue;
         const int each = ((tm - full * (CUS / s)) * LUT_TX + CUS * full - 1) / (CUS * full);
-        const float folded = (float)full * (1.f + block_row / s + each * (0.55f + 1.3f * block_row / LUT_TX)) + 0.3f;
+        const float tail_row = k == 4 ? 0.4f + 2.3f * block_row / LUT_TX : 0.55f + 1.3f * block_row / LUT_TX;
+        const float folded = (float)full * (workgroup + each * tail_row) + (k == 4 ? 0.45f : 0.3f);
         if (each <= LUT_MAX_TAIL && folded < least) best = {s, full * (CUS / s)}, least = folded;
     }
     return best;
@@ -433,7 +437,7 @@ template <int K>
 static hipError_t lut_matvec_t(const uint32_t *codes, const uint16_t *tab, int m, int n, const void *x,
                                const void *scale, float *y, hipStream_t st) {
     const int tn = n / LUT_TY;
-    const auto [s, tm] = pick_lut_split(m / LUT_TX, n);
+    const auto [s, tm] = pick_lut_split(K, m / LUT_TX, n);
     const int tail_rows = m - LUT_TX * tm;  // (with a tail every workgroup of the grid has a part of a block row)
     const dim3 grid((tm + 7) / 8 * 8 * s);
 #define QTIP_LUT_MV2(S, NW, TAIL)                                                                             \

@@ -49,11 +49,12 @@ class Product:
 
 
 # (times of the fewer rows over those of the more with the parts of the rows behind whole rounds in more than one round of
-# their own: 1.3 to 1.75; the lookup-only code's with rows round the workgroups at too low a price: 1.25 to 1.47)
+# their own: 1.3 to 1.75; the lookup-only code's with rows round the workgroups or quarters at too low a price: 1.25 to 1.47)
 @pytest.mark.parametrize("code,k,fewer,more,n", [
     (CODE_HYB, 4, 7168, 8192, 14336), (CODE_HYB, 3, 11264, 12288, 14336), (CODE_HYB2, 4, 11264, 12288, 14336),
     (CODE_3INST, 4, 7168, 8192, 14336), (CODE_HYB1, 4, 7168, 8192, 28672),
-    (CODE_LUT, 4, 3200, 4096, 28672), (CODE_LUT, 4, 6912, 8192, 14464), (CODE_LUT, 4, 6912, 8192, 28672)])
+    (CODE_LUT, 4, 3200, 4096, 28672), (CODE_LUT, 4, 6912, 8192, 14464), (CODE_LUT, 4, 6912, 8192, 28672),
+    (CODE_LUT, 4, 22528, 24576, 28672)])
 def test_fewer_rows_take_no_longer(code, k, fewer, more, n):
     product = Product(code, k, more, n)
     a, b = product.us(fewer), product.us(more)
