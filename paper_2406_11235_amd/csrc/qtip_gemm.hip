@@ -54,12 +54,19 @@ __device__ __forceinline__ void add_halves_last(uint32_t y0, uint32_t y1, uint32
         : "v"(y0), "v"(y1));
 }
 
-// Eight weights from the 64 bits at their first one, one per call of step<c>, as four packed pairs.
+// Eight weights from the 64 bits at their first one: what step<0> .. step<7>, called one after the other, leave in `raw` is made
+// four packed pairs by packed(), a step later, so that nothing waits for a table read just made.
+//   The hash codes hash two states at once in the halves of a register: states 4 K bits apart, which are two halves of
+// one window at k = 4 and otherwise brought together by one v_perm_b32.  (One state at a time, values taken as soon as read and the
+// table behind the first 64 KiB of LDS, where a read's address needs an instruction more: 64 rows of 8192 x 8192, k = 2 HYB 18.2 us
+// and now 16.9, k = 3 HYB2 20.3 and 18.6, k = 4 HYB1 25.6 and 22.2; 40 rows of 4096 x 14336, HYB1, 29.3 and 25.0; with what is said
+// at the copies of a stage.)
 template <int K, int CODE> struct EightWeights {
+    static constexpr int RAW = CODE == CODE_HYB2 ? 6 : CODE == CODE_HYB1 || CODE == CODE_LUT ? 8 : 4;
     uint64_t b64;
     uint32_t mm, lane4;
     const uint32_t *lut;  // LDS
-    uint32_t w[2], t[4];
+    uint32_t w[2], t[2];
     __device__ __forceinline__ void init(const uint32_t *lds_lut) {
         lut = lds_lut;
         lane4 = (threadIdx.x & 31u) << 2;
@@ -77,39 +84,68 @@ template <int K, int CODE> struct EightWeights {
             w[1] = K == 2 ? 0u : w1 << shift;
         }
     }
-    template <int c> __device__ __forceinline__ void step(uint32_t (&h)[4]) {
+    // the states at bits P (high half) and P + 4 K (low half)
+    template <int P> __device__ __forceinline__ uint32_t state_pair() const {
+        if constexpr (K == 4) return window32(w, P);
+        else if constexpr (K == 2) return __builtin_amdgcn_perm(w[0] << P, w[0] << P, 0x03020201u);
+        else return __builtin_amdgcn_perm(window32(w, P), window32(w, P + 12), 0x07060302u);
+    }
+    // low 16 bits of x x + x of both halves
+    __device__ __forceinline__ static uint32_t hash_pair(uint32_t R) {
+        uint32_t H;
+        asm("v_pk_mad_u16 %0, %1, %1, %1" : "=v"(H) : "v"(R));
+        return H;
+    }
+    template <int c> __device__ __forceinline__ void step(uint32_t (&raw)[RAW]) {
         if constexpr (CODE == CODE_3INST) {
             // (four vector instructions per call: a weight's sum of halves goes behind the next one's multiply-add,
             // which needs a wait state before its result is read)
             const uint32_t Z = lcg_mad64(window16(w, c * K), INST_A, b64);
-            if constexpr (c % 2 == 1 && c < 7) add_halves_low(t[0], h[c / 2]);
-            if constexpr (c % 2 == 0 && c > 0) add_halves_high(t[1], h[c / 2 - 1]);
+            if constexpr (c % 2 == 1 && c < 7) add_halves_low(t[0], raw[c / 2]);
+            if constexpr (c % 2 == 0 && c > 0) add_halves_high(t[1], raw[c / 2 - 1]);
             t[c & 1] = (Z & INST_MASK) ^ mm;
-            if constexpr (c == 7) add_halves_last(t[0], t[1], h[3]);
+            if constexpr (c == 7) add_halves_last(t[0], t[1], raw[3]);
         } else if constexpr (CODE == CODE_1MAD) {
             const uint32_t X = lcg_mad64(window16(w, c * K), MAD_A, b64);
             const uint32_t s = __builtin_amdgcn_sad_u8(X, 0u, 0x4B000000u);  // float 2^23 + s
             t[c & 1] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(float, s) - 8389118.0f) * MAD_INV_SCALE);
             if constexpr (c & 1)
-                h[c / 2] = as_u32(half2_t{(half_t)__builtin_bit_cast(float, t[0]), (half_t)__builtin_bit_cast(float, t[1])});
+                raw[c / 2] = as_u32(half2_t{(half_t)__builtin_bit_cast(float, t[0]), (half_t)__builtin_bit_cast(float, t[1])});
         } else if constexpr (code_is_hyb(CODE)) {
-            if constexpr ((c & 1) == 0) {
-                const uint32_t st = window16(w, c * K);
-                const uint32_t X = st * st + st;
-                h[c / 2] = hyb_signed_lookup(lut, (X >> 4) & 0xFFCu);
-                if constexpr (CODE == CODE_HYB2) h[c / 2] ^= (X >> 16) & 0x8000u;
+            constexpr int j = c / 4;  // states j and j + 2
+            if constexpr (c % 4 == 0) {
+                const uint32_t R = state_pair<2 * K * j>();
+                if constexpr (CODE == CODE_HYB2) raw[4 + j] = hyb2_sign_mask(R);
+                t[0] = hash_pair(R);
+                raw[j] = hyb_signed_lookup(lut, (t[0] >> 20) & 0xFFCu);
+            } else if constexpr (c % 4 == 2) {
+                raw[j + 2] = hyb_signed_lookup(lut, (t[0] >> 4) & 0xFFCu);
             }
         } else if constexpr (CODE == CODE_HYB1) {
-            const uint32_t st = window16(w, c * K);
-            const uint32_t X = st * st + st;
-            t[c & 1] = hyb_signed_lookup(lut, ((X >> 2) & 0x3F80u) | lane4);
-            if constexpr (c & 1) h[c / 2] = hyb1_pair(t[0], t[1]);
+            constexpr int j = c / 2;  // states j and j + 4
+            if constexpr (c % 2 == 0) {
+                t[0] = hash_pair(state_pair<K * j>());
+                raw[j] = hyb_signed_lookup(lut, ((t[0] >> 18) & 0x3F80u) | lane4);
+            } else {
+                raw[j + 4] = hyb_signed_lookup(lut, ((t[0] >> 2) & 0x3F80u) | lane4);
+            }
         } else {
             // 14 state bits to bits 14..1
             const uint32_t off = c * K < 17 ? (w[0] >> (17 - c * K)) & 0x7FFEu : window32(w, c * K - 17) & 0x7FFEu;
-            t[c & 1] = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(lut) + off);
-            if constexpr (c & 1) h[c / 2] = t[0] | (t[1] << 16);
+            raw[c] = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(lut) + off);
         }
+    }
+    __device__ __forceinline__ static half8_t packed(const uint32_t (&raw)[RAW]) {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 h;
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            if constexpr (CODE == CODE_HYB1) h[c] = hyb1_pair(raw[2 * c], raw[2 * c + 1]);
+            else if constexpr (CODE == CODE_LUT) h[c] = raw[2 * c] | (raw[2 * c + 1] << 16);
+            else if constexpr (CODE == CODE_HYB2) h[c] = raw[c] ^ ((c < 2 ? raw[4 + c] >> 16 : raw[2 + c]) & 0x8000u);
+            else h[c] = raw[c];
+        }
+        return __builtin_bit_cast(half8_t, h);
     }
 };
 
@@ -156,7 +192,7 @@ template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS> struct GemmL
     // batch groups whose partial sums are in LDS at the same time, in the room of the activations
     static constexpr int SUM_BYTES = WM * WK * RB * 4096;
     static constexpr int SUMS = WK == 1 ? 0 : NBB * SUM_BYTES <= 2 * WK * SLICE ? NBB : (2 * WK * SLICE) / SUM_BYTES;
-    static constexpr int BYTES = 2 * WK * SLICE + WM * WK * 2 * CODE_STAGE + 4 * TABLE_WORDS;
+    static constexpr int BYTES = 2 * WK * SLICE + WM * WK * 2 * CODE_STAGE + (4 * TABLE_WORDS + 1023) / 1024 * 1024;
     static_assert(WK == 1 || (SUMS >= 1 && NBB % SUMS == 0), "whole rounds of partial sums");
 };
 
@@ -185,25 +221,55 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
     constexpr int STEP_BYTES = Lds::STEP_BYTES, CODE_ROW = Lds::CODE_ROW, CODE_ROWS = Lds::CODE_ROWS;
     constexpr int CODE_COPIES = Lds::CODE_COPIES, CODE_STAGE = Lds::CODE_STAGE;
     constexpr int COPIES = CODE_COPIES + NCOPY;
-    constexpr auto copy_group = [](int c) { return c * (GROUPS / 2) / COPIES; };
-    static_assert(KS >= 2 && COPIES <= 60, "a stage holds the step after the next; the count of a wait");
+    // The group behind which a copy is made: the next stage's are spread over the first half of this one.  Code words come from
+    // memory, not from the caches, and are waited for in the middle of a stage.  Where few batch rows make stages short, those
+    // of the stage after the next are asked for as soon as this one's have all been read, at step KS - 2, a whole stage
+    // ahead of that wait in place of half of one (8192 x 8192, 4-bit HYB, 32 rows 16.3 -> 14.8 us, 64 rows 21.4 -> 20.9, one
+    // stage more ahead 22.1; but 200 rows of 12288 x 8192, 3-bit 3INST, 73.7 -> 75.0).
+    constexpr bool EARLY = WM == 1;
+    constexpr auto copy_group = [](int c) {
+        if (!EARLY) return c * (GROUPS / 2) / COPIES;
+        return c < CODE_COPIES ? (KS - 2) * NBB * RB + RB - 1 + c * (GROUPS / KS) / CODE_COPIES
+                               : (c - CODE_COPIES) * (GROUPS / 2) / NCOPY;
+    };
+    // Copies made behind the code words of the next stage at the wait for them, and behind the next stage's last activations.
+    constexpr int WAIT_GROUP = ((KS - 2) * NBB + NBB / 2) * RB;
+    constexpr int BEHIND_CODES = [=] {
+        int count = 0;
+        for (int c = EARLY ? 0 : CODE_COPIES; c < COPIES; c++) count += copy_group(c) <= WAIT_GROUP;
+        return count;
+    }();
+    constexpr int BEHIND_X = [=] {
+        int count = 0;
+        for (int c = 0; c < CODE_COPIES; c++) count += copy_group(c) > copy_group(COPIES - 1);
+        return count;
+    }();
+    static_assert(KS >= 2 && 2 * CODE_COPIES + NCOPY <= 60, "a stage holds the step after the next; the count of a wait");
     static_assert(BT % (RPI * WM) == 0, "whole copies");
-    __shared__ __attribute__((aligned(16))) uint32_t s_lut[Lds::TABLE_WORDS];
-    __shared__ __attribute__((aligned(1024))) char s_x[2 * WK * SLICE];
-    __shared__ __attribute__((aligned(1024))) char s_codes[WM * WK * 2 * CODE_STAGE];
+    // (in this order: the table's place in a read's 16 bits of offset)
+    __shared__ struct {
+        __attribute__((aligned(1024))) uint32_t lut[Lds::TABLE_WORDS];
+        __attribute__((aligned(1024))) char x[2 * WK * SLICE];
+        __attribute__((aligned(1024))) char codes[WM * WK * 2 * CODE_STAGE];
+    } s_all;
+    uint32_t *const s_lut = s_all.lut;
+    char *const s_x = s_all.x, *const s_codes = s_all.codes;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wm = wave % WM, wk = wave / WM;
     const int i = lane & 31, h = lane >> 5;
     const int o0 = (blockIdx.x * WM + wm) * (32 * RB);  // first output
     const int b0 = blockIdx.y * BT;
-    const int tn = (n + 15) / 16;                         // steps
-    const int per = (tn + WK * KS - 1) / (WK * KS) * KS;  // of a slice
-    const int J0 = wk * per, Jend = min(tn, J0 + per);
-    const int stages = per / KS;
+    // Places along the inputs are counted in pieces of eight, half a step each.  A slice's stages end where the slice ends, so
+    // that a stage with less than KS steps is the first one, copied ahead of the loop: in the loop no copy looks where it
+    // is (at 32 x 64, 4-bit HYB, 72 vector instructions a stage with that, 58 without).
+    const int all = n / 8, per = (all + WK * UNITS - 1) / (WK * UNITS) * UNITS;  // of a slice
+    const int P0 = wk * per, Pend = min(all, P0 + per);
+    const int stages = per / UNITS, mine = P0 < Pend ? (Pend - P0 + UNITS - 1) / UNITS : 0;
+    const int Pfirst = Pend - mine * UNITS;  // (may be less than P0, and less than 0)
 
-    // The wave's code words of a stage: the KS tiles of a tile row lie one after the other, so whole pieces of 16
-    // bytes are copied into LDS as they are.  (Behind a row's last tile comes the next row, behind the buffer
-    // zeros: any weights do there, their inputs are zeros.)
+    // The wave's code words of a stage: the KS tiles of a tile row lie one after the other, so whole 16
+    // bytes are copied into LDS as they are.  (Any weights do ahead of a slice, their inputs are zeros.  The copies that the last
+    // stage makes for one that does not come stay inside the buffer or bring zeros.)
     constexpr int r_first = LUT ? 32 : 16;
     const size_t line = (size_t)(LUT ? n / 8 : n / 16) * (4 * NWORDS);  // bytes of a tile row
     const int I_base = min(o0, m - 1) / r_first;
@@ -211,50 +277,54 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
         buffer_of(reinterpret_cast<const char *>(codes) + (size_t)I_base * line, ((size_t)(m / r_first) - I_base) * line);
     char *const my_codes = s_codes + wave * (2 * CODE_STAGE);
     uint32_t coff[CODE_COPIES];
+    int ahead[CODE_COPIES];  // bytes from there to the first stage's
 #pragma unroll
     for (int q = 0; q < CODE_COPIES; q++) {
         const int at = (64 * q + lane) * 16, r = min(at / CODE_ROW, CODE_ROWS - 1);
         const int I = min(o0 + r * r_first, m - 1) / r_first - I_base;  // (beyond m: any row)
         coff[q] = (uint32_t)I * (uint32_t)line + at % CODE_ROW;
+        ahead[q] = max(at % CODE_ROW + Pfirst * (STEP_BYTES / 2), 0) - at % CODE_ROW;
     }
     const int bit = first_bit<K, CODE>(i, h);
     const int w0 = bit >> 5, w1 = (w0 + 1) % NWORDS;  // (wraps inside a tile: tail-biting)
     const uint32_t selector = 0x07060504u - (uint32_t)((bit & 31) >> 3) * 0x01010101u, shift = bit & 31;
     const char *const code_words = my_codes + (LUT ? h * 4 * NWORDS : (i >> 4) * CODE_ROW);
-    auto copy_codes = [&](auto qc, int J, int buffer) {
+    auto copy_codes = [&](auto qc, uint32_t offset, uint32_t at, int buffer) {
         constexpr int q = decltype(qc)::value;
-        copy_to_lds(code_buffer, coff[q], min(J, tn - 1) * STEP_BYTES, my_codes + buffer * CODE_STAGE + q * 1024);
+        copy_to_lds(code_buffer, offset, at, my_codes + buffer * CODE_STAGE + q * 1024);
     };
     // copies into LDS: lane = (row within the instruction, place of the piece)
     auto swizzle = [](int row) { return (row / (16 / UNITS)) & (UNITS - 1); };
     const int crow = lane / UNITS;
     char *const slice = s_x + wk * (2 * SLICE);
-    const int rows = min(BT, B - b0), pieces = min(2 * Jend, n / 8);
+    const int rows = min(BT, B - b0);
     uint32_t xoff[NCOPY];
-    int piece[NCOPY];
-#pragma unroll
-    for (int q = 0; q < NCOPY; q++) {
-        const int b = (wm * NCOPY + q) * RPI + crow;
-        piece[q] = (lane % UNITS) ^ swizzle(q * RPI + crow) ^ (NCOPY % 2 ? swizzle(wm * NCOPY * RPI) : 0);
-        xoff[q] = (uint32_t)min(b, rows - 1) * (uint32_t)(2 * n) + 16 * piece[q];
-    }
     const char *const xbase = reinterpret_cast<const char *>(X + (size_t)b0 * n);
     const u32x4_t x_buffer = buffer_of(xbase, (size_t)rows * 2 * n);
-    auto copy_x = [&](auto qc, int J, int buffer) {
+    auto copy_x = [&](auto qc, uint32_t offset, uint32_t at, int buffer) {
         constexpr int q = decltype(qc)::value;
-        // Pieces beyond the slice's end are asked for beyond the buffer's end, so that zeros arrive: the weights of
-        // their steps are the last tile's again.
-        // (the uniform offset stays inside the buffer: the check subtracts it from the buffer's size)
-        copy_to_lds(x_buffer, 2 * J + piece[q] < pieces ? xoff[q] : 0xFFFFFF00u, 32 * min(J, tn - 1),
-                    slice + buffer * SLICE + (wm * NCOPY + q) * 1024);
+        copy_to_lds(x_buffer, offset, at, slice + buffer * SLICE + (wm * NCOPY + q) * 1024);
     };
+    // (the first stage's, on their way while the table is filled)
+    static_for<CODE_COPIES>([&](auto qc) {
+        if (mine > 0) copy_codes(qc, coff[decltype(qc)::value] + (uint32_t)ahead[decltype(qc)::value], 0, 0);
+    });
+    static_for<NCOPY>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        const int b = (wm * NCOPY + q) * RPI + crow;
+        const int piece = (lane % UNITS) ^ swizzle(q * RPI + crow) ^ (NCOPY % 2 ? swizzle(wm * NCOPY * RPI) : 0);
+        xoff[q] = (uint32_t)min(b, rows - 1) * (uint32_t)(2 * n) + 16 * piece;
+        // what lies ahead of the slice is asked for beyond the buffer's end, so that zeros arrive
+        if (mine > 0) copy_x(qc, Pfirst + piece >= P0 ? xoff[q] + (uint32_t)(16 * Pfirst) : 0xFFFFFF00u, 0, 0);
+    });
+    if constexpr (EARLY) {
+        static_for<CODE_COPIES>([&](auto qc) {
+            if (mine > 0) copy_codes(qc, coff[decltype(qc)::value], (uint32_t)min(Pfirst + UNITS, all - 1) * (STEP_BYTES / 2), 1);
+        });
+    }
     // a lane's place in a buffer: row i, piece 2 j + h
     const uint32_t xread = (uint32_t)i * ROW + (uint32_t)((h ^ swizzle(i)) << 4);
 
-    if (J0 < Jend) {
-        static_for<CODE_COPIES>([&](auto q) { copy_codes(q, J0, 0); });
-        static_for<NCOPY>([&](auto q) { copy_x(q, J0, 0); });
-    }
     if constexpr (LUT) {
         const uint4 *src = reinterpret_cast<const uint4 *>(lut);
         uint4 *dst = reinterpret_cast<uint4 *>(s_lut);
@@ -280,7 +350,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
             for (int nb = 0; nb < NBB; nb++) total[rb][nb] += acc[rb][nb];
     };
 
-    uint32_t wnext[RB][4];  // the decoded weights of the next step
+    uint32_t wnext[RB][EightWeights<K, CODE>::RAW];  // the weights of the next step
     uint32_t cw[RB][2];  // the two words that the next eight weights start in
     auto read_codes = [&](int step, int buffer) {
 #pragma unroll
@@ -292,7 +362,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
     };
     __builtin_amdgcn_s_waitcnt(vmcnt_only(0));  // the first stage is there
     __syncthreads();
-    if (J0 < Jend) {
+    if (mine > 0) {
         read_codes(0, 0);
 #pragma unroll
         for (int rb = 0; rb < RB; rb++) {
@@ -301,11 +371,11 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
         }
         read_codes(1, 0);
     }
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const int mine = J0 < Jend ? (Jend - J0 + KS - 1) / KS : 0;
     // fresh: the running sums start again
     auto stage = [&](int s, auto fresh) {
-        const int J = J0 + s * KS;
+        // first pieces of the next stage, and of the stage whose code words are copied in this one
+        const uint32_t next = min(Pfirst + (s + 1) * UNITS, all - 1);
+        const uint32_t codes_of = EARLY ? min(Pfirst + (s + 2) * UNITS, all - 1) : next;
         const char *const buf = slice + (s & 1) * SLICE;
         // the activations of a stage, KS * NBB operands, are read from LDS AHEAD operands before their use
         half8_t xv[AHEAD + 1];
@@ -320,7 +390,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
             half8_t wv[RB];
 #pragma unroll
             for (int rb = 0; rb < RB; rb++) {
-                wv[rb] = __builtin_bit_cast(half8_t, u32x4{wnext[rb][0], wnext[rb][1], wnext[rb][2], wnext[rb][3]});
+                wv[rb] = EightWeights<K, CODE>::packed(wnext[rb]);
                 dec[rb].start(cw[rb][0], cw[rb][1], selector, shift);
             }
             static_for<NBB>([&](auto nbc) {
@@ -335,10 +405,15 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
                     static_for<COPIES>([&](auto cc) {
                         constexpr int c = decltype(cc)::value;
                         if constexpr (copy_group(c) == group) {
+                            if constexpr (EARLY && c == 0) {  // (the words read last, which the copy replaces, are in registers)
+#pragma unroll
+                                for (int rb = 0; rb < RB; rb++) asm volatile("" : "+v"(cw[rb][0]), "+v"(cw[rb][1]));
+                            }
                             if constexpr (c < CODE_COPIES)
-                                copy_codes(std::integral_constant<int, c>{}, J + KS, (s + 1) & 1);
+                                copy_codes(std::integral_constant<int, c>{}, coff[c], codes_of * (STEP_BYTES / 2),
+                                           (s + !EARLY) & 1);
                             else
-                                copy_x(std::integral_constant<int, c - CODE_COPIES>{}, J + KS, (s + 1) & 1);
+                                copy_x(std::integral_constant<int, c - CODE_COPIES>{}, xoff[c - CODE_COPIES], 16 * next, (s + 1) & 1);
                         }
                     });
                     static_for<8 / NBB>([&](auto pc) {
@@ -349,7 +424,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
                         if constexpr (j + 2 < KS) {
                             read_codes(j + 2, s & 1);
                         } else {
-                            if constexpr (j + 2 == KS) __builtin_amdgcn_s_waitcnt(vmcnt_only(COPIES - CODE_COPIES));
+                            if constexpr (j + 2 == KS) __builtin_amdgcn_s_waitcnt(vmcnt_only(BEHIND_CODES));
                             read_codes(j + 2 - KS, (s + 1) & 1);
                         }
                     }
@@ -360,7 +435,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
         // The copies of this stage have landed, everywhere.  Where waves own different inputs (WM = 1) each reads only what
         // it copied, and waits for nothing else: in step they all decoded and all used the matrix cores at the same time
         // (8192 x 8192, 4-bit HYB, 64 rows 24.8 -> 21.0 us, 32 rows 17.8 -> 16.9).
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(BEHIND_X));
         asm volatile("" ::: "memory");
         if constexpr (WM > 1) {
             __builtin_amdgcn_s_barrier();
@@ -382,6 +457,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
     }();
     if constexpr (WM > 1)
         for (int s = mine; s < stages; s++) __builtin_amdgcn_s_barrier();  // (a slice with less or nothing to do)
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));  // (no copy is under way when the workgroup's LDS is another's)
     __syncthreads();
 
     // D element e of a lane: batch row 8 (e / 4) + 4 h + e % 4, output i

@@ -51,6 +51,15 @@ def test_splits(q, code, k):
         check(q, code, k, m, n, B, scaled=i % 2 == 0, seed=i)
 
 
+@pytest.mark.parametrize("code", list(CODES))
+@pytest.mark.parametrize("B", [20, 50, 70, 130])
+def test_slices_that_are_not_whole_stages(q, code, B):
+    """One to nine steps, and around whole stages of eight, four and two slices of the inputs: a slice's first stage begins
+    ahead of the slice, and of the row, with zeros for inputs."""
+    for n in [*range(16, 160, 16), 16 * 31, 16 * 32, 16 * 33, 16 * 61, 16 * 97]:
+        check(q, code, 2 + n // 16 % 3, 96, n, B, scaled=False, seed=n)
+
+
 def test_half_a_step_of_the_lookup_only_code(q):
     for n in (8, 24, 8 * 65, 8 * 129):
         for m, B in ((32, 18), (64, 70), (4128, 300), (16416, 700)):
