@@ -45,25 +45,29 @@ namespace {
 // panel's block columns.  Those with everything further right are taken beside the next panel, in its launch.
 // What bounds it is the chain of block columns, 4330 cycles each: rows of the pivot 280, inversion 2280, its way to LDS 530, the
 // meeting 160, two dependent products 900, the loop 190; the first three of a panel wait 2500 more for the products of the other
-// rows, which have three SIMDs; and the launch between two panels, 4.8 us.  n = 2048, g = 16: 1744 us with two launches
+// rows, which have three SIMDs; and the launch between two panels, 4 us.  n = 2048, g = 16: 1744 us with two launches
 // per block column, the inversion with five barriers per pivot and the products on the vector units, 388 us with the pivots
-// inverted by the waves of their rows, 343 us now; g = 8: 475 us -> 386 (144 bytes a lane of its pivots' wave lie in private
-// memory).  Meeting twice, or handing the next pivot's products' operands over through a flag half-way through the
+// inverted by the waves of their rows, 343 with a wave for the pivots, 318 us now; g = 8: 475 us -> 383 -> 368 (144 bytes a lane
+// of its pivots' wave lie in private memory).  Meeting twice, or handing the next pivot's products' operands over through a flag half-way through the
 // inversion, so that they run before the meeting, is no faster (350 to 371 us): the other rows are what is late then.
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef double double2_t __attribute__((ext_vector_type(2)));
-constexpr int LDL_PANEL = 8, LDL_MAX_ROWS = 4;
+constexpr int LDL_PANEL = 8;
 
 __device__ __forceinline__ double *ldl_block(double *base, int nb, int k, int i) {
     return base + ((size_t)k * nb + i) * 256;
 }
+// (a lane's four numbers are neighbours: two 16-byte accesses, in LDS as in memory; as four of 8 bytes n = 1040 took 154.0 us in
+// place of 150.5, 2048 331 in place of 318, 4096 1123 in place of 1077)
 __device__ __forceinline__ double4_t ldl_load(const double *block, int lane) {
-    return double4_t{block[lane], block[64 + lane], block[128 + lane], block[192 + lane]};
+    const double2_t lo = *reinterpret_cast<const double2_t *>(block + 4 * lane);
+    const double2_t hi = *reinterpret_cast<const double2_t *>(block + 4 * lane + 2);
+    return double4_t{lo[0], lo[1], hi[0], hi[1]};
 }
 __device__ __forceinline__ void ldl_store(double *block, int lane, double4_t v) {
-#pragma unroll
-    for (int t = 0; t < 4; t++) block[64 * t + lane] = v[t];
+    *reinterpret_cast<double2_t *>(block + 4 * lane) = double2_t{v[0], v[1]};
+    *reinterpret_cast<double2_t *>(block + 4 * lane + 2) = double2_t{v[2], v[3]};
 }
 // c + X^T Y, the contraction over the rows of X and Y
 __device__ __forceinline__ double4_t ldl_product(double4_t x, double4_t y, double4_t c) {
@@ -74,26 +78,39 @@ __device__ __forceinline__ double4_t ldl_product(double4_t x, double4_t y, doubl
 
 // T from the lower triangle of H, a diagonal block's upper half from its lower one (what H holds above its diagonal is
 // nobody's to read, the blocks between the two 8 x 8 blocks of a g = 8 pivot included), and zeros where A has no block of
-// its own.
-__global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict__ H, double *__restrict__ T,
-                                                       float *__restrict__ A, int n) {
-    const int nb = n >> 4, lane = threadIdx.x & 63;
-    const int i = blockIdx.y, r = lane >> 2, m = lane & 3;  // row r, columns 4 m .. 4 m + 3 of the block
+// its own: block row i, four block columns from j0 on, by one wave.
+__device__ __forceinline__ void ldl_init(const double *__restrict__ H, double *__restrict__ T, float *__restrict__ A, int n,
+                                         int i, int j0, int lane) {
+    const int nb = n >> 4, r = lane >> 2, m = lane & 3;  // row r, columns 4 m .. 4 m + 3 of the block
     const double *h = H + (size_t)(16 * i + r) * n + 4 * m;
     float *a = A + (size_t)(16 * i + r) * n + 4 * m;
+    double v[4][4];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-        const int j = blockIdx.x * 16 + 4 * e + (threadIdx.x >> 6);
+        const int j = j0 + e;
+        if (j >= nb || j > i) continue;
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+            v[e][c] = j < i || 4 * m + c <= r ? h[16 * j + c] : H[(size_t)(16 * i + 4 * m + c) * n + 16 * i + r];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const int j = j0 + e;
         if (j < nb && j >= i) {
 #pragma unroll
             for (int c = 0; c < 4; c++) a[16 * j + c] = 0.f;
         }
-        if (j > i) continue;
-        double *t = ldl_block(T, nb, j, i) + 64 * m + r;
+        if (j >= nb || j > i) continue;
+        double *t = ldl_block(T, nb, j, i) + lane;
 #pragma unroll
-        for (int c = 0; c < 4; c++)
-            t[16 * c] = j < i || 4 * m + c <= r ? h[16 * j + c] : H[(size_t)(16 * i + 4 * m + c) * n + 16 * i + r];
+        for (int c = 0; c < 4; c++) t[64 * c] = v[e][c];
     }
+}
+// Block columns below `columns`, four per wave.
+__global__ __launch_bounds__(256) void ldl_init_kernel(const double *__restrict__ H, double *__restrict__ T,
+                                                       float *__restrict__ A, int n, int columns) {
+    const int w = blockIdx.x * 4 + (threadIdx.x >> 6), of = (columns + 3) / 4;
+    if (w < of * (n >> 4)) ldl_init(H, T, A, n, w / of, 4 * (w % of), threadIdx.x & 63);
 }
 
 // The value that lane p of this row of 16 lanes has.  (What reads across lanes may not follow the vector instruction that
@@ -245,12 +262,32 @@ __device__ __forceinline__ void ldl_update_triangle(double *T, const double *Ms,
     while (ip * (ip + 1) / 2 > w) ip--;
     ldl_update<TB>(T, Ms, nb, J0, b0 + TB * (w - ip * (ip + 1) / 2), b0 + TB * ip, lane);
 }
-// The block columns of the panel behind the one at J0.
+// The block columns of the panel behind the one at J0: a block per workgroup, two of the panel's block columns per wave, all
+// operands asked for at once.  (A block per wave was 32 matrix instructions one behind the other: with this and with T made beside
+// the first panel n = 512 takes 71.8 us in place of 75.3, 1040 154.7 in place of 163.9, 2048 332 in place of 342.)
 __global__ __launch_bounds__(256) void ldl_update_panel_kernel(double *__restrict__ T, const double *__restrict__ Ms,
                                                                int nb, int J0) {
-    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    const int k = J0 + LDL_PANEL + w % LDL_PANEL, i = J0 + LDL_PANEL + w / LDL_PANEL;
-    if (i < nb && k <= i) ldl_update<1>(T, Ms, nb, J0, k, i, threadIdx.x & 63);
+    static_assert(LDL_PANEL == 8, "four waves of two block columns");
+    __shared__ __attribute__((aligned(16))) double s_sum[3][256];
+    const int w = blockIdx.x, k = J0 + LDL_PANEL + w % LDL_PANEL, i = J0 + LDL_PANEL + w / LDL_PANEL;
+    if (i >= nb || k > i) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, j = J0 + 2 * wave;
+    double *const block = ldl_block(T, nb, k, i);
+    double4_t x[2], y[2], old = {0.0, 0.0, 0.0, 0.0}, sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        x[e] = ldl_load(ldl_block(T, nb, j + e, k), lane);
+        y[e] = ldl_load(ldl_block(const_cast<double *>(Ms), nb, j + e, i), lane);
+    }
+    if (wave == 0) old = ldl_load(block, lane);
+#pragma unroll
+    for (int e = 0; e < 2; e++) sum = ldl_product(x[e], y[e], sum);
+    if (wave > 0) ldl_store(s_sum[wave - 1], lane, sum);
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int e = 0; e < 3; e++) sum += ldl_load(s_sum[e], lane);
+    ldl_store(block, lane, old - sum);
 }
 
 // The waves of a panel's workgroup: wave 0 inverts pivots, the others whose number is not a multiple of 4 have a block row
@@ -264,13 +301,13 @@ __device__ __forceinline__ int ldl_row_of(int p) {
 __device__ __forceinline__ void ldl_meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // The first `groups` workgroups: block columns J0 .. J0 + np - 1, and `rows` block rows below them per workgroup.  The others:
-// what the panel before has to subtract behind this one, TB x TB blocks per wave, on the CUs that the chain leaves idle.
-template <int G, int TB>
-__global__ __launch_bounds__(ldl_waves(LDL_MAX_ROWS) * 64) void ldl_panel_kernel(double *__restrict__ T,
-                                                                                 double *__restrict__ Ms,
-                                                                                 float *__restrict__ A, int n, int J0,
-                                                                                 int groups, int rows, int pairs,
-                                                                                 double *__restrict__ Dout) {
+// what the panel before has to subtract behind this one, TB x TB blocks per wave, on the CUs that the chain leaves idle; beside
+// the first panel the blocks of T behind it, where H is given.
+template <int G, int TB, int rows>
+__global__ __launch_bounds__(ldl_waves(rows) * 64) void ldl_panel_kernel(double *__restrict__ T, double *__restrict__ Ms,
+                                                                         float *__restrict__ A, int n, int J0, int groups,
+                                                                         int pairs, double *__restrict__ Dout,
+                                                                         const double *__restrict__ H) {
     static_assert(LDL_PANEL == 8, "ldl_row_of");
     // D_j^-1 as an A operand, and what L_ij^T is made with (for G = 8 see below)
     __shared__ __attribute__((aligned(16))) double s_inv[2][256];
@@ -281,8 +318,12 @@ __global__ __launch_bounds__(ldl_waves(LDL_MAX_ROWS) * 64) void ldl_panel_kernel
     const int nb = n >> 4, np = min(LDL_PANEL, nb - J0);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if ((int)blockIdx.x >= groups) {
-        const int w = (blockIdx.x - groups) * ldl_waves(rows) + wave;
-        if (w < pairs) ldl_update_triangle<TB>(T, Ms, nb, J0 - LDL_PANEL, J0 + LDL_PANEL, w, lane);
+        const int w0 = (blockIdx.x - groups) * ldl_waves(rows) + wave, waves = (gridDim.x - groups) * ldl_waves(rows);
+        for (int w = w0; w < pairs; w += waves) ldl_update_triangle<TB>(T, Ms, nb, J0 - LDL_PANEL, J0 + LDL_PANEL, w, lane);
+        if (H) {
+            const int of = (nb - LDL_PANEL + 3) / 4;
+            for (int w = w0; w < of * nb; w += waves) ldl_init(H, T, A, n, w / of, LDL_PANEL + 4 * (w % of), lane);
+        }
         return;
     }
     const double4_t zero = {0.0, 0.0, 0.0, 0.0};
@@ -321,7 +362,8 @@ __global__ __launch_bounds__(ldl_waves(LDL_MAX_ROWS) * 64) void ldl_panel_kernel
             ldl_meet();
             if (blockIdx.x == 0 && Dout) {
                 if constexpr (G == 16) {
-                    ldl_store(Dout + (size_t)(J0 + j) * 256, lane, d);
+#pragma unroll
+                    for (int q = 0; q < 4; q++) Dout[(size_t)(J0 + j) * 256 + 64 * q + lane] = d[q];
                 } else if (row < 8) {
 #pragma unroll
                     for (int q = 0; q < 2; q++) Dout[(size_t)(J0 + j) * 128 + (4 * q + g) * 8 + row] = d[q];
@@ -449,23 +491,33 @@ static hipError_t block_ldl_t(const double *H, int n, float *A, double *Dout, vo
     double *T = (double *)ws;
     double *Ms = (double *)((char *)ws + align256((size_t)n * n * sizeof(double)));
     const int nb = n / 16;
-    hipLaunchKernelGGL(ldl_init_kernel, dim3((nb + 15) / 16, nb), dim3(256), 0, st, H, T, A, n);
+    // T behind the first panel beside that panel's chain, if a quarter of the CUs is idle there.
+    const bool late = nb > LDL_PANEL && nb - LDL_PANEL <= CUS * 3 / 4;
+    const int columns = late ? LDL_PANEL : nb;
+    hipLaunchKernelGGL(ldl_init_kernel, dim3(((columns + 3) / 4 * nb + 3) / 4), dim3(256), 0, st, H, T, A, n, columns);
     for (int J0 = 0; J0 < nb; J0 += LDL_PANEL) {
         const int below = nb - J0 - LDL_PANEL;  // block rows below the panel
         // as few rows per workgroup as keep it at one workgroup per CU: they take the matrix cores from the chain
-        const int rows = below <= 256 ? 1 : below <= 512 ? 2 : LDL_MAX_ROWS;
+        const int rows = below <= 256 ? 1 : below <= 512 ? 2 : 4;
         const int groups = below > 0 ? (below + rows - 1) / rows : 1, waves = ldl_waves(rows);
         // 2 x 2 blocks per wave while that is half a wave per SIMD; single blocks, a shorter chain, otherwise
         const int p2 = J0 > 0 && below > 0 ? (below + 1) / 2 : 0, pairs2 = p2 * (p2 + 1) / 2;
-        const int pairs = pairs2 >= 512 ? pairs2 : p2 > 0 ? below * (below + 1) / 2 : 0;
-        const dim3 grid(groups + (pairs + waves - 1) / waves), block(waves * 64);
-        if (pairs2 >= 512)
-            hipLaunchKernelGGL((ldl_panel_kernel<G, 2>), grid, block, 0, st, T, Ms, A, n, J0, groups, rows, pairs, Dout);
-        else
-            hipLaunchKernelGGL((ldl_panel_kernel<G, 1>), grid, block, 0, st, T, Ms, A, n, J0, groups, rows, pairs, Dout);
+        const int pairs = rows > 1 || pairs2 >= 512 ? pairs2 : p2 > 0 ? below * (below + 1) / 2 : 0;
+        // Workgroups beside the chain: no more than there are CUs for, if that is at least half of them.
+        const int idle = CUS - groups;
+        int beside = J0 == 0 && late ? idle : (pairs + waves - 1) / waves;
+        if (idle > 0 && beside > idle && beside <= 2 * idle) beside = idle;
+        const dim3 grid(groups + beside), block(waves * 64);
+        const double *const behind = J0 == 0 && late ? H : nullptr;
+#define QTIP_LDL_PANEL(TB, ROWS) \
+    hipLaunchKernelGGL((ldl_panel_kernel<G, TB, ROWS>), grid, block, 0, st, T, Ms, A, n, J0, groups, pairs, Dout, behind)
+        if (rows == 4) QTIP_LDL_PANEL(2, 4);
+        else if (rows == 2) QTIP_LDL_PANEL(2, 2);
+        else if (pairs2 >= 512) QTIP_LDL_PANEL(2, 1);
+        else QTIP_LDL_PANEL(1, 1);
+#undef QTIP_LDL_PANEL
         if (below > 0)
-            hipLaunchKernelGGL(ldl_update_panel_kernel, dim3((below * LDL_PANEL + 3) / 4), dim3(256), 0, st, T,
-                               (const double *)Ms, nb, J0);
+            hipLaunchKernelGGL(ldl_update_panel_kernel, dim3(below * LDL_PANEL), dim3(256), 0, st, T, (const double *)Ms, nb, J0);
     }
     return hipGetLastError();
 }

@@ -37,6 +37,30 @@ def test_reconstructs(n, g):
 
 
 @pytest.mark.parametrize("g", [8, 16])
+@pytest.mark.parametrize("n", [2048, 3200, 3216, 4240, 8336])
+def test_reconstructs_large(n, g):
+    """More work beside a panel's chain than idle CUs, T made beside the first panel or ahead of it, one, two and four block
+    rows per workgroup."""
+    import torch
+    import paper_2406_11235_amd as q
+    gen = torch.Generator(device="cuda").manual_seed(n + g)
+    X = torch.randn(n, n, dtype=torch.float64, device="cuda", generator=gen)
+    H = X.T.contiguous() @ X / n + torch.eye(n, dtype=torch.float64, device="cuda")
+    A = torch.full((n, n), float("nan"), device="cuda")
+    D = torch.full((n // g, g, g), float("nan"), dtype=torch.float64, device="cuda")
+    size = q.qtip_block_ldl_workspace(n)
+    ws = torch.full((size // 8,), float("nan"), dtype=torch.float64, device="cuda")
+    q.qtip_block_ldl(torch.tril(H), n, g, A, D, ws, size)
+    blk = torch.arange(n, device="cuda") // g
+    assert bool((A[blk[:, None] <= blk[None, :]] == 0).all())
+    L = A.double().view(n, n // g, g)  # block columns
+    L = L + torch.eye(n, dtype=torch.float64, device="cuda").view(n, n // g, g)
+    LD = torch.matmul(L.transpose(0, 1).contiguous(), D).transpose(0, 1).reshape(n, n)
+    back = LD @ L.reshape(n, n).T.contiguous()
+    assert float((back - H).norm() / H.norm()) < 1e-7  # A is rounded to binary32
+
+
+@pytest.mark.parametrize("g", [8, 16])
 @pytest.mark.parametrize("filled", ["lower triangle", "g x g blocks", "everything"])
 def test_what_stands_above_the_diagonal_does_not_matter(g, filled):
     """H filled in with zeros above its diagonal, above its diagonal blocks of g, and whole: the same A and D."""
