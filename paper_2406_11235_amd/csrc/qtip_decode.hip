@@ -6,6 +6,8 @@
 // once by their owner and no atomics or zero-filled buffers are needed.  The
 // waves of a workgroup take contiguous J ranges and their partial sums meet in
 // LDS at the end.
+#include <type_traits>
+
 #include "qtip_device.h"
 #include "qtip_internal.h"
 #include "qtip_rht_device.h"
@@ -413,39 +415,49 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
 // The words that hold tile row i (16 K bits from bit 16 K i) and the 16 - K V bits after it, brought to bit offset 0;
 // words behind a row's own wrap inside the tile (tail-biting).  At k = 2 and 4 a row is one or two whole words and
 // the word behind it is the first one of the next row, which the next lane of a row of 16 lanes has: one load per row.
-template <int K>
-__device__ __forceinline__ void load_row_words(const uint32_t *__restrict__ tile, int i, uint32_t (&w)[3]) {
-    constexpr int NWORDS = 8 * K;
-    if constexpr (K == 2) {
-        w[0] = stream_load(tile + i);
-    } else if constexpr (K == 4) {
-        const u32x2_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(tile + 2 * i));
-        w[0] = t.x;
-        w[1] = t.y;
-    } else {
-        const int w0 = (16 * K * i) >> 5;
-        w[0] = stream_load(tile + w0);
-        w[1] = stream_load(tile + (w0 + 1) % NWORDS);
-        w[2] = stream_load(tile + (w0 + 2) % NWORDS);
-    }
-}
-// (every lane of the wave makes the call)
-template <int K>
-__device__ __forceinline__ void align_row_words(int i, uint32_t (&w)[3]) {
-    if constexpr (K == 3) {
-        if (i & 1) {  // odd rows start in the middle of a word
-            w[0] = __builtin_amdgcn_alignbit(w[0], w[1], 16);
-            w[1] = __builtin_amdgcn_alignbit(w[1], w[2], 16);
-            w[2] <<= 16;
+// (NEXT: where lane i has tile row i; else the word behind is a load of its own.)
+template <int K, bool NEXT> struct RowWords {
+    static constexpr int NWORDS = 8 * K;
+    int row;
+    uint32_t first, behind;  // byte offsets in a tile: of the row's words, of the word behind them
+    __device__ __forceinline__ explicit RowWords(int row)
+        : row(row), first(4 * (K * row / 2)), behind(4 * ((K * row / 2 + (K == 2 ? 1 : 2)) % NWORDS)) {}
+    // from the tile `offset` bytes behind `base`, which all lanes share
+    __device__ __forceinline__ void load(const uint32_t *__restrict__ base, uint32_t offset, uint32_t (&w)[3]) const {
+        auto at = [&](uint32_t o) { return reinterpret_cast<const char *>(base) + (offset + o); };
+        if constexpr (K == 2) {
+            w[0] = stream_load(reinterpret_cast<const uint32_t *>(at(first)));
+        } else {  // (at k = 3 on four bytes)
+            typedef uint32_t two_words __attribute__((ext_vector_type(2), aligned(4)));
+            const u32x2_t t = __builtin_nontemporal_load(reinterpret_cast<const two_words *>(at(first)));
+            w[0] = t.x;
+            w[1] = t.y;
         }
-    } else {
-        w[K / 2] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[0], 0x12F, 0xF, 0xF, false);  // row rotate by 15
+        if constexpr (K == 3 || !NEXT) w[K == 2 ? 1 : 2] = stream_load(reinterpret_cast<const uint32_t *>(at(behind)));
     }
-}
+    // (every lane of the wave makes the call)
+    __device__ __forceinline__ void align(uint32_t (&w)[3]) const {
+        if constexpr (K == 3) {
+            if (row & 1) {  // odd rows start in the middle of a word
+                w[0] = __builtin_amdgcn_alignbit(w[0], w[1], 16);
+                w[1] = __builtin_amdgcn_alignbit(w[1], w[2], 16);
+                w[2] <<= 16;
+            }
+        } else if constexpr (NEXT) {
+            w[K / 2] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[0], 0x12F, 0xF, 0xF, false);  // row rotate by 15
+        }
+    }
+};
 
 // SPREAD: the HYB table in 16 copies, as in the batch-1 kernel (64 KiB: only next to the
 // small partial-sum buffer of NB = 1).
-template <int K, int V, int CODE, int R, int NB, int NW, bool STAGE, bool SPREAD = false>
+//
+// S = 2 (R = 1): the 16 rows of a tile row go to two workgroups, each of which still fills the A operand: lane row i is row
+// i % 8 of the workgroup's own in one of twice as many tiles, J0 + 4 u + s with u = i / 8.  The B operand belongs to the tile,
+// so there is one per u and twice as many MFMAs, of which each makes 8 rows of D that count; the decoding is no more than
+// the rows'.  At the end a lane takes the rows it has from the u they belong to, and the two lanes with the same rows add up.
+// (Four workgroups of four rows each, us, 8 batch rows, 2-bit 3INST: 1024 x 14336 8.9, two 8.4; whole 11.7.)
+template <int K, int V, int CODE, int R, int NB, int NW, int SR, bool SPREAD = false, int S = 1>
 __global__ __launch_bounds__(NW * 64) void matmat_kernel(const uint32_t *__restrict__ codes,
                                                          const uint32_t *__restrict__ lut,
                                                          int tm, int tn, const half_t *__restrict__ X,
@@ -456,154 +468,184 @@ __global__ __launch_bounds__(NW * 64) void matmat_kernel(const uint32_t *__restr
     // one buffer, used twice: in the loop each wave's staging region (SR batch rows at a
     // time, 128 bytes each, padded to 144 so that the row-wise writes and the
     // column-wise reads both spread over the banks), after it the partial sums
-    constexpr int SR = NB >= 2 ? 32 : 16, NH = 16 * NB / SR, XST = 144;
-    constexpr int PART_FLOATS = (NW - 1) * R * NB * 256;
+    constexpr bool STAGE = SR > 0;
+    constexpr int NH = NB == 1 ? 1 : 16 * NB / SR, XST = 144;  // staging rounds; bytes of a staged row
+    constexpr int LOADS = !STAGE ? NB : NB == 1 ? SR / 8 : 2 * NB, NX = STAGE ? LOADS : 2 * NB;  // rows, pieces of X per lane
+    constexpr int ROWS = 16 / S, TILES = 4 * S;  // rows of a workgroup's tile row, tiles of a wave's step
+    static_assert(S == 1 || (S == 2 && R == 1), "halves of one tile row");
+    constexpr int PART_FLOATS = NW * R * NB * 256;
     constexpr int STAGE_FLOATS = STAGE ? NW * SR * XST / 4 : 0;
     __shared__ __attribute__((aligned(16))) float s_buf[PART_FLOATS > STAGE_FLOATS ? PART_FLOATS : STAGE_FLOATS];
-    float(*s_part)[R][NB][4][64] = reinterpret_cast<float(*)[R][NB][4][64]>(s_buf);
-    stage_code_table<CODE, SPREAD>(lut, s_lut, NW * 64);
-    RowDecode<K, CODE, SPREAD> rdec;
-    rdec.init(s_lut);
-    const int I0 = blockIdx.x * R;
+    float(*s_part)[R * NB * 4][64] = reinterpret_cast<float(*)[R * NB * 4][64]>(s_buf);
+    // (workgroups go round the eight XCDs: those of one tile row, which read the same cache lines, stay on one)
+    const int local = blockIdx.x >> 3;
+    const int I0 = S == 1 ? blockIdx.x * R : local / S * 8 + (blockIdx.x & 7);
+    if (S > 1 && I0 >= tm) return;
     const int b0 = blockIdx.y * (16 * NB);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 15, s = lane >> 4;
+    const int row = S == 1 ? i : local % S * ROWS + i % ROWS, sub = 4 * (i / ROWS) + s;  // the lane's row, tile of a step
     const size_t n = (size_t)tn * 16;
     const int m = tm * 16;
-    const int chunk = ((tn + NW * 4 - 1) / (NW * 4)) * 4;
+    const int chunk = ((tn + NW * TILES - 1) / (NW * TILES)) * TILES;
     const int J0 = wave * chunk;
-    const int Jend = min(tn, J0 + chunk);
-    bool row_ok[R];
-#pragma unroll
-    for (int r = 0; r < R; r++) row_ok[r] = I0 + r < tm;
+    const int tiles = max(min(tn, J0 + chunk) - J0, 0), steps = (tiles + TILES - 1) / TILES;
 
-    float4_t acc[R][NB];
+    // Addresses: a wave's step moves uniform bases (codes) and adds one uniform number per row of X; all that is the lane's is
+    // made here.  Only the last step of a slice that is no whole number of them looks where its tiles end.
+    const uint32_t *row_codes[R];
 #pragma unroll
-    for (int r = 0; r < R; r++)
+    for (int r = 0; r < R; r++) row_codes[r] = codes + ((size_t)min(I0 + r, tm - 1) * tn + J0) * NWORDS;
+    const RowWords<K, S == 1> words(row);
+    const int lr = lane >> 3, ch = lane & 7;  // STAGE: the lane loads piece ch of batch rows 8 q + lr
+    const half_t *xrow[LOADS];
+#pragma unroll
+    for (int q = 0; q < LOADS; q++) {
+        const int b = b0 + (STAGE ? 8 * q + lr : 16 * q + i);
+        xrow[q] = X + (size_t)min(b, B - 1) * n + 16 * J0 + (STAGE ? 8 * ch : 16 * s);
+    }
+    char *const stage = reinterpret_cast<char *>(s_buf) + wave * (SR * XST);
+
+    float4_t acc[R * S][NB];
+#pragma unroll
+    for (int r = 0; r < R * S; r++)
 #pragma unroll
         for (int nb = 0; nb < NB; nb++) acc[r][nb] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    // software pipeline: operands of step t+1 are loaded while step t runs
-    uint32_t wn[R][3];
-    half8_t xn[NB][2];  // STAGE: piece (lane % 8) of batch rows 8 q + lane / 8, q = 2 nb + h
-    const int lr = lane >> 3, ch = lane & 7;
-    char *const stage = reinterpret_cast<char *>(s_buf) + wave * (SR * XST);
-    auto issue = [&](int Jb) {
-        const int J = min(Jb + s, Jend - 1);  // slots past the end re-read the last tile
+    // software pipeline: operands of step t + 1 are loaded while step t runs (code words two or three steps ahead: 8192 x
+    // 8192 4-bit HYB, 8 rows, 10.7 us -> 12.1 and 12.9)
+    struct Operands {
+        uint32_t w[R][3];
+        half8_t x[S][NX];
+    };
+    auto load = [&](Operands &o, int t, auto partial) {
+        // (slots past the end re-read the last tile)
+        const int last = tiles - 1 - t * TILES;
+        const uint32_t back = partial ? (uint32_t)max(sub - last, 0) * (4 * NWORDS) : 0;
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int I = row_ok[r] ? I0 + r : I0;
-            load_row_words<K>(codes + ((size_t)I * tn + J) * NWORDS, i, wn[r]);
-        }
-        if constexpr (STAGE) {
-            const int Jx = min(Jb + (ch >> 1), Jend - 1);
+        for (int r = 0; r < R; r++)
+            words.load(row_codes[r] + (size_t)t * (TILES * NWORDS), (uint32_t)sub * (4 * NWORDS) - back, o.w[r]);
 #pragma unroll
-            for (int q = 0; q < 2 * NB; q++) {
-                const int b = b0 + 8 * q + lr;
-                xn[q >> 1][q & 1] = *reinterpret_cast<const half8_t *>(
-                    X + (size_t)min(b, B - 1) * n + 16 * Jx + 8 * (ch & 1));
-            }
-        } else {
+        for (int u = 0; u < S; u++) {
+            const int xback = partial ? max(4 * u + (STAGE ? ch >> 1 : s) - last, 0) : 0;
 #pragma unroll
-            for (int nb = 0; nb < NB; nb++) {
-                const int b = b0 + 16 * nb + i;
-                const half_t *xp = X + (size_t)min(b, B - 1) * n + 16 * J;
-                xn[nb][0] = *reinterpret_cast<const half8_t *>(xp);
-                xn[nb][1] = *reinterpret_cast<const half8_t *>(xp + 8);
+            for (int q = 0; q < LOADS; q++) {
+                const half8_t *const x =
+                    reinterpret_cast<const half8_t *>(xrow[q] + (size_t)t * (16 * TILES) + 64 * u - (partial ? 16 * xback : 0));
+                if constexpr (STAGE) {
+                    o.x[u][q] = x[0];
+                } else {
+                    o.x[u][2 * q] = x[0];
+                    o.x[u][2 * q + 1] = x[1];
+                }
             }
         }
     };
-    if (J0 < Jend) issue(J0);
-    for (int Jb = J0; Jb < Jend; Jb += 4) {
-        uint32_t w[R][3];
-        half8_t xb[NB][2];
+    auto issue = [&](Operands &o, int t) {
+        if ((t + 1) * TILES <= tiles) load(o, t, std::false_type{});
+        else load(o, t, std::true_type{});
+    };
+    RowDecode<K, CODE, SPREAD> rdec;
+    auto compute = [&](Operands &o, int t) {
+        half8_t xb[S][NB][2];
 #pragma unroll
-        for (int r = 0; r < R; r++)
+        for (int u = 0; u < S; u++) {
+            if constexpr (STAGE) {
+                // The lanes of the wave exchange data through LDS without a workgroup barrier:
+                // the LDS operations of one wave complete in order, and the fences keep the
+                // compiler from moving them across each other.
 #pragma unroll
-            for (int t = 0; t < 3; t++) w[r][t] = wn[r][t];
-        const bool live = Jb + s < Jend;
-        if constexpr (STAGE) {
-            // The lanes of the wave exchange data through LDS without a workgroup barrier:
-            // the LDS operations of one wave complete in order, and the fences keep the
-            // compiler from moving them across each other.
+                for (int hf = 0; hf < NH; hf++) {
 #pragma unroll
-            for (int hf = 0; hf < NH; hf++) {
+                    for (int qq = 0; qq < SR / 8; qq++)
+                        *reinterpret_cast<half8_t *>(stage + (8 * qq + lr) * XST + 16 * ch) = o.x[u][hf * (SR / 8) + qq];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-                for (int qq = 0; qq < SR / 8; qq++) {
-                    const int q = hf * (SR / 8) + qq;
-                    *reinterpret_cast<half8_t *>(stage + (8 * qq + lr) * XST + 16 * ch) = xn[q >> 1][q & 1];
+                    for (int nbb = 0; nbb < (SR + 15) / 16; nbb++)
+#pragma unroll
+                        for (int h = 0; h < 2; h++)
+                            xb[u][hf * (SR / 16) + nbb][h] = *reinterpret_cast<const half8_t *>(
+                                stage + (SR == 8 ? i & 7 : 16 * nbb + i) * XST + 16 * (2 * s + h));
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            } else {
 #pragma unroll
-                for (int nbb = 0; nbb < SR / 16; nbb++)
+                for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+                    for (int h = 0; h < 2; h++) xb[u][nb][h] = o.x[u][2 * nb + h];
+            }
+        }
+        // (a batch row past the end is another column of D, which nobody takes: only dead slots are cleared)
+        if ((t + 1) * TILES > tiles) {
+            asm volatile("");  // (a branch, or every step would have the selects)
+#pragma unroll
+            for (int u = 0; u < S; u++)
+#pragma unroll
+                for (int nb = 0; nb < NB; nb++)
 #pragma unroll
                     for (int h = 0; h < 2; h++)
-                        xb[hf * (SR / 16) + nbb][h] = *reinterpret_cast<const half8_t *>(
-                            stage + (16 * nbb + i) * XST + 16 * (2 * s + h));
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
+                        if (t * TILES + 4 * u + s >= tiles) xb[u][nb][h] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
         }
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++) {
-            const bool bok = live && (b0 + 16 * nb + i < B);
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                if constexpr (!STAGE) xb[nb][h] = xn[nb][h];
-                if (!bok) xb[nb][h] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};  // dead slot / batch row
-            }
-        }
-        if (Jb + 4 < Jend) issue(Jb + 4);
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            align_row_words<K>(i, w[r]);
+            words.align(o.w[r]);
             uint32_t hrow[8];
-            rdec.run(w[r], 0, hrow);
+            rdec.run(o.w[r], 0, hrow);
 #pragma unroll
             for (int h = 0; h < 2; h++) {
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
                 const half8_t a = __builtin_bit_cast(
                     half8_t, u32x4{hrow[4 * h], hrow[4 * h + 1], hrow[4 * h + 2], hrow[4 * h + 3]});
 #pragma unroll
-                for (int nb = 0; nb < NB; nb++)
-                    acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xb[nb][h], acc[r][nb], 0, 0, 0);
+                for (int u = 0; u < S; u++)
+#pragma unroll
+                    for (int nb = 0; nb < NB; nb++)
+                        acc[r * S + u][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xb[u][nb][h], acc[r * S + u][nb], 0, 0, 0);
             }
         }
+    };
+    stage_code_table<CODE, SPREAD>(lut, s_lut, NW * 64);
+    rdec.init(s_lut);
+    // (one copy of the loop's body: with two, for alternating operand sets without moves, or with the first operands asked for
+    // ahead of the table, small products take 0.2 to 0.5 us longer)
+    Operands now, next;
+    if (steps > 0) issue(next, 0);
+    for (int t = 0; t < steps; t++) {
+        now = next;
+        if (t + 1 < steps) issue(next, t + 1);
+        compute(now, t);
+    }
+
+    // (S = 2: D rows 4 s + e are rows (4 s + e) % 8 of the workgroup's, of sub-step u = s / 2)
+    const int sum_row = S == 1 ? 4 * s : (local % S) * ROWS + 4 * (s & 1);
+    if constexpr (S > 1) {
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const float v = s < 2 ? acc[0][nb][e] : acc[S - 1][nb][e];
+                acc[0][nb][e] = v + __shfl_xor(v, 32, 64);
+            }
     }
     if constexpr (STAGE) __syncthreads();  // the staging regions become the partial sums
-    if (wave > 0) {
 #pragma unroll
-        for (int r = 0; r < R; r++)
+    for (int r = 0; r < R; r++)
 #pragma unroll
-            for (int nb = 0; nb < NB; nb++)
+        for (int nb = 0; nb < NB; nb++)
 #pragma unroll
-                for (int e = 0; e < 4; e++) s_part[wave - 1][r][nb][e][lane] = acc[r][nb][e];
-    }
+            for (int e = 0; e < 4; e++) s_part[wave][(r * NB + nb) * 4 + e][lane] = acc[S == 1 ? r : 0][nb][e];
     __syncthreads();
-    if (wave == 0) {
+    // (the waves share the sums: one wave with all of them took 0.3 us longer at R = 2)
+    for (int part = wave; part < R * NB * 4; part += NW) {
+        float v = 0.f;
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            if (!row_ok[r]) continue;
-#pragma unroll
-            for (int nb = 0; nb < NB; nb++) {
-                const int b = b0 + 16 * nb + i;
-                if (b >= B) continue;
-                float4_t v = acc[r][nb];
-#pragma unroll
-                for (int wv = 0; wv < NW - 1; wv++)
-#pragma unroll
-                    for (int e = 0; e < 4; e++) v[e] += s_part[wv][r][nb][e][lane];
-                const int orow = 16 * (I0 + r) + 4 * s;
-                if (scale) {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) v[e] *= (float)scale[orow + e];
-                }
-                *reinterpret_cast<float4_t *>(Y + (size_t)b * m + orow) = v;
-            }
-        }
+        for (int wv = 0; wv < NW; wv++) v += s_part[wv][part][lane];
+        const int I = I0 + part / (4 * NB), b = b0 + 16 * (part / 4 % NB) + i, orow = 16 * I + sum_row + part % 4;
+        if (I < tm && b < B && s < 4 / S) Y[(size_t)b * m + orow] = scale ? v * (float)scale[orow] : v;
     }
 }
 
@@ -783,32 +825,60 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     // 7.2 and 8.8, 200 rows 13.4 and 8.9; 4096 outputs 24 rows 6.8 and 6.8, 48 rows 10.0 and 8.7, 200 rows 39.8 and 21.7).
     if (groups > 1 && (long)tm * groups > 512) {
         if (groups == 2)
-            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 2, 8, true>), dim3((tm + 1) / 2), dim3(8 * 64), 0, st, codes,
+            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 2, 8, 32>), dim3((tm + 1) / 2), dim3(8 * 64), 0, st, codes,
                                lut, tm, tn, Xh, B, sc, Y);
         else
-            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 4, 8, true>), dim3((tm + 1) / 2, (groups + 3) / 4),
+            hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 4, 8, 32>), dim3((tm + 1) / 2, (groups + 3) / 4),
                                dim3(8 * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y);
         return hipGetLastError();
     }
-    constexpr bool HYB = CODE == CODE_HYB;
-    // (measured: the 16 table copies pay at 9 to 16 batch rows, 8192 x 8192 13.1 -> 12.3 us and
-    // 8192 x 28672 35 -> 31 us, and make no difference below)
-    const bool spread = HYB && pick_hyb_spread(CODE, n) && B > 8;
-    // Two tile rows per workgroup share what is loaded of X; one where that gives a CU less to do: matrices of
-    // at most 4096 rows, which would fill half of the CUs (then with 16 waves: 4 rows, 4096 x 14336 2-bit 3INST
-    // 22.3 -> 14.1 us, 4096 x 4096 8.4 -> 5.9), and row counts between the rounds (10240: 37.2 -> 33.8).
-#define QTIP_MM(R, NW, STAGE, SPREAD)                                                                              \
-    hipLaunchKernelGGL((matmat_kernel<K, V, CODE, R, 1, NW, STAGE, SPREAD>), dim3((tm + R - 1) / R, groups),      \
+    // 16 batch rows.  Two tile rows per workgroup (R = 2) share what is loaded of X; a tile row by itself is for at most one
+    // per CU, and half of one for at most half of that.  With 16 waves (NW) a workgroup has a CU's issue slots to itself, with 8
+    // several share them.  Up to 8 rows a wave loads its activations as operands, in a half's kernel, which has twice as many,
+    // and beyond that through LDS (SR).
+    // Of those below, each forced in turn for ten codecs, 768 to 28672 outputs, 1024 to 28672 inputs and 2, 8, 9 and 16 rows, the
+    // pick takes 1.0 % more than the fastest, 23 % at worst (a quarter of a tile row each, which is not kept: 768 x 28672).  us,
+    // 8 rows, 2-bit 3INST: 1024 x 14336 whole 11.7, halves 8.4; 14336 x 4096 and 14336 x 1024 with 16 waves 11.2 and 5.03, with 8
+    // 11.8 and 5.01; 10240 x 8192 (2.5 tile rows per CU) with single rows 16.5, with pairs 20.
+    constexpr bool HYB = CODE == CODE_HYB, HASH = code_is_hyb(CODE);
+    const bool big = B > 8;
+    if (groups == 1 && tm <= (HASH && K == 4 && big ? CUS / 4 : CUS / 2) && tn >= (HASH ? 256 : 64)) {
+        // (at 4 bits table reads, not the decoding, take the time, and beyond 8 rows what is loaded of X: 2048 x 8192, 16 rows,
+        // 9.1 us whole, 9.6 in halves)
+        const dim3 grid((tm + 7) / 8 * 8 * 2);
+#define QTIP_MM_HALF(NW, SR) \
+    hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, 1, NW, SR, false, 2>), grid, dim3(NW * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y)
+        if (tn > 64) {
+            if (big) QTIP_MM_HALF(16, 16);
+            else QTIP_MM_HALF(16, 8);
+        } else {
+            if (big) QTIP_MM_HALF(8, 16);
+            else QTIP_MM_HALF(8, 8);
+        }
+#undef QTIP_MM_HALF
+        return hipGetLastError();
+    }
+    // The 16 copies of the HYB table: a step's 16 reads of one copy take the LDS 112 cycles, of 16 copies about 70, and filling
+    // them 0.5 us (us, one copy and 16: 8 rows k = 2 8192 x 14336 16.4 12.8, 8192 x 4096 7.0 6.5, 8192 x 1024 4.1 4.5, k = 4 8192 x
+    // 14336 16.2 15.4, 8192 x 8192 10.6 11.1; 16 rows k = 2 4096 x 28672 24.9 20.9).
+    const bool spread = HYB && (tm <= CUS || big ? big && n >= 8192 : K == 2 ? n >= 4096 : K == 4 && n >= 12288);
+#define QTIP_MM(R, NW, SR, SPREAD)                                                                              \
+    hipLaunchKernelGGL((matmat_kernel<K, V, CODE, R, 1, NW, SR, SPREAD>), dim3((tm + R - 1) / R, groups),      \
                        dim3(NW * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y)
-#define QTIP_MM_BATCH(R, NW)                                    \
-    if (B <= 8) QTIP_MM(R, NW, false, false); /* few distinct batch rows: load the B operand directly */ \
-    else if (spread) QTIP_MM(R, NW, true, HYB);                 \
-    else QTIP_MM(R, NW, true, false)
-    if (tm <= 256) {
+#define QTIP_MM_BATCH(R, NW)                  \
+    if (big && spread) QTIP_MM(R, NW, 16, HYB); \
+    else if (big) QTIP_MM(R, NW, 16, false);  \
+    else if (spread) QTIP_MM(R, NW, 0, HYB);  \
+    else QTIP_MM(R, NW, 0, false)
+    // (row counts between the rounds of pairs, but not where the table reads of long rows count for more than an idle CU: HYB
+    // k = 3 10240 x 14336, 8 rows, single rows 42.5 us, pairs 35.0)
+    const bool between = tm <= 4 * CUS && !spread && !(HASH && n >= 8192) && (tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256);
+    const bool few_waves = (!big && (spread || (HYB && K == 4))) || (!spread && tn < (tm > 4 * CUS ? 768 : big ? 512 : 256));
+    if (tm <= CUS) {
         QTIP_MM_BATCH(1, 16);
-    } else if ((tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256)) {
+    } else if (between) {
         QTIP_MM_BATCH(1, 8);
-    } else if (tm <= 512) {  // (at most one per CU: 16 waves, 8192 x 8192 4-bit HYB 12.9 -> 11.6 us)
+    } else if (tm <= 2 * CUS || !few_waves) {
         QTIP_MM_BATCH(2, 16);
     } else {
         QTIP_MM_BATCH(2, 8);

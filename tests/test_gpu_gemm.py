@@ -1,4 +1,4 @@
-"""The product for more than 16 batch rows at the sizes where its splits can go wrong: every split of outputs, batch rows
+"""The batched product at the sizes where its splits can go wrong: every split of outputs, batch rows
 and inputs (by sizes that the launcher's rule gives to it), edges of tiles, odd numbers of steps, the smallest of
 everything, for every code, against the decoded matrix times the activations in binary64."""
 import pytest
@@ -49,6 +49,20 @@ def check(q, code, k, m, n, B, scaled, seed=0):
 def test_splits(q, code, k):
     for i, (m, n, B) in enumerate(SHAPES):
         check(q, code, k, m, n, B, scaled=i % 2 == 0, seed=i)
+
+
+# up to 16 batch rows: halves of tile rows, with 8 and 16 waves and steps that do not fill; one and two tile rows per
+# workgroup, with 8 and 16 waves, the last pair half empty; one and 16 copies of the hash code's table; slices with nothing
+UP_TO_16 = [(16, 16), (1024, 1040), (2048, 4112), (1008, 4128), (2064, 4144), (4112, 272), (4112, 4128), (4112, 8208),
+            (10256, 144), (14352, 80), (14352, 4112), (14352, 8208), (16400, 272)]
+
+
+@pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_up_to_16_rows(q, code, k):
+    for i, (m, n) in enumerate(UP_TO_16):
+        for B in ((2, 9) if i % 2 else (8, 16)):
+            check(q, code, k, m, n, B, scaled=B < 9, seed=i)
 
 
 @pytest.mark.parametrize("code", list(CODES))
