@@ -817,12 +817,17 @@ template <int K, int V, int CODE>
 static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, int m, int n,
                                   const void *X, int B, const void *scale, float *Y,
                                   hipStream_t st) {
-    const int groups = (B + 15) / 16;  // more than one only where the large-batch kernel does not reach
+    const int groups = (B + 15) / 16;  // more than one only where matmat_takes them or the large-batch kernel does not reach
     const int tm = m / 16, tn = n / 16;
     const half_t *Xh = (const half_t *)X, *sc = (const half_t *)scale;
-    // There a workgroup decodes a weight for 16 batch rows while that makes at most two workgroups per CU, and for 32
+    // Rows of more than 2^22 inputs: a workgroup decodes a weight for 16 batch rows while that makes at most two workgroups per CU, and for 32
     // or 64 otherwise (2^22 inputs, 2-bit 3INST, ms for 16 and for 32 or 64: 1024 outputs 64 rows 3.8 and 8.7, 128 rows
     // 7.2 and 8.8, 200 rows 13.4 and 8.9; 4096 outputs 24 rows 6.8 and 6.8, 48 rows 10.0 and 8.7, 200 rows 39.8 and 21.7).
+    if (groups > 1 && n <= 1 << 22 && (long)tm * groups > CUS && (long)tm * ((groups + 1) / 2) <= CUS) {
+        hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, 2, 16, 32>), dim3(tm, (groups + 1) / 2), dim3(16 * 64), 0, st, codes, lut,
+                           tm, tn, Xh, B, sc, Y);
+        return hipGetLastError();
+    }
     if (groups > 1 && (long)tm * groups > 512) {
         if (groups == 2)
             hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 2, 8, 32>), dim3((tm + 1) / 2), dim3(8 * 64), 0, st, codes,
@@ -842,10 +847,11 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     // 11.8 and 5.01; 10240 x 8192 (2.5 tile rows per CU) with single rows 16.5, with pairs 20.
     constexpr bool HYB = CODE == CODE_HYB, HASH = code_is_hyb(CODE);
     const bool big = B > 8;
-    if (groups == 1 && tm <= (HASH && K == 4 && big ? CUS / 4 : CUS / 2) && tn >= (HASH ? 256 : 64)) {
+    if (groups == 1 ? tm <= (HASH && K == 4 && big ? CUS / 4 : CUS / 2) && tn >= (HASH ? 256 : 64)
+                    : n <= 1 << 22 && (long)tm * groups <= CUS / 2 && tn >= (HASH ? 256 : 64)) {
         // (at 4 bits table reads, not the decoding, take the time, and beyond 8 rows what is loaded of X: 2048 x 8192, 16 rows,
         // 9.1 us whole, 9.6 in halves)
-        const dim3 grid((tm + 7) / 8 * 8 * 2);
+        const dim3 grid((tm + 7) / 8 * 8 * 2, groups);
 #define QTIP_MM_HALF(NW, SR) \
     hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, 1, NW, SR, false, 2>), grid, dim3(NW * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y)
         if (tn > 64) {
@@ -937,12 +943,27 @@ hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const ui
     QTIP_DISPATCH(launch_matvec_t, codes, lut, m, n, x, signs, log2_block, scale, y, st);
 }
 
+// More than 16 batch rows by the kernel for 16 (or 32) of them at a time: where workgroups of one tile row and 32 batch rows are
+// one per CU at most, which leaves gemm_kernel, 32 outputs and eight waves each, fewer CUs and longer slices; and up to 32
+// rows where its workgroups are more than one round of which the last may be nearly empty, but for the hash codes' long rows.
+// us, that kernel and this one: 2-bit 3INST 1024 x 14336 32 rows 21.1 11.6, 64 rows 21.2 13.7, 128 rows 22.3 16.9, 4096 x 4096 17 rows
+// 8.5 6.7, 4096 x 14336 32 rows 22.9 18.2, 14336 x 4096 32 rows 17.0 14.9, 5120 x 4096 32 rows 8.7 9.7; 4-bit HYB 1024 x 14336 32 rows
+// 19.0 13.4, 2048 x 4096 64 rows 8.0 8.0, 14336 x 14336 32 rows 44.5 45.8.  Six codes, 21 heights, 1024 to 28672 inputs, 17 to
+// 128 rows: where the rule takes them 0.97 to 2.1 times as fast, 1.2 on average.
+static bool matmat_takes(int code_id, int m, int n, int B) {
+    const int tm = m / 16, groups = (B + 15) / 16;
+    if (code_id == CODE_LUT) return false;
+    return (long)tm * ((groups + 1) / 2) <= CUS || (groups == 2 && tm > 2 * CUS && !(code_is_hyb(code_id) && n >= 8192));
+}
+
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                          int n, const void *X, int B, const void *scale, float *Y,
                          hipStream_t st) {
-    // (17 to 32 rows: as fast or up to 10 % faster than two groups of 16 here; 64 rows, 4096 x 4096 2-bit 3INST: 14.6 ->
-    // 10.7 us, 8192 x 8192 4-bit HYB 28.1 -> 24.6; 997 rows, 14336 x 4096: 311 -> 116 us)
-    if (B > 16 && gemm_takes(code_id, n, B)) return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
+    // The lookup-only code's own kernel, for rows too long for the other one, decodes 16 waves' shares of 32 outputs one wait
+    // after the other (us, 16 rows, k = 2, and gemm_kernel: 1024 x 2048 8.2 8.2, 8192 x 8192 26.0 21.3, 4128 x 14464 39.8 31.9).
+    if (code_id == CODE_LUT ? gemm_takes(code_id, n, B) && (B > 16 || n <= 1 << 22)
+                            : B > 16 && gemm_takes(code_id, n, B) && !matmat_takes(code_id, m, n, B))
+        return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
     if (code_id == CODE_LUT) return launch_lut_matmat(k, codes, lut, m, n, X, B, scale, Y, st);
     QTIP_DISPATCH(launch_matmat_t, codes, lut, m, n, X, B, scale, Y, st);
 }

@@ -65,6 +65,33 @@ def test_up_to_16_rows(q, code, k):
             check(q, code, k, m, n, B, scaled=B < 9, seed=i)
 
 
+# above that: 16 and 32 rows at a time, halves of tile rows, the last group nearly empty; up to 32 rows of many outputs; and the
+# 32 x 32, 32 x 64 and 64 x 128 splits where outputs are too many for these
+MORE_THAN_16 = [(16, 1040, 17), (240, 4112, 100), (1024, 1056, 64), (1040, 144, 49), (2032, 4128, 50), (48, 80, 1000),
+                (4096, 272, 17), (8208, 144, 32), (14352, 4112, 18), (4112, 208, 17), (2080, 1056, 40), (2080, 272, 100)]
+
+
+@pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_more_than_16_rows_at_a_time(q, code, k):
+    for i, (m, n, B) in enumerate(MORE_THAN_16):
+        check(q, code, k, m, n, B, scaled=i % 2 == 0, seed=i)
+
+
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_up_to_16_rows_of_the_lookup_only_code(q, k):
+    for m, n, B in ((32, 8, 2), (96, 1032, 9), (4128, 2056, 16), (8224, 264, 3), (32, 14464, 8)):
+        check(q, CODE_LUT, k, m, n, B, scaled=B > 8)
+
+
+@pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
+@pytest.mark.parametrize("B, m", [(20, 4128), (50, 2080), (70, 1408), (130, 864)])
+def test_slices_that_are_not_whole_stages_of_many_outputs(q, code, B, m):
+    """The next test for the codes of 16 x 16 tiles, whose few outputs are another kernel's."""
+    for n in [*range(16, 160, 16), 16 * 31, 16 * 32, 16 * 33, 16 * 61, 16 * 97]:
+        check(q, code, 2 + n // 16 % 3, m, n, B, scaled=False, seed=n)
+
+
 @pytest.mark.parametrize("code", list(CODES))
 @pytest.mark.parametrize("B", [20, 50, 70, 130])
 def test_slices_that_are_not_whole_stages(q, code, B):
