@@ -40,7 +40,8 @@
 // bits, and not for the lookup-only code, which it has no trees for: they take several launches whatever their number).
 // The copies go through the caches as they come: written and read with the non-temporal hint the same
 // case takes 46.4 ms, and thousands of sequences the same.
-// Algorithm 4 is forward / walk to the middle / constrained forward / full walk.
+// Algorithm 4 is forward / walk to the middle / constrained forward / full walk; what the constraint already says about the
+// ends of the second pass is not searched for (VitGeo::FORCED).
 //
 // Arithmetic (fixed, so that a CPU reference can repeat every decision): binary32,
 //   e_j = C[y][j] - s[V t + j];
@@ -81,8 +82,7 @@ struct VitGeo {
     static constexpr int J = KV == 2 ? (LB == 16 ? 5 : 4) : KV == 3 ? 3 : KV == 4 ? 2 : 1;
     static constexpr int NLEAF = 1 << (KV * J);
     static constexpr int LOWB = LB - KV * (J + 1);  // low prefix bits, fixed within one tree
-    static constexpr int NSEG = (G - 1 + J - 1) / J;  // trees of a whole walk; the last one
-    static constexpr int LAST = (G - 1) - (NSEG - 1) * J;  // has LAST levels and starts at step 0
+    static constexpr int NSEG = (G - 1 + J - 1) / J;  // trees of a walk from G - 1 to 0
     // Up to this many sequences a walk has four waves: a tree is a serial chain (leaves from memory,
     // about 1 us, then J levels), and four waves have a quarter of the leaves each.  Not at J < 3, where a
     // wave's share of the chain is no shorter than the exchange at the root (HYB k = 2, 256 tiles: 1009 us
@@ -93,6 +93,17 @@ struct VitGeo {
     static constexpr int MID = G / 2 - 1;           // the step the first walk goes down to
     static constexpr int NSEG_MID = (G - 1 - MID + J - 1) / J;
     static_assert(LOWB >= 0, "a tree's leaves are distinct states");
+    // Algorithm 4's second pass knows the states around its ends: the first state's top bits are the overlap, so that one walk
+    // leads to each of the 4096 states that the first T0 steps can reach, and `best` of step T0 is made at once; the last
+    // state's low bits are the overlap too, so that the 2^kV states it may be are level 1 of a tree below a step G that only has
+    // that prefix.  The pass takes steps T0 .. G - J - 1, and its walk trees down from G, the last one to step T0.  (Not at kV = 6
+    // and 8, where that is one step, and not for the lookup-only code.)
+    static constexpr bool FORCED = KV <= 4 && LB == 16;
+    static constexpr int T0 = FORCED ? 12 / KV : 0, END = FORCED ? G : G - 1;
+    static constexpr int NSEG2 = FORCED ? (G - T0 + J - 1) / J : NSEG;  // trees of a whole walk
+    static constexpr int LAST2 = END - T0 - (NSEG2 - 1) * J;            // levels of the last one
+    static constexpr int COPIES = FORCED ? NSEG2 : NSEG - 1;  // of a whole walk
+    static_assert(COPIES == NSEG - 1 && (!FORCED || KV * T0 == 12), "as many copies either way");
     // LDS place of best[hi] (floats).  kV = 2 and 3: a thread's 16 or 8 minima are one row; written
     // as they stand, the 16-byte stores of neighbouring lanes would be a whole row apart and
     // land on two (four) of the eight 16-byte bank groups, so the row's pieces are rotated by an
@@ -109,6 +120,10 @@ struct VitGeo {
     // place of best[hi] in a stored copy
     __device__ static __forceinline__ uint32_t stored(uint32_t hi) {
         return ((hi & ((1u << LOWB) - 1u)) << (KV * J)) | (hi >> LOWB);
+    }
+    // the prefix at place i of a stored copy
+    __device__ static __forceinline__ uint32_t prefix_at(uint32_t i) {
+        return ((i & ((1u << (KV * J)) - 1u)) << LOWB) | (i >> (KV * J));
     }
 };
 
@@ -207,9 +222,35 @@ __device__ __forceinline__ void thread_minima(const float (&b)[Hang<KV>::COUNT],
     }
 }
 
-// Steps 0 .. t_end - 1 of sequence tile0 + blockIdx.x, with `best` stored after every J steps
-// counted from the last (copies c_lo .. c_hi - 1, copy c at step G - 1 - J (c + 1)), and, when
-// t_end = G - 1, the best final state.  overlap != null: the first state's top L-kV bits and the
+// `best` of step T0 where the first state's top bits are O: entries ((O << 12) | 4 tid + i) mod NP, the others are infinite.  The
+// one walk to each: minima over one finite value, in the order and with the roundings of the steps.
+// (The second pass's 255 steps and the search for its last state are 245 steps at kV = 2, 242 or 243 in one launch: us, all steps and
+// so, one card, 64 | 400 | 4096 sequences: 3INST k = 2 611 588 | 1256 1220 | 9235 9186, k = 3 638 620 | 1275 1243 | 8861 8707, k = 4
+// 629 626 | 1313 1318 | 8245 8250, HYB k = 2 795 770 | 1512 1474 | 10634 10277, HYB1 k = 2 630 612 | 1380 1285 | 9784 9216.)
+template <int KV, int V, int CODE, class Sample>
+__device__ __forceinline__ float4_t forced_entries(uint32_t O, int tid, const uint32_t *__restrict__ lut, Sample sample) {
+    using Geo = VitGeo<KV, V, 16>;
+    constexpr int T0 = Geo::T0;
+    auto state = [&](int j, uint32_t e) { return ((O << (KV * (j + 1))) | (e >> (KV * (T0 - 1 - j)))) & 0xFFFFu; };
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < T0 - 1; j++)
+        v = state_value<V>(code_register<CODE>(state(j, 4u * tid), lut), sample(j, 0), V == 2 ? sample(j, 1) : 0.f, v);
+    float4_t best;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        best[i] = state_value<V>(code_register<CODE>(state(T0 - 1, 4u * tid + i), lut), sample(T0 - 1, 0),
+                                 V == 2 ? sample(T0 - 1, 1) : 0.f, v);
+    return best;
+}
+// Digit of step j < T0 of such a walk: the top kV bits of its state.
+template <int KV> __device__ __forceinline__ uint32_t forced_digit(uint32_t O, int j) {
+    return (O >> (16 - KV - KV * (j + 1))) & ((1u << KV) - 1u);
+}
+
+// Steps 0 (T0 where the ends are forced, see VitGeo) .. t_end - 1 of sequence tile0 + blockIdx.x, with `best` stored after every J steps
+// counted from the last, G - 1 (copies c_lo .. c_hi - 1, copy c at step G - 1 - J (c + 1)), and, when
+// t_end = G - 1, the best final state.  Where the ends are forced, copies are counted from G and the last one is of T0.  overlap != null: the first state's top L-kV bits and the
 // last state's low L-kV bits are forced to overlap[slot] (Algorithm 4's second call).
 // (four waves per SIMD, i.e. at most 128 registers, also where a workgroup is only four waves)
 template <int KV, int V, int CODE>
@@ -233,7 +274,9 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
     const uint32_t O = constrained ? overlap[slot] : 0u;
 
     if (tid < VT_T) s_seq[tid] = sequence_element<CODE>(W, n, tn, tile0 + slot, tid, rotate);
-    for (int i = tid; i < NP; i += NT) s_best[0][Geo::place(i)] = (constrained && (uint32_t)i != O) ? INF : 0.f;
+    // (0 at step 0, but for a first state's top bits that are O; of step T0 all but the forced entries)
+    for (int i = tid; i < NP; i += NT)
+        s_best[0][Geo::place(i)] = constrained && (Geo::FORCED || (uint32_t)i != O) ? INF : 0.f;
 
     // register r of this thread is state (p, hi): WHOLE: p = r % NC, prefix NB tid + r / NC;
     // else (kV = 8) a quarter of a prefix's predecessors, p = 64 (lane / 16) + r
@@ -255,7 +298,27 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
     int until = (G - 1) % J;  // steps to the next one that is a multiple of J from the last
     if (until == 0) until = J;
     int c_now = (G - 1 - until) / J - 1;  // the copy that belongs to it
-    float s0 = s_seq[0], s1 = V == 2 ? s_seq[1] : 0.f;
+    int t = 0;
+    if constexpr (Geo::FORCED) {
+        if (constrained) {
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));  // (nothing that is made with it here is worth a register later)
+            const float4_t first = forced_entries<KV, V, CODE>(O, tid, lut, [&](int u, int e) { return s_seq[V * u + e]; });
+            *reinterpret_cast<float4_t *>(s_best[0] + Geo::place((int)(((O << 12) | (4u * tid)) & (uint32_t)(NP - 1)))) = first;
+            __syncthreads();
+            // (a loop of few registers, which the code values have, and of neighbouring stores: in the order of the prefixes
+            // 256 workgroups of kV = 4 took 12 us for it)
+            if (c_hi == Geo::NSEG2) {
+                float *const dst = store_base + (size_t)(Geo::NSEG2 - 1 - c_lo) * NP;
+#pragma unroll 1
+                for (uint32_t i = tid; i < (uint32_t)NP; i += NT) dst[i] = s_best[0][Geo::place((int)Geo::prefix_at(i))];
+            }
+            t = Geo::T0;
+            until = Geo::LAST2;
+            c_now = Geo::NSEG2 - 2;
+        }
+    }
+    float s0 = s_seq[V * t], s1 = V == 2 ? s_seq[V * t + 1] : 0.f;
 
     auto step = [&](const float *__restrict__ in, float *__restrict__ out, int t) {
         // (the next step's samples are read ahead of the barrier)
@@ -310,7 +373,6 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
         s1 = n1;
         __syncthreads();
     };
-    int t = 0;
     for (; t + 1 < t_end; t += 2) {
         step(s_best[0], s_best[1], t);
         step(s_best[1], s_best[0], t + 1);
@@ -330,7 +392,7 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
 #pragma unroll
     for (int r = 0; r < VT_REGS; r++) {
         const uint32_t y = state_of(r);
-        take_better(!constrained | ((y & (uint32_t)(NP - 1)) == O),
+        take_better(Geo::FORCED || !constrained || (y & (uint32_t)(NP - 1)) == O,
                     state_value<V>(cr[r], s0, s1, in[Geo::place((int)(y >> KV))]), y);
     }
 #pragma unroll
@@ -391,7 +453,7 @@ struct WalkTree {
     const uint32_t *lut;
     const float *seq;  // LDS
     WalkRoot *root;    // LDS
-    float best;        // of the wave, at the root
+    float best;        // of the wave, at the root; of the tree when run() is through
     uint32_t args[JJ + 1];  // args[j]: kV bits per register of level j - 1
 
     __device__ __forceinline__ uint32_t node_state(int j, int m) const {  // level j, register m
@@ -489,6 +551,7 @@ struct WalkTree {
                 l = take ? ol : l;
             }
             l = __builtin_amdgcn_readfirstlane(l);
+            best = bv;
 #pragma unroll
             for (int j = 1; j <= JJ; j++) digit[j] = (l >> (KV * (j - 1))) & ((1u << KV) - 1u);
         }
@@ -507,7 +570,7 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
     const float *__restrict__ final_value, int count, uint32_t *__restrict__ overlap, uint32_t *__restrict__ codes,
     float *__restrict__ tile_err) {
     using Geo = VitGeo<KV, V, code_state_bits(CODE)>;
-    constexpr int OV = Geo::OV, NP = Geo::NP, G = Geo::G, J = Geo::J, NSEG = Geo::NSEG, LB = code_state_bits(CODE);
+    constexpr int OV = Geo::OV, NP = Geo::NP, G = Geo::G, J = Geo::J, LB = code_state_bits(CODE);
     constexpr int NWORDS = KV * G / 32;
     __shared__ float s_seq[4][VT_T];
     __shared__ uint32_t s_sym[4][VT_T / 4];  // one byte per step
@@ -529,14 +592,18 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    uint32_t y = __builtin_amdgcn_readfirstlane(final_state[slot]) & ((1u << LB) - 1u);
+    const bool forced = Geo::FORCED && constrained;
+    const int end = forced ? Geo::END : G - 1;
+    // (a forced walk begins at a step G whose state has the overlap for a prefix)
+    uint32_t y = __builtin_amdgcn_readfirstlane(forced && c_lo == 0 ? O << KV : final_state[slot]) & ((1u << LB) - 1u);
     s_sym[wave][lane] = 0;
     wave_sync();
-    if (c_lo == 0 && lane == 0) sym[G - 1] = (uint8_t)(y >> OV);
+    if (!forced && c_lo == 0 && lane == 0) sym[G - 1] = (uint8_t)(y >> OV);
+    if (forced && c_hi == Geo::NSEG2 && lane < Geo::T0) sym[lane] = (uint8_t)forced_digit<KV>(O, lane);
     const float *my_store = store + (size_t)slot * slots * NP;
     auto tree = [&](auto jj, int c) {
         constexpr int JJ = decltype(jj)::value;
-        const int t = G - 1 - J * c;
+        const int t = end - J * c;
         WalkTree<KV, V, CODE, JJ, WB> w;
         w.y = y;
         w.t = t;
@@ -547,6 +614,7 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
         w.seq = seq;
         uint32_t digit[JJ + 1];
         w.run(t > JJ ? my_store + (size_t)(c - c_lo) * NP : nullptr, constrained, O, c & 1, digit);
+        if (forced && first && c == 0 && tile_err && lane == 0) tile_err[tile0 + slot] = w.best;
 #pragma unroll
         for (int j = 1; j <= JJ; j++) {
             y = (digit[j] << OV) | (y >> KV);
@@ -555,12 +623,12 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
         }
     };
     for (int c = c_lo; c < c_hi; c++) {
-        if (c == NSEG - 1) tree(std::integral_constant<int, Geo::LAST>{}, c);
+        if (c == Geo::NSEG2 - 1) tree(std::integral_constant<int, Geo::LAST2>{}, c);  // (never the first pass's)
         else tree(std::integral_constant<int, J>{}, c);
     }
     if (!first || (pass == 1 && c_hi >= Geo::NSEG_MID)) return;
     wave_sync();
-    if (c_hi < NSEG && lane == 0) final_state[slot] = y;
+    if (c_hi < Geo::NSEG2 && lane == 0) final_state[slot] = y;
     if (pass == 1) return;
     if (lane < NWORDS) {
         uint32_t *const out = codes + (size_t)(tile0 + slot) * NWORDS + lane;
@@ -572,7 +640,7 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
         }
         *out = c_lo == 0 ? word : *out | word;
     }
-    if (tile_err && lane == 0) tile_err[tile0 + slot] = final_value[slot];
+    if (!forced && tile_err && lane == 0) tile_err[tile0 + slot] = final_value[slot];
 }
 
 // --------------------------------------------------- few sequences: all of Algorithm 4 in one workgroup
@@ -585,7 +653,7 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
 // copies asks for: `nseg` segments of T + F steps, lengths differing by one at most.
 // The last forward step of a segment is only taken for the prefixes that the tree hangs on, a few of each thread; with F = 0
 // level T takes entries and codes from the registers they arrive in.
-//   What bounds it is still the issue of the forward steps: 255 of 2043 cycles in each pass (kV = 2, V = 1), 453 of 620 to 635 us.
+//   What bounds it is still the issue of the forward steps: 255 and 242 of 2043 cycles (kV = 2, V = 1), 441 of 590 to 615 us.
 // (Several launches and this one are compared where the launcher chooses; BlockLDLQ of 2048 x 256 11.44 | 10.01 ms, of 3-bit
 // 1024 x 256 15.94 | 10.34.  With every copy through LDS and all of a tree's codes formed anew, 128 sequences, against 635,
 // 641, 635 and 800 us on that card: 3INST k = 2 to 4 671, 693, 648, HYB 821.)
@@ -595,7 +663,8 @@ template <int KV, int V> struct FewGeo : VitGeo<KV, V, 16> {
     static constexpr int FIXED = 4 - KV;                       // low bits that the prefixes of a tree's leaves share
     static constexpr int ARRAYS = KV == 3 ? 4 : 2;             // room for `best` of consecutive steps
     static constexpr int LONGEST = T + ARRAYS;                 // segment
-    static constexpr int D1 = VitGeo<KV, V, 16>::G - 1 - VitGeo<KV, V, 16>::MID, D2 = VitGeo<KV, V, 16>::G - 1;  // steps walked
+    static constexpr int D1 = VitGeo<KV, V, 16>::G - 1 - VitGeo<KV, V, 16>::MID,
+                         D2 = VitGeo<KV, V, 16>::G - VitGeo<KV, V, 16>::T0;  // steps walked
     static_assert(16 - KV * T == 4 && NODES <= 1024, "4096 leaves");
     static_assert(D1 > LONGEST, "two segments at least, so one copy");
     static constexpr bool fits(int d, int nseg) { return nseg > 0 && (d + nseg - 1) / nseg <= LONGEST; }
@@ -644,34 +713,53 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
 
     uint32_t O = 0;
     for (int pass = 1; pass <= 2; pass++) {
-        const bool constrained = pass == 2;
-        const int rotate = pass == 1 ? VT_T / 2 : 0;
-        const int nseg = pass == 1 ? nseg1 : nseg2, D = pass == 1 ? Geo::D1 : Geo::D2;
-        const int base = D / nseg, longer = D % nseg, copies = pass == 1 ? nseg : nseg - 1;
+        // (the second pass's ends are forced, see VitGeo: it begins at T0, and its walk at G, whose first segment's `best` is
+        // where the forward pass stops and needs no copy)
+        const int rotate = pass == 1 ? VT_T / 2 : 0, begin = pass == 1 ? 0 : Geo::T0, end = pass == 1 ? G - 1 : G;
+        const int nseg = pass == 1 ? nseg1 : nseg2, D = pass == 1 ? Geo::D1 : Geo::D2, uncopied = pass - 1;
+        const int base = D / nseg, longer = D % nseg;
         auto sample = [&](int t, int e) { return s_seq[(V * t + e + rotate) & (VT_T - 1)]; };
         // the step that copy c, under segment c from the end, belongs to
-        auto step_of = [&](int c) { return G - 1 - (c + 1) * base - min(c + 1, longer); };
+        auto step_of = [&](int c) { return end - (c + 1) * base - min(c + 1, longer); };
         auto put = [&](float *to, const float *best) {
 #pragma unroll
             for (int i = 0; i < NB; i += 4)
                 *reinterpret_cast<float4_t *>(to + Geo::place(my_hi + i)) =
                     float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
         };
-        // (entry `hi` of step 0)
-        auto first = [&](int hi) { return constrained && (uint32_t)hi != O ? INF : 0.f; };
         {
             float best[NB];
 #pragma unroll
-            for (int i = 0; i < NB; i++) best[i] = first(my_hi + i);
+            for (int i = 0; i < NB; i++) best[i] = pass == 1 ? 0.f : INF;
             put(s_best[0], best);
         }
         __syncthreads();
-        int c_now = copies - 1, t_next = step_of(c_now);
-        float s0 = sample(0, 0), s1 = V == 2 ? sample(0, 1) : 0.f;
+        int c_now = nseg - 1, t_next = step_of(c_now);
+        auto copy_at = [&](int c) { return my_store + (size_t)(c - uncopied) * NP; };
         auto next_copy = [&] {
             c_now--;
-            t_next = c_now >= 0 ? step_of(c_now) : -1;
+            t_next = c_now >= uncopied ? step_of(c_now) : -1;
         };
+        auto store_copy = [&](const float *best) {
+            float4_t *const to = reinterpret_cast<float4_t *>(copy_at(c_now));
+#pragma unroll
+            for (int i = 0; i < NB; i += 4)
+                to[(uint32_t)(NB / 4 * tid + i / 4)] = float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
+            next_copy();
+        };
+        if (pass == 2) {
+            const float4_t first = forced_entries<KV, V, CODE>(O, tid, lut, sample);
+            *reinterpret_cast<float4_t *>(s_best[0] + Geo::place((int)(((O << 12) | (4u * tid)) & (uint32_t)(NP - 1)))) = first;
+            if (tid < Geo::T0) sym[tid] = (uint8_t)forced_digit<KV>(O, tid);
+            __syncthreads();
+            if constexpr (KV > 2) {
+                float best[NB];
+#pragma unroll
+                for (int i = 0; i < NB; i++) best[i] = s_best[0][Geo::place(my_hi + i)];
+                store_copy(best);
+            }
+        }
+        float s0 = sample(begin, 0), s1 = V == 2 ? sample(begin, 1) : 0.f;
         auto step = [&](const float *in, float *out, int t) {
             // (the next step's samples are read ahead of the barrier)
             const float n0 = sample(t + 1, 0), n1 = V == 2 ? sample(t + 1, 1) : 0.f;
@@ -680,7 +768,7 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             // A copy of step t_next is stored as it will be read, coalesced both times.
             if constexpr (KV == 2) {
                 if (t == t_next) {
-                    float4_t *const to = reinterpret_cast<float4_t *>(my_store + (size_t)c_now * NP);
+                    float4_t *const to = reinterpret_cast<float4_t *>(copy_at(c_now));
 #pragma unroll
                     for (int p = 0; p < NC; p++)
                         (to + 1024 * p)[(uint32_t)tid] = float4_t{b[4 * p], b[4 * p + 1], b[4 * p + 2], b[4 * p + 3]};
@@ -692,44 +780,41 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             s1 = n1;
             put(out, best);
             if constexpr (KV > 2) {
-                if (t + 1 == t_next) {
-                    float4_t *const to = reinterpret_cast<float4_t *>(my_store + (size_t)c_now * NP);
-#pragma unroll
-                    for (int i = 0; i < NB; i += 4)
-                        to[(uint32_t)(NB / 4 * tid + i / 4)] = float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
-                    next_copy();
-                }
+                if (t + 1 == t_next) store_copy(best);
             }
             __syncthreads();
         };
-        for (int t = 0; t + 1 < G - 1; t += 2) {
+        const int stop = pass == 1 ? G - 1 : step_of(0);
+        int t = begin;
+        for (; t + 1 < stop; t += 2) {
             step(s_best[0], s_best[1], t);
             step(s_best[1], s_best[0], t + 1);
         }
+        if (t < stop) step(s_best[0], s_best[1], t);
         static_assert((G - 1) % 2 == 1, "one step over");
-        step(s_best[0], s_best[1], G - 2);
 
-        // the best allowed final state, lowest state on ties
+        // the best final state, lowest state on ties
         float bv = INF;
         uint32_t by = 0xFFFFFFFFu;
-        auto take_better = [&](bool ok, float v, uint32_t y) {
-            const bool take = ok & ((v < bv) | ((v == bv) & (y < by)));
+        auto take_better = [&](float v, uint32_t y) {
+            const bool take = (v < bv) | ((v == bv) & (y < by));
             bv = take ? v : bv;
             by = take ? y : by;
         };
+        if (pass == 1) {
 #pragma unroll
-        for (int r = 0; r < VT_REGS; r++) {
-            const uint32_t y = ((uint32_t)(r % NC) << OV) | (uint32_t)(my_hi + r / NC);
-            take_better(!constrained | ((y & (uint32_t)(NP - 1)) == O),
-                        state_value<V>(cr[r], s0, s1, s_best[1][Geo::place((int)(y >> KV))]), y);
+            for (int r = 0; r < VT_REGS; r++) {
+                const uint32_t y = ((uint32_t)(r % NC) << OV) | (uint32_t)(my_hi + r / NC);
+                take_better(state_value<V>(cr[r], s0, s1, s_best[1][Geo::place((int)(y >> KV))]), y);
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) take_better(__shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
+            if (lane == 0) s_rv[wave] = bv, s_ry[wave] = by;
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) take_better(true, __shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
-        if (lane == 0) s_rv[wave] = bv, s_ry[wave] = by;
         // (a segment's copy, on the way while the one before is walked)
         float pre[AHEAD];
         auto fetch = [&](int c) {  // (whether there is one or not: else the last one would have to be kept meanwhile)
-            const float *const from = my_store + (size_t)min(c, copies - 1) * NP;
+            const float *const from = copy_at(min(c, nseg - 1));
             if constexpr (KV == 3) {
 #pragma unroll
                 for (int p = 0; p < NC; p++) pre[p] = (from + (p << (OV - KV)))[(uint32_t)tid];
@@ -742,18 +827,27 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 }
             }
         };
-        fetch(0);
-        __syncthreads();
-        bv = INF;
-        by = 0xFFFFFFFFu;
-        for (int w = 0; w < 16; w++) take_better(true, s_rv[w], s_ry[w]);
-        uint32_t y = __builtin_amdgcn_readfirstlane(by) & 0xFFFFu;
-        if (pass == 2 && tid == 0) {
-            sym[G - 1] = (uint8_t)(y >> OV);
-            if (tile_err) tile_err[slot] = bv;
+        uint32_t y;
+        if (pass == 1) {
+            fetch(0);
+            __syncthreads();
+            bv = INF;
+            by = 0xFFFFFFFFu;
+            for (int w = 0; w < 16; w++) take_better(s_rv[w], s_ry[w]);
+            y = __builtin_amdgcn_readfirstlane(by) & 0xFFFFu;
+        } else {  // what a copy of this step would bring, and a state of step G with the overlap for a prefix
+            const float *const at = s_best[(stop - begin) & 1];
+            if constexpr (KV == 4) {
+#pragma unroll
+                for (int i = 0; i < NB; i++) pre[i] = at[Geo::place(my_hi + i)];
+            } else {
+                thread_reads<KV, V, LB>(at, tid, pre);
+            }
+            __syncthreads();
+            y = O << KV;
         }
 
-        int t = G - 1;
+        t = end;
         for (int c = 0; c < nseg; c++) {
             const int length = base + (c < longer), forward = length - T, u = t - length;
             // (nothing that depends on these is worth a register across segments: it would be one of the spilled ones)
@@ -767,19 +861,8 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 else return pre;
             }();
             if constexpr (KV == 4) {
-                if (c == copies) {
-#pragma unroll
-                    for (int i = 0; i < NB; i++) pre[i] = first(my_hi + i);
-                }
                 put(s_best[0], pre);
                 __syncthreads();
-            } else if (c == copies) {
-#pragma unroll
-                for (int p = 0; p < NC; p++) {
-#pragma unroll
-                    for (int a = 0; a < COUNT / NC; a++)
-                        pre[COUNT / NC * p + a] = first((p << (OV - KV)) + COUNT / NC * tid + a);
-                }
             }
             const uint32_t under = (y >> (KV * T)) & 15u;  // low bits of the leaves
             if (forward > 0) {
@@ -950,6 +1033,7 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 if constexpr (ROOTS >= 2) across(std::integral_constant<int, 2>{});
                 across(std::integral_constant<int, 1>{});
                 walk = __builtin_amdgcn_readfirstlane(walk);
+                if (pass == 2 && c == 0 && tile_err && lane == 0) tile_err[slot] = m;
                 if (lane < T) sym[t - 1 - lane] = (uint8_t)((walk >> (KV * lane)) & (uint32_t)(NC - 1));
                 uint32_t z = (walk << 4) | under;
                 // and the steps that were taken forward
@@ -1012,10 +1096,18 @@ struct Plan {
     int slots;
     double cost;  // steps of one workgroup's passes, all batches together
 };
+// Trees of a pass's walk, and the step that its forward pass goes up to for copies from c on.
 template <class Geo>
-double pass_steps(int slots, int nseg) {
+int segments_of(int pass) { return pass == 1 ? Geo::NSEG_MID : Geo::NSEG2; }
+template <class Geo>
+int last_step(int pass, int c) {
+    if (pass == 2 && Geo::FORCED) return Geo::END - Geo::J * (c + 1) > Geo::T0 ? Geo::END - Geo::J * (c + 1) : Geo::T0;
+    return c == 0 ? Geo::G - 1 : Geo::G - 1 - Geo::J * (c + 1);
+}
+template <class Geo>
+double pass_steps(int slots, int pass) {
     double steps = 0;
-    for (int c = 0; c < nseg; c += slots) steps += c == 0 ? Geo::G - 1 : Geo::G - 1 - Geo::J * (c + 1);
+    for (int c = 0; c < segments_of<Geo>(pass); c += slots) steps += last_step<Geo>(pass, c) - (pass == 2 ? Geo::T0 : 0);
     return steps;
 }
 template <class Geo>
@@ -1031,10 +1123,10 @@ Plan plan_for(long tiles, long ntiles, size_t ws_bytes) {
     }
     if (tiles <= 0 || head_bytes(tiles) >= ws_bytes) return p;
     const size_t copies = (ws_bytes - head_bytes(tiles)) / ((size_t)tiles * Geo::NP * sizeof(float));
-    p.slots = (int)(copies < (size_t)(Geo::NSEG - 1) ? copies : (size_t)(Geo::NSEG - 1));
+    p.slots = (int)(copies < (size_t)Geo::COPIES ? copies : (size_t)Geo::COPIES);
     if (p.slots <= 0) return p;
     p.tiles = tiles;
-    const double steps = pass_steps<Geo>(p.slots, Geo::NSEG_MID) + pass_steps<Geo>(p.slots, Geo::NSEG);
+    const double steps = pass_steps<Geo>(p.slots, 1) + pass_steps<Geo>(p.slots, 2);
     for (long t = 0; t < ntiles; t += tiles)
         p.cost += steps * (double)((((ntiles - t < tiles) ? ntiles - t : tiles) + RESIDENT - 1) / RESIDENT);
     return p;
@@ -1048,7 +1140,7 @@ Plan make_plan(long ntiles, size_t ws_bytes, size_t sized_for) {
         while (t > 0 && head_bytes(t) + (size_t)t * per_tile > ws_bytes) t--;
         return t;
     };
-    const Plan a = plan_for<Geo>(room_for((size_t)(Geo::NSEG - 1) * Geo::NP * sizeof(float)), ntiles, ws_bytes);
+    const Plan a = plan_for<Geo>(room_for((size_t)Geo::COPIES * Geo::NP * sizeof(float)), ntiles, ws_bytes);
     const Plan b = plan_for<Geo>(room_for(sized_for), ntiles, ws_bytes);
     if (b.tiles == 0) return a;
     return a.tiles && a.cost <= b.cost ? a : b;
@@ -1074,10 +1166,12 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
             const size_t copy_bytes = (size_t)ntiles * Geo::NP * sizeof(float);
             const size_t room = ws_bytes > head_bytes(ntiles) ? (ws_bytes - head_bytes(ntiles)) / copy_bytes : 0;
             const long slots = (long)(room < (size_t)VT_T ? room : (size_t)VT_T);
-            const bool pays = ntiles <= (KV == 2 ? CUS / 2 : KV == 3 ? 2 * CUS : CUS) || slots < Geo::NSEG - 1;
+            const bool pays = ntiles <= (KV == 2 ? CUS / 2 : KV == 3 ? 2 * CUS : CUS) || slots < Geo::COPIES;
             const int nseg1 = (int)(slots < Few::D1 / Few::T ? slots : Few::D1 / Few::T);
             const int nseg2 = (int)(slots + 1 < Few::D2 / Few::T ? slots + 1 : Few::D2 / Few::T);
-            if (pays && Few::fits(Few::D1, nseg1) && Few::fits(Few::D2, nseg2)) {
+            // (copies for segments of a walk over all steps: at some sizes one fewer would do)
+            const bool room_for_walk = Few::fits(Geo::G - 1, (int)slots + 1);
+            if (pays && room_for_walk && Few::fits(Few::D1, nseg1) && Few::fits(Few::D2, nseg2)) {
                 hipLaunchKernelGGL((viterbi_few_kernel<KV, V, CODE>), dim3((unsigned)ntiles), dim3(1024), 0, st, W, ld, tn,
                                    lut, (float *)((char *)ws + head_bytes(ntiles)), slots, nseg1, nseg2, codes, tile_err);
                 return hipGetLastError();
@@ -1096,12 +1190,12 @@ hipError_t quantize_gpu_t(const float *W, int m, int n, int ld, const uint32_t *
         const int cnt = (int)(ntiles - tile0 < cap ? ntiles - tile0 : cap);
         const bool few = cnt <= Geo::FEW;
         for (int pass = 1; pass <= 2; pass++) {
-            const int nseg = pass == 1 ? Geo::NSEG_MID : Geo::NSEG;
+            const int nseg = segments_of<Geo>(pass);
             for (int c_lo = 0; c_lo < nseg; c_lo += plan.slots) {
-                // (the last tree of a whole walk starts at step 0 and needs no copy)
+                // (the last tree of a whole walk that is not forced starts at step 0 and needs no copy)
                 int c_hi = c_lo + plan.slots < nseg ? c_lo + plan.slots : nseg;
-                if (c_hi == Geo::NSEG - 1) c_hi = Geo::NSEG;
-                const int t_end = c_lo == 0 ? Geo::G - 1 : Geo::G - 1 - Geo::J * (c_lo + 1);
+                if (!Geo::FORCED && c_hi == Geo::NSEG - 1) c_hi = Geo::NSEG;
+                const int t_end = last_step<Geo>(pass, c_lo);
                 if (t_end > 0)
                     hipLaunchKernelGGL((viterbi_forward_kernel<KV, V, CODE>), dim3(cnt), dim3(Geo::NT), 0, st, W, ld,
                                        tn, tile0, lut, pass == 1, pass == 1 ? (const uint32_t *)nullptr : overlap,
