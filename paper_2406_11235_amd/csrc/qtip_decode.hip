@@ -865,19 +865,22 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
         return hipGetLastError();
     }
     // The 16 copies of the HYB table: a step's 16 reads of one copy take the LDS 112 cycles, of 16 copies about 70, and filling
-    // them 0.5 us (us, one copy and 16: 8 rows k = 2 8192 x 14336 16.4 12.8, 8192 x 4096 7.0 6.5, 8192 x 1024 4.1 4.5, k = 4 8192 x
-    // 14336 16.2 15.4, 8192 x 8192 10.6 11.1; 16 rows k = 2 4096 x 28672 24.9 20.9).
-    const bool spread = HYB && (tm <= CUS || big ? big && n >= 8192 : K == 2 ? n >= 4096 : K == 4 && n >= 12288);
+    // them 0.5 us (us, one copy and 16: 8 rows k = 2 8192 x 14336 16.2 13.3, 8192 x 4096 7.0 6.5, 8192 x 1024 4.1 4.5; 16 rows k = 2 4096 x
+    // 28672 24.9 20.9).  At 3 and 4 bits it pays with the activations through LDS, which leaves the texture path to the code words
+    // (one copy, 16, 16 and so: k = 3 8192 x 8192 12.3 12.9 11.1, 14336 x 14336 34.0 34.8 29.2, k = 4 14336 x 14336 27.2 26.7 25.3, 8192 x 28672
+    // 29.7 26.9 26.2, but k = 2 14336 x 14336 26.7 21.9 25.8).
+    const bool long_row = K == 2 ? n >= 4096 : K == 3 ? n >= (tm <= 2 * CUS ? 4096 : 8192) : n >= (tm <= 2 * CUS ? 12288 : 8192);
+    const bool spread = HYB && (big ? n >= 8192 : tm > CUS && long_row);
 #define QTIP_MM(R, NW, SR, SPREAD)                                                                              \
     hipLaunchKernelGGL((matmat_kernel<K, V, CODE, R, 1, NW, SR, SPREAD>), dim3((tm + R - 1) / R, groups),      \
                        dim3(NW * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y)
 #define QTIP_MM_BATCH(R, NW)                  \
     if (big && spread) QTIP_MM(R, NW, 16, HYB); \
     else if (big) QTIP_MM(R, NW, 16, false);  \
-    else if (spread) QTIP_MM(R, NW, 0, HYB);  \
+    else if (spread) QTIP_MM(R, NW, K == 2 ? 0 : 8, HYB);  \
     else QTIP_MM(R, NW, 0, false)
-    // (row counts between the rounds of pairs, but not where the table reads of long rows count for more than an idle CU: HYB
-    // k = 3 10240 x 14336, 8 rows, single rows 42.5 us, pairs 35.0)
+    // (row counts between the rounds of pairs, but not where the table reads of long rows count for more than an idle CU: HYB2
+    // k = 4 12288 x 14336, 8 rows, single rows 32.2 us, pairs 27.6)
     const bool between = tm <= 4 * CUS && !spread && !(HASH && n >= 8192) && (tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256);
     const bool few_waves = (!big && (spread || (HYB && K == 4))) || (!spread && tn < (tm > 4 * CUS ? 768 : big ? 512 : 256));
     if (tm <= CUS) {
