@@ -589,7 +589,11 @@ double orc_tailbiting_quantize(const double *S, int T, int L, int k, int V, cons
  *   V = 2: value(y) = (min over predecessors) + fmaf(e_1, e_1, e_0*e_0)
  * (the form a GPU takes: one fused operation per state for V = 1, a per-step
  * table of the 2^(Q+1) possible errors for the V = 2 codes).
- * Minima and ties are as in orc_viterbi.  V <= 2.
+ * Minima and ties are as in orc_viterbi, also between values that overflowed:
+ * the lowest predecessor, the lowest allowed final state.  Undefined values
+ * (a sample that is none leaves no other) are smaller than nothing: the first
+ * predecessor, and, with none of the final states below or at infinity, the
+ * last state of all and the value infinity.  V <= 2.
  */
 float orc_viterbi_f32(const float *S, int T, int L, int k, int V, const float *C,
                       int first_top, int last_low, uint32_t *states_out) {
@@ -617,13 +621,13 @@ float orc_viterbi_f32(const float *S, int T, int L, int k, int V, const float *C
                 d = fmaf(e1, e1, d);
             }
             if (t == 0) {
-                if (first_top >= 0 && (y >> kV) != (uint32_t)first_top) d = INFINITY;
+                if (first_top >= 0 && (y >> kV) != (uint32_t)first_top) d += INFINITY;
                 nxt[y] = d;
                 continue;
             }
-            float best = INFINITY;
-            uint32_t arg = 0;
-            for (uint32_t p = 0; p < nin; p++) {
+            uint32_t arg = y >> kV;
+            float best = val[arg];
+            for (uint32_t p = 1; p < nin; p++) {
                 uint32_t x = (p << ov) | (y >> kV);
                 if (val[x] < best) {
                     best = val[x];
@@ -638,14 +642,15 @@ float orc_viterbi_f32(const float *S, int T, int L, int k, int V, const float *C
         nxt = tmp;
     }
     float best = INFINITY;
-    uint32_t arg = 0;
+    uint32_t arg = NS;
     for (uint32_t y = 0; y < NS; y++) {
         if (last_low >= 0 && (y & ovmask) != (uint32_t)last_low) continue;
-        if (val[y] < best) {
+        if (val[y] < best || (arg == NS && val[y] == best)) {
             best = val[y];
             arg = y;
         }
     }
+    if (arg == NS) arg = NS - 1;
     for (int t = G - 1; t >= 0; t--) {
         states_out[t] = arg;
         if (t > 0) arg = back[(size_t)t * NS + arg];

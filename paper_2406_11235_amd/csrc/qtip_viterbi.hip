@@ -97,13 +97,14 @@ struct VitGeo {
     // leads to each of the 4096 states that the first T0 steps can reach, and `best` of step T0 is made at once; the last
     // state's low bits are the overlap too, so that the 2^kV states it may be are level 1 of a tree below a step G that only has
     // that prefix.  The pass takes steps T0 .. G - J - 1, and its walk trees down from G, the last one to step T0.  (Not at kV = 6
-    // and 8, where that is one step, and not for the lookup-only code.)
+    // and 8, where that is one step, and not for the lookup-only code; and not for a sequence that is unbounded(), see there.)
     static constexpr bool FORCED = KV <= 4 && LB == 16;
     static constexpr int T0 = FORCED ? 12 / KV : 0, END = FORCED ? G : G - 1;
     static constexpr int NSEG2 = FORCED ? (G - T0 + J - 1) / J : NSEG;  // trees of a whole walk
-    static constexpr int LAST2 = END - T0 - (NSEG2 - 1) * J;            // levels of the last one
-    static constexpr int COPIES = FORCED ? NSEG2 : NSEG - 1;  // of a whole walk
-    static_assert(COPIES == NSEG - 1 && (!FORCED || KV * T0 == 12), "as many copies either way");
+    static constexpr int LAST = G - 1 - (NSEG - 1) * J;                 // levels of the last one
+    static constexpr int COPIES = NSEG - 1;  // of a whole walk
+    static_assert(!FORCED || (KV * T0 == 12 && NSEG2 == COPIES && END - T0 - (NSEG2 - 1) * J == LAST),
+                  "forced or not, as many copies, and as many levels of the last tree");
     // LDS place of best[hi] (floats).  kV = 2 and 3: a thread's 16 or 8 minima are one row; written
     // as they stand, the 16-byte stores of neighbouring lanes would be a whole row apart and
     // land on two (four) of the eight 16-byte bank groups, so the row's pieces are rotated by an
@@ -222,6 +223,26 @@ __device__ __forceinline__ void thread_minima(const float (&b)[Hang<KV>::COUNT],
     }
 }
 
+// Whether a sequence's values might not all be finite: a sample beyond 2^59 or none at all, or a table entry that is not
+// finite.  (Below that 256 squares of differences to code values, 65504 at most, stay below 2^127.)  Where all of
+// them are finite, what the ends of the second pass are forced to is what a search finds: only walks from the forced first
+// state have a finite value.  Where they are not, minima over infinite and undefined values decide, and the second pass
+// searches over all states and steps.  `element` is the thread's of the sequence, if it has one; true for threads of the
+// workgroup that see such a value.
+template <int CODE> __device__ __forceinline__ bool unbounded(float element, int tid, const uint32_t *__restrict__ lut) {
+    auto not_finite = [](uint32_t h) { return (h & 0x7C00u) == 0x7C00u; };
+    bool is = tid < VT_T && !(__builtin_fabsf(element) <= 0x1p59f);
+    if constexpr (CODE == CODE_HYB1) {
+        if (tid < 1 << HYB1_Q) is |= not_finite(reinterpret_cast<const uint16_t *>(lut)[tid]);
+    } else if constexpr (code_is_hyb(CODE)) {
+        const uint32_t pair = tid < 1 << HYB_Q ? lut[tid] : 0u;
+        is |= not_finite(pair) || not_finite(pair >> 16);
+    }
+    return is;
+}
+// Goes with a sequence's final state and overlap where its second pass has to be searched.
+constexpr uint32_t SEARCHED = 0x80000000u;
+
 // `best` of step T0 where the first state's top bits are O: entries ((O << 12) | 4 tid + i) mod NP, the others are infinite.  The
 // one walk to each: minima over one finite value, in the order and with the roundings of the steps.
 // (The second pass's 255 steps and the search for its last state are 245 steps at kV = 2, 242 or 243 in one launch: us, all steps and
@@ -250,7 +271,8 @@ template <int KV> __device__ __forceinline__ uint32_t forced_digit(uint32_t O, i
 
 // Steps 0 (T0 where the ends are forced, see VitGeo) .. t_end - 1 of sequence tile0 + blockIdx.x, with `best` stored after every J steps
 // counted from the last, G - 1 (copies c_lo .. c_hi - 1, copy c at step G - 1 - J (c + 1)), and, when
-// t_end = G - 1, the best final state.  Where the ends are forced, copies are counted from G and the last one is of T0.  overlap != null: the first state's top L-kV bits and the
+// t_end = G - 1, the best final state.  Where the ends are forced, copies are counted from G and the last one is of T0 (t_end is
+// theirs: a pass that is searched all the same goes up to its own).  overlap != null: the first state's top L-kV bits and the
 // last state's low L-kV bits are forced to overlap[slot] (Algorithm 4's second call).
 // (four waves per SIMD, i.e. at most 128 registers, also where a workgroup is only four waves)
 template <int KV, int V, int CODE>
@@ -265,18 +287,29 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
     __shared__ __attribute__((aligned(16))) float s_best[2][Geo::BEST_FLOATS];
     __shared__ __attribute__((aligned(16))) float s_seq[VT_T + 4];
     __shared__ float s_rv[NT / 64];
-    __shared__ uint32_t s_ry[NT / 64];
+    __shared__ uint32_t s_ry[NT / 64], s_searched;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int slot = blockIdx.x;
     const float INF = __builtin_inff();
     const bool constrained = overlap != nullptr;
-    const uint32_t O = constrained ? overlap[slot] : 0u;
+    const uint32_t given = constrained ? overlap[slot] : 0u, O = given & (uint32_t)(NP - 1);
+    const bool forced = Geo::FORCED && constrained && !(given & SEARCHED);
+    if (Geo::FORCED && constrained && !forced) t_end = c_lo == 0 ? G - 1 : G - 1 - J * (c_lo + 1);
 
-    if (tid < VT_T) s_seq[tid] = sequence_element<CODE>(W, n, tn, tile0 + slot, tid, rotate);
+    if constexpr (Geo::FORCED) {
+        if (!constrained) {
+            if (tid == 0) s_searched = 0u;
+            __syncthreads();
+        }
+    }
+    const float element = tid < VT_T ? sequence_element<CODE>(W, n, tn, tile0 + slot, tid, rotate) : 0.f;
+    if (tid < VT_T) s_seq[tid] = element;
+    if constexpr (Geo::FORCED) {
+        if (!constrained && unbounded<CODE>(element, tid, lut)) s_searched = SEARCHED;
+    }
     // (0 at step 0, but for a first state's top bits that are O; of step T0 all but the forced entries)
-    for (int i = tid; i < NP; i += NT)
-        s_best[0][Geo::place(i)] = constrained && (Geo::FORCED || (uint32_t)i != O) ? INF : 0.f;
+    for (int i = tid; i < NP; i += NT) s_best[0][Geo::place(i)] = constrained && (forced || (uint32_t)i != O) ? INF : 0.f;
 
     // register r of this thread is state (p, hi): WHOLE: p = r % NC, prefix NB tid + r / NC;
     // else (kV = 8) a quarter of a prefix's predecessors, p = 64 (lane / 16) + r
@@ -300,7 +333,7 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
     int c_now = (G - 1 - until) / J - 1;  // the copy that belongs to it
     int t = 0;
     if constexpr (Geo::FORCED) {
-        if (constrained) {
+        if (forced) {
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));  // (nothing that is made with it here is worth a register later)
             const float4_t first = forced_entries<KV, V, CODE>(O, tid, lut, [&](int u, int e) { return s_seq[V * u + e]; });
@@ -314,7 +347,7 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
                 for (uint32_t i = tid; i < (uint32_t)NP; i += NT) dst[i] = s_best[0][Geo::place((int)Geo::prefix_at(i))];
             }
             t = Geo::T0;
-            until = Geo::LAST2;
+            until = Geo::LAST;
             c_now = Geo::NSEG2 - 2;
         }
     }
@@ -392,7 +425,7 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
 #pragma unroll
     for (int r = 0; r < VT_REGS; r++) {
         const uint32_t y = state_of(r);
-        take_better(Geo::FORCED || !constrained || (y & (uint32_t)(NP - 1)) == O,
+        take_better(!constrained | ((y & (uint32_t)(NP - 1)) == O),
                     state_value<V>(cr[r], s0, s1, in[Geo::place((int)(y >> KV))]), y);
     }
 #pragma unroll
@@ -404,7 +437,7 @@ __global__ __launch_bounds__((VitGeo<KV, V, code_state_bits(CODE)>::NT), 4) void
     __syncthreads();
     if (tid == 0) {
         for (int w = 1; w < NT / 64; w++) take_better(true, s_rv[w], s_ry[w]);
-        final_state[slot] = by;
+        final_state[slot] = Geo::FORCED && !constrained ? by | s_searched : by;
         final_value[slot] = bv;
     }
 }
@@ -585,21 +618,25 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
     for (int i = 0; i < VT_T / 64; i++)
         seq[64 * i + lane] = sequence_element<CODE>(W, n, tn, tile0 + slot, 64 * i + lane, pass == 1);
     const bool constrained = pass == 2;
-    const uint32_t O = constrained ? overlap[slot] : 0u;
+    const uint32_t given = constrained ? overlap[slot] : 0u, O = given & (uint32_t)(NP - 1);
     // (the wave's own LDS: its operations complete in order, the fences keep the compiler in line)
     auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    const bool forced = Geo::FORCED && constrained;
-    const int end = forced ? Geo::END : G - 1;
+    const bool forced = Geo::FORCED && constrained && !(given & SEARCHED);
+    const int end = forced ? Geo::END : G - 1, nseg = forced ? Geo::NSEG2 : Geo::NSEG;
+    // (the last tree of a walk that is not forced starts at step 0 and needs no copy)
+    if (Geo::FORCED && constrained && !forced && c_hi == Geo::COPIES) c_hi = Geo::NSEG;
     // (a forced walk begins at a step G whose state has the overlap for a prefix)
-    uint32_t y = __builtin_amdgcn_readfirstlane(forced && c_lo == 0 ? O << KV : final_state[slot]) & ((1u << LB) - 1u);
+    const uint32_t from = __builtin_amdgcn_readfirstlane(forced && c_lo == 0 ? O << KV : final_state[slot]);
+    const uint32_t searched = constrained ? 0u : from & SEARCHED;
+    uint32_t y = from & ((1u << LB) - 1u);
     s_sym[wave][lane] = 0;
     wave_sync();
     if (!forced && c_lo == 0 && lane == 0) sym[G - 1] = (uint8_t)(y >> OV);
-    if (forced && c_hi == Geo::NSEG2 && lane < Geo::T0) sym[lane] = (uint8_t)forced_digit<KV>(O, lane);
+    if (forced && c_hi == nseg && lane < Geo::T0) sym[lane] = (uint8_t)forced_digit<KV>(O, lane);
     const float *my_store = store + (size_t)slot * slots * NP;
     auto tree = [&](auto jj, int c) {
         constexpr int JJ = decltype(jj)::value;
@@ -619,16 +656,16 @@ __global__ __launch_bounds__(256) void viterbi_walk_kernel(
         for (int j = 1; j <= JJ; j++) {
             y = (digit[j] << OV) | (y >> KV);
             if (lane == 0) sym[t - j] = (uint8_t)digit[j];
-            if (first && pass == 1 && t - j == Geo::MID && lane == 0) overlap[slot] = y & (uint32_t)(NP - 1);
+            if (first && pass == 1 && t - j == Geo::MID && lane == 0) overlap[slot] = (y & (uint32_t)(NP - 1)) | searched;
         }
     };
     for (int c = c_lo; c < c_hi; c++) {
-        if (c == Geo::NSEG2 - 1) tree(std::integral_constant<int, Geo::LAST2>{}, c);  // (never the first pass's)
+        if (c == nseg - 1) tree(std::integral_constant<int, Geo::LAST>{}, c);  // (never the first pass's)
         else tree(std::integral_constant<int, J>{}, c);
     }
     if (!first || (pass == 1 && c_hi >= Geo::NSEG_MID)) return;
     wave_sync();
-    if (c_hi < Geo::NSEG2 && lane == 0) final_state[slot] = y;
+    if (c_hi < nseg && lane == 0) final_state[slot] = y | searched;
     if (pass == 1) return;
     if (lane < NWORDS) {
         uint32_t *const out = codes + (size_t)(tile0 + slot) * NWORDS + lane;
@@ -664,7 +701,7 @@ template <int KV, int V> struct FewGeo : VitGeo<KV, V, 16> {
     static constexpr int ARRAYS = KV == 3 ? 4 : 2;             // room for `best` of consecutive steps
     static constexpr int LONGEST = T + ARRAYS;                 // segment
     static constexpr int D1 = VitGeo<KV, V, 16>::G - 1 - VitGeo<KV, V, 16>::MID,
-                         D2 = VitGeo<KV, V, 16>::G - VitGeo<KV, V, 16>::T0;  // steps walked
+                         D2 = VitGeo<KV, V, 16>::G - VitGeo<KV, V, 16>::T0, D2_SEARCHED = VitGeo<KV, V, 16>::G - 1;  // steps walked
     static_assert(16 - KV * T == 4 && NODES <= 1024, "4096 leaves");
     static_assert(D1 > LONGEST, "two segments at least, so one copy");
     static constexpr bool fits(int d, int nseg) { return nseg > 0 && (d + nseg - 1) / nseg <= LONGEST; }
@@ -695,14 +732,20 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
     __shared__ float s_seq[VT_T];
     __shared__ uint32_t s_sym[VT_T / 4];  // one byte per step
     __shared__ float s_rv[16];
-    __shared__ uint32_t s_ry[16], s_state;
+    __shared__ uint32_t s_ry[16], s_state, s_searched;
     int tid = threadIdx.x, my_hi = NB * tid;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), slot = blockIdx.x;
     const float INF = __builtin_inff();
     uint8_t *const sym = reinterpret_cast<uint8_t *>(s_sym);
     float *const my_store = store + (size_t)slot * slots * NP;
 
-    if (tid < VT_T) s_seq[tid] = sequence_element<CODE>(W, n, tn, slot, tid, 0);
+    if (tid == 0) s_searched = 0u;
+    __syncthreads();
+    {
+        const float element = tid < VT_T ? sequence_element<CODE>(W, n, tn, slot, tid, 0) : 0.f;
+        if (tid < VT_T) s_seq[tid] = element;
+        if (unbounded<CODE>(element, tid, lut)) s_searched = SEARCHED;
+    }
     if (tid < VT_T / 4) s_sym[tid] = 0;
     uint32_t cr[VT_REGS];
 #pragma unroll
@@ -715,8 +758,12 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
     for (int pass = 1; pass <= 2; pass++) {
         // (the second pass's ends are forced, see VitGeo: it begins at T0, and its walk at G, whose first segment's `best` is
         // where the forward pass stops and needs no copy)
-        const int rotate = pass == 1 ? VT_T / 2 : 0, begin = pass == 1 ? 0 : Geo::T0, end = pass == 1 ? G - 1 : G;
-        const int nseg = pass == 1 ? nseg1 : nseg2, D = pass == 1 ? Geo::D1 : Geo::D2, uncopied = pass - 1;
+        const bool constrained = pass == 2;
+        const bool forced = constrained && !__builtin_amdgcn_readfirstlane(s_searched);
+        const int rotate = constrained ? 0 : VT_T / 2, begin = forced ? Geo::T0 : 0, end = forced ? G : G - 1;
+        const int nseg = !constrained ? nseg1 : forced ? nseg2 : min((int)slots + 1, Geo::D2_SEARCHED / T);
+        const int D = !constrained ? Geo::D1 : forced ? Geo::D2 : Geo::D2_SEARCHED;
+        const int uncopied = forced, last_copy = nseg - 1 - (constrained && !forced);  // (searched: the last segment starts at step 0)
         const int base = D / nseg, longer = D % nseg;
         auto sample = [&](int t, int e) { return s_seq[(V * t + e + rotate) & (VT_T - 1)]; };
         // the step that copy c, under segment c from the end, belongs to
@@ -727,14 +774,16 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 *reinterpret_cast<float4_t *>(to + Geo::place(my_hi + i)) =
                     float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
         };
+        // (entry `hi` of step 0)
+        auto first = [&](int hi) { return constrained && (uint32_t)hi != O ? INF : 0.f; };
         {
             float best[NB];
 #pragma unroll
-            for (int i = 0; i < NB; i++) best[i] = pass == 1 ? 0.f : INF;
+            for (int i = 0; i < NB; i++) best[i] = forced ? INF : first(my_hi + i);
             put(s_best[0], best);
         }
         __syncthreads();
-        int c_now = nseg - 1, t_next = step_of(c_now);
+        int c_now = last_copy, t_next = step_of(c_now);
         auto copy_at = [&](int c) { return my_store + (size_t)(c - uncopied) * NP; };
         auto next_copy = [&] {
             c_now--;
@@ -747,7 +796,7 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 to[(uint32_t)(NB / 4 * tid + i / 4)] = float4_t{best[i], best[i + 1], best[i + 2], best[i + 3]};
             next_copy();
         };
-        if (pass == 2) {
+        if (forced) {
             const float4_t first = forced_entries<KV, V, CODE>(O, tid, lut, sample);
             *reinterpret_cast<float4_t *>(s_best[0] + Geo::place((int)(((O << 12) | (4u * tid)) & (uint32_t)(NP - 1)))) = first;
             if (tid < Geo::T0) sym[tid] = (uint8_t)forced_digit<KV>(O, tid);
@@ -784,7 +833,7 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             }
             __syncthreads();
         };
-        const int stop = pass == 1 ? G - 1 : step_of(0);
+        const int stop = forced ? step_of(0) : G - 1;
         int t = begin;
         for (; t + 1 < stop; t += 2) {
             step(s_best[0], s_best[1], t);
@@ -793,28 +842,32 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
         if (t < stop) step(s_best[0], s_best[1], t);
         static_assert((G - 1) % 2 == 1, "one step over");
 
-        // the best final state, lowest state on ties
+        // the best allowed final state, lowest state on ties
         float bv = INF;
         uint32_t by = 0xFFFFFFFFu;
-        auto take_better = [&](float v, uint32_t y) {
-            const bool take = (v < bv) | ((v == bv) & (y < by));
+        auto take_better = [&](bool ok, float v, uint32_t y) {
+            const bool take = ok & ((v < bv) | ((v == bv) & (y < by)));
             bv = take ? v : bv;
             by = take ? y : by;
         };
-        if (pass == 1) {
+        if (!forced) {
+            // (what is made with it here is not worth a register in the steps)
+            int my_hi = NB * (int)threadIdx.x;
+            asm volatile("" : "+v"(my_hi));
 #pragma unroll
             for (int r = 0; r < VT_REGS; r++) {
                 const uint32_t y = ((uint32_t)(r % NC) << OV) | (uint32_t)(my_hi + r / NC);
-                take_better(state_value<V>(cr[r], s0, s1, s_best[1][Geo::place((int)(y >> KV))]), y);
+                take_better(!constrained | ((y & (uint32_t)(NP - 1)) == O),
+                            state_value<V>(cr[r], s0, s1, s_best[1][Geo::place((int)(y >> KV))]), y);
             }
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) take_better(__shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
+            for (int off = 32; off > 0; off >>= 1) take_better(true, __shfl_xor(bv, off, 64), __shfl_xor(by, off, 64));
             if (lane == 0) s_rv[wave] = bv, s_ry[wave] = by;
         }
         // (a segment's copy, on the way while the one before is walked)
         float pre[AHEAD];
         auto fetch = [&](int c) {  // (whether there is one or not: else the last one would have to be kept meanwhile)
-            const float *const from = copy_at(min(c, nseg - 1));
+            const float *const from = copy_at(min(c, last_copy));
             if constexpr (KV == 3) {
 #pragma unroll
                 for (int p = 0; p < NC; p++) pre[p] = (from + (p << (OV - KV)))[(uint32_t)tid];
@@ -828,13 +881,17 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
             }
         };
         uint32_t y;
-        if (pass == 1) {
+        if (!forced) {
             fetch(0);
             __syncthreads();
             bv = INF;
             by = 0xFFFFFFFFu;
-            for (int w = 0; w < 16; w++) take_better(s_rv[w], s_ry[w]);
+            for (int w = 0; w < 16; w++) take_better(true, s_rv[w], s_ry[w]);
             y = __builtin_amdgcn_readfirstlane(by) & 0xFFFFu;
+            if (constrained && tid == 0) {
+                sym[G - 1] = (uint8_t)(y >> OV);
+                if (tile_err) tile_err[slot] = bv;
+            }
         } else {  // what a copy of this step would bring, and a state of step G with the overlap for a prefix
             const float *const at = s_best[(stop - begin) & 1];
             if constexpr (KV == 4) {
@@ -861,8 +918,19 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 else return pre;
             }();
             if constexpr (KV == 4) {
+                if (c > last_copy) {
+#pragma unroll
+                    for (int i = 0; i < NB; i++) pre[i] = first(my_hi + i);
+                }
                 put(s_best[0], pre);
                 __syncthreads();
+            } else if (c > last_copy) {
+#pragma unroll
+                for (int p = 0; p < NC; p++) {
+#pragma unroll
+                    for (int a = 0; a < COUNT / NC; a++)
+                        pre[COUNT / NC * p + a] = first((p << (OV - KV)) + COUNT / NC * tid + a);
+                }
             }
             const uint32_t under = (y >> (KV * T)) & 15u;  // low bits of the leaves
             if (forward > 0) {
@@ -1033,7 +1101,7 @@ __global__ __launch_bounds__(1024, 4) void viterbi_few_kernel(const float *__res
                 if constexpr (ROOTS >= 2) across(std::integral_constant<int, 2>{});
                 across(std::integral_constant<int, 1>{});
                 walk = __builtin_amdgcn_readfirstlane(walk);
-                if (pass == 2 && c == 0 && tile_err && lane == 0) tile_err[slot] = m;
+                if (forced && c == 0 && tile_err && lane == 0) tile_err[slot] = m;
                 if (lane < T) sym[t - 1 - lane] = (uint8_t)((walk >> (KV * lane)) & (uint32_t)(NC - 1));
                 uint32_t z = (walk << 4) | under;
                 // and the steps that were taken forward
