@@ -188,12 +188,14 @@ template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS> struct GemmL
     static constexpr int STEP_BYTES = (LUT ? 8 : 4) * 8 * K;               // code words of a tile row and step
     static constexpr int CODE_ROW = KS * STEP_BYTES, CODE_ROWS = LUT ? RB : 2 * RB;  // of a wave and stage
     static constexpr int CODE_COPIES = (CODE_ROWS * CODE_ROW + 1023) / 1024, CODE_STAGE = CODE_COPIES * 1024;
-    static constexpr int TABLE_WORDS = LUT ? 1 << 13 : code_lds_words(CODE);
+    static constexpr int TABLE_WORDS = LUT ? 1 << 13 : code_lds_words(CODE) > 1 ? code_lds_words(CODE) : 0;
     // batch groups whose partial sums are in LDS at the same time, in the room of the activations
     static constexpr int SUM_BYTES = WM * WK * RB * 4096;
     static constexpr int SUMS = WK == 1 ? 0 : NBB * SUM_BYTES <= 2 * WK * SLICE ? NBB : (2 * WK * SLICE) / SUM_BYTES;
     static constexpr int BYTES = 2 * WK * SLICE + WM * WK * 2 * CODE_STAGE + (4 * TABLE_WORDS + 1023) / 1024 * 1024;
     static_assert(WK == 1 || (SUMS >= 1 && NBB % SUMS == 0), "whole rounds of partial sums");
+    // (a kilobyte more, and one: us, 2-bit 3INST 4128 x 2048, 96 rows, 9.4 and 11.1, 10240 x 2048, 192 rows, 18.4 and 21.1)
+    static_assert(TABLE_WORDS > 0 || RB * NBB > 1 || 2 * BYTES <= 160 * 1024, "32 x 32: two workgroups per CU");
 };
 
 template <int K, int CODE, int RB, int NBB, int WM, int WK, int KS>
@@ -252,6 +254,7 @@ __global__ __launch_bounds__(WM *WK * 64, RB *NBB > 4 ? 1 : 2) void gemm_kernel(
         __attribute__((aligned(1024))) char x[2 * WK * SLICE];
         __attribute__((aligned(1024))) char codes[WM * WK * 2 * CODE_STAGE];
     } s_all;
+    static_assert(sizeof(s_all) == Lds::BYTES, "as the launcher counts");
     uint32_t *const s_lut = s_all.lut;
     char *const s_x = s_all.x, *const s_codes = s_all.codes;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;

@@ -75,8 +75,9 @@ def test_rows_in_halves(code, k, m, n, halves):
     assert torch.equal(product(2048), product(m)[:2048]) == halves
 
 
-# (with one time per round for all codes: 1.16 to 1.41)
+# (with one time per round for all codes: 1.16 to 1.41; with one workgroup of 32 x 32 on a CU, where there is room for two, 1.15)
 @pytest.mark.parametrize("code,k,m,n,fewer,more", [
+    (CODE_3INST, 2, 4128, 768, 96, 128),
     (CODE_HYB, 2, 9216, 4096, 96, 128), (CODE_HYB1, 2, 6400, 2048, 160, 192), (CODE_3INST, 3, 4128, 14464, 224, 256),
     (CODE_LUT, 2, 8192, 1024, 160, 192), (CODE_LUT, 4, 6144, 4096, 192, 224)])
 def test_fewer_batch_rows_take_no_longer(code, k, m, n, fewer, more):
