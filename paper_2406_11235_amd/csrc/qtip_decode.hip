@@ -879,11 +879,22 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     else if (big) QTIP_MM(R, NW, 16, false);  \
     else if (spread) QTIP_MM(R, NW, K == 2 ? 0 : 8, HYB);  \
     else QTIP_MM(R, NW, 0, false)
-    // (row counts between the rounds of pairs, but not where the table reads of long rows count for more than an idle CU: HYB2
-    // k = 4 12288 x 14336, 8 rows, single rows 32.2 us, pairs 27.6)
-    const bool between = tm <= 4 * CUS && !spread && !(HASH && n >= 8192) && (tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256);
-    const bool few_waves = (!big && (spread || (HYB && K == 4))) || (!spread && tn < (tm > 4 * CUS ? 768 : big ? 512 : 256));
-    if (tm <= CUS) {
+    // Single rows at row counts between the rounds of pairs (beyond four rounds for the V = 1 hash code alone: single rows and
+    // pairs, us, k = 3 28672 x 4096, 2 rows, 25.4 28.4; 3-bit 3INST 20480 x 14336, 8 rows, 64.5 54.9), but not where the table reads
+    // of long rows count for more than an idle CU: HYB2 k = 4 12288 x 14336, 8 rows, 33.7 30.6; k = 3, 16 rows, 38.9 41.6.  With
+    // 16 waves at 3 bits and up to 8 rows, where code words are two loads a lane (8 waves and 16: 3INST 10240 x 14336 42.5 37.7,
+    // 1MAD 12288 x 28672 81.4 75.2; V = 1 hash code 12288 x 8192 28.5 27.4, but 4096 inputs 13.4 15.2).
+    const bool between = (tm <= 4 * CUS || (CODE == CODE_HYB1 && n >= 2048)) && !spread && !(HASH && n >= 8192 && !(K == 3 && big)) &&
+                         (tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256);
+    const bool between_16 = between && K == 3 && !big && tm <= 4 * CUS && n >= (CODE == CODE_HYB1 ? 8192 : 4096);
+    // Eight waves for more than two tile rows per CU where a row is short, and where code values and batch rows leave too few
+    // registers for two workgroups of 16 (16 waves and 8, us: V = 1 hash code k = 3 14336 x 4096, 8 rows, 18.6 16.9; 16 rows, 2-bit 3INST
+    // 16400 x 14336 54.2 48.7, HYB2 k = 3 14336 x 8192 27.0 25.3; but 8 rows, 2-bit 1MAD 14336 x 14336 36.8 39.1).  Over 15 codecs, 4112 to
+    // 28672 outputs, 1024 to 28672 inputs and 2, 8, 9 and 16 rows, each of the four forced in turn, 1.6 % above the fastest.
+    const bool few_waves = (!big && (spread || (HYB && K == 4))) ||
+                           (!spread && (tn < (tm > 4 * CUS ? 768 : big ? 512 : 256) || (K == 3 && (big || !HASH)) ||
+                                        (!HASH && (big || (CODE == CODE_3INST && K == 4)))));
+    if (tm <= CUS || between_16) {
         QTIP_MM_BATCH(1, 16);
     } else if (between) {
         QTIP_MM_BATCH(1, 8);

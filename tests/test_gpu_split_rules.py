@@ -84,3 +84,18 @@ def test_fewer_batch_rows_take_no_longer(code, k, m, n, fewer, more):
     product = Product(code, k, m, n, more)
     a, b = product.us(m, fewer), product.us(m, more)
     assert a <= 1.1 * b, (a, b)
+
+
+# (two and more batch rows, up to 16: a row's sum is over 16 waves' slices of the inputs or over eight's, whatever rows share a
+# workgroup; 4096 rows have 16 waves.  Before the rule looked at the code: V = 1 hash code, 14336 x 4096, 3 bits, 8 rows 16.6 us with
+# eight waves, 19.0 with 16; HYB2 3 bits 10240 x 8192, 16 rows, single rows 22.8, pairs 25.8)
+@pytest.mark.parametrize("code,k,m,n,B,waves", [
+    (CODE_HYB1, 3, 14336, 4096, 8, 8), (CODE_HYB1, 3, 10240, 4096, 8, 8), (CODE_HYB1, 3, 10240, 8192, 8, 16),
+    (CODE_HYB1, 2, 14336, 4096, 8, 16), (CODE_HYB1, 2, 14336, 8192, 16, 8), (CODE_HYB1, 3, 16400, 4096, 2, 8),
+    (CODE_3INST, 3, 10240, 4096, 2, 16), (CODE_3INST, 2, 14336, 8192, 8, 16), (CODE_3INST, 2, 14336, 8192, 9, 8),
+    (CODE_3INST, 4, 14336, 8192, 8, 8), (CODE_1MAD, 4, 14336, 8192, 8, 16), (CODE_1MAD, 3, 8192, 4096, 16, 16),
+    (CODE_HYB2, 3, 10240, 8192, 16, 8), (CODE_HYB2, 4, 10240, 8192, 16, 16), (CODE_HYB, 4, 14336, 2048, 8, 8)])
+def test_waves_of_up_to_16_batch_rows(code, k, m, n, B, waves):
+    import torch
+    product = Product(code, k, m, n, B)
+    assert torch.equal(product(4096, B), product(m, B)[:, :4096]) == (waves == 16)
