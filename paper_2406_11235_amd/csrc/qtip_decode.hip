@@ -820,14 +820,16 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     const int groups = (B + 15) / 16;  // more than one only where matmat_takes them or the large-batch kernel does not reach
     const int tm = m / 16, tn = n / 16;
     const half_t *Xh = (const half_t *)X, *sc = (const half_t *)scale;
-    // Rows of more than 2^22 inputs: a workgroup decodes a weight for 16 batch rows while that makes at most two workgroups per CU, and for 32
-    // or 64 otherwise (2^22 inputs, 2-bit 3INST, ms for 16 and for 32 or 64: 1024 outputs 64 rows 3.8 and 8.7, 128 rows
-    // 7.2 and 8.8, 200 rows 13.4 and 8.9; 4096 outputs 24 rows 6.8 and 6.8, 48 rows 10.0 and 8.7, 200 rows 39.8 and 21.7).
+    // Few outputs, where 16 batch rows at a time are more than one workgroup per CU and 32 are not.
     if (groups > 1 && n <= 1 << 22 && (long)tm * groups > CUS && (long)tm * ((groups + 1) / 2) <= CUS) {
         hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 1, 2, 16, 32>), dim3(tm, (groups + 1) / 2), dim3(16 * 64), 0, st, codes, lut,
                            tm, tn, Xh, B, sc, Y);
         return hipGetLastError();
     }
+    // Many outputs, 17 to 32 batch rows; and rows of more than 2^22 inputs: there a workgroup decodes a weight for 16 batch rows
+    // while that makes at most two workgroups per CU, and for 32 or 64 otherwise (2^22 inputs, 2-bit 3INST, ms for 16 and for 32
+    // or 64: 1024 outputs 64 rows 3.8 and 8.7, 128 rows 7.2 and 8.8, 200 rows 13.4 and 8.9; 4096 outputs 24 rows 6.8 and 6.8, 48
+    // rows 10.0 and 8.7, 200 rows 39.8 and 21.7).
     if (groups > 1 && (long)tm * groups > 512) {
         if (groups == 2)
             hipLaunchKernelGGL((matmat_kernel<K, V, CODE, 2, 2, 8, 32>), dim3((tm + 1) / 2), dim3(8 * 64), 0, st, codes,
@@ -957,17 +959,21 @@ hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const ui
     QTIP_DISPATCH(launch_matvec_t, codes, lut, m, n, x, signs, log2_block, scale, y, st);
 }
 
-// More than 16 batch rows by the kernel for 16 (or 32) of them at a time: where workgroups of one tile row and 32 batch rows are
+// 17 to 256 batch rows by the kernel for 16 (or 32) of them at a time: where workgroups of one tile row and 32 batch rows are
 // one per CU at most, which leaves gemm_kernel, 32 outputs and eight waves each, fewer CUs and longer slices; and up to 32
-// rows where its workgroups are more than one round of which the last may be nearly empty, but for the hash codes' long rows.
+// rows of many outputs for the codes with a table, which leaves room for one workgroup of gemm_kernel on a CU (the others have two),
+// if rows are not long.
 // us, that kernel and this one: 2-bit 3INST 1024 x 14336 32 rows 21.1 11.6, 64 rows 21.2 13.7, 128 rows 22.3 16.9, 4096 x 4096 17 rows
-// 8.5 6.7, 4096 x 14336 32 rows 22.9 18.2, 14336 x 4096 32 rows 17.0 14.9, 5120 x 4096 32 rows 8.7 9.7; 4-bit HYB 1024 x 14336 32 rows
-// 19.0 13.4, 2048 x 4096 64 rows 8.0 8.0, 14336 x 14336 32 rows 44.5 45.8.  Six codes, 21 heights, 1024 to 28672 inputs, 17 to
-// 128 rows: where the rule takes them 0.97 to 2.1 times as fast, 1.2 on average.
+// 8.5 6.7, 4096 x 14336 32 rows 22.9 18.2, 5120 x 4096 32 rows 8.7 9.7; 4-bit HYB 1024 x 14336 32 rows 19.0 13.4, 2048 x 4096 64 rows
+// 8.0 8.0.  Six codes, 16 to 4096 outputs, 16 to 2^20 inputs: up to 256 rows 0.97 to 2.1 times as fast, 1.5 on average; more rows,
+// which are few outputs, are not taken (16 x 4096, 512 rows 0.8 times, 2000 rows 8.9 us and 34).  17 to 32 rows of more than 8192
+// outputs, time of this kernel over that one's: V = 1 hash code 0.73 at 64 inputs, 0.94 at 6144, 1.0 at 8192, 1.05 at 28672; HYB and
+// HYB2 0.76, 0.98 at 4096, 1.0 at 6144, 1.05; codes without a table 0.95 at 64 inputs, 1.02 at 2048, 1.1 at 8192.
 static bool matmat_takes(int code_id, int m, int n, int B) {
     const int tm = m / 16, groups = (B + 15) / 16;
-    if (code_id == CODE_LUT) return false;
-    return (long)tm * ((groups + 1) / 2) <= CUS || (groups == 2 && tm > 2 * CUS && !(code_is_hyb(code_id) && n >= 8192));
+    if (code_id == CODE_LUT || B > 256) return false;
+    return (long)tm * ((groups + 1) / 2) <= CUS ||
+           (groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192));
 }
 
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
