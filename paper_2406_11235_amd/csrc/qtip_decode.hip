@@ -976,13 +976,16 @@ static bool matmat_takes(int code_id, int m, int n, int B) {
            (groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192));
 }
 
+// The lookup-only code's own kernel decodes 16 waves' shares of 32 outputs one wait after the other.  It is the faster one
+// where at most eight CUs have one, of code words from the caches, and for what the other one does not take (us, up to 16
+// rows, k = 2, gemm_kernel and it: 32 x 14464 30.2 28.8, 256 x 4096 11.3 11.2, 256 x 2048 7.6 7.6, 256 x 65536 122 133, 1024 x 14464 31.1 34.3; and where it
+// was the only one until now, 96 x 2^24 30.3 and 38.8 ms, 32 x 2^23 k = 4 15.1 and 19.6).
+static bool lut_matmat_takes(int m, int n, int B) { return B <= 16 && m <= 256 && n > 2048 && n <= 16384; }
+
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                          int n, const void *X, int B, const void *scale, float *Y,
                          hipStream_t st) {
-    // The lookup-only code's own kernel, for rows too long for the other one, decodes 16 waves' shares of 32 outputs one wait
-    // after the other (us, 16 rows, k = 2, and gemm_kernel: 1024 x 2048 8.2 8.2, 8192 x 8192 26.0 21.3, 4128 x 14464 39.8 31.9).
-    if (code_id == CODE_LUT ? gemm_takes(code_id, n, B) && (B > 16 || n <= 1 << 22)
-                            : B > 16 && gemm_takes(code_id, n, B) && !matmat_takes(code_id, m, n, B))
+    if (gemm_takes(code_id, n, B) && (code_id == CODE_LUT ? !lut_matmat_takes(m, n, B) : B > 16 && !matmat_takes(code_id, m, n, B)))
         return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
     if (code_id == CODE_LUT) return launch_lut_matmat(k, codes, lut, m, n, X, B, scale, Y, st);
     QTIP_DISPATCH(launch_matmat_t, codes, lut, m, n, X, B, scale, Y, st);

@@ -80,8 +80,16 @@ def test_more_than_16_rows_at_a_time(q, code, k):
 
 @pytest.mark.parametrize("k", [2, 3, 4])
 def test_up_to_16_rows_of_the_lookup_only_code(q, k):
-    for m, n, B in ((32, 8, 2), (96, 1032, 9), (4128, 2056, 16), (8224, 264, 3), (32, 14464, 8)):
+    for m, n, B in ((32, 8, 2), (96, 1032, 9), (4128, 2056, 16), (8224, 264, 3), (32, 14464, 8), (32, 16392, 8)):
         check(q, CODE_LUT, k, m, n, B, scaled=B > 8)
+
+
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_few_outputs_of_the_lookup_only_code(q, k):
+    """Its own kernel's: at most 16 batch rows of 256 outputs; an odd number of blocks, slices that do not fill."""
+    for m, n in ((32, 2056), (96, 4104), (224, 8192), (256, 16384)):
+        for B in (2, 3, 9, 16):
+            check(q, CODE_LUT, k, m, n, B, scaled=B > 8, seed=n)
 
 
 @pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
@@ -191,12 +199,12 @@ def test_stages_of_two_tiles(q, k, m, n, B):
     assert (Y.double() - ref).norm() <= 1.4e-7 * ref.norm()
 
 
-def check_sparse(q, code, m, n, rows):
+def check_sparse(q, code, m, n, rows, k=None):
     """All but about 1200 inputs, the first, the last and some everywhere, are zeros, so that a single wrong tile shows: a
     wave's running sum changes in at most 400 of its additions, each of which is off by at most a unit of the sum, 2^-23."""
     import torch
     L, V, entries = CODES[code]
-    k = 2 + code % 3
+    k = k or 2 + code % 3
     g = torch.Generator(device="cuda").manual_seed(code)
     codes = torch.randint(-2**31, 2**31, (m * n // 256, 8 * k), dtype=torch.int32, device="cuda", generator=g)
     lut = torch.randn(entries, device="cuda", generator=g).half() if entries else None
@@ -222,6 +230,13 @@ def check_sparse(q, code, m, n, rows):
 def test_very_long_rows(q, code, n):
     """Lengths at which the larger splits' 32-bit offsets, and then every split's, do not reach."""
     check_sparse(q, code, 32 if code == CODE_LUT else 48, n, (17, 32, 33, 65))
+
+
+@pytest.mark.parametrize("k", [2, 3, 4])
+@pytest.mark.parametrize("n", [2**22, 2**22 + 80, 2**25 + 80])
+def test_very_long_rows_of_few_batch_rows(q, k, n):
+    """The lookup-only code where its own kernel gets what the other one's offsets do not reach, and before."""
+    check_sparse(q, CODE_LUT, 32, n, (2, 9, 16), k)
 
 
 @pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
