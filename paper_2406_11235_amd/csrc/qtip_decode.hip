@@ -969,11 +969,21 @@ hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const ui
 // which are few outputs, are not taken (16 x 4096, 512 rows 0.8 times, 2000 rows 8.9 us and 34).  17 to 32 rows of more than 8192
 // outputs, time of this kernel over that one's: V = 1 hash code 0.73 at 64 inputs, 0.94 at 6144, 1.0 at 8192, 1.05 at 28672; HYB and
 // HYB2 0.76, 0.98 at 4096, 1.0 at 6144, 1.05; codes without a table 0.95 at 64 inputs, 1.02 at 2048, 1.1 at 8192.
-static bool matmat_takes(int code_id, int m, int n, int B) {
+// Where 16 rows at a time would be more than one workgroup per CU and 32 are not, long rows that begin in the middle of a cache line
+// go to the other kernel, which reads each half as often: a step's 64 inputs of 32 batch rows are 64 lines there, not 32.  Time of this kernel over
+// that one's for more than 4096 inputs, in whole cache lines and not: codes without a table 0.83 on average and 1.05 at most, 1.00 and 1.30; HYB
+// and HYB2 0.90 and 1.01, 1.09 and 1.35 (480 x 28400, 3 bits, 140 rows 54.5 us and 40.5); V = 1 hash code, whose table reads take longer
+// than either, 0.75 and 0.85.  Up to 4096 inputs 0.87 either way.  HYB at 3 and 4 bits is as close as 0.93 up to 64 rows, and above
+// 64 of more than 8192 inputs, which the L2s do not hold beside the code words, 1.04 and 1.18.
+static bool matmat_takes(int k, int code_id, int m, int n, int B) {
     const int tm = m / 16, groups = (B + 15) / 16;
     if (code_id == CODE_LUT || B > 256) return false;
-    return (long)tm * ((groups + 1) / 2) <= CUS ||
-           (groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192));
+    if ((long)tm * groups <= CUS) return true;
+    if ((long)tm * ((groups + 1) / 2) <= CUS) {
+        if (n <= 4096 || code_id == CODE_HYB1) return true;
+        return n % 64 == 0 && !(code_id == CODE_HYB && k > 2 && groups > 4 && n > 8192);
+    }
+    return groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192);
 }
 
 // The lookup-only code's own kernel decodes 16 waves' shares of 32 outputs one wait after the other.  It is the faster one
@@ -985,7 +995,7 @@ static bool lut_matmat_takes(int m, int n, int B) { return B <= 16 && m <= 256 &
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                          int n, const void *X, int B, const void *scale, float *Y,
                          hipStream_t st) {
-    if (gemm_takes(code_id, n, B) && (code_id == CODE_LUT ? !lut_matmat_takes(m, n, B) : B > 16 && !matmat_takes(code_id, m, n, B)))
+    if (gemm_takes(code_id, n, B) && (code_id == CODE_LUT ? !lut_matmat_takes(m, n, B) : B > 16 && !matmat_takes(k, code_id, m, n, B)))
         return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
     if (code_id == CODE_LUT) return launch_lut_matmat(k, codes, lut, m, n, X, B, scale, Y, st);
     QTIP_DISPATCH(launch_matmat_t, codes, lut, m, n, X, B, scale, Y, st);
