@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 CODES = {CODE_1MAD: (16, 1, 0), CODE_3INST: (16, 1, 0), CODE_HYB: (16, 2, 1024), CODE_HYB2: (16, 2, 1024),
          CODE_LUT: (14, 1, 1 << 14), CODE_HYB1: (16, 1, 64)}
-# m, n, B: 32 x 32, 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 128 x 256 outputs x batch rows of a workgroup
+# m, n, B: 32 x 32, 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 128 x 256 outputs x batch rows of a workgroup (32 x 32, the first three,
+# for the lookup-only code alone: the others' few outputs are another kernel's, and the end of MORE_THAN_16 has theirs)
 SHAPES = [(32, 16, 17), (96, 208, 33), (544, 1056, 40), (8192, 80, 49), (8224, 48, 64), (16384, 144, 100),
           (8224, 112, 200), (16416, 80, 1000), (16384, 272, 769)]
 
@@ -66,7 +67,7 @@ def test_up_to_16_rows(q, code, k):
 
 
 # above that: 16 and 32 rows at a time, halves of tile rows, the last group nearly empty; up to 32 rows of many outputs; and the
-# 32 x 32, 32 x 64 and 64 x 128 splits where outputs are too many for these
+# 32 x 32 and 32 x 64 splits where outputs are too many for these
 MORE_THAN_16 = [(16, 1040, 17), (240, 4112, 100), (1024, 1056, 64), (1040, 144, 49), (2032, 4128, 50), (48, 80, 1000),
                 (4096, 272, 17), (8208, 144, 32), (14352, 4112, 18), (4112, 208, 17), (2080, 1056, 40), (2080, 272, 100)]
 
@@ -115,19 +116,28 @@ def test_half_a_step_of_the_lookup_only_code(q):
             check(q, CODE_LUT, 2 + n % 3, m, n, B, scaled=False)
 
 
-def test_a_batch_row_meets_nothing_but_itself(q):
-    """An infinity in one batch row leaves the others finite; rows of a last, partly filled tile included."""
+# few outputs, 16 batch rows at a time (32 x 32 for the lookup-only code); and 32 x 64, 32 x 32 and 64 x 128 outputs x batch rows,
+# whose copies of a slice's last stage run into the next row and whose first stage begins ahead of the row: whole stages of all
+# slices, one step more, half and less
+@pytest.mark.parametrize("code", [CODE_3INST, CODE_HYB, CODE_LUT])
+@pytest.mark.parametrize("m,B", [(64, 37), (4128, 37), (4128, 70), (8192, 200)])
+@pytest.mark.parametrize("n", [16, 80, 528, 1024, 1040])
+def test_a_batch_row_meets_nothing_but_itself(q, code, m, B, n):
+    """An infinity among a batch row's first, last or other inputs leaves the others finite, and as they are without it; rows
+    of a last, partly filled tile included."""
     import torch
-    m, n, B = 64, 80, 37
+    L, V, entries = CODES[code]
     codes = torch.randint(-2**31, 2**31, (m * n // 256, 16), dtype=torch.int32, device="cuda")
+    lut = torch.randn(entries, device="cuda").half() if entries else None
     X = torch.randn(B, n, device="cuda").half()
-    X[5, 3] = float("inf")
-    Y = torch.empty(B, m, device="cuda")
-    q.qtip_decode_matmat(codes, 16, 2, 1, CODE_3INST, None, m, n, X, B, None, Y)
-    torch.cuda.synchronize()
-    ok = torch.ones(B, dtype=torch.bool, device="cuda")
-    ok[5] = False
-    assert torch.isfinite(Y[ok]).all() and not torch.isfinite(Y[5]).any()
+    Y, without = torch.empty(B, m, device="cuda"), torch.empty(B, m, device="cuda")
+    q.qtip_decode_matmat(codes, L, 2, V, code, lut, m, n, X, B, None, without)
+    for row, place in ((5, 3), (0, n - 1), (B - 2, 0), (B - 2, n - 1), (B - 1, 0)):
+        Z = X.clone()
+        Z[row, place] = float("inf")
+        q.qtip_decode_matmat(codes, L, 2, V, code, lut, m, n, Z, B, None, Y)
+        ok = torch.arange(B, device="cuda") != row
+        assert torch.equal(Y[ok], without[ok]) and not torch.isfinite(Y[row]).any(), (row, place)
 
 
 @pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
