@@ -868,9 +868,10 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     }
     // The 16 copies of the HYB table: a step's 16 reads of one copy take the LDS 112 cycles, of 16 copies about 70, and filling
     // them 0.5 us (us, one copy and 16: 8 rows k = 2 8192 x 14336 16.2 13.3, 8192 x 4096 7.0 6.5, 8192 x 1024 4.1 4.5; 16 rows k = 2 4096 x
-    // 28672 24.9 20.9).  At 3 and 4 bits it pays with the activations through LDS, which leaves the texture path to the code words
-    // (one copy, 16, 16 and so: k = 3 8192 x 8192 12.3 12.9 11.1, 14336 x 14336 34.0 34.8 29.2, k = 4 14336 x 14336 27.2 26.7 25.3, 8192 x 28672
-    // 29.7 26.9 26.2, but k = 2 14336 x 14336 26.7 21.9 25.8).
+    // 28672 24.9 20.9).  At 3 and 4 bits it pays with the activations through LDS: the address half of the texture units, busy for
+    // 58 400 of 80 000 cycles otherwise, then has 40 000 of 59 100 (k = 3 14336 x 14336, 8 rows; us, one copy, 16, 16 and so:
+    // k = 3 8192 x 8192 12.3 12.9 11.1, 14336 x 14336 34.0 34.8 29.2, k = 4 14336 x 14336 27.2 26.7 25.3, 8192 x 28672 29.7 26.9
+    // 26.2, but k = 2 14336 x 14336 26.7 21.9 25.8).
     const bool long_row = K == 2 ? n >= 4096 : K == 3 ? n >= (tm <= 2 * CUS ? 4096 : 8192) : n >= (tm <= 2 * CUS ? 12288 : 8192);
     const bool spread = HYB && (big ? n >= 8192 : tm > CUS && long_row);
 #define QTIP_MM(R, NW, SR, SPREAD)                                                                              \
@@ -969,20 +970,19 @@ hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const ui
 // which are few outputs, are not taken (16 x 4096, 512 rows 0.8 times, 2000 rows 8.9 us and 34).  17 to 32 rows of more than 8192
 // outputs, time of this kernel over that one's: V = 1 hash code 0.73 at 64 inputs, 0.94 at 6144, 1.0 at 8192, 1.05 at 28672; HYB and
 // HYB2 0.76, 0.98 at 4096, 1.0 at 6144, 1.05; codes without a table 0.95 at 64 inputs, 1.02 at 2048, 1.1 at 8192.
-// Where 16 rows at a time would be more than one workgroup per CU and 32 are not, long rows that begin in the middle of a cache line
-// go to the other kernel, which reads each half as often: a step's 64 inputs of 32 batch rows are 64 lines there, not 32.  Time of this kernel over
-// that one's for more than 4096 inputs, in whole cache lines and not: codes without a table 0.83 on average and 1.05 at most, 1.00 and 1.30; HYB
-// and HYB2 0.90 and 1.01, 1.09 and 1.35 (480 x 28400, 3 bits, 140 rows 54.5 us and 40.5); V = 1 hash code, whose table reads take longer
-// than either, 0.75 and 0.85.  Up to 4096 inputs 0.87 either way.  HYB at 3 and 4 bits is as close as 0.93 up to 64 rows, and above
-// 64 of more than 8192 inputs, which the L2s do not hold beside the code words, 1.04 and 1.18.
+// Where 16 rows at a time would be more than one workgroup per CU and 32 are not, what is read of X decides: there are twice as many
+// workgroups as the other kernel's to read it, and rows that do not begin with a cache line have 64 lines in a step's 64 inputs of 32
+// batch rows, not 32.  Time of this kernel over that one's: codes without a table 0.84 in whole lines, 0.9 otherwise up to 4096
+// inputs and 1.4 at worst beyond (480 x 28400, 140 rows, 3-bit HYB 54.5 us and 38.6; 592 x 19728, 136 rows, 2-bit 3INST 38.7 28.6); V = 1 hash
+// code, with the most table reads, 0.86, 0.9 up to 8192 inputs and 1.05 beyond; HYB and HYB2 0.93 up to 2048 inputs, then 0.95 in whole
+// lines at 2 bits, and 0.98 to 1.1 at 3 and 4, where that kernel hashes two states at once.
 static bool matmat_takes(int k, int code_id, int m, int n, int B) {
     const int tm = m / 16, groups = (B + 15) / 16;
     if (code_id == CODE_LUT || B > 256) return false;
     if ((long)tm * groups <= CUS) return true;
-    if ((long)tm * ((groups + 1) / 2) <= CUS) {
-        if (n <= 4096 || code_id == CODE_HYB1) return true;
-        return n % 64 == 0 && !(code_id == CODE_HYB && k > 2 && groups > 4 && n > 8192);
-    }
+    if ((long)tm * ((groups + 1) / 2) <= CUS)
+        return n <= (code_is_hyb(code_id) ? 2048 : code_id == CODE_HYB1 ? 8192 : 4096) ||
+               (n % 64 == 0 && (k == 2 || !code_is_hyb(code_id)));
     return groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192);
 }
 
