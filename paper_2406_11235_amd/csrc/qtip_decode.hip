@@ -402,13 +402,12 @@ __global__ __launch_bounds__(NW * 64, (CODE == CODE_HYB1 || FUSED) ? 4 : 8) void
 //   one 16-byte load; A and B pair contraction slots by (s, element), so the order
 //   in which the hardware numbers them does not matter;
 //   D[4 (l / 16) + r][l % 16] = output row 16 I + 4 (l/16) + r for batch row b0 + l % 16.
-// A wave owns R = 2 neighbouring tile rows so that every B operand it loads feeds
-// two MFMAs; NB groups of 16 batch rows share every decoded weight.  The waves of
+// A wave owns R tile rows, two where there are enough, so that every B operand it loads
+// feeds two MFMAs; NB groups of 16 batch rows share every decoded weight.  The waves of
 // a workgroup split the tiles of the row band and meet in LDS.
 // The B operand puts neighbouring lanes on different batch rows, that is on different
-// cache lines, and the texture path serves such a 16-byte-per-lane load at a fraction
-// of the rate of one whose neighbouring lanes read neighbouring addresses.  With few
-// distinct batch rows that does not matter; at larger batch (STAGE) a wave loads its
+// cache lines, for each of which the texture units' address half takes cycles of its own.  With
+// few distinct batch rows that rarely matters; otherwise (STAGE) a wave loads its
 // activations line by line (8 lanes = the 128 bytes that one batch row has under the
 // four tiles of a step) and transposes them through a private piece of LDS.
 
@@ -986,16 +985,14 @@ static bool matmat_takes(int k, int code_id, int m, int n, int B) {
     return groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192);
 }
 
-// The lookup-only code's own kernel decodes 16 waves' shares of 32 outputs one wait after the other.  It is the faster one
-// where at most eight CUs have one, of code words from the caches, and for what the other one does not take (us, up to 16
-// rows, k = 2, gemm_kernel and it: 32 x 14464 30.2 28.8, 256 x 4096 11.3 11.2, 256 x 2048 7.6 7.6, 256 x 65536 122 133, 1024 x 14464 31.1 34.3; and where it
-// was the only one until now, 96 x 2^24 30.3 and 38.8 ms, 32 x 2^23 k = 4 15.1 and 19.6).
-static bool lut_matmat_takes(int m, int n, int B) { return B <= 16 && m <= 256 && n > 2048 && n <= 16384; }
-
+// The lookup-only code's own kernel decodes 16 waves' shares of 32 outputs one wait after the other; it is for what the other one does
+// not take (us, up to 16 rows, code words from memory, it and gemm_kernel: k = 2 1024 x 14464 34.7 30.8, k = 4 1472 x 24152 56.6 48.4,
+// 256 x 11736 30.0 25.3; up to 256 outputs it takes 0.97 to 1.19 times as long, 1.02 on average, and from the caches 0.95 to 0.98; ms,
+// 96 x 2^24 38.8 30.3).
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                          int n, const void *X, int B, const void *scale, float *Y,
                          hipStream_t st) {
-    if (gemm_takes(code_id, n, B) && (code_id == CODE_LUT ? !lut_matmat_takes(m, n, B) : B > 16 && !matmat_takes(k, code_id, m, n, B)))
+    if (gemm_takes(code_id, n, B) && (code_id == CODE_LUT || (B > 16 && !matmat_takes(k, code_id, m, n, B))))
         return launch_gemm(k, code_id, codes, lut, m, n, X, B, scale, Y, st);
     if (code_id == CODE_LUT) return launch_lut_matmat(k, codes, lut, m, n, X, B, scale, Y, st);
     QTIP_DISPATCH(launch_matmat_t, codes, lut, m, n, X, B, scale, Y, st);

@@ -14,7 +14,7 @@ hipError_t launch_matvec(int k, int code_id, const uint32_t *codes, const uint32
 hipError_t launch_matmat(int k, int code_id, const uint32_t *codes, const uint32_t *lut, int m,
                          int n, const void *X, int B, const void *scale, float *Y, hipStream_t st);
 // The product for more than 16 batch rows, of the lookup-only code for more than one (qtip_gemm.hip), where gemm_takes() the
-// sizes and neither matmat_takes() nor lut_matmat_takes() (qtip_decode.hip) does.
+// sizes and matmat_takes() (qtip_decode.hip) does not.
 bool gemm_takes(int code_id, int n, int B);
 hipError_t launch_gemm(int k, int code_id, const uint32_t *codes, const void *lut, int m, int n, const void *X, int B,
                        const void *scale, float *Y, hipStream_t st);

@@ -87,7 +87,7 @@ def test_up_to_16_rows_of_the_lookup_only_code(q, k):
 
 @pytest.mark.parametrize("k", [2, 3, 4])
 def test_few_outputs_of_the_lookup_only_code(q, k):
-    """Its own kernel's: at most 16 batch rows of 256 outputs; an odd number of blocks, slices that do not fill."""
+    """Up to eight workgroups; an odd number of blocks, slices that do not fill."""
     for m, n in ((32, 2056), (96, 4104), (224, 8192), (256, 16384)):
         for B in (2, 3, 9, 16):
             check(q, CODE_LUT, k, m, n, B, scaled=B > 8, seed=n)

@@ -117,12 +117,3 @@ def test_which_kernel_takes_more_than_16_batch_rows(code, k, m, n, B, same):
     import torch
     product = Product(code, k, m, n, B)
     assert torch.equal(product(m, 16), product(m, B)[:16]) == same
-
-
-@pytest.mark.parametrize("k", [2, 3, 4])
-@pytest.mark.parametrize("n,B,own", [(2048, 8, False), (2056, 2, True), (4096, 16, True), (16384, 9, True), (16392, 9, False),
-                                     (4096, 17, False)])
-def test_which_kernel_takes_few_outputs_of_the_lookup_only_code(k, n, B, own):
-    import torch
-    product = Product(CODE_LUT, k, 288, n, B)
-    assert torch.equal(product(256, B), product(288, B)[:, :256]) != own
