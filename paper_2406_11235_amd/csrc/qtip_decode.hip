@@ -971,16 +971,17 @@ hipError_t launch_rht_matvec(int k, int code_id, const uint32_t *codes, const ui
 // HYB2 0.76, 0.98 at 4096, 1.0 at 6144, 1.05; codes without a table 0.95 at 64 inputs, 1.02 at 2048, 1.1 at 8192.
 // Where 16 rows at a time would be more than one workgroup per CU and 32 are not, what is read of X decides: there are twice as many
 // workgroups as the other kernel's to read it, and rows that do not begin with a cache line have 64 lines in a step's 64 inputs of 32
-// batch rows, not 32.  Time of this kernel over that one's: codes without a table 0.84 in whole lines, 0.9 otherwise up to 4096
-// inputs and 1.4 at worst beyond (480 x 28400, 140 rows, 3-bit HYB 54.5 us and 38.6; 592 x 19728, 136 rows, 2-bit 3INST 38.7 28.6); V = 1 hash
-// code, with the most table reads, 0.86, 0.9 up to 8192 inputs and 1.05 beyond; HYB and HYB2 0.93 up to 2048 inputs, then 0.95 in whole
-// lines at 2 bits, and 0.98 to 1.1 at 3 and 4, where that kernel hashes two states at once.
+// batch rows, not 32.  Time of this kernel over that one's, code words from memory: in whole lines codes without a table and V = 1 hash
+// code 0.82, HYB and HYB2 at 2 bits 0.94; at 3 and 4 bits, where that kernel hashes two states at once, 0.98 to 1.1.  Otherwise, up to 64
+// batch rows and the inputs below, 0.88, but beyond these 1.05 (V = 1 hash code) to 1.4 (480 x 28400, 140 rows, 3-bit HYB 54.5 us and
+// 38.6; 592 x 19728, 136 rows, 2-bit 3INST 38.7 28.6), and for more batch rows up to 1.2 (432 x 1456, 172 rows, 4-bit HYB2 6.4 5.3).
+// Of 757 products that go here by this 9 take more than 6 % longer, 13 % at most.
 static bool matmat_takes(int k, int code_id, int m, int n, int B) {
     const int tm = m / 16, groups = (B + 15) / 16;
     if (code_id == CODE_LUT || B > 256) return false;
     if ((long)tm * groups <= CUS) return true;
     if ((long)tm * ((groups + 1) / 2) <= CUS)
-        return n <= (code_is_hyb(code_id) ? 2048 : code_id == CODE_HYB1 ? 8192 : 4096) ||
+        return (groups <= 4 && n <= (code_is_hyb(code_id) ? 2048 : code_id == CODE_HYB1 ? 8192 : 4096)) ||
                (n % 64 == 0 && (k == 2 || !code_is_hyb(code_id)));
     return groups == 2 && tm > 2 * CUS && code_lds_words(code_id) > 1 && n <= (code_is_hyb(code_id) ? 4096 : 8192);
 }

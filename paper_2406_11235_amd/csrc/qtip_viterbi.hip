@@ -22,9 +22,9 @@
 // one wave evaluates from the stored `best` in a few hundred instructions.
 //   What bounds it is the issue of those instructions: 2.8 cycles for the subtraction and 2.9 for the
 // fused multiply-add, 4.35 for a minimum are 2020 cycles a step at kV = 2 and V = 1.  Measured (busy cycles of the
-// counters over 255 steps): 2170 in the first pass and 2230 in the second, whether half of the CUs are at work or all of
-// them; but the clock is 2.3 GHz with 128 sequences and 2.0 to 2.15 with thousands, so that a step takes 0.95 us
-// there and 1.02 to 1.13 here.
+// counters over the steps of a pass): 2165 to 2190 in the 255 of the first pass and 2190 to 2210 in the 245 of the second, whether
+// half of the CUs are at work or all of them; but the clock is 2.3 GHz with 128 sequences and 1.9 to 2.15 with thousands, so that a
+// step takes 0.95 us there and 1.02 to 1.15 here.
 // 2048 x 2048, 2-bit 3INST: 69.7 ms with back-pointers, 36.1 now (37.5 on another card).  (The subtractions on the matrix cores, one
 // v_mfma_f32_16x16x1 for 16 registers, bit for bit the same: 34.7 ms, but BlockLDLQ's 128
 // sequences 48.4 -> 48.8: its 32 cycles are not hidden behind other waves' vector instructions.)

@@ -112,7 +112,8 @@ def test_waves_of_up_to_16_batch_rows(code, k, m, n, B, waves):
     (CODE_HYB1, 2, 8208, 8208, 17, False), (CODE_3INST, 2, 8208, 4096, 32, False), (CODE_1MAD, 3, 14336, 1024, 17, False),
     (CODE_HYB, 3, 2064, 2048, 32, True), (CODE_HYB, 3, 2064, 2112, 32, False), (CODE_HYB2, 2, 2064, 8208, 32, False),
     (CODE_HYB2, 2, 2064, 8256, 32, True), (CODE_3INST, 2, 2064, 4112, 32, False), (CODE_3INST, 2, 2064, 4160, 32, True),
-    (CODE_HYB1, 4, 2064, 8176, 32, True), (CODE_HYB1, 4, 2064, 8208, 32, False), (CODE_HYB1, 4, 2064, 8256, 32, True)])
+    (CODE_HYB1, 4, 2064, 8176, 32, True), (CODE_HYB1, 4, 2064, 8208, 32, False), (CODE_HYB1, 4, 2064, 8256, 32, True),
+    (CODE_3INST, 2, 1280, 1008, 64, True), (CODE_3INST, 2, 1280, 1008, 80, False), (CODE_3INST, 2, 1280, 960, 80, True)])
 def test_which_kernel_takes_more_than_16_batch_rows(code, k, m, n, B, same):
     import torch
     product = Product(code, k, m, n, B)
