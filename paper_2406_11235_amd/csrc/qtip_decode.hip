@@ -886,7 +886,11 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
     // of long rows count for more than an idle CU: HYB2 k = 4 12288 x 14336, 8 rows, 33.7 30.6; k = 3, 16 rows, 38.9 41.6.  With
     // 16 waves at 3 bits and up to 8 rows, where code words are two loads a lane (8 waves and 16: 3INST 10240 x 14336 42.5 37.7,
     // 1MAD 12288 x 28672 81.4 75.2; V = 1 hash code 12288 x 8192 28.5 27.4, but 4096 inputs 13.4 15.2).
-    const bool between = (tm <= 4 * CUS || (CODE == CODE_HYB1 && n >= 2048)) && !spread && !(HASH && n >= 8192 && !(K == 3 && big)) &&
+    // And not for nearly 16 batch rows of 64 inputs in two cache lines each, where pairs read half of those: time over that of single
+    // rows, more than 12 rows of inputs that are not whole lines, 2 bits, code words from memory: 3INST, HYB and HYB2 2048 to 8192
+    // inputs 0.94, 3INST beyond 0.96, V = 1 hash code beyond 16384 0.86; 1MAD 1.12, whatever the code below 2048 inputs 1.06.
+    const bool two_lines = K == 2 && B > 12 && n % 64 != 0 && n >= (CODE == CODE_HYB1 ? 16384 : 2048) && CODE != CODE_1MAD;
+    const bool between = (tm <= 4 * CUS || (CODE == CODE_HYB1 && n >= 2048)) && !spread && !two_lines && !(HASH && n >= 8192 && !(K == 3 && big)) &&
                          (tm + 255) / 256 < 2 * (((tm + 1) / 2 + 255) / 256);
     const bool between_16 = between && K == 3 && !big && tm <= 4 * CUS && n >= (CODE == CODE_HYB1 ? 8192 : 4096);
     // Eight waves for more than two tile rows per CU where a row is short, and where code values and batch rows leave too few

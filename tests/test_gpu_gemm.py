@@ -53,9 +53,10 @@ def test_splits(q, code, k):
 
 
 # up to 16 batch rows: halves of tile rows, with 8 and 16 waves and steps that do not fill; one and two tile rows per
-# workgroup, with 8 and 16 waves, the last pair half empty; one and 16 copies of the hash code's table; slices with nothing
+# workgroup, with 8 and 16 waves, the last pair half empty; one and 16 copies of the hash code's table; slices with nothing; pairs
+# between the rounds where rows are not whole cache lines
 UP_TO_16 = [(16, 16), (1024, 1040), (2048, 4112), (1008, 4128), (2064, 4144), (4112, 272), (4112, 4128), (4112, 8208),
-            (10256, 144), (14352, 80), (14352, 4112), (14352, 8208), (16400, 272)]
+            (10256, 144), (14352, 80), (14352, 4112), (14352, 8208), (16400, 272), (10256, 2064), (10256, 4112)]
 
 
 @pytest.mark.parametrize("code", [c for c in CODES if c != CODE_LUT])
