@@ -130,12 +130,18 @@ int qtip_decode_matvec(const uint32_t *codes, int L, int k, int V, int code_id,
  * X_f16: device, B x n row-major fp16.  Y: device, B x m row-major fp32,
  * overwritten.  row_scale_f16: device, m fp16, or NULL for no scale.  B >= 1.
  * B = 1 runs the batch-1 kernel on the vector ALUs (for QTIP_CODE_1MAD with the unrounded
- * quotient, as qtip_decode_matvec); every B >= 2 runs on the matrix cores (MFMA): up to 16
- * rows with the decoded 16x16 tile as one operand (Section 4: T_x = T_y = 16 matches a
- * 16x16 matrix-multiply tile; with QTIP_CODE_LUT two neighbouring 32 x 8 blocks are the
- * 32 x 16 operand of the 32x32x16 instruction), more rows with 32 outputs x 16 inputs, decoded
- * once for 32 to 256 batch rows, as the operand of that instruction.  Y must be 16-byte aligned (and m a multiple
- * of 16, as everywhere): outputs are stored four at a time.
+ * quotient, as qtip_decode_matvec); every B >= 2 runs on the matrix cores (MFMA), in one of
+ * two ways.  Up to 16 rows, and up to 256 of so few outputs that a workgroup for each
+ * 16 of them leaves CUs idle, with the decoded 16x16 tile as one operand (Section 4:
+ * T_x = T_y = 16 matches a 16x16 matrix-multiply tile), 16 or 32 batch rows at a time; and
+ * 17 to 32 rows of many outputs and not so many inputs, for the codes with a table.  Other
+ * products of more than 16 rows, and QTIP_CODE_LUT's from 2 rows on, with 32 outputs x
+ * 16 inputs, decoded once for 32 to 256 batch rows, as an operand of the 32x32x16 instruction.
+ * (QTIP_CODE_LUT beyond 2^25 inputs: two neighbouring 32 x 8 blocks are that operand, decoded
+ * again for every 32 rows.  The other codes beyond 2^22 inputs: the first way, for 16, 32 or 64
+ * rows at a time.)
+ * The choice is by sizes and code alone.  Y must be 16-byte aligned (and m a multiple of 16,
+ * as everywhere).
  */
 int qtip_decode_matmat(const uint32_t *codes, int L, int k, int V, int code_id,
                        const void *lut_f16, int m, int n, const void *X_f16, int B,
