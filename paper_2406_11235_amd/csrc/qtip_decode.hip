@@ -876,11 +876,24 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
 #define QTIP_MM(R, NW, SR, SPREAD)                                                                              \
     hipLaunchKernelGGL((matmat_kernel<K, V, CODE, R, 1, NW, SR, SPREAD>), dim3((tm + R - 1) / R, groups),      \
                        dim3(NW * 64), 0, st, codes, lut, tm, tn, Xh, B, sc, Y)
-#define QTIP_MM_BATCH(R, NW)                  \
-    if (big && spread) QTIP_MM(R, NW, 16, HYB); \
-    else if (big) QTIP_MM(R, NW, 16, false);  \
-    else if (spread) QTIP_MM(R, NW, K == 2 ? 0 : 8, HYB);  \
-    else QTIP_MM(R, NW, 0, false)
+    // (COPIES: where 16 copies can be picked: nowhere, beyond 8 batch rows alone, everywhere)
+#define QTIP_MM_BATCH(R, NW, COPIES)                       \
+    do {                                                   \
+        if constexpr (HYB && COPIES > 0) {                 \
+            if (big && spread) {                           \
+                QTIP_MM(R, NW, 16, true);                  \
+                break;                                     \
+            }                                              \
+        }                                                  \
+        if constexpr (HYB && COPIES > 1) {                 \
+            if (spread) {                                  \
+                QTIP_MM(R, NW, (K == 2 ? 0 : 8), true);    \
+                break;                                     \
+            }                                              \
+        }                                                  \
+        if (big) QTIP_MM(R, NW, 16, false);                \
+        else QTIP_MM(R, NW, 0, false);                     \
+    } while (0)
     // Single rows at row counts between the rounds of pairs (beyond four rounds for the V = 1 hash code alone: single rows and
     // pairs, us, k = 3 28672 x 4096, 2 rows, 25.4 28.4; 3-bit 3INST 20480 x 14336, 8 rows, 64.5 54.9), but not where the table reads
     // of long rows count for more than an idle CU: HYB2 k = 4 12288 x 14336, 8 rows, 33.7 30.6; k = 3, 16 rows, 38.9 41.6.  With
@@ -901,13 +914,13 @@ static hipError_t launch_matmat_t(const uint32_t *codes, const uint32_t *lut, in
                            (!spread && (tn < (tm > 4 * CUS ? 768 : big ? 512 : 256) || (K == 3 && (big || !HASH)) ||
                                         (!HASH && (big || (CODE == CODE_3INST && K == 4)))));
     if (tm <= CUS || between_16) {
-        QTIP_MM_BATCH(1, 16);
+        QTIP_MM_BATCH(1, 16, 1);
     } else if (between) {
-        QTIP_MM_BATCH(1, 8);
+        QTIP_MM_BATCH(1, 8, 0);
     } else if (tm <= 2 * CUS || !few_waves) {
-        QTIP_MM_BATCH(2, 16);
+        QTIP_MM_BATCH(2, 16, 2);
     } else {
-        QTIP_MM_BATCH(2, 8);
+        QTIP_MM_BATCH(2, 8, 2);
     }
 #undef QTIP_MM_BATCH
 #undef QTIP_MM
